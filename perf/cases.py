@@ -1,0 +1,210 @@
+"""The work that users of this framework have it do, as measured cases.
+
+One pass goes through the public entry points of `paper_2403_09195_amd.binding`: the attention operator on its own
+(inference), forward plus backward (training), and the encoder stack with its projections (the whole image encoder's
+attention).  Shapes are those of the paper's image sizes (16 x 16 patches: 256^2 -> 256 tokens, 512^2 -> 1024,
+1024^2 -> 4096, 2048^2 -> 16384; 12 heads of 64, or 6 for the student model) and generic ragged ones.
+"""
+from __future__ import annotations
+
+import numpy as np
+import torch
+
+from paper_2403_09195_amd import binding
+
+D = 64
+SCALE = 0.125                       # 1 / sqrt(D)
+
+
+def _case(name, kind, dtype, B, H, N, branches, packed=False, explicit=False, layers=0):
+    return {"name": name, "kind": kind, "dtype": dtype, "B": B, "H": H, "N": N, "branches": branches,
+            "packed": packed, "explicit_offsets": explicit, "layers": layers}
+
+
+def listed():
+    return [
+        # one small image through the operator: nothing but latency (launches, host work, the start of a tile)
+        _case("forward_256px", "forward", "bf16", 1, 12, 256, "64:1,128:2,256:4"),
+        # one image of the encoder's own size, a single attention call of an interactive segmentation request
+        _case("forward_1024px", "forward", "bf16", 1, 12, 4096, "1024:1,2048:2,4096:4"),
+        # the throughput workload: a batch of images, offline segmentation
+        _case("forward_batch", "forward", "bf16", 16, 12, 4096, "1024:1,2048:2,4096:4"),
+        # high-resolution images, four branches
+        _case("forward_2048px", "forward", "bf16", 2, 12, 16384, "2048:1,4096:2,8192:4,16384:8"),
+        # a crop whose token count suits nothing: ragged segments, rates without a common factor, a table of
+        # start offsets, q/k/v read in place from a packed projection output
+        _case("forward_ragged", "forward", "bf16", 3, 6, 1500, "400:1,750:3,1500:5", packed=True, explicit=True),
+        # the whole encoder's attention for one image (latency) ...
+        _case("stack_one", "stack", "bf16", 1, 12, 4096, "1024:1,2048:2,4096:4", layers=12),
+        # ... and for a batch (throughput)
+        _case("stack_batch", "stack", "bf16", 8, 12, 4096, "1024:1,2048:2,4096:4", layers=12),
+        # a training step's attention, forward and backward: a small batch of small images (student model) ...
+        _case("train_512px", "train", "bf16", 4, 6, 1024, "256:1,512:2,1024:4"),
+        # ... one 800^2 image (50 x 50 tokens, windows that end inside a tile), q/k/v from a packed projection ...
+        _case("train_800px", "train", "bf16", 1, 12, 2500, "625:1,1250:2,2500:4", packed=True),
+        # ... and a full batch
+        _case("train_batch", "train", "bf16", 16, 12, 4096, "1024:1,2048:2,4096:4"),
+        # callers whose model runs in fp32: inference on one image, a training step on small ones
+        _case("forward_fp32", "forward", "fp32", 1, 12, 4096, "1024:1,2048:2,4096:4"),
+        _case("train_fp32", "train", "fp32", 2, 6, 1024, "256:1,512:2,1024:4"),
+    ]
+
+
+def _branches(case):
+    return [tuple(int(x) for x in part.split(":")) for part in case["branches"].split(",")]
+
+
+def _offsets(case, branches):
+    """Explicit start offsets per branch and head (None: head h starts at h mod r)."""
+    if not case["explicit_offsets"]:
+        return None
+    return [[(3 * h + x + 1) % r for h in range(case["H"])] for x, (_, r) in enumerate(branches)]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(float(np.exp(rng.uniform(np.log(lo), np.log(hi))))))
+
+
+def _pattern(rng, N):
+    kind = rng.choice(["three", "three", "four", "coprime", "window", "dense", "dilated"])
+    if kind == "three":
+        br = [(max(N // 4, 1), 1), (max(N // 2, 1), 2), (N, 4)]
+    elif kind == "four":
+        br = [(max(N // 8, 1), 1), (max(N // 4, 1), 2), (max(N // 2, 1), 4), (N, 8)]
+    elif kind == "coprime":
+        br = [(max(N // 4 + rng.randint(-9, 9), 1), 1), (max(N // 2 + rng.randint(-9, 9), 1), 3), (N, 5)]
+    elif kind == "window":
+        br = [(max(N // rng.randint(2, 8), 1), 1)]
+    elif kind == "dense":
+        br = [(N, 1)]
+    else:                                                   # one dilated branch: most rows are kept by nothing
+        br = [(max(N // rng.randint(1, 4), 1), rng.choice([2, 3]))]
+    return ",".join(f"{w}:{r}" for w, r in br)
+
+
+# no drawn case does more work than the listed one of its kind
+_MOST = {("forward", "bf16"): "forward_2048px", ("train", "bf16"): "train_batch", ("stack", "bf16"): "stack_batch",
+         ("forward", "fp32"): "forward_fp32", ("train", "fp32"): "train_fp32"}
+
+
+def draw(rng):
+    kind, dtype = rng.choice([("forward", "bf16")] * 4 + [("train", "bf16")] * 3 + [("stack", "bf16")] * 2 +
+                             [("forward", "fp32"), ("train", "fp32")])
+    most = {c["name"]: c for c in listed()}[_MOST[(kind, dtype)]]
+    most_work = work(most)
+    for _ in range(100):
+        if kind == "stack":
+            H = rng.choice([6, 12])
+            N = 256 * _log_int(rng, 1, 16)                  # projections take whole 256-row tiles
+            c = _case("", kind, dtype, _log_int(rng, 1, 8), H, N, f"{N // 4}:1,{N // 2}:2,{N}:4", layers=rng.choice([2, 6, 12]))
+        else:
+            N = _log_int(rng, 200, most["N"])
+            if rng.random() < 0.3:
+                N = max(N // 64, 4) * 64
+            c = _case("", kind, dtype, _log_int(rng, 1, 16), rng.choice([3, 6, 8, 12, 16]), N, _pattern(rng, N),
+                      packed=rng.random() < 0.5, explicit=rng.random() < 0.3)
+        w = work(c)
+        if w["flops"] <= most_work["flops"] and w["bytes"] <= most_work["bytes"]:
+            break
+    else:
+        c = dict(most)
+    c.pop("name")
+    return c
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda").manual_seed(int(seed))
+    dt = torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
+    B, H, N = case["B"], case["H"], case["N"]
+
+    def normal(shape, std=1.0):
+        return torch.empty(shape, dtype=torch.float32, device="cuda").normal_(0.0, std, generator=gen).to(dt)
+
+    branches = _branches(case)
+    st = {"kind": case["kind"], "branches": branches, "offsets": _offsets(case, branches), "H": H}
+    if case["kind"] == "stack":
+        E, L = H * D, case["layers"]
+        st["x"] = normal((B, N, E))
+        st["w_qkv"] = normal((L, 3 * E, E), 0.02)
+        st["w_o"] = normal((L, E, E), 0.02)
+        # a serving program keeps these from one request to the next
+        st["buffers"] = (torch.empty((B, N, 3, H, D), dtype=dt, device="cuda"),
+                         torch.empty((B, N, H, D), dtype=dt, device="cuda"),
+                         torch.empty((B, N, E), dtype=dt, device="cuda"))
+        return st
+    if case["packed"]:
+        qkv = normal((B, N, 3, H, D))
+        st["q"], st["k"], st["v"] = qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2]
+    else:
+        st["q"], st["k"], st["v"] = (normal((B, N, H, D)) for _ in range(3))
+    if case["kind"] == "train":
+        st["dout"] = normal((B, N, H, D))
+    return st
+
+
+def run(st):
+    if st["kind"] == "stack":
+        return binding.encoder_stack(st["x"], st["w_qkv"], st["w_o"], st["H"], st["branches"], SCALE, buffers=st["buffers"])
+    q, k, v = st["q"], st["k"], st["v"]
+    out, lse = binding.forward(q, k, v, st["branches"], SCALE, head_offsets=st["offsets"])
+    if st["kind"] == "forward":
+        return out, lse
+    dq, dk, dv = binding.backward(q, k, v, out, lse, st["dout"], st["branches"], SCALE, head_offsets=st["offsets"])
+    return out, lse, dq, dk, dv
+
+
+def _pairs(case):
+    """Distinct (query, key) pairs of one image over all heads: a key that several branches pair with a row counts once
+    (its weight in the merged softmax is a factor, not another product)."""
+    N, H = case["N"], case["H"]
+    branches = _branches(case)
+    offsets = _offsets(case, branches)
+    n = np.arange(N)
+    seen, total = {}, 0
+    for h in range(H):
+        offs = tuple(offsets[x][h] if offsets else h % r for x, (_, r) in enumerate(branches))
+        if offs not in seen:
+            part = np.empty((len(branches), N), dtype=np.int64)
+            for x, (w, r) in enumerate(branches):
+                pos = n % w - offs[x]
+                part[x] = np.where((pos >= 0) & (pos % r == 0), n // w, -1)
+            sigs, rows = np.unique(part, axis=1, return_counts=True)
+            pairs = 0
+            for s in range(sigs.shape[1]):
+                keys = np.zeros(N, dtype=bool)
+                for x in range(len(branches)):
+                    if sigs[x, s] >= 0:
+                        keys |= part[x] == sigs[x, s]
+                pairs += int(rows[s]) * int(keys.sum())
+            seen[offs] = pairs
+        total += seen[offs]
+    return total
+
+
+def work(case):
+    B, H, N = case["B"], case["H"], case["N"]
+    es = 2 if case["dtype"] == "bf16" else 4
+    rows, pairs = B * N * H, B * _pairs(case)
+    tensor = rows * D * es
+    if case["kind"] == "forward":                           # q, k, v in; out, lse out.  Two products of 2 D per pair
+        return {"bytes": 4 * tensor + 4 * rows, "flops": 4 * D * pairs}
+    if case["kind"] == "train":                             # q, k, v, dout in; out, lse, dq, dk, dv out.  2 + 5 products
+        return {"bytes": 8 * tensor + 4 * rows, "flops": 14 * D * pairs}
+    E, L = H * D, case["layers"]                            # x and the weights in; y, the last qkv and attention out
+    return {"bytes": 6 * tensor + L * 4 * E * E * es,
+            "flops": L * (4 * D * pairs + 2 * B * N * E * 4 * E)}
+
+
+def tolerance(case):
+    # Each path was compared once with the same computation in fp64 (listed shapes, up to two images, and drawn ones);
+    # "seen" is the worst output of that comparison, the figures stated are about four times as much.  Two correct
+    # implementations at one precision differ by no more.
+    if case["kind"] == "stack":                             # seen: rel 4.9e-3, max 2.1e-2 (roundings of 12 layers)
+        return {"rel": 2e-2, "max": 8e-2}
+    if case["dtype"] == "bf16":
+        if case["kind"] == "train":                         # seen: rel 2.5e-3, max 4.5e-2 (P, dS and results in bf16)
+            return {"rel": 1e-2, "max": 0.18}
+        return {"rel": 1e-2, "max": 6e-2}                   # seen: rel 2.3e-3, max 1.5e-2 (P and results in bf16)
+    if case["kind"] == "train":                             # seen: rel 5.8e-7, max 5.0e-6
+        return {"rel": 2.5e-6, "max": 2e-5}
+    return {"rel": 3.5e-6, "max": 2.5e-5}                   # seen: rel 8.5e-7, max 6.1e-6 (sums over up to 4096 keys)
