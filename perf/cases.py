@@ -153,6 +153,67 @@ def run(st):
     return out, lse, dq, dk, dv
 
 
+def _weights(branches, offs, rows, N):
+    """How many branches hold each (query, key) pair, queries `rows`, all keys, of a head with start offsets `offs`."""
+    keys = torch.arange(N, device=rows.device)
+
+    def part(t, w, r, o):                                   # the segment that keeps token t, -1: not kept
+        pos = t % w - o
+        return torch.where((pos >= 0) & (pos % r == 0), t // w, -1)
+
+    m = torch.zeros((rows.numel(), N), dtype=torch.float64, device=rows.device)
+    for (w, r), o in zip(branches, offs):
+        pq, pk = part(rows, w, r, o), part(keys, w, r, o)
+        m += (pq[:, None] == pk[None, :]) & (pq >= 0)[:, None]
+    return m
+
+
+def _attention64(q, k, v, branches, offsets, dout=None):
+    """The operator by its definition, a softmax over the multiset union of a row's key lists, in fp64 with dense
+    matrices, and its gradients by the chain rule."""
+    B, N, H, D_ = q.shape
+    out = torch.zeros((B, N, H, D_), dtype=torch.float64, device=q.device)
+    lse = torch.empty((B, H, N), dtype=torch.float64, device=q.device)
+    grads = [torch.zeros_like(out) for _ in range(3)] if dout is not None else None
+    step = max(1, min(N, (1 << 26) // N))
+    for h in range(H):
+        offs = [offsets[x][h] if offsets else h % r for x, (_, r) in enumerate(branches)]
+        for n0 in range(0, N, step):
+            rows = torch.arange(n0, min(n0 + step, N), device=q.device)
+            m = _weights(branches, offs, rows, N)
+            bias = torch.log(m)
+            for b in range(B):
+                qb, kb, vb = (t[b, :, h].double().contiguous() for t in (q, k, v))
+                s = qb[n0:n0 + step] @ kb.T
+                s = s.mul_(SCALE).add_(bias)
+                l = torch.logsumexp(s, dim=1)
+                kept = torch.isfinite(l)
+                p = torch.where(kept[:, None], torch.exp(s - l[:, None]), 0.0)
+                o = p @ vb
+                out[b, n0:n0 + step, h], lse[b, h, n0:n0 + step] = o, l
+                if dout is None:
+                    continue
+                do = dout[b, n0:n0 + step, h].double().contiguous()
+                ds = p * (do @ vb.T - (do * o).sum(1, keepdim=True)) * SCALE
+                grads[0][b, n0:n0 + step, h] = ds @ kb
+                grads[1][b, :, h] += ds.T.contiguous() @ qb[n0:n0 + step]
+                grads[2][b, :, h] += p.T.contiguous() @ do
+    return (out, lse) if dout is None else (out, lse, *grads)
+
+
+def exact(case, seed):
+    st = prepare(case, seed)
+    if st["kind"] != "stack":
+        return _attention64(st["q"], st["k"], st["v"], st["branches"], st["offsets"], st.get("dout"))
+    x = st["x"].double()
+    B, N, E = x.shape
+    for w_qkv, w_o in zip(st["w_qkv"], st["w_o"]):
+        qkv = (x.view(B * N, E) @ w_qkv.double().T.contiguous()).view(B, N, 3, st["H"], D)
+        attn = _attention64(qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2], st["branches"], None)[0]
+        x = (attn.view(B * N, E) @ w_o.double().T.contiguous()).view(B, N, E)
+    return x, qkv, attn
+
+
 def _pairs(case):
     """Distinct (query, key) pairs of one image over all heads: a key that several branches pair with a row counts once
     (its weight in the merged softmax is a factor, not another product)."""
