@@ -37,6 +37,7 @@ struct DevicePlan {
     const float* block_mult = nullptr;   // plans of the bf16 forward only
     bool packed_tiles = false;          // some tile packs several row groups: the kernel variant that reads block_mult
     int32_t n_items = 0;
+    int32_t max_tile_rows = 1;     // most rows of any tile
     int device = 0;
     size_t bytes = 0;
     // launches with few workgroups walk their tiles with n_split_wgs workgroups in all (see split_plan and
@@ -71,6 +72,7 @@ struct PackedPlan {
     size_t off_segs = 0, off_items = 0, off_split_wgs = 0, off_item_parts = 0, off_block_mult = 0;
     int32_t n_items = 0;
     int32_t n_split_wgs = 0;
+    int32_t max_tile_rows = 1;
     bool packed_tiles = false;
 };
 
@@ -120,6 +122,7 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
     out->n_items = (int32_t)hp.items.size();
     out->n_split_wgs = (int32_t)hp.split_wgs.size();
     out->packed_tiles = hp.packed_tiles;
+    for (const Tile& t : hp.tiles) out->max_tile_rows = std::max(out->max_tile_rows, t.nrows);
     return DFA_OK;
 }
 
@@ -137,6 +140,7 @@ void point_plan(DevicePlan* dp, void* base, const PackedPlan& pp, int device) {
     dp->n_split_wgs = pp.n_split_wgs;
     dp->block_mult = reinterpret_cast<const float*>(b + pp.off_block_mult);
     dp->packed_tiles = pp.packed_tiles;
+    dp->max_tile_rows = pp.max_tile_rows;
 }
 
 std::vector<int32_t> plan_key(int device, bool packed, int32_t B, int32_t H, int32_t N, const dfa_branch_t* br,
@@ -334,7 +338,7 @@ int launch_forward(const DevicePlan& dp, const void* q, const void* k, const voi
     } else if (dt == DFA_BF16) {
         e = launch_fwd_bf16(p, dp.n_items, out_f32, dp.packed_tiles, st);
     } else {
-        e = launch_fwd_f32(p, dp.n_items, st);         // fp32 inputs always give fp32 output
+        e = launch_fwd_f32(p, dp.n_items, dp.max_tile_rows, st);         // fp32 inputs always give fp32 output
     }
     return e == hipSuccess ? DFA_OK : DFA_ERR_LAUNCH;
 }
@@ -565,7 +569,7 @@ int dfa_backward(const void* q, const void* k, const void* v, const void* out, c
         p.lse = lse; p.ndelta = delta_ws; p.lse2 = delta_ws + (int64_t)B * H * N; p.dq = dq; p.dk = dk; p.dv = dv;
         p.rows = dp.rows; p.segs = dp.segs; p.items = dp.items;
         p.H = H; p.N = N; p.scale = scale;
-        return launch_bwd(p, dp.n_items, B, dt == DFA_BF16, static_cast<hipStream_t>(stream)) == hipSuccess
+        return launch_bwd(p, dp.n_items, dp.max_tile_rows, B, dt == DFA_BF16, static_cast<hipStream_t>(stream)) == hipSuccess
                    ? DFA_OK : DFA_ERR_LAUNCH;
     } catch (const std::bad_alloc&) {
         return DFA_ERR_LAUNCH;

@@ -10,71 +10,29 @@
 // above is linear in P).
 //
 // This file: the per-row preparation of the fp32 path (delta, and lse in base-2 units; the bf16 path does it in
-// its dq kernel) and
-// the fp32 path, correctness-first kernels in fp32 vector arithmetic on the same launch plan as
-// the forward pass, one lane per row of a tile.  bf16 operands go to the matrix-core kernels.  In a
-// segment the kept rows are queries and keys alike, so a tile's key lists are also the lists of
-// queries that see its rows as keys: the dq kernel walks them as keys, the dk and dv kernels walk
-// them as queries, and no gradient needs an atomic or a second pass over partial sums.
+// its dq kernel) and the fp32 path on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: full fp32 products and sums).
+// bf16 operands go to the kernels of dfa_bwd_bf16.hip.  In a segment the kept rows are queries and keys alike, so a
+// tile's key lists are also the lists of queries that see its rows as keys: the dq workgroups walk them as keys, the
+// dk/dv workgroups walk them as queries, and no gradient needs an atomic or a second pass over partial sums.
+//
+// Bound: the fp32 matrix cores (a 32 x 32 block of pairs takes 96 MFMAs of 64 cycles for dq and 128 for dk and dv).
+// As in the forward a workgroup owns 32 rows of a tile and its four waves a quarter of the walked 32-row blocks each
+// (small images are what fp32 training runs on: 12 heads of 1024 rows are 384 workgroups for either gradient kernel).
+// The dq and the dk/dv workgroups ride in one launch, so that together they fill the chip.  Buffers are refilled
+// as soon as a block's last product with them is through, each landing under a product with the other one.
+// Measured, forward and backward of two 512^2 images (6 heads x 1024 tokens): 93 us (one lane per row on the vector units,
+// a launch per gradient: 1554 us), error of the gradients against fp64 4.2e-7 of their 2-norm (5.6e-7).
 #include "dfa_device.h"
+#include "dfa_mfma_f32.h"
 
 namespace dfa {
 
 namespace {
 
-template <typename T>
-__device__ __forceinline__ float4 load4(const T* p);
-template <>
-__device__ __forceinline__ float4 load4<float>(const float* p) { return *reinterpret_cast<const float4*>(p); }
-template <typename T>
-__device__ __forceinline__ void store4v(T* p, float a, float b, float c, float d);
-template <>
-__device__ __forceinline__ void store4v<float>(float* p, float a, float b, float c, float d) {
-    *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
-}
-
-template <typename T>
-__device__ __forceinline__ void load_row(const T* p, float (&x)[kD]) {
-#pragma unroll
-    for (int d = 0; d < kD; d += 4) {
-        const float4 t = load4<T>(p + d);
-        x[d] = t.x; x[d + 1] = t.y; x[d + 2] = t.z; x[d + 3] = t.w;
-    }
-}
-template <typename T>
-__device__ __forceinline__ void store_row(T* p, const float (&x)[kD]) {
-#pragma unroll
-    for (int d = 0; d < kD; d += 4) store4v<T>(p + d, x[d], x[d + 1], x[d + 2], x[d + 3]);
-}
-
-__device__ __forceinline__ float dot_row(const float (&a)[kD], const float* b) {
-    float d0 = 0.f, d1 = 0.f, d2 = 0.f, d3 = 0.f;               // four interleaved partial sums
-#pragma unroll
-    for (int d = 0; d < kD; d += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(b + d);
-        d0 = fmaf(a[d], x.x, d0);
-        d1 = fmaf(a[d + 1], x.y, d1);
-        d2 = fmaf(a[d + 2], x.z, d2);
-        d3 = fmaf(a[d + 3], x.w, d3);
-    }
-    return (d0 + d1) + (d2 + d3);
-}
-__device__ __forceinline__ void axpy_row(float s, const float* b, float (&acc)[kD]) {
-#pragma unroll
-    for (int d = 0; d < kD; d += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(b + d);
-        acc[d] = fmaf(s, x.x, acc[d]);
-        acc[d + 1] = fmaf(s, x.y, acc[d + 1]);
-        acc[d + 2] = fmaf(s, x.z, acc[d + 2]);
-        acc[d + 3] = fmaf(s, x.w, acc[d + 3]);
-    }
-}
-
 // ndelta[b][h][n] = -(dout[b][n][h][:] . out[b][n][h][:]) and lse2 = lse * log2(e); 16 lanes per row, 4 d each.
 // grid = (16 * rows of one image / 256, B): one image is indexed with 32-bit arithmetic.
-template <typename T>
 __global__ __launch_bounds__(256)
-void bwd_delta_kernel(const T* out, const T* dout, const float* lse, float* ndelta, float* lse2, int32_t H, int32_t N) {
+void bwd_delta_kernel(const float* out, const float* dout, const float* lse, float* ndelta, float* lse2, int32_t H, int32_t N) {
     const uint32_t x = blockIdx.x * 256u + threadIdx.x;
     const uint32_t t = x >> 4;                                       // n * H + h
     const int part = (int)(x & 15u);
@@ -83,7 +41,8 @@ void bwd_delta_kernel(const T* out, const T* dout, const float* lse, float* ndel
     const int64_t rowid = b * N * H + t;                             // (b, n, h) flattened
     float s = 0.f;
     if (in) {
-        const float4 a = load4<T>(out + rowid * kD + 4 * part), g = load4<T>(dout + rowid * kD + 4 * part);
+        const float4 a = *reinterpret_cast<const float4*>(out + rowid * kD + 4 * part);
+        const float4 g = *reinterpret_cast<const float4*>(dout + rowid * kD + 4 * part);
         s = (a.x * g.x + a.y * g.y) + (a.z * g.z + a.w * g.w);
     }
 #pragma unroll
@@ -96,119 +55,230 @@ void bwd_delta_kernel(const T* out, const T* dout, const float* lse, float* ndel
     }
 }
 
-// Stages 64 rows of a strided tensor (rows key0 + stride * j of image b, head h) into LDS as fp32;
-// positions past the end of the list re-read its last row.
-template <typename T>
-__device__ __forceinline__ void stage_rows(const T* base, int64_t sn, const KeySeg& seg, int t, float* lds, int tid) {
+// What a workgroup works on: 32 rows of a tile.
+struct BwdBlock {
+    Tile tile;
+    int b, h, nrows;
+    const int32_t* rows;
+};
+
+// Sum of the four waves' [32][64] results, written to rows of a contiguous [B, N, H, D] tensor.  Every wave has
+// finished with its own region of LDS.
+__device__ __forceinline__ void write_sum(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems], int tid,
+                                          const floatx16 (&acc)[2], void* grad) {
+    result_to_lds(acc, lds[tid >> 6], tid & 63);
+    __syncthreads();
+    const int row = tid >> 3, d = (tid & 7) * 8;
+    if (row < k.nrows) {
+        float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int kr = (tid >> 4) + 16 * u;
-        const int j = min(t * kKeyTile + kr, seg.count - 1);
-        const int64_t row = kept_row(seg.key0, seg.stride, j);
-        const int cch = (tid & 15) * 4;
-        *reinterpret_cast<float4*>(lds + kr * kD + cch) = load4<T>(base + row * sn + cch);
+        for (int x = 0; x < kF32Waves; ++x) {
+            const float4 u = *reinterpret_cast<const float4*>(lds[x] + row * kF32RedPitch + d);
+            const float4 v = *reinterpret_cast<const float4*>(lds[x] + row * kF32RedPitch + d + 4);
+            a.x += u.x; a.y += u.y; a.z += u.z; a.w += u.w;
+            c.x += v.x; c.y += v.y; c.z += v.z; c.w += v.w;
+        }
+        float4* const dst = reinterpret_cast<float4*>(static_cast<float*>(grad) +
+                                                      (((int64_t)k.b * p.N + k.rows[row]) * p.H + k.h) * kD + d);
+        dst[0] = a;
+        dst[1] = c;
     }
 }
 
-// kMode 0: dq of the tile's rows (they are queries; the lists are walked as keys)
-// kMode 1: dv of the tile's rows (they are keys; the lists are walked as queries)
-// kMode 2: dk of the tile's rows (likewise)
-template <typename T, int kMode>
-__global__ __launch_bounds__(256)
-void bwd_kernel(const BwdParams p) {
-    __shared__ __attribute__((aligned(16))) float a_lds[kKeyTile * kD];   // k rows (mode 0) or q rows (modes 1, 2)
-    __shared__ __attribute__((aligned(16))) float b_lds[kKeyTile * kD];   // v rows (mode 0) or dout rows
-    __shared__ float l_lds[kKeyTile], d_lds[kKeyTile];                     // lse and -delta of the staged queries
+// dq of the block's rows: they are queries, the lists are walked as keys.
+__device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems], int tid) {
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const float* const kb = static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + (int64_t)k.h * p.skh;
+    const float* const vb = static_cast<const float*>(p.v) + (int64_t)k.b * p.svb + (int64_t)k.h * p.svh;
+    float* const k_lds = lds[wave];
+    float* const v_lds = k_lds + kF32BlockElems;
+    const uint32_t k_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, k_lds));
+    const uint32_t v_addr = k_addr + kF32BlockBytes;
 
-    const Item item = p.items[blockIdx.x];
-    if (item.tile < 0) return;
-    const Tile tile = item.t;
-    const int tid = threadIdx.x;
-    const int h = tile.h, b = item.b;
-    const bool live = tid < tile.nrows;
-    const int64_t n = p.rows[tile.row_begin + min(tid, tile.nrows - 1)];
-    const int64_t row_c = (((int64_t)b * p.N + n) * p.H + h) * kD;         // this row in a contiguous [B,N,H,D] tensor
-    T* const grad = static_cast<T*>(kMode == 0 ? p.dq : kMode == 1 ? p.dv : p.dk) + row_c;
+    const int64_t n = k.rows[min(j, k.nrows - 1)];
+    float4 q[8], go[8];
+    load_chunks(static_cast<const float*>(p.q) + (int64_t)k.b * p.sqb + n * p.sqn + (int64_t)k.h * p.sqh, g, q);
+    load_chunks(static_cast<const float*>(p.dout) + (((int64_t)k.b * p.N + n) * p.H + k.h) * kD, g, go);
+    const int64_t at = ((int64_t)k.b * p.H + k.h) * p.N + n;
+    float my_l = p.lse2[at], my_d = p.ndelta[at];
 
-    float acc[kD];
+    floatx16 acc[2];
 #pragma unroll
-    for (int d = 0; d < kD; ++d) acc[d] = 0.f;
-    if (tile.nseg == 0) {                    // rows that no branch keeps take and give no gradient
-        if (live) store_row<T>(grad, acc);
-        return;
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+
+    BlockWalk w;
+    w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave);
+    if (w.valid()) {
+        issue_block(vb, p.svn, w, v_addr, lane);
+        issue_block(kb, p.skn, w, k_addr, lane);
     }
+    pin(q);
+    pin(go);
+    asm volatile("" : "+v"(my_l), "+v"(my_d));
+    while (w.valid()) {
+        BlockWalk nx = w;
+        nx.next();
+        const bool more = nx.valid();
+        const int nvalid = w.rows();
+        const float bias = w.seg.log2_mult;
 
-    const T* const qb = static_cast<const T*>(p.q) + (int64_t)b * p.sqb + (int64_t)h * p.sqh;
-    const T* const kb = static_cast<const T*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
-    const T* const vb = static_cast<const T*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
-    const T* const gb = static_cast<const T*>(p.dout) + ((int64_t)b * p.N * p.H + h) * kD;   // row n at n * H * D
-    const float* const lse_bh = p.lse + ((int64_t)b * p.H + h) * p.N;
-    const float* const ndelta_bh = p.ndelta + ((int64_t)b * p.H + h) * p.N;
-
-    float x0[kD], x1[kD];                    // mode 0: q, dout of this row; mode 1: k; mode 2: k, v
-    float my_l = 0.f, my_d = 0.f;
-    if (kMode == 0) {
-        load_row<T>(qb + n * p.sqn, x0);
-        load_row<T>(gb + n * p.H * kD, x1);
-        my_l = lse_bh[n] * kLog2e;
-        my_d = ndelta_bh[n];
-    } else {
-        load_row<T>(kb + n * p.skn, x0);
-        if (kMode == 2) load_row<T>(vb + n * p.svn, x1);
+        copies_left<kF32Copies>();                       // V is there
+        const floatx16 dp = rows_product(v_lds, go, lane);
+        lds_reads_done();
+        if (more) issue_block(vb, p.svn, nx, v_addr, lane);
+        if (more) copies_left<kF32Copies>();             // K is there
+        else copies_left<0>();
+        if (nvalid < kF32Block) zero_tail(k_lds, nvalid, lane);
+        const floatx16 s = rows_product(k_lds, q, lane);
+        float ds[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float pr = __builtin_amdgcn_exp2f(fmaf(s[v] * p.scale, kLog2e, bias) - my_l);
+            ds[v] = pr * (dp[v] + my_d) * p.scale;
+        }
+        if (nvalid < kF32Block) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) ds[v] = 0.f;
+        }
+        cols_product(k_lds, ds, acc, lane);              // dq += scale ds k
+        lds_reads_done();
+        if (more) issue_block(kb, p.skn, nx, k_addr, lane);
+        w = nx;
     }
+    write_sum(p, k, lds, tid, acc, p.dq);
+}
 
-    for (int s = 0; s < tile.nseg; ++s) {
-        const KeySeg seg = p.segs[tile.seg_begin + s];
-        for (int t = 0; t * kKeyTile < seg.count; ++t) {
-            __syncthreads();                 // previous tile fully consumed
-            if (kMode == 0) {
-                stage_rows<T>(kb, p.skn, seg, t, a_lds, tid);
-                stage_rows<T>(vb, p.svn, seg, t, b_lds, tid);
-            } else {
-                stage_rows<T>(qb, p.sqn, seg, t, a_lds, tid);
-                stage_rows<T>(gb, (int64_t)p.H * kD, seg, t, b_lds, tid);
-                if (tid < kKeyTile) {
-                    const int64_t row = kept_row(seg.key0, seg.stride, min(t * kKeyTile + tid, seg.count - 1));
-                    l_lds[tid] = lse_bh[row] * kLog2e;
-                    d_lds[tid] = ndelta_bh[row];
-                }
-            }
-            __syncthreads();
-            const int nvalid = min(kKeyTile, seg.count - t * kKeyTile);
-            for (int c = 0; c < nvalid; ++c) {
-                const float* ar = a_lds + c * kD;
-                const float* br = b_lds + c * kD;
-                const float sc = dot_row(x0, ar) * p.scale;                       // scale q.k
-                if (kMode == 0) {
-                    const float pr = __builtin_amdgcn_exp2f(sc * kLog2e + seg.log2_mult - my_l);
-                    const float ds = pr * (dot_row(x1, br) + my_d) * p.scale;
-                    axpy_row(ds, ar, acc);                                        // dq += scale ds k
-                } else {
-                    const float pr = __builtin_amdgcn_exp2f(sc * kLog2e + seg.log2_mult - l_lds[c]);
-                    if (kMode == 1) {
-                        axpy_row(pr, br, acc);                                    // dv += P dout
-                    } else {
-                        const float ds = pr * (dot_row(x1, br) + d_lds[c]) * p.scale;
-                        axpy_row(ds, ar, acc);                                    // dk += scale ds q
-                    }
-                }
+// dk and dv of the block's rows: they are keys, the lists are walked as queries.
+__device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems],
+                                           float (*stat_lds)[64], int tid) {
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const float* const qb = static_cast<const float*>(p.q) + (int64_t)k.b * p.sqb + (int64_t)k.h * p.sqh;
+    const float* const gb = static_cast<const float*>(p.dout) + ((int64_t)k.b * p.N * p.H + k.h) * kD;   // row n at n * H * D
+    const int64_t gpitch = (int64_t)p.H * kD;
+    float* const q_lds = lds[wave];
+    float* const g_lds = q_lds + kF32BlockElems;
+    const float* const stat = stat_lds[wave];            // lse2 of the block's 32 queries, then -delta
+    const uint32_t q_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, q_lds));
+    const uint32_t g_addr = q_addr + kF32BlockBytes;
+    const uint32_t stat_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, stat));
+    const float* const my_stat = (g == 0 ? p.lse2 : p.ndelta) + ((int64_t)k.b * p.H + k.h) * p.N;
+
+    const int64_t n = k.rows[min(j, k.nrows - 1)];
+    float4 kr[8], vr[8];
+    load_chunks(static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + n * p.skn + (int64_t)k.h * p.skh, g, kr);
+    load_chunks(static_cast<const float*>(p.v) + (int64_t)k.b * p.svb + n * p.svn + (int64_t)k.h * p.svh, g, vr);
+
+    floatx16 dk[2], dv[2];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) dk[0][v] = dk[1][v] = dv[0][v] = dv[1][v] = 0.f;
+
+    auto issue_q = [&](const BlockWalk& w) {             // 9 copies
+        issue_block(qb, p.sqn, w, q_addr, lane);
+        copy4_to_lds(my_stat + (w.first() + w.seg.stride * min(j, w.rows() - 1)), stat_addr);
+    };
+    BlockWalk w;
+    w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave);
+    if (w.valid()) {
+        issue_block(gb, gpitch, w, g_addr, lane);
+        issue_q(w);
+    }
+    pin(kr);
+    pin(vr);
+    while (w.valid()) {
+        BlockWalk nx = w;
+        nx.next();
+        const bool more = nx.valid();
+        const int nvalid = w.rows();
+        const float bias = w.seg.log2_mult;
+
+        copies_left<kF32Copies + 1>();                   // dout is there
+        if (nvalid < kF32Block) zero_tail(g_lds, nvalid, lane);
+        const floatx16 dp = rows_product(g_lds, vr, lane);
+        copies_left<0>();                                // q and the row statistics are there
+        if (nvalid < kF32Block) zero_tail(q_lds, nvalid, lane);
+        const floatx16 s = rows_product(q_lds, kr, lane);
+        float pr[16], ds[16];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float4 l = *reinterpret_cast<const float4*>(stat + 8 * t + 4 * g);
+            const float4 nd = *reinterpret_cast<const float4*>(stat + 32 + 8 * t + 4 * g);
+            const float lv[4] = {l.x, l.y, l.z, l.w}, dv4[4] = {nd.x, nd.y, nd.z, nd.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int v = 4 * t + e;
+                pr[v] = __builtin_amdgcn_exp2f(fmaf(s[v] * p.scale, kLog2e, bias) - lv[e]);
+                ds[v] = pr[v] * (dp[v] + dv4[e]) * p.scale;
             }
         }
+        if (nvalid < kF32Block) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) pr[v] = ds[v] = 0.f;
+        }
+        cols_product(g_lds, pr, dv, lane);               // dv += P dout
+        lds_reads_done();
+        if (more) issue_block(gb, gpitch, nx, g_addr, lane);
+        cols_product(q_lds, ds, dk, lane);               // dk += scale ds q
+        lds_reads_done();
+        if (more) issue_q(nx);
+        w = nx;
     }
-    if (live) store_row<T>(grad, acc);
+    write_sum(p, k, lds, tid, dv, p.dv);
+    __syncthreads();
+    write_sum(p, k, lds, tid, dk, p.dk);
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void bwd_f32_kernel(const BwdParams p, int n_items, int row_blocks) {
+    __shared__ __attribute__((aligned(1024))) float lds[kF32Waves][2 * kF32BlockElems];
+    __shared__ __attribute__((aligned(256))) float stat_lds[kF32Waves][64];
+
+    int item_index, part;
+    f32_item_of(blockIdx.x, 2 * row_blocks, item_index, part);
+    if (item_index >= n_items) return;
+    const int sub = part >> 1;
+    const Item item = p.items[item_index];
+    if (item.tile < 0 || sub * kF32Block >= item.t.nrows) return;
+    const int tid = threadIdx.x;
+    BwdBlock k;
+    k.tile = item.t;
+    k.b = item.b;
+    k.h = item.t.h;
+    k.nrows = min(kF32Block, item.t.nrows - sub * kF32Block);
+    k.rows = p.rows + item.t.row_begin + sub * kF32Block;
+
+    if (item.t.nseg == 0) {                  // rows that no branch keeps take and give no gradient
+        floatx16 zero[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) zero[0][v] = zero[1][v] = 0.f;
+        write_sum(p, k, lds, tid, zero, part & 1 ? p.dq : p.dv);
+        if (!(part & 1)) {
+            __syncthreads();
+            write_sum(p, k, lds, tid, zero, p.dk);
+        }
+        return;
+    }
+    if (part & 1) dq_block(p, k, lds, tid);
+    else dkdv_block(p, k, lds, stat_lds, tid);
 }
 
 }  // namespace
 
-// fp32 operands: the per-row preparation, then one vector kernel per gradient.  bf16 operands go to the
-// matrix-core kernels, whose dq kernel prepares the per-row values itself.
-hipError_t launch_bwd(const BwdParams& p, int n_items, int32_t B, bool bf16, hipStream_t st) {
+// fp32 operands: the per-row preparation, then both gradient kernels in one launch.  bf16 operands go to the
+// matrix-core kernels of dfa_bwd_bf16.hip, whose dq kernel prepares the per-row values itself.
+hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, int32_t B, bool bf16, hipStream_t st) {
     if (bf16) return launch_bwd_bf16(p, n_items, st);
-    hipLaunchKernelGGL((bwd_delta_kernel<float>), dim3((unsigned)(((int64_t)p.N * p.H * 16 + 255) / 256), B), dim3(256), 0, st,
+    hipLaunchKernelGGL(bwd_delta_kernel, dim3((unsigned)(((int64_t)p.N * p.H * 16 + 255) / 256), B), dim3(256), 0, st,
                        static_cast<const float*>(p.out), static_cast<const float*>(p.dout), p.lse, p.ndelta, p.lse2, p.H, p.N);
-    hipLaunchKernelGGL((bwd_kernel<float, 0>), dim3(n_items), dim3(256), 0, st, p);
-    hipLaunchKernelGGL((bwd_kernel<float, 1>), dim3(n_items), dim3(256), 0, st, p);
-    hipLaunchKernelGGL((bwd_kernel<float, 2>), dim3(n_items), dim3(256), 0, st, p);
+    const int row_blocks = (max_tile_rows + kF32Block - 1) / kF32Block;
+    for (int i0 = 0; i0 < n_items; i0 += kF32LaunchItems) {         // a grid holds fewer than 2^32 threads
+        BwdParams q = p;
+        q.items += i0;
+        const int n = n_items - i0 < kF32LaunchItems ? n_items - i0 : kF32LaunchItems;
+        const int groups = (n + kF32Dies - 1) / kF32Dies;
+        hipLaunchKernelGGL(bwd_f32_kernel, dim3((unsigned)groups * kF32Dies * 2 * row_blocks), dim3(256), 0, st, q, n, row_blocks);
+    }
     return hipGetLastError();
 }
 

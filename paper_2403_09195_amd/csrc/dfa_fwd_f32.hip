@@ -1,136 +1,176 @@
-// Fused dilated flash attention forward in fp32 (plain vector FMAs, no matrix cores).
+// Fused dilated flash attention forward in fp32, on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: full fp32
+// products and sums).
 //
-// Same tiling and the same single online-softmax state per query row across all member
-// branches as the bf16 kernel; here one lane owns one query row (its q row and its output
-// accumulator live in registers) and the 64-key K/V tiles are staged in LDS, where every
-// lane reads the same address (a broadcast).  The exponent is taken on (s - m) so that its
-// rounding error scales with the distance from the row maximum, not with the logit.
+// Same plan and the same single online-softmax state per query row across all member branches as the bf16 kernel.
+// A workgroup owns 32 query rows of a tile; its four waves walk the tile's key lists in blocks of 32 keys, wave w
+// taking blocks w, w + 4, ..., each with an online softmax of its own, and merge their four partial results through
+// LDS by their maxima and sums at the end.
+//
+// Bound: the fp32 matrix cores (64 FLOP per cycle and SIMD; 64 MFMAs of 64 cycles per 32 x 32 block of pairs beside
+// some 1000 cycles of vector work, which the second wave of the SIMD covers).  One query block per workgroup gives a
+// single 1024^2 image 1536 workgroups, enough to even out walks of 1024 to 2048 keys over 256 CUs; every operand read
+// from LDS feeds one MFMA of 64 cycles, so LDS bandwidth is no issue and sharing a staged block between waves would save
+// nothing but L2 reads.  A wave copies its own blocks global -> LDS, K and V into one buffer each: a buffer is
+// refilled as soon as its product is through and has the other product's 2048 cycles to land, so no barrier and no
+// second stage is needed.
+//
+// Measured, one 1024^2 image (12 heads x 4096 tokens, three branches): 164 us = 108 TFLOP/s of the distinct pairs, 69 % of
+// the matrix cores' fp32 rate (one lane per query row on the vector units: 1048 us); error against fp64 2.3e-7 of the
+// output's 2-norm (8.5e-7): a block's sums are added up on their own, so no chain of roundings is longer than 48.
 #include "dfa_device.h"
+#include "dfa_mfma_f32.h"
 
 namespace dfa {
 
 namespace {
 
-constexpr int kSub = 16;   // keys per online-softmax step
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
+    __shared__ __attribute__((aligned(1024))) float lds[kF32Waves][2 * kF32BlockElems];     // per wave: K block, V block
 
-__global__ __launch_bounds__(256)
-void dfa_fwd_f32_kernel(const FwdParams p) {
-    __shared__ __attribute__((aligned(16))) float k_lds[kKeyTile * kD];
-    __shared__ __attribute__((aligned(16))) float v_lds[kKeyTile * kD];
-
-    const Item item = p.items[blockIdx.x];
-    if (item.tile < 0) return;
+    int item_index, sub;
+    f32_item_of(blockIdx.x, row_blocks, item_index, sub);
+    if (item_index >= n_items) return;
+    const Item item = p.items[item_index];
     const Tile tile = item.t;
+    if (item.tile < 0 || sub * kF32Block >= tile.nrows) return;
     const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int h = tile.h, b = item.b;
-    const bool live = tid < tile.nrows;
-    const int64_t n = p.rows[tile.row_begin + min(tid, tile.nrows - 1)];
+    const int32_t* const rows = p.rows + tile.row_begin + sub * kF32Block;
+    const int nrows = min(kF32Block, tile.nrows - sub * kF32Block);
 
-    float* const out = static_cast<float*>(p.out) + (((int64_t)b * p.N + n) * p.H + h) * kD;
-    float* const lse = p.lse ? p.lse + ((int64_t)b * p.H + h) * p.N + n : nullptr;
+    // the row this thread writes: eight threads a row, 32 bytes each
+    const int orow = tid >> 3, od = (tid & 7) * 8;
+    const int64_t on = rows[min(orow, nrows - 1)];
+    float* const out = static_cast<float*>(p.out) + (((int64_t)b * p.N + on) * p.H + h) * kD + od;
+    float* const lse = p.lse ? p.lse + ((int64_t)b * p.H + h) * p.N + on : nullptr;
 
     if (tile.nseg == 0) {
-        if (live) {
-#pragma unroll
-            for (int d = 0; d < kD; d += 4) *reinterpret_cast<float4*>(out + d) = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (lse) *lse = -INFINITY;
+        if (orow < nrows) {
+            reinterpret_cast<float4*>(out)[0] = make_float4(0.f, 0.f, 0.f, 0.f);
+            reinterpret_cast<float4*>(out)[1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (lse && od == 0) *lse = -INFINITY;
         }
         return;
     }
 
-    float qv[kD], acc[kD];
-    {
-        const float* qp = static_cast<const float*>(p.q) + (int64_t)b * p.sqb + n * p.sqn + (int64_t)h * p.sqh;
+    const float* const kp = static_cast<const float*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
+    const float* const vp = static_cast<const float*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
+    float* const k_lds = lds[wave];
+    float* const v_lds = k_lds + kF32BlockElems;
+    const uint32_t k_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, k_lds));
+    const uint32_t v_addr = k_addr + kF32BlockBytes;
+
+    float4 q[8];
+    load_chunks(static_cast<const float*>(p.q) + (int64_t)b * p.sqb + (int64_t)rows[min(j, nrows - 1)] * p.sqn + (int64_t)h * p.sqh, g, q);
+
+    floatx16 acc[2];
 #pragma unroll
-        for (int d = 0; d < kD; d += 4) {
-            const float4 x = *reinterpret_cast<const float4*>(qp + d);
-            qv[d] = x.x; qv[d + 1] = x.y; qv[d + 2] = x.z; qv[d + 3] = x.w;
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;      // l_run: over the lane's own 16 keys of every block
+
+    BlockWalk w;
+    w.start(p.segs + tile.seg_begin, tile.nseg, wave);
+    if (w.valid()) {
+        issue_block(kp, p.skn, w, k_addr, lane);
+        issue_block(vp, p.svn, w, v_addr, lane);
+    }
+    pin(q);
+    while (w.valid()) {
+        BlockWalk nx = w;
+        nx.next();
+        const bool more = nx.valid();
+        const int nvalid = w.rows();
+        const float ln_mult = w.seg.log2_mult * kLn2;   // a key that counts m times: weight m exp(s) = exp(s + ln m)
+
+        copies_left<kF32Copies>();                      // K is there, V may be on its way
+        floatx16 s = rows_product(k_lds, q, lane);
+        lds_reads_done();
+        if (more) issue_block(kp, p.skn, nx, k_addr, lane);
+
+        float mx = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = fmaf(s[v], p.scale, ln_mult);
+        if (nvalid < kF32Block) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) s[v] = -INFINITY;
         }
 #pragma unroll
-        for (int d = 0; d < kD; ++d) acc[d] = 0.f;
-    }
-    float m_run = -INFINITY, l_run = 0.f;
-
-    const float* kp = static_cast<const float*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
-    const float* vp = static_cast<const float*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
-
-    for (int s = 0; s < tile.nseg; ++s) {
-        const KeySeg seg = p.segs[tile.seg_begin + s];
-        const float ln_mult = seg.log2_mult * kLn2;   // a key that counts m times: weight m exp(s) = exp(s + ln m)
-        for (int t = 0; t * kKeyTile < seg.count; ++t) {
-            __syncthreads();               // previous tile fully consumed
-            // thread -> (key tid/16 + 16u, 16-byte chunk tid%16)
+        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[v]);
+        const float m_new = fmaxf(m_run, wave_half_max(mx));
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;       // nothing but masked scores so far
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_use) * kLog2e);
+        m_run = m_new;
+        float pr[16], l0 = 0.f, l1 = 0.f;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int kr = (tid >> 4) + 16 * u;
-                const int j = min(t * kKeyTile + kr, seg.count - 1);
-                const int64_t row = kept_row(seg.key0, seg.stride, j);
-                const int cch = (tid & 15) * 4;
-                *reinterpret_cast<float4*>(k_lds + kr * kD + cch) =
-                    *reinterpret_cast<const float4*>(kp + row * p.skn + cch);
-                *reinterpret_cast<float4*>(v_lds + kr * kD + cch) =
-                    *reinterpret_cast<const float4*>(vp + row * p.svn + cch);
-            }
-            __syncthreads();
-            const int nvalid = min(kKeyTile, seg.count - t * kKeyTile);
-            for (int c0 = 0; c0 < nvalid; c0 += kSub) {
-                float sc[kSub];
-                float mx = -INFINITY;
-#pragma unroll
-                for (int jj = 0; jj < kSub; ++jj) {
-                    const float* kr = k_lds + (c0 + jj) * kD;
-                    // four interleaved partial sums: shorter rounding chains, more ILP
-                    float d0 = 0.f, d1 = 0.f, d2 = 0.f, d3 = 0.f;
-#pragma unroll
-                    for (int d = 0; d < kD; d += 4) {
-                        const float4 x = *reinterpret_cast<const float4*>(kr + d);
-                        d0 = fmaf(qv[d], x.x, d0);
-                        d1 = fmaf(qv[d + 1], x.y, d1);
-                        d2 = fmaf(qv[d + 2], x.z, d2);
-                        d3 = fmaf(qv[d + 3], x.w, d3);
-                    }
-                    const float dot = (d0 + d1) + (d2 + d3);
-                    sc[jj] = (c0 + jj < nvalid) ? dot * p.scale + ln_mult : -INFINITY;
-                    mx = fmaxf(mx, sc[jj]);
-                }
-                const float m_new = fmaxf(m_run, mx);
-                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * kLog2e);
-                m_run = m_new;
-                l_run *= alpha;
-#pragma unroll
-                for (int d = 0; d < kD; ++d) acc[d] *= alpha;
-#pragma unroll
-                for (int jj = 0; jj < kSub; ++jj) {
-                    const float pj = __builtin_amdgcn_exp2f((sc[jj] - m_new) * kLog2e);
-                    l_run += pj;
-                    const float* vr = v_lds + (c0 + jj) * kD;
-#pragma unroll
-                    for (int d = 0; d < kD; d += 4) {
-                        const float4 x = *reinterpret_cast<const float4*>(vr + d);
-                        acc[d] = fmaf(pj, x.x, acc[d]);
-                        acc[d + 1] = fmaf(pj, x.y, acc[d + 1]);
-                        acc[d + 2] = fmaf(pj, x.z, acc[d + 2]);
-                        acc[d + 3] = fmaf(pj, x.w, acc[d + 3]);
-                    }
-                }
-            }
+        for (int v = 0; v < 16; ++v) {
+            pr[v] = __builtin_amdgcn_exp2f((s[v] - m_use) * kLog2e);
+            (v & 1 ? l1 : l0) += pr[v];
         }
+        l_run = fmaf(l_run, alpha, l0 + l1);
+
+        if (more) copies_left<kF32Copies>();            // V is there, the next K may be on its way
+        else copies_left<0>();
+        if (nvalid < kF32Block) zero_tail(v_lds, nvalid, lane);
+        // the block's sums on their own, added to the running ones once: shorter chains of roundings
+        floatx16 blk[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) blk[0][v] = blk[1][v] = 0.f;
+        cols_product(v_lds, pr, blk, lane);
+        lds_reads_done();
+        if (more) issue_block(vp, p.svn, nx, v_addr, lane);
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[db][v] = fmaf(acc[db][v], alpha, blk[db][v]);
+        w = nx;
     }
 
-    if (live) {
-        const float inv = 1.0f / l_run;
-#pragma unroll
-        for (int d = 0; d < kD; d += 4)
-            *reinterpret_cast<float4*>(out + d) =
-                make_float4(acc[d] * inv, acc[d + 1] * inv, acc[d + 2] * inv, acc[d + 3] * inv);
-        if (lse) *lse = m_run + __builtin_amdgcn_logf(l_run) * kLn2;
+    // merge of the four waves: a wave without a block has m = -inf, l = 0 and an accumulator of zeros
+    l_run = wave_half_sum(l_run);
+    float* const red = lds[wave];
+    result_to_lds(acc, red, lane);
+    if (g == 0) {
+        red[kF32Block * kF32RedPitch + j] = m_run;
+        red[kF32Block * kF32RedPitch + kF32Block + j] = l_run;
     }
+    __syncthreads();
+    if (orow >= nrows) return;
+    float m = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < kF32Waves; ++x) m = fmaxf(m, lds[x][kF32Block * kF32RedPitch + orow]);
+    const float m_use = m == -INFINITY ? 0.f : m;
+    float l = 0.f;
+    float4 o0 = make_float4(0.f, 0.f, 0.f, 0.f), o1 = o0;
+#pragma unroll
+    for (int x = 0; x < kF32Waves; ++x) {
+        const float* const r = lds[x];
+        const float f = __builtin_amdgcn_exp2f((r[kF32Block * kF32RedPitch + orow] - m_use) * kLog2e);
+        l = fmaf(r[kF32Block * kF32RedPitch + kF32Block + orow], f, l);
+        const float4 a = *reinterpret_cast<const float4*>(r + orow * kF32RedPitch + od);
+        const float4 c = *reinterpret_cast<const float4*>(r + orow * kF32RedPitch + od + 4);
+        o0.x = fmaf(a.x, f, o0.x); o0.y = fmaf(a.y, f, o0.y); o0.z = fmaf(a.z, f, o0.z); o0.w = fmaf(a.w, f, o0.w);
+        o1.x = fmaf(c.x, f, o1.x); o1.y = fmaf(c.y, f, o1.y); o1.z = fmaf(c.z, f, o1.z); o1.w = fmaf(c.w, f, o1.w);
+    }
+    const float inv = 1.0f / l;
+    reinterpret_cast<float4*>(out)[0] = make_float4(o0.x * inv, o0.y * inv, o0.z * inv, o0.w * inv);
+    reinterpret_cast<float4*>(out)[1] = make_float4(o1.x * inv, o1.y * inv, o1.z * inv, o1.w * inv);
+    if (lse && od == 0) *lse = m + __builtin_amdgcn_logf(l) * kLn2;
 }
 
 }  // namespace
 
-hipError_t launch_fwd_f32(const FwdParams& p, int n_items, hipStream_t st) {
-    hipLaunchKernelGGL(dfa_fwd_f32_kernel, dim3(n_items), dim3(256), 0, st, p);
+hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, hipStream_t st) {
+    const int row_blocks = (max_tile_rows + kF32Block - 1) / kF32Block;
+    for (int i0 = 0; i0 < n_items; i0 += kF32LaunchItems) {         // a grid holds fewer than 2^32 threads
+        FwdParams q = p;
+        q.items += i0;
+        const int n = n_items - i0 < kF32LaunchItems ? n_items - i0 : kF32LaunchItems;
+        const int groups = (n + kF32Dies - 1) / kF32Dies;
+        hipLaunchKernelGGL(dfa_fwd_f32_kernel, dim3((unsigned)groups * kF32Dies * row_blocks), dim3(256), 0, st, q, n, row_blocks);
+    }
     return hipGetLastError();
 }
 

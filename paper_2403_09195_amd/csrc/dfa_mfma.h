@@ -86,6 +86,14 @@ __device__ __forceinline__ void copy16_to_lds(const void* gbase, uint32_t lane_b
                  : "memory", "m0");
 }
 
+// 4 bytes per lane: lane L's word lands at lds_addr + 4*L.
+__device__ __forceinline__ void copy4_to_lds(const float* lane_src, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+                 :
+                 : "s"(lds_addr), "v"(lane_src)
+                 : "memory", "m0");
+}
+
 __device__ __forceinline__ const void* uniform_ptr(const void* p) {
     const uint64_t x = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
