@@ -321,6 +321,165 @@ void linear_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restri
     }
 }
 
+// ---- the resident form for launches that 256-row tiles do not fill -----------------------------------------------
+// 128 x BN tiles (BN = 128, 96 or 64; launch_linear_bf16 says when).  A workgroup of 4 waves stays for the whole launch and
+// works through its CU's tiles one after the other, as one stream of 64-k steps: stage i + S of the ring is fetched as
+// soon as every wave has stage i in registers, whichever tile it belongs to, so neither the first trip to memory of a tile
+// nor the write-out of the one before it stops the copies.  A wave (one per SIMD) computes 64 rows x BN/2 features.  Its
+// fragments are double-buffered in registers: while the MFMAs of one 32-k half run, the fragments of the next half are
+// read, also across the one barrier of a step.
+// Bound: with all CUs at it the L2's byte rate (28 KB per step of a 128 x 96 tile in 0.46 us and CU, 15 TB/s over the chip;
+// alone on the chip a workgroup takes 0.21 us).  One 1024^2 image: output projection (256 tiles) 13.0 -> 9.6 us, QKV
+// projection (768 tiles) 25.4 -> 22.5 us.
+// (512 threads in the launch bounds keep the compiler within 256 registers: above that it moves the accumulators through the
+// second half of the register file, two copies per product.)
+constexpr int kStreamBM = 128;
+template <int BN> constexpr uint32_t kStreamStageBytes = (kStreamBM + BN) * kLinBK * 2;
+template <int BN> constexpr int kStreamStages = BN == 128 ? 4 : BN == 96 ? 5 : 6;      // 128, 140 and 144 KB
+template <int BN> constexpr int kStreamOutPitch = BN + 16;      // bytes: BN / 2 features of one row, padded
+
+template <int BN>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void linear_stream_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, uint16_t* __restrict__ y,
+                          int K, int64_t ldx, int64_t ldw, int64_t ldy, int tiles, int tiles_n, int dies, int cus_per_die) {
+    constexpr int BM = kStreamBM, S = kStreamStages<BN>, MT = BM / 32, NT = BN / 32;              // 16-row / 16-feature blocks per wave
+    constexpr int kCopies = MT + NT;                                                  // copies per wave and stage
+    constexpr uint32_t kStage = kStreamStageBytes<BN>, kWBase = BM * kLinBK * 2;
+    constexpr int kPitch = kStreamOutPitch<BN>;
+    __shared__ __attribute__((aligned(1024))) char lds[S * kStage + 4 * 16 * kPitch];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
+    const int r8 = lane >> 3;
+    const int chunk = (lane & 7) ^ lin_swizzle(r8);
+    const uint32_t x_step = (uint32_t)(16 * ldx), w_step = (uint32_t)(16 * ldw);      // bytes per 8 rows
+    const uint32_t x_off = (uint32_t)(((BM / 4) * wave + r8) * ldx * 2) + 16u * chunk;
+    const uint32_t w_off = (uint32_t)(((BN / 4) * wave + r8) * ldw * 2) + 16u * chunk;
+    const uint32_t lds_addr = (uint32_t)(uintptr_t)DFA_LDS_PTR(void, &lds[0]);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int frag = r16 * kLinBK + 8 * (g4 ^ lin_swizzle(r16));
+
+    // this workgroup's tiles: first, first + cus_per_die, ... of its die's list
+    const int die = blockIdx.x % dies, per_die = (tiles + dies - 1) / dies;
+    const int die_first = die * per_die, die_tiles = min(per_die, tiles - die_first);
+    const int first = blockIdx.x / dies;
+    if (first >= die_tiles) return;
+    const int n_k = K / kLinBK;
+    const int total = ((die_tiles - first - 1) / cus_per_die + 1) * n_k;             // k-steps of all its tiles
+
+    // the stream of copies
+    int ij = first, iks = 0, issued = 0;
+    auto issue = [&](int slot) {
+        const int t = die_first + ij;
+        const void* const xb = uniform_ptr(x + (int64_t)(t / tiles_n) * BM * ldx + (int64_t)iks * kLinBK);
+        const void* const wb = uniform_ptr(w + (int64_t)(t % tiles_n) * BN * ldw + (int64_t)iks * kLinBK);
+        const uint32_t at = lds_addr + slot * kStage;
+#pragma unroll
+        for (int u = 0; u < MT; ++u) copy16_to_lds(xb, x_off + u * x_step, at + ((BM / 4) * wave + 8 * u) * 128);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) copy16_to_lds(wb, w_off + u * w_step, at + kWBase + ((BN / 4) * wave + 8 * u) * 128);
+        if (++iks == n_k) { iks = 0; ij += cus_per_die; }
+        ++issued;
+    };
+    // waits until all but the youngest `ahead` stages of this wave's copies have landed (stores of a tile before count as
+    // well: the wait is then longer than it has to be, never shorter)
+    auto landed = [&](int ahead) {
+        // (S - 2 at most)
+        if (S > 5 && ahead >= 4) wait_vmcnt<(S > 5 ? 4 : 0) * kCopies>();
+        else if (S > 4 && ahead >= 3) wait_vmcnt<(S > 4 ? 3 : 0) * kCopies>();
+        else if (S > 3 && ahead >= 2) wait_vmcnt<(S > 3 ? 2 : 0) * kCopies>();
+        else if (S > 2 && ahead >= 1) wait_vmcnt<kCopies>();
+        else wait_vmcnt<0>();
+    };
+    struct Frags { bf16x8 w[NT], x[MT]; };
+    auto read = [&](Frags& f, int slot, int kh) {
+        const uint16_t* xs = reinterpret_cast<const uint16_t*>(lds + slot * kStage) + (BM / 2) * wm * kLinBK + (frag ^ (32 * kh));
+        const uint16_t* ws = reinterpret_cast<const uint16_t*>(lds + slot * kStage + kWBase) + (BN / 2) * wn * kLinBK + (frag ^ (32 * kh));
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) f.w[nt] = *reinterpret_cast<const bf16x8*>(ws + 16 * nt * kLinBK);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) f.x[mt] = *reinterpret_cast<const bf16x8*>(xs + 16 * mt * kLinBK);
+    };
+
+    floatx4 acc[NT][MT];                   // [16-feature block][16-row block], as in linear_tile
+    auto multiply = [&](const Frags& f) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.x[mt], acc[nt][mt], 0, 0, 0);
+    };
+    // the reads of one half spread over the MFMAs of the other
+    auto weave = [&]() {
+#pragma unroll
+        for (int i = 0; i < MT + NT; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, MT * NT / (MT + NT), 0);
+        }
+    };
+
+    for (int s = 0; s < S && s < total; ++s) issue(s);
+    landed(issued - 1);
+    __syncthreads();
+    Frags f0, f1;
+    read(f0, 0, 0);
+    int step = 0, slot = 0;
+    for (int j = first; j < die_tiles; j += cus_per_die) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int ks = 0; ks < n_k; ++ks, ++step) {
+            read(f1, slot, 1);
+            multiply(f0);
+            weave();
+            const int next_slot = slot + 1 == S ? 0 : slot + 1;
+            // every wave has the whole of this slot in registers, and stage step + 1 has landed for every wave
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            landed(issued - step - 2);
+            __syncthreads();
+            if (issued < total) issue(slot);
+            read(f0, next_slot, 0);        // past the last step: an old slot, not used
+            multiply(f1);
+            weave();
+            slot = next_slot;
+        }
+        // write-out: 16 rows of the wave's tile at a time through its own piece of LDS.  No barrier: the piece belongs to
+        // this wave alone, and LDS operations of a wave complete in order.
+        const int t = die_first + j;
+        const int64_t m0 = (int64_t)(t / tiles_n) * BM + (BM / 2) * wm, n0 = (int64_t)(t % tiles_n) * BN + (BN / 2) * wn;
+        constexpr int kLanesPerRow = BN / 16, kChunks = 16 * kLanesPerRow;             // 16-byte pieces of BN / 2 features
+        char* const mine = lds + S * kStage + wave * (16 * kPitch);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const floatx4& a = acc[nt][mt];
+                const bf16x4 o = {(__bf16)a[0], (__bf16)a[1], (__bf16)a[2], (__bf16)a[3]};
+                *reinterpret_cast<bf16x4*>(mine + r16 * kPitch + (16 * nt + 4 * g4) * 2) = o;
+            }
+#pragma unroll
+            for (int c0 = 0; c0 < kChunks; c0 += 64) {
+                const int c = c0 + lane, row = c / kLanesPerRow, ch = c % kLanesPerRow;
+                if (kChunks % 64 == 0 || c < kChunks)
+                    *reinterpret_cast<u32x4*>(y + (m0 + 16 * mt + row) * ldy + n0 + 8 * ch) =
+                        *reinterpret_cast<const u32x4*>(mine + row * kPitch + 16 * ch);
+            }
+        }
+    }
+}
+
+template <int BN>
+hipError_t launch_stream(const void* x, const void* w, void* y, int64_t M, int32_t N, int32_t K,
+                         int64_t ldx, int64_t ldw, int64_t ldy, const ChipShape& chip, hipStream_t st) {
+    const int dies = chip.dies > 0 ? chip.dies : 1, cus_per_die = chip.cus / dies > 0 ? chip.cus / dies : 1;
+    const int tiles_n = N / BN, tiles = (int)(M / kStreamBM) * tiles_n, per_die = (tiles + dies - 1) / dies;
+    hipLaunchKernelGGL((linear_stream_kernel<BN>), dim3((per_die < cus_per_die ? per_die : cus_per_die) * dies), dim3(256), 0, st,
+                       static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), static_cast<uint16_t*>(y),
+                       K, ldx, ldw, ldy, tiles, tiles_n, dies, cus_per_die);
+    return hipGetLastError();
+}
+
 // A batch of independent products of one shape: workgroup (t, z) computes tile t of matrix z = z0 * batch_inner + z1,
 // whose operands start at x + z0 * xs0 + z1 * xs1 (elements), and likewise for w and y.  Plain tile order.
 template <int BN>
@@ -355,16 +514,38 @@ hipError_t launch_tiles(const void* x, const void* w, void* y, int64_t M, int32_
 
 hipError_t launch_linear_bf16(const void* x, const void* w, void* y, int64_t M, int32_t N, int32_t K,
                               int64_t ldx, int64_t ldw, int64_t ldy, const ChipShape& chip, hipStream_t st) {
-    // One workgroup per CU at a time.  The 256-feature tile moves fewer bytes per flop; the 128-feature
-    // tile is taken when the last round of wide tiles would leave too much of the chip idle.
-    bool wide = N % 256 == 0;
-    if (wide) {
-        const int64_t cus = chip.cus > 0 ? chip.cus : 1;
-        const int64_t tiles = (M / kLinBM) * (N / 256), rounds = (tiles + cus - 1) / cus;
-        wide = tiles * 10 >= rounds * cus * 8;
+    // One workgroup per CU at a time, so a launch lasts as long as the CU with most tiles.  A round of tiles costs about as
+    // much as the bytes it fetches, 64 (BM + BN) per k-step and CU, a round of 256 x 256 tiles 1.28 times that (its MFMAs
+    // show): measured over 256 to 32768 rows and 384 to 2304 features (K = 384 and 768), the least estimate is the fastest
+    // form or within 2 % of it.  Rows x features, us, 256 x 256 / 256 x 128 / 128 x 96 / 128 x 64 tiles at K = 768:
+    // 2048 x 768 13.0 / 12.5 / 9.6 / 9.4, 4096 x 768 13.4 / 13.0 / 9.6 / 13.1, 2048 x 2304 15.0 / 14.1 / 15.6 / 18.5,
+    // 4096 x 2304 22.7 / 25.4 / 22.5 / 28.5, 8192 x 2304 34.0 / 38.0 / 41.9 / 48.6.
+    const int64_t dies = chip.dies > 0 ? chip.dies : 1, cus = chip.cus / dies > 0 ? chip.cus / dies : 1;
+    auto per_die = [&](int bm, int bn) { return ((M / bm) * (N / bn) + dies - 1) / dies; };
+    auto rounds = [&](int bm, int bn) { return (per_die(bm, bn) + cus - 1) / cus; };
+    int64_t least = rounds(256, 128) * (256 + 128);
+    int form = 0;                                                   // 256 x 128
+    auto consider = [&](int f, int64_t cost) {
+        if (cost < least) { least = cost; form = f; }
+    };
+    if (N % 256 == 0) {
+        // a last round that is at most half full goes in 128-feature halves (launch_tiles)
+        const int64_t rem = per_die(256, 256) % cus, halves = rem > 0 && 2 * rem <= cus;
+        consider(256, (rounds(256, 256) - halves) * 655 + halves * (256 + 128));
     }
-    return wide ? launch_tiles<256>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st)
-                : launch_tiles<128>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
+    // its copy lanes address 128 rows with 32-bit byte offsets
+    if (ldx < (1 << 22) && ldw < (1 << 22)) {
+        consider(128, rounds(128, 128) * (128 + 128));
+        if (N % 96 == 0) consider(96, rounds(128, 96) * (128 + 96));
+        consider(64, rounds(128, 64) * (128 + 64));
+    }
+    switch (form) {
+        case 256: return launch_tiles<256>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
+        case 128: return launch_stream<128>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
+        case 96: return launch_stream<96>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
+        case 64: return launch_stream<64>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
+        default: return launch_tiles<128>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
+    }
 }
 
 hipError_t launch_linear_bf16_batched(const void* x, const void* w, void* y, int64_t M, int32_t N, int32_t K,

@@ -66,6 +66,20 @@ def test_linear_identity_and_row_selection(B):
     assert B.linear(x, wide[:, :K], out=out) is out and bool((out == x[:, perm]).all())
 
 
+# one case per tile form of the launch rule and edge of its stream of k-steps: 128 x 64 (one tile per workgroup at most; a
+# single k-step, fewer k-steps than stages, more), 128 x 128 (feature counts that 96 does not divide), 128 x 96 (one tile per
+# workgroup, and three, whose k-steps follow one another in the ring: 3, 9 and 15 of them over 5 stages), 256 x 128
+@pytest.mark.parametrize("M,N,K", [(256, 128, 320), (2048, 768, 64), (1024, 384, 448), (4096, 1024, 64), (4096, 1024, 320),
+                                   (4096, 768, 192), (8192, 1152, 64), (8192, 1152, 192), (7936, 1152, 320), (2048, 2304, 128)])
+def test_linear_tile_forms(B, oracle, M, N, K):
+    x, xe = _bf16(403, 3, (M, K))
+    wide, we = _bf16(403, 10, (N, K + 8), std=0.02)
+    y = B.linear(x, wide[:, :K])                   # weight rows wider apart than K
+    ref = oracle.linear(xe, we[:, :K])
+    err = np.abs(to_f64(y) - ref)
+    assert np.all(err <= _linear_bar(xe, we[:, :K], ref))
+
+
 def test_linear_rejects_bad_shapes(B):
     import torch
     x = torch.zeros((256, 64), dtype=torch.bfloat16, device="cuda")
