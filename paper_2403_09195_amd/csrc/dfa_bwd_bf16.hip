@@ -11,13 +11,12 @@
 // rows are queries and keys alike, so the lists are the tile's keys when its rows act as
 // queries (dq) and the queries that see its rows when they act as keys (dk, dv): no gradient
 // needs an atomic.  The rows of the tile stay in registers as B operands; the walked rows go
-// global -> LDS (global_load_lds) three stages deep, each tensor in the layout its use needs:
-//   "A" layout: rows permuted by sigma and 16-byte chunks swizzled, read back as 32 rows x 16 d
-//               A operands of the first products (S^T and dP^T, walked row = MFMA row),
-//   "T" layout: rows in list order, unswizzled, read back transposed (ds_read_b64_tr_b16) as
-//               32 d x 16 rows A operands of the second product, whose B operand is the packed
-//               bf16 result of the first products straight from registers (the register order
-//               of the first product's result is the contraction order sigma fixes).
+// global -> LDS (global_load_lds) several stages deep, once per tensor, rows permuted by sigma and
+// 16-byte chunks swizzled (bwd_swizzle), and are read back in two ways:
+//   rows:       32 rows x 16 d A operands of the first products (S^T and dP^T, walked row = MFMA row),
+//   transposed: (ds_read_b64_tr_b16) 32 d x 16 rows A operands of the second product, whose B
+//               operand is the packed bf16 result of the first products straight from registers
+//               (the register order of the first product's result is the contraction order sigma fixes).
 // Per 32 walked rows:
 //   dq:  S^T = K~ Q^T, dP^T = V~ dO^T, dS^T = P (dP - delta), dQ^T += K~^T dS^T   (times scale at the end)
 //   dk, dv:  S = Q~ K^T, dP - delta = dO~ V^T started from -delta, P = exp2(..), dS = P (dP - delta),
@@ -31,7 +30,10 @@ namespace dfa {
 
 namespace {
 
-constexpr int kBwdStages = 3;
+constexpr int kDqStages = 4, kDkdvStages = 4;      // 64-row stages in LDS; all but one of them in flight or in use
+constexpr int kDkdvRows = 128;                     // rows of a dk/dv workgroup: a tile is up to kDkdvParts of them
+constexpr int kDkdvParts = kTileRows / kDkdvRows;
+constexpr int kDies = 8;                           // launch order of a plan: item i on die i mod 8
 
 // 4 bytes per lane from global memory straight into LDS: lane L's word lands at lds_addr + 4*L.
 __device__ __forceinline__ void copy4_to_lds(const void* gbase, uint32_t lane_byte_offset, uint32_t lds_addr) {
@@ -41,15 +43,47 @@ __device__ __forceinline__ void copy4_to_lds(const void* gbase, uint32_t lane_by
                  : "memory", "m0");
 }
 
+// 16-byte chunk swizzle of a stage: chunk c of LDS row rho sits at chunk c ^ bwd_swizzle(rho).  Any map of bits
+// 1 to 3 of rho onto 0 .. 7 spreads one chunk column of sixteen consecutive rows over all 64 banks (row reads); with bit
+// 1 on the chunk's top bit, the 32 lanes that read 64 bytes of each of four consecutive rows (transposed reads)
+// are spread over all banks too.
+__device__ __forceinline__ int bwd_swizzle(int rho) { return ((rho & 2) << 1) | ((rho & 4) >> 1) | ((rho & 8) >> 3); }
+
+// Element offsets of a lane's transposed reads inside a 16-row group of a stage: 32-d block db, walked positions
+// (lane & 15) / 4 + 8 * g (+ 4 for the second half), which sigma puts into LDS rows (lane & 15) / 4 + 4 * g (+ 8).
+struct TransposedLane {
+    int lo[2], hi[2];
+};
+__device__ __forceinline__ TransposedLane transposed_lane(int lane) {
+    const int g = lane >> 5, row = ((lane & 15) >> 2) + 4 * g;
+    const int chunk = (2 * ((lane >> 4) & 1) + ((lane >> 1) & 1)) ^ bwd_swizzle(row);
+    const int lo = row * kRowElems + 8 * chunk + 4 * (lane & 1);
+    TransposedLane t;
+    t.lo[0] = lo;
+    t.lo[1] = lo ^ 32;                            // db = 1: chunk + 4
+    t.hi[0] = (lo ^ 8) + 8 * kRowElems;           // eight rows down: the swizzle's lowest bit
+    t.hi[1] = (lo ^ 40) + 8 * kRowElems;
+    return t;
+}
+__device__ __forceinline__ bf16x8 read_transposed(const uint16_t* rows16, const TransposedLane& t, int db) {
+    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(DFA_LDS_PTR(short4v, rows16 + t.lo[db]));
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(DFA_LDS_PTR(short4v, rows16 + t.hi[db]));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // What a lane fetches in the two 1 KB copies a wave contributes to one 8 KB tensor stage: copy u
 // of wave w fills LDS rows rho = 8*(2w+u) .. +7, lane L lands at row L/8, chunk L%8.
 struct BwdCopyLane {
-    int a_pos, a_chunk;    // "A" layout: list position sigma(rho) and byte offset of the swizzled chunk (copy 0;
-                           // copy 1: position + 4, chunk ^ 64)
-    int t_pos, t_chunk;    // "T" layout: position rho, chunk in place (copy 1: position + 8)
+    int pos, chunk;        // list position sigma(rho) and byte offset of the swizzled chunk (copy 0; copy 1: position + 4, chunk ^ 16)
 };
+__device__ __forceinline__ BwdCopyLane bwd_copy_lane(int wave, int lane) {
+    BwdCopyLane cl;
+    const int rho = 16 * wave + (lane >> 3);                                    // LDS row of copy 0 (bit 3 clear)
+    cl.pos = (rho & 0x33) | ((rho & 4) << 1);                                   // sigma(rho)
+    cl.chunk = 16 * ((lane & 7) ^ bwd_swizzle(rho));
+    return cl;
+}
 
-template <bool kLayoutA>
 __device__ __forceinline__ void issue_tensor(const uint16_t* base, int64_t row_pitch, const KeyCursor& c,
                                              const BwdCopyLane& cl, int wave, uint32_t lds_stage) {
     const int j0 = c.t * kKeyTile;
@@ -60,10 +94,7 @@ __device__ __forceinline__ void issue_tensor(const uint16_t* base, int64_t row_p
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const uint32_t blk = (uint32_t)(2 * wave + u) * 1024u;
-        if (kLayoutA)
-            copy16_to_lds(gb, (uint32_t)min(cl.a_pos + 4 * u, room) * pitch + (cl.a_chunk ^ (64 * u)), lds_stage + blk);
-        else
-            copy16_to_lds(gb, (uint32_t)min(cl.t_pos + 8 * u, room) * pitch + cl.t_chunk, lds_stage + blk);
+        copy16_to_lds(gb, (uint32_t)min(cl.pos + 4 * u, room) * pitch + (cl.chunk ^ (16 * u)), lds_stage + blk);
     }
 }
 
@@ -135,13 +166,13 @@ __device__ __forceinline__ floatx16 load_ndelta(const float* dl) {
     return r;
 }
 
-// dq of a tile: its rows are queries, the lists are walked as keys (K in "A" and "T" layout, V in "A"
-// layout).  Four waves of 64 rows each.
+// dq of a tile: its rows are queries, the lists are walked as keys.  Four waves of 64 rows each.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void bwd_dq_bf16_kernel(const BwdParams p) {
-    constexpr int kTensors = 3;
+    constexpr int kTensors = 2;                                      // K, V
+    constexpr int kStages = kDqStages, kAhead = kStages - 1;
     constexpr int kCopies = 2 * kTensors;                            // per wave per stage
-    __shared__ __attribute__((aligned(1024))) uint16_t t_lds[kTensors][kBwdStages][kStageElems];
+    __shared__ __attribute__((aligned(1024))) uint16_t t_lds[kTensors][kStages][kStageElems];
     __shared__ int32_t row_idx[kTileRows];
     __shared__ KeySeg seg_lds[kMaxTileSegs];
 
@@ -186,42 +217,32 @@ void bwd_dq_bf16_kernel(const BwdParams p) {
     auto copy_lane = [&]() {
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        BwdCopyLane cl;
-        const int rho = 16 * wave + (ln >> 3);                                  // LDS row of copy 0 (bit 3 clear)
-        cl.a_pos = (rho & 0x33) | ((rho & 4) << 1);                             // sigma(rho)
-        cl.a_chunk = 16 * ((ln & 7) ^ k_swizzle(rho));
-        cl.t_pos = rho;
-        cl.t_chunk = 16 * (ln & 7);
-        return cl;
+        return bwd_copy_lane(wave, ln);
     };
-    // fragment reads: "A" layout row j of a 32-row block, chunk (2*kk + g) ^ swizzle(j); "T" layout as
-    // read_v_frag describes
-    const int frag_a = j * kRowElems + 8 * (g ^ k_swizzle(j));
-    const int frag_t = (((lane & 15) >> 2) + 8 * g) * kRowElems + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    // fragment reads: row j of a 32-row block, chunk (2*kk + g) ^ swizzle(j); transposed as TransposedLane describes
+    const int frag_a = j * kRowElems + 8 * (g ^ bwd_swizzle(j));
+    const TransposedLane frag_t = transposed_lane(lane);
 
     int n_steps = tile.n_steps;
 
     const uint32_t t_addr = (uint32_t)(uintptr_t)DFA_LDS_PTR(void, &t_lds[0][0][0]);
-    constexpr uint32_t kStageBytes = kStageElems * 2, kTensorBytes = kBwdStages * kStageBytes;
+    constexpr uint32_t kStageBytes = kStageElems * 2, kTensorBytes = kStages * kStageBytes;
 
     auto issue = [&](const KeyCursor& c, int slot) {
         const uint32_t st = t_addr + slot * kStageBytes;
         const BwdCopyLane cl = copy_lane();
-        issue_tensor<true>(kp, p.skn, c, cl, wave, st);
-        issue_tensor<true>(vp, p.svn, c, cl, wave, st + kTensorBytes);
-        issue_tensor<false>(kp, p.skn, c, cl, wave, st + 2 * kTensorBytes);
+        issue_tensor(kp, p.skn, c, cl, wave, st);
+        issue_tensor(vp, p.svn, c, cl, wave, st + kTensorBytes);
     };
 
-    // first two stages on their way before anything else
+    // first stages on their way before anything else
     KeyCursor pf;
     pf.s = 0;
     pf.t = 0;
     cursor_load(pf, seg_lds);
     KeyCursor cur = pf;
-    issue(pf, 0);
-    cursor_next(pf, seg_lds, tile.nseg);
-    if (n_steps > 1) {
-        issue(pf, 1);
+    for (int s = 0; s < min(kAhead, n_steps); ++s) {
+        issue(pf, s);
         cursor_next(pf, seg_lds, tile.nseg);
     }
 
@@ -295,12 +316,12 @@ void bwd_dq_bf16_kernel(const BwdParams p) {
             my_l2[1] -= cur.bias - bias_cur;
             bias_cur = cur.bias;
         }
-        // stage i has landed once at most the copies of stage i+1 are still outstanding (the loads of
-        // the own rows were issued after the first two stages, so the first wait covers them)
-        if (i == 0 || i + 1 >= n_steps) wait_vmcnt<0>(); else wait_vmcnt<kCopies>();
+        // stage i has landed once at most the copies of the kAhead - 1 stages after it are still outstanding (the loads of
+        // the own rows were issued after the first stages, so the first wait covers them)
+        if (i == 0 || i + kAhead > n_steps) wait_vmcnt<0>(); else wait_vmcnt<(kAhead - 1) * kCopies>();
         __syncthreads();       // every wave's share is in LDS, and everyone is done with stage i-1
-        if (i + 2 < n_steps) {
-            issue(pf, slot == 0 ? 2 : slot - 1);               // (slot + 2) % 3
+        if (i + kAhead < n_steps) {
+            issue(pf, slot == 0 ? kStages - 1 : slot - 1);     // the slot of stage i - 1
             cursor_next(pf, seg_lds, tile.nseg);
         }
         const int nvalid = min(kKeyTile, cur.count - cur.t * kKeyTile);
@@ -338,7 +359,7 @@ void bwd_dq_bf16_kernel(const BwdParams p) {
                 for (int db = 0; db < 2; ++db)
 #pragma unroll
                     for (int st = 0; st < 2; ++st) {
-                        const bf16x8 kt = read_v_frag(t_lds[2][slot] + (32 * ws + 16 * st) * kRowElems + frag_t + 32 * db);
+                        const bf16x8 kt = read_transposed(ka + 16 * st * kRowElems, frag_t, db);
 #pragma unroll
                         for (int blk = 0; blk < 2; ++blk)
                             acc[db][blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt, __builtin_bit_cast(bf16x8, pb[blk][st]), acc[db][blk], 0, 0, 0);
@@ -346,14 +367,15 @@ void bwd_dq_bf16_kernel(const BwdParams p) {
             }
         }
         cursor_next(cur, seg_lds, tile.nseg);
-        slot = slot == kBwdStages - 1 ? 0 : slot + 1;
+        slot = slot == kStages - 1 ? 0 : slot + 1;
     }
 
     // ---- epilogue: each wave lays its 64 rows out row-major in a piece of the (now idle) stages, at a
     // pitch of 144 bytes, and stores them 16 bytes per lane, eight lanes to a row, at the rows' tokens
     __syncthreads();           // every wave is done with the stages
     constexpr int kPitch = kD * 2 + 16;
-    char* mine = reinterpret_cast<char*>(&t_lds[wave >> 1][0][0]) + (wave & 1) * (64 * kPitch);
+    static_assert(sizeof(t_lds) >= 4 * 64 * kPitch, "every wave's rows fit the stages");
+    char* mine = reinterpret_cast<char*>(&t_lds[0][0][0]) + wave * (64 * kPitch);
     if (wave_live) {
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk)
@@ -381,24 +403,30 @@ void bwd_dq_bf16_kernel(const BwdParams p) {
 
 // dk and dv of a tile in one walk over its query lists.  Eight waves of 32 rows each (both
 // gradients of 64 rows would not fit a wave's registers): the scores are computed once for both,
-// and the walked Q and dO rows are copied once, each in both layouts.
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void bwd_dkdv_bf16_kernel(const BwdParams p) {
-    constexpr int kTensors = 4;                                      // Q "A", dO "A", Q "T", dO "T"
-    constexpr int kCopies = kTensors + 2;                            // per wave per stage, with lse and delta
-    __shared__ __attribute__((aligned(1024))) uint16_t t_lds[kTensors][kBwdStages][kStageElems];
-    __shared__ __attribute__((aligned(256))) float sc_lds[2][kBwdStages][kKeyTile];
-    __shared__ int32_t row_idx[kTileRows];
+// and the walked Q and dO rows are copied once.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void bwd_dkdv_bf16_kernel(const BwdParams p, int n_items) {
+    constexpr int kTensors = 2;                                      // Q, dO
+    constexpr int kStages = kDkdvStages, kAhead = kStages - 1;
+    constexpr int kCopies = 2 * kTensors + 1;                        // per wave per stage, with lse or delta
+    __shared__ __attribute__((aligned(1024))) uint16_t t_lds[kTensors][kStages][kStageElems];
+    __shared__ __attribute__((aligned(256))) float sc_lds[2][kStages][kKeyTile];
+    __shared__ int32_t row_idx[kDkdvRows];
     __shared__ KeySeg seg_lds[kMaxTileSegs];
 
-    const Item item = p.items[blockIdx.x];
-    if (item.tile < 0) return;
+    // the workgroups of a tile stay on the tile's die (see build_plan: item i runs on die i mod 8)
+    const int group = blockIdx.x / (kDies * kDkdvParts), rem = blockIdx.x % (kDies * kDkdvParts);
+    const int item_index = group * kDies + rem % kDies, row0 = rem / kDies * kDkdvRows;
+    if (item_index >= n_items) return;
+    const Item item = p.items[item_index];
+    if (item.tile < 0 || row0 >= item.t.nrows) return;
     const Tile tile = item.t;
+    const int nrows = min(kDkdvRows, tile.nrows - row0);
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int h = tile.h, b = item.b;
 
-    if (tid < kTileRows) row_idx[tid] = p.rows[tile.row_begin + min(tid, tile.nrows - 1)];
+    if (tid < kDkdvRows) row_idx[tid] = p.rows[tile.row_begin + row0 + min(tid, nrows - 1)];
     if (tid < tile.nseg) seg_lds[tid] = p.segs[tile.seg_begin + tid];
     __syncthreads();
 
@@ -409,7 +437,7 @@ void bwd_dkdv_bf16_kernel(const BwdParams p) {
     if (tile.nseg == 0) {
         // rows that no branch keeps take and give no gradient
         constexpr int kChunks = kD * 2 / 16;
-        for (int x = tid; x < tile.nrows * kChunks; x += 512) {
+        for (int x = tid; x < nrows * kChunks; x += 256) {
             const int rr = x / kChunks, ch = x % kChunks;
             const int64_t at = (out_bh + (int64_t)row_idx[rr] * p.H) * kD;
             *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(grad_k + at) + 16 * ch) = u32x4{0u, 0u, 0u, 0u};
@@ -426,35 +454,22 @@ void bwd_dkdv_bf16_kernel(const BwdParams p) {
     const float* const ndelta_bh = p.ndelta + ((int64_t)b * p.H + h) * p.N;
     const float* const lse2_bh = p.lse2 + ((int64_t)b * p.H + h) * p.N;
 
-    // one 1 KB copy per wave and tensor: wave w fills LDS rows rho = 8w .. 8w+7, lane L lands at row L/8, chunk L%8
-    const int rho = 8 * wave + (lane >> 3);
-    const int a_pos = (rho & 0x33) | ((rho & 4) << 1) | ((rho & 8) >> 1);      // sigma(rho)
-    const int a_chunk = 16 * ((lane & 7) ^ k_swizzle(rho));
-    const int t_chunk = 16 * (lane & 7);
-    const int frag_a = j * kRowElems + 8 * (g ^ k_swizzle(j));
-    const int frag_t = (((lane & 15) >> 2) + 8 * g) * kRowElems + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    const BwdCopyLane cl = bwd_copy_lane(wave, lane);
+    const int frag_a = j * kRowElems + 8 * (g ^ bwd_swizzle(j));
+    const TransposedLane frag_t = transposed_lane(lane);
 
     int n_steps = tile.n_steps;
 
     const uint32_t t_addr = (uint32_t)(uintptr_t)DFA_LDS_PTR(void, &t_lds[0][0][0]);
     const uint32_t sc_addr = (uint32_t)(uintptr_t)DFA_LDS_PTR(void, &sc_lds[0][0][0]);
-    constexpr uint32_t kStageBytes = kStageElems * 2, kTensorBytes = kBwdStages * kStageBytes;
+    constexpr uint32_t kStageBytes = kStageElems * 2, kTensorBytes = kStages * kStageBytes;
 
     auto issue = [&](const KeyCursor& c, int slot) {
-        const int j0 = c.t * kKeyTile;
-        const int room = c.count - 1 - j0;   // positions past the end of the list re-read its last row
-        const int64_t first = kept_row(c.key0, c.stride, j0);
-        const uint32_t qpitch = (uint32_t)(c.stride * p.sqn * 2), gpitch = (uint32_t)(c.stride * g_pitch * 2);
-        const void* qb = uniform_ptr(qp + first * p.sqn);
-        const void* gb = uniform_ptr(gp + first * g_pitch);
-        const uint32_t st = t_addr + slot * kStageBytes + wave * 1024u;
-        const uint32_t pa = (uint32_t)min(a_pos, room), pt = (uint32_t)min(rho, room);
-        copy16_to_lds(qb, pa * qpitch + a_chunk, st);
-        copy16_to_lds(gb, pa * gpitch + a_chunk, st + kTensorBytes);
-        copy16_to_lds(qb, pt * qpitch + t_chunk, st + 2 * kTensorBytes);
-        copy16_to_lds(gb, pt * gpitch + t_chunk, st + 3 * kTensorBytes);
-        issue_scalars(lse2_bh, c, lane, sc_addr + slot * (kKeyTile * 4));
-        issue_scalars(ndelta_bh, c, lane, sc_addr + (kBwdStages + slot) * (kKeyTile * 4));
+        const uint32_t st = t_addr + slot * kStageBytes;
+        issue_tensor(qp, p.sqn, c, cl, wave, st);
+        issue_tensor(gp, g_pitch, c, cl, wave, st + kTensorBytes);
+        // waves 0 and 1 bring lse, waves 2 and 3 delta (a copy per wave, so that every wave counts the same)
+        issue_scalars(wave < 2 ? lse2_bh : ndelta_bh, c, lane, sc_addr + ((wave >> 1) * kStages + slot) * (kKeyTile * 4));
     };
 
     KeyCursor pf;
@@ -462,10 +477,8 @@ void bwd_dkdv_bf16_kernel(const BwdParams p) {
     pf.t = 0;
     cursor_load(pf, seg_lds);
     KeyCursor cur = pf;
-    issue(pf, 0);
-    cursor_next(pf, seg_lds, tile.nseg);
-    if (n_steps > 1) {
-        issue(pf, 1);
+    for (int s = 0; s < min(kAhead, n_steps); ++s) {
+        issue(pf, s);
         cursor_next(pf, seg_lds, tile.nseg);
     }
 
@@ -495,14 +508,14 @@ void bwd_dkdv_bf16_kernel(const BwdParams p) {
         dk_acc[db] = zero16();
         dv_acc[db] = zero16();
     }
-    const bool wave_live = wave * 32 < tile.nrows;
+    const bool wave_live = wave * 32 < nrows;
 
     int slot = 0;
     for (int i = 0; i < n_steps; ++i) {
-        if (i == 0 || i + 1 >= n_steps) wait_vmcnt<0>(); else wait_vmcnt<kCopies>();
+        if (i == 0 || i + kAhead > n_steps) wait_vmcnt<0>(); else wait_vmcnt<(kAhead - 1) * kCopies>();
         __syncthreads();       // every wave's share is in LDS, and everyone is done with stage i-1
-        if (i + 2 < n_steps) {
-            issue(pf, slot == 0 ? 2 : slot - 1);               // (slot + 2) % 3
+        if (i + kAhead < n_steps) {
+            issue(pf, slot == 0 ? kStages - 1 : slot - 1);     // the slot of stage i - 1
             cursor_next(pf, seg_lds, tile.nseg);
         }
         const int nvalid = min(kKeyTile, cur.count - cur.t * kKeyTile);
@@ -535,23 +548,23 @@ void bwd_dkdv_bf16_kernel(const BwdParams p) {
                 for (int db = 0; db < 2; ++db)
 #pragma unroll
                     for (int st = 0; st < 2; ++st) {
-                        const int off = (32 * ws + 16 * st) * kRowElems + frag_t + 32 * db;
-                        const bf16x8 qt = read_v_frag(t_lds[2][slot] + off);
-                        const bf16x8 gt = read_v_frag(t_lds[3][slot] + off);
+                        const bf16x8 qt = read_transposed(qa + 16 * st * kRowElems, frag_t, db);
+                        const bf16x8 gt = read_transposed(ga + 16 * st * kRowElems, frag_t, db);
                         dv_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt, __builtin_bit_cast(bf16x8, pp[st]), dv_acc[db], 0, 0, 0);
                         dk_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt, __builtin_bit_cast(bf16x8, ps[st]), dk_acc[db], 0, 0, 0);
                     }
             }
         }
         cursor_next(cur, seg_lds, tile.nseg);
-        slot = slot == kBwdStages - 1 ? 0 : slot + 1;
+        slot = slot == kStages - 1 ? 0 : slot + 1;
     }
 
     // ---- epilogue: each wave lays its 32 rows of both gradients out row-major in a piece of the idle
     // stages (pitch 144 bytes) and stores them 16 bytes per lane, eight lanes to a row
     __syncthreads();           // every wave is done with the stages
     constexpr int kPitch = kD * 2 + 16;
-    char* mine = reinterpret_cast<char*>(&t_lds[wave >> 1][0][0]) + (wave & 1) * (64 * kPitch);   // 2 x 32 rows
+    static_assert(sizeof(t_lds) >= 4 * 64 * kPitch, "every wave's rows fit the stages");
+    char* mine = reinterpret_cast<char*>(&t_lds[0][0][0]) + wave * (64 * kPitch);   // 2 x 32 rows
     if (wave_live) {
 #pragma unroll
         for (int which = 0; which < 2; ++which)
@@ -572,7 +585,7 @@ void bwd_dkdv_bf16_kernel(const BwdParams p) {
             for (int s = 0; s < 4; ++s) {
                 const int row = 8 * s + srow, slot_r = wave * 32 + row;
                 const u32x4 val = *reinterpret_cast<const u32x4*>(mine + (32 * which + row) * kPitch + 16 * schunk);
-                if (slot_r < tile.nrows) {
+                if (slot_r < nrows) {
                     const int64_t n = row_idx[slot_r];
                     uint16_t* dst = (which == 0 ? grad_k : grad_v) + (out_bh + n * p.H) * kD;
                     *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(dst) + 16 * schunk) = val;
@@ -585,7 +598,7 @@ void bwd_dkdv_bf16_kernel(const BwdParams p) {
 
 hipError_t launch_bwd_bf16(const BwdParams& p, int n_items, hipStream_t st) {
     hipLaunchKernelGGL(bwd_dq_bf16_kernel, dim3(n_items), dim3(256), 0, st, p);
-    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel, dim3(n_items), dim3(512), 0, st, p);
+    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel, dim3((n_items + kDies - 1) / kDies * kDies * kDkdvParts), dim3(256), 0, st, p, n_items);
     return hipGetLastError();
 }
 
