@@ -35,12 +35,13 @@ struct DevicePlan {
     const KeySeg* segs = nullptr;
     const Item* items = nullptr;
     const float* block_mult = nullptr;   // plans of the bf16 forward only
+    bool short_walk = false;            // bf16 forward: the plan of short_plan, walked by launch_fwd_short
     bool packed_tiles = false;          // some tile packs several row groups: the kernel variant that reads block_mult
     int32_t n_items = 0;
     int32_t max_tile_rows = 1;     // most rows of any tile
     int device = 0;
     size_t bytes = 0;
-    // launches with few workgroups walk their tiles with n_split_wgs workgroups in all (see split_plan and
+    // other launches with few workgroups walk their tiles with n_split_wgs workgroups in all (see split_plan and
     // launch_fwd_bf16_split) when the caller brings a workspace for their partial results; 0: never split
     const SplitWg* split_wgs = nullptr;
     const ItemParts* item_parts = nullptr;
@@ -73,6 +74,7 @@ struct PackedPlan {
     int32_t n_items = 0;
     int32_t n_split_wgs = 0;
     int32_t max_tile_rows = 1;
+    bool short_walk = false;
     bool packed_tiles = false;
 };
 
@@ -94,10 +96,18 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
     HostPlan hp;
     build_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, packed, &hp);
     if (hp.items.size() > (size_t)0x7fffffff) return DFA_ERR_TOO_LARGE;
+    if (packed) {
+        split_plan(&hp, chip);
+        out->n_split_wgs = (int32_t)hp.split_wgs.size();
+        HostPlan sp;
+        if (short_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, hp, &sp)) {
+            out->short_walk = true;
+            hp = std::move(sp);
+        }
+    }
     const size_t b_rows = align256(hp.rows.size() * sizeof(int32_t));
     const size_t b_segs = align256(hp.segs.size() * sizeof(KeySeg) + sizeof(KeySeg));
     const size_t b_items = align256(hp.items.size() * sizeof(Item));
-    if (packed) split_plan(&hp, chip);
     const size_t b_wgs = align256(hp.split_wgs.size() * sizeof(SplitWg));
     const size_t b_parts = align256(hp.item_parts.size() * sizeof(ItemParts));
     const size_t b_wmult = packed ? align256((hp.segs.size() + 1) * kTileBlocks * sizeof(float)) : 0;
@@ -120,7 +130,6 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
         std::memcpy(out->bytes.data() + out->off_item_parts, hp.item_parts.data(), hp.item_parts.size() * sizeof(ItemParts));
     }
     out->n_items = (int32_t)hp.items.size();
-    out->n_split_wgs = (int32_t)hp.split_wgs.size();
     out->packed_tiles = hp.packed_tiles;
     for (const Tile& t : hp.tiles) out->max_tile_rows = std::max(out->max_tile_rows, t.nrows);
     return DFA_OK;
@@ -140,6 +149,7 @@ void point_plan(DevicePlan* dp, void* base, const PackedPlan& pp, int device) {
     dp->n_split_wgs = pp.n_split_wgs;
     dp->block_mult = reinterpret_cast<const float*>(b + pp.off_block_mult);
     dp->packed_tiles = pp.packed_tiles;
+    dp->short_walk = pp.short_walk;
     dp->max_tile_rows = pp.max_tile_rows;
 }
 
@@ -331,7 +341,9 @@ int launch_forward(const DevicePlan& dp, const void* q, const void* k, const voi
     p.split_wgs = dp.split_wgs; p.item_parts = dp.item_parts; p.split_ws = split_ws;
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
-    if (dt == DFA_BF16 && !out_f32 && dp.n_split_wgs > 0 && split_ws) {
+    if (dt == DFA_BF16 && !out_f32 && dp.short_walk) {
+        e = launch_fwd_short(p, dp.n_items, st);
+    } else if (dt == DFA_BF16 && !out_f32 && dp.n_split_wgs > 0 && split_ws) {
         // few workgroups: partial results per share of the key walk, then their log-sum-exp merge
         e = launch_fwd_bf16_split(p, dp.n_split_wgs, dp.packed_tiles, st);
         if (e == hipSuccess) e = launch_merge_split(p, dp.n_items, st);

@@ -1,0 +1,148 @@
+// Device-side building blocks of the kernels whose waves walk 32-row blocks of a tile's key lists on their own (small
+// launches, fp32), and of the transposed reads of swizzled stages (gfx950).
+#pragma once
+#include "dfa_device.h"
+#include "dfa_mfma.h"
+
+namespace dfa {
+
+constexpr int kDies = 8;                   // launch order of a plan: item i on die i mod 8
+constexpr int kLaunchItems = 1 << 19;      // most items of one launch (at most 16 workgroups of 256 threads each: a grid
+                                           // holds fewer than 2^32 threads)
+
+constexpr int kRedPitch = kD + 4;          // row pitch of the per-wave results in LDS (floats)
+constexpr int kBlockElems = kWalkBlock * kRowElems;      // one bf16 block of one tensor in LDS: 4 KB
+constexpr int kBlockBytes = kBlockElems * 2;
+constexpr int kBlockCopies = 4;            // wave-level copies per bf16 block (1 KB = 8 rows each)
+
+// Workgroup x of a launch of `parts` workgroups per item -> (item, part); the parts of an item stay on the item's die.
+__device__ __forceinline__ void item_of_part(int x, int parts, int& item, int& part) {
+    const int group = x / (kDies * parts), rem = x % (kDies * parts);
+    item = group * kDies + rem % kDies;
+    part = rem / kDies;
+}
+
+// A launch item in one scalar load.
+__device__ __forceinline__ Item load_item(const Item* items, int i) {
+    typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
+    static_assert(sizeof(Item) == sizeof(i32x8), "a launch item is eight words");
+    const i32x8 x = *reinterpret_cast<const __attribute__((address_space(4))) i32x8*>(reinterpret_cast<uintptr_t>(items + i));
+    return Item{x[0], x[1], Tile{x[2], x[3], x[4], x[5], x[6], x[7]}};
+}
+
+// The 32-row blocks of a tile's progressions, counted through; wave w takes blocks w, w + 4, w + 8, ...
+struct BlockWalk {
+    const KeySeg* segs;
+    int nseg, s, t;              // progression, block within it
+    KeySeg seg;
+
+    // through the constant address space: a scalar load.  (After the copies' memory clobber the compiler takes a vector
+    // load instead, whose wait would drain the copies in flight.)
+    __device__ __forceinline__ void load() {
+        typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+        const i32x4 x = *reinterpret_cast<const __attribute__((address_space(4))) i32x4*>(reinterpret_cast<uintptr_t>(segs + s));
+        seg.key0 = x[0];
+        seg.stride = x[1];
+        seg.count = x[2];
+        const int32_t mult = x[3];          // (the bit cast of an element in place would be that of element 0)
+        seg.log2_mult = __builtin_bit_cast(float, mult);
+    }
+    __device__ __forceinline__ void settle() {
+        while (s < nseg && t * kWalkBlock >= seg.count) {
+            t -= (seg.count + kWalkBlock - 1) / kWalkBlock;
+            if (++s < nseg) load();
+        }
+    }
+    __device__ __forceinline__ void start(const KeySeg* list, int n, int wave) {
+        segs = list;
+        nseg = n;
+        s = 0;
+        t = wave;
+        load();
+        settle();
+    }
+    __device__ __forceinline__ void next() {
+        t += kWalkWaves;
+        settle();
+    }
+    __device__ __forceinline__ bool valid() const { return s < nseg; }
+    __device__ __forceinline__ int rows() const { return min(kWalkBlock, seg.count - t * kWalkBlock); }
+    __device__ __forceinline__ int32_t first() const { return kept_row(seg.key0, seg.stride, t * kWalkBlock); }
+};
+
+// Record i of a list cut into blocks, through the constant address space: a scalar load.  (After the copies' memory
+// clobber the compiler takes a vector load instead, whose wait would drain the copies in flight.)
+__device__ __forceinline__ KeySeg load_block(const KeySeg* list, int i) {
+    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+    const i32x4 x = *reinterpret_cast<const __attribute__((address_space(4))) i32x4*>(reinterpret_cast<uintptr_t>(list + i));
+    const int32_t mult = x[3];              // (the bit cast of an element in place would be that of element 0)
+    return KeySeg{x[0], x[1], x[2], __builtin_bit_cast(float, mult)};
+}
+
+// All LDS reads of this wave so far have returned; no memory access moves across.
+__device__ __forceinline__ void lds_reads_done() {
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    asm volatile("" ::: "memory");
+}
+template <int N>
+__device__ __forceinline__ void copies_left() {
+    wait_vmcnt<N>();
+    asm volatile("" ::: "memory");
+}
+
+// 16-byte chunk swizzle of a stage: chunk c of LDS row rho sits at chunk c ^ stage_swizzle(rho).  Any map of bits
+// 1 to 3 of rho onto 0 .. 7 spreads one chunk column of sixteen consecutive rows over all 64 banks (row reads); with bit
+// 1 on the chunk's top bit, the 32 lanes that read 64 bytes of each of four consecutive rows (transposed reads)
+// are spread over all banks too.
+__device__ __forceinline__ int stage_swizzle(int rho) { return ((rho & 2) << 1) | ((rho & 4) >> 1) | ((rho & 8) >> 3); }
+
+// Element offsets of a lane's transposed reads inside a 16-row group of a stage: 32-d block db, walked positions
+// (lane & 15) / 4 + 8 * g (+ 4 for the second half), which sigma puts into LDS rows (lane & 15) / 4 + 4 * g (+ 8).
+struct TransposedLane {
+    int lo[2], hi[2];
+};
+__device__ __forceinline__ TransposedLane transposed_lane(int lane) {
+    const int g = lane >> 5, row = ((lane & 15) >> 2) + 4 * g;
+    const int chunk = (2 * ((lane >> 4) & 1) + ((lane >> 1) & 1)) ^ stage_swizzle(row);
+    const int lo = row * kRowElems + 8 * chunk + 4 * (lane & 1);
+    TransposedLane t;
+    t.lo[0] = lo;
+    t.lo[1] = lo ^ 32;                            // db = 1: chunk + 4
+    t.hi[0] = (lo ^ 8) + 8 * kRowElems;           // eight rows down: the swizzle's lowest bit
+    t.hi[1] = (lo ^ 40) + 8 * kRowElems;
+    return t;
+}
+__device__ __forceinline__ bf16x8 read_transposed(const uint16_t* rows16, const TransposedLane& t, int db) {
+    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(DFA_LDS_PTR(short4v, rows16 + t.lo[db]));
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(DFA_LDS_PTR(short4v, rows16 + t.hi[db]));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Issues the copies of one bf16 block into a wave's own LDS: rows key0 + stride * i of a tensor with row pitch sn
+// (elements), permuted by sigma (swap bits 2 and 3) and swizzled like a stage; rows past the end of the list re-read its
+// last one.
+__device__ __forceinline__ void issue_rows(const uint16_t* base, int64_t sn, const KeySeg& blk, uint32_t lds_addr, int lane) {
+    const void* const ub = uniform_ptr(base + (int64_t)blk.key0 * sn);
+    const uint32_t pitch = (uint32_t)(blk.stride * sn * 2);
+    const int room = blk.count - 1, r = lane >> 3;
+    const int pos = (r & 3) | ((r & 4) << 1);
+    const uint32_t chunk = 16u * ((lane & 7) ^ stage_swizzle(r));
+#pragma unroll
+    for (int u = 0; u < kBlockCopies; ++u)
+        copy16_to_lds(ub, (uint32_t)min(pos | ((u & 1) << 2) | ((u & 2) << 3), room) * pitch + (chunk ^ (16u * (u & 1))),
+                      lds_addr + 1024u * u);
+}
+
+// A wave's [32 rows][64 d] result, held transposed (lane (j, g), register v of half db: row j, d = 32*db + kappa(v, g)),
+// into its own region of LDS.
+__device__ __forceinline__ void result_to_lds(const floatx16 (&acc)[2], float* region, int lane) {
+    const int j = lane & 31, g = lane >> 5;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            *reinterpret_cast<float4*>(region + j * kRedPitch + 32 * db + 8 * t + 4 * g) =
+                make_float4(acc[db][4 * t], acc[db][4 * t + 1], acc[db][4 * t + 2], acc[db][4 * t + 3]);
+}
+
+}  // namespace dfa

@@ -72,9 +72,9 @@ __device__ __forceinline__ void write_sum(const BwdParams& p, const BwdBlock& k,
     if (row < k.nrows) {
         float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
 #pragma unroll
-        for (int x = 0; x < kF32Waves; ++x) {
-            const float4 u = *reinterpret_cast<const float4*>(lds[x] + row * kF32RedPitch + d);
-            const float4 v = *reinterpret_cast<const float4*>(lds[x] + row * kF32RedPitch + d + 4);
+        for (int x = 0; x < kWalkWaves; ++x) {
+            const float4 u = *reinterpret_cast<const float4*>(lds[x] + row * kRedPitch + d);
+            const float4 v = *reinterpret_cast<const float4*>(lds[x] + row * kRedPitch + d + 4);
             a.x += u.x; a.y += u.y; a.z += u.z; a.w += u.w;
             c.x += v.x; c.y += v.y; c.z += v.z; c.w += v.w;
         }
@@ -128,7 +128,7 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
         if (more) issue_block(vb, p.svn, nx, v_addr, lane);
         if (more) copies_left<kF32Copies>();             // K is there
         else copies_left<0>();
-        if (nvalid < kF32Block) zero_tail(k_lds, nvalid, lane);
+        if (nvalid < kWalkBlock) zero_tail(k_lds, nvalid, lane);
         const floatx16 s = rows_product(k_lds, q, lane);
         float ds[16];
 #pragma unroll
@@ -136,7 +136,7 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
             const float pr = __builtin_amdgcn_exp2f(fmaf(s[v] * p.scale, kLog2e, bias) - my_l);
             ds[v] = pr * (dp[v] + my_d) * p.scale;
         }
-        if (nvalid < kF32Block) {
+        if (nvalid < kWalkBlock) {
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) ds[v] = 0.f;
@@ -193,10 +193,10 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
         const float bias = w.seg.log2_mult;
 
         copies_left<kF32Copies + 1>();                   // dout is there
-        if (nvalid < kF32Block) zero_tail(g_lds, nvalid, lane);
+        if (nvalid < kWalkBlock) zero_tail(g_lds, nvalid, lane);
         const floatx16 dp = rows_product(g_lds, vr, lane);
         copies_left<0>();                                // q and the row statistics are there
-        if (nvalid < kF32Block) zero_tail(q_lds, nvalid, lane);
+        if (nvalid < kWalkBlock) zero_tail(q_lds, nvalid, lane);
         const floatx16 s = rows_product(q_lds, kr, lane);
         float pr[16], ds[16];
 #pragma unroll
@@ -211,7 +211,7 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
                 ds[v] = pr[v] * (dp[v] + dv4[e]) * p.scale;
             }
         }
-        if (nvalid < kF32Block) {
+        if (nvalid < kWalkBlock) {
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) pr[v] = ds[v] = 0.f;
@@ -231,22 +231,22 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void bwd_f32_kernel(const BwdParams p, int n_items, int row_blocks) {
-    __shared__ __attribute__((aligned(1024))) float lds[kF32Waves][2 * kF32BlockElems];
-    __shared__ __attribute__((aligned(256))) float stat_lds[kF32Waves][64];
+    __shared__ __attribute__((aligned(1024))) float lds[kWalkWaves][2 * kF32BlockElems];
+    __shared__ __attribute__((aligned(256))) float stat_lds[kWalkWaves][64];
 
     int item_index, part;
-    f32_item_of(blockIdx.x, 2 * row_blocks, item_index, part);
+    item_of_part(blockIdx.x, 2 * row_blocks, item_index, part);
     if (item_index >= n_items) return;
     const int sub = part >> 1;
     const Item item = p.items[item_index];
-    if (item.tile < 0 || sub * kF32Block >= item.t.nrows) return;
+    if (item.tile < 0 || sub * kWalkBlock >= item.t.nrows) return;
     const int tid = threadIdx.x;
     BwdBlock k;
     k.tile = item.t;
     k.b = item.b;
     k.h = item.t.h;
-    k.nrows = min(kF32Block, item.t.nrows - sub * kF32Block);
-    k.rows = p.rows + item.t.row_begin + sub * kF32Block;
+    k.nrows = min(kWalkBlock, item.t.nrows - sub * kWalkBlock);
+    k.rows = p.rows + item.t.row_begin + sub * kWalkBlock;
 
     if (item.t.nseg == 0) {                  // rows that no branch keeps take and give no gradient
         floatx16 zero[2];
@@ -271,13 +271,13 @@ hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, int32_
     if (bf16) return launch_bwd_bf16(p, n_items, st);
     hipLaunchKernelGGL(bwd_delta_kernel, dim3((unsigned)(((int64_t)p.N * p.H * 16 + 255) / 256), B), dim3(256), 0, st,
                        static_cast<const float*>(p.out), static_cast<const float*>(p.dout), p.lse, p.ndelta, p.lse2, p.H, p.N);
-    const int row_blocks = (max_tile_rows + kF32Block - 1) / kF32Block;
-    for (int i0 = 0; i0 < n_items; i0 += kF32LaunchItems) {         // a grid holds fewer than 2^32 threads
+    const int row_blocks = (max_tile_rows + kWalkBlock - 1) / kWalkBlock;
+    for (int i0 = 0; i0 < n_items; i0 += kLaunchItems) {         // a grid holds fewer than 2^32 threads
         BwdParams q = p;
         q.items += i0;
-        const int n = n_items - i0 < kF32LaunchItems ? n_items - i0 : kF32LaunchItems;
-        const int groups = (n + kF32Dies - 1) / kF32Dies;
-        hipLaunchKernelGGL(bwd_f32_kernel, dim3((unsigned)groups * kF32Dies * 2 * row_blocks), dim3(256), 0, st, q, n, row_blocks);
+        const int n = n_items - i0 < kLaunchItems ? n_items - i0 : kLaunchItems;
+        const int groups = (n + kDies - 1) / kDies;
+        hipLaunchKernelGGL(bwd_f32_kernel, dim3((unsigned)groups * kDies * 2 * row_blocks), dim3(256), 0, st, q, n, row_blocks);
     }
     return hipGetLastError();
 }

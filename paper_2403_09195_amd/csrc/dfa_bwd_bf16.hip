@@ -12,7 +12,7 @@
 // queries (dq) and the queries that see its rows when they act as keys (dk, dv): no gradient
 // needs an atomic.  The rows of the tile stay in registers as B operands; the walked rows go
 // global -> LDS (global_load_lds) several stages deep, once per tensor, rows permuted by sigma and
-// 16-byte chunks swizzled (bwd_swizzle), and are read back in two ways:
+// 16-byte chunks swizzled (stage_swizzle), and are read back in two ways:
 //   rows:       32 rows x 16 d A operands of the first products (S^T and dP^T, walked row = MFMA row),
 //   transposed: (ds_read_b64_tr_b16) 32 d x 16 rows A operands of the second product, whose B
 //               operand is the packed bf16 result of the first products straight from registers
@@ -24,7 +24,7 @@
 // (~ marks the walked rows).  lse and delta of the walked queries travel with the rows as 4-byte
 // copies.  P is recomputed from lse; there is no online softmax and no rescaling here.
 #include "dfa_device.h"
-#include "dfa_mfma.h"
+#include "dfa_blocks.h"
 
 namespace dfa {
 
@@ -33,7 +33,6 @@ namespace {
 constexpr int kDqStages = 4, kDkdvStages = 4;      // 64-row stages in LDS; all but one of them in flight or in use
 constexpr int kDkdvRows = 128;                     // rows of a dk/dv workgroup: a tile is up to kDkdvParts of them
 constexpr int kDkdvParts = kTileRows / kDkdvRows;
-constexpr int kDies = 8;                           // launch order of a plan: item i on die i mod 8
 
 // 4 bytes per lane from global memory straight into LDS: lane L's word lands at lds_addr + 4*L.
 __device__ __forceinline__ void copy4_to_lds(const void* gbase, uint32_t lane_byte_offset, uint32_t lds_addr) {
@@ -41,34 +40,6 @@ __device__ __forceinline__ void copy4_to_lds(const void* gbase, uint32_t lane_by
                  :
                  : "s"(lds_addr), "v"(lane_byte_offset), "s"(gbase)
                  : "memory", "m0");
-}
-
-// 16-byte chunk swizzle of a stage: chunk c of LDS row rho sits at chunk c ^ bwd_swizzle(rho).  Any map of bits
-// 1 to 3 of rho onto 0 .. 7 spreads one chunk column of sixteen consecutive rows over all 64 banks (row reads); with bit
-// 1 on the chunk's top bit, the 32 lanes that read 64 bytes of each of four consecutive rows (transposed reads)
-// are spread over all banks too.
-__device__ __forceinline__ int bwd_swizzle(int rho) { return ((rho & 2) << 1) | ((rho & 4) >> 1) | ((rho & 8) >> 3); }
-
-// Element offsets of a lane's transposed reads inside a 16-row group of a stage: 32-d block db, walked positions
-// (lane & 15) / 4 + 8 * g (+ 4 for the second half), which sigma puts into LDS rows (lane & 15) / 4 + 4 * g (+ 8).
-struct TransposedLane {
-    int lo[2], hi[2];
-};
-__device__ __forceinline__ TransposedLane transposed_lane(int lane) {
-    const int g = lane >> 5, row = ((lane & 15) >> 2) + 4 * g;
-    const int chunk = (2 * ((lane >> 4) & 1) + ((lane >> 1) & 1)) ^ bwd_swizzle(row);
-    const int lo = row * kRowElems + 8 * chunk + 4 * (lane & 1);
-    TransposedLane t;
-    t.lo[0] = lo;
-    t.lo[1] = lo ^ 32;                            // db = 1: chunk + 4
-    t.hi[0] = (lo ^ 8) + 8 * kRowElems;           // eight rows down: the swizzle's lowest bit
-    t.hi[1] = (lo ^ 40) + 8 * kRowElems;
-    return t;
-}
-__device__ __forceinline__ bf16x8 read_transposed(const uint16_t* rows16, const TransposedLane& t, int db) {
-    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(DFA_LDS_PTR(short4v, rows16 + t.lo[db]));
-    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(DFA_LDS_PTR(short4v, rows16 + t.hi[db]));
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // What a lane fetches in the two 1 KB copies a wave contributes to one 8 KB tensor stage: copy u
@@ -80,7 +51,7 @@ __device__ __forceinline__ BwdCopyLane bwd_copy_lane(int wave, int lane) {
     BwdCopyLane cl;
     const int rho = 16 * wave + (lane >> 3);                                    // LDS row of copy 0 (bit 3 clear)
     cl.pos = (rho & 0x33) | ((rho & 4) << 1);                                   // sigma(rho)
-    cl.chunk = 16 * ((lane & 7) ^ bwd_swizzle(rho));
+    cl.chunk = 16 * ((lane & 7) ^ stage_swizzle(rho));
     return cl;
 }
 
@@ -220,7 +191,7 @@ void bwd_dq_bf16_kernel(const BwdParams p) {
         return bwd_copy_lane(wave, ln);
     };
     // fragment reads: row j of a 32-row block, chunk (2*kk + g) ^ swizzle(j); transposed as TransposedLane describes
-    const int frag_a = j * kRowElems + 8 * (g ^ bwd_swizzle(j));
+    const int frag_a = j * kRowElems + 8 * (g ^ stage_swizzle(j));
     const TransposedLane frag_t = transposed_lane(lane);
 
     int n_steps = tile.n_steps;
@@ -415,8 +386,9 @@ void bwd_dkdv_bf16_kernel(const BwdParams p, int n_items) {
     __shared__ KeySeg seg_lds[kMaxTileSegs];
 
     // the workgroups of a tile stay on the tile's die (see build_plan: item i runs on die i mod 8)
-    const int group = blockIdx.x / (kDies * kDkdvParts), rem = blockIdx.x % (kDies * kDkdvParts);
-    const int item_index = group * kDies + rem % kDies, row0 = rem / kDies * kDkdvRows;
+    int item_index, part;
+    item_of_part(blockIdx.x, kDkdvParts, item_index, part);
+    const int row0 = part * kDkdvRows;
     if (item_index >= n_items) return;
     const Item item = p.items[item_index];
     if (item.tile < 0 || row0 >= item.t.nrows) return;
@@ -455,7 +427,7 @@ void bwd_dkdv_bf16_kernel(const BwdParams p, int n_items) {
     const float* const lse2_bh = p.lse2 + ((int64_t)b * p.H + h) * p.N;
 
     const BwdCopyLane cl = bwd_copy_lane(wave, lane);
-    const int frag_a = j * kRowElems + 8 * (g ^ bwd_swizzle(j));
+    const int frag_a = j * kRowElems + 8 * (g ^ stage_swizzle(j));
     const TransposedLane frag_t = transposed_lane(lane);
 
     int n_steps = tile.n_steps;

@@ -26,19 +26,19 @@ namespace {
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
-    __shared__ __attribute__((aligned(1024))) float lds[kF32Waves][2 * kF32BlockElems];     // per wave: K block, V block
+    __shared__ __attribute__((aligned(1024))) float lds[kWalkWaves][2 * kF32BlockElems];     // per wave: K block, V block
 
     int item_index, sub;
-    f32_item_of(blockIdx.x, row_blocks, item_index, sub);
+    item_of_part(blockIdx.x, row_blocks, item_index, sub);
     if (item_index >= n_items) return;
     const Item item = p.items[item_index];
     const Tile tile = item.t;
-    if (item.tile < 0 || sub * kF32Block >= tile.nrows) return;
+    if (item.tile < 0 || sub * kWalkBlock >= tile.nrows) return;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int h = tile.h, b = item.b;
-    const int32_t* const rows = p.rows + tile.row_begin + sub * kF32Block;
-    const int nrows = min(kF32Block, tile.nrows - sub * kF32Block);
+    const int32_t* const rows = p.rows + tile.row_begin + sub * kWalkBlock;
+    const int nrows = min(kWalkBlock, tile.nrows - sub * kWalkBlock);
 
     // the row this thread writes: eight threads a row, 32 bytes each
     const int orow = tid >> 3, od = (tid & 7) * 8;
@@ -92,7 +92,7 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
         float mx = -INFINITY;
 #pragma unroll
         for (int v = 0; v < 16; ++v) s[v] = fmaf(s[v], p.scale, ln_mult);
-        if (nvalid < kF32Block) {
+        if (nvalid < kWalkBlock) {
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) s[v] = -INFINITY;
@@ -113,7 +113,7 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
 
         if (more) copies_left<kF32Copies>();            // V is there, the next K may be on its way
         else copies_left<0>();
-        if (nvalid < kF32Block) zero_tail(v_lds, nvalid, lane);
+        if (nvalid < kWalkBlock) zero_tail(v_lds, nvalid, lane);
         // the block's sums on their own, added to the running ones once: shorter chains of roundings
         floatx16 blk[2];
 #pragma unroll
@@ -133,24 +133,24 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
     float* const red = lds[wave];
     result_to_lds(acc, red, lane);
     if (g == 0) {
-        red[kF32Block * kF32RedPitch + j] = m_run;
-        red[kF32Block * kF32RedPitch + kF32Block + j] = l_run;
+        red[kWalkBlock * kRedPitch + j] = m_run;
+        red[kWalkBlock * kRedPitch + kWalkBlock + j] = l_run;
     }
     __syncthreads();
     if (orow >= nrows) return;
     float m = -INFINITY;
 #pragma unroll
-    for (int x = 0; x < kF32Waves; ++x) m = fmaxf(m, lds[x][kF32Block * kF32RedPitch + orow]);
+    for (int x = 0; x < kWalkWaves; ++x) m = fmaxf(m, lds[x][kWalkBlock * kRedPitch + orow]);
     const float m_use = m == -INFINITY ? 0.f : m;
     float l = 0.f;
     float4 o0 = make_float4(0.f, 0.f, 0.f, 0.f), o1 = o0;
 #pragma unroll
-    for (int x = 0; x < kF32Waves; ++x) {
+    for (int x = 0; x < kWalkWaves; ++x) {
         const float* const r = lds[x];
-        const float f = __builtin_amdgcn_exp2f((r[kF32Block * kF32RedPitch + orow] - m_use) * kLog2e);
-        l = fmaf(r[kF32Block * kF32RedPitch + kF32Block + orow], f, l);
-        const float4 a = *reinterpret_cast<const float4*>(r + orow * kF32RedPitch + od);
-        const float4 c = *reinterpret_cast<const float4*>(r + orow * kF32RedPitch + od + 4);
+        const float f = __builtin_amdgcn_exp2f((r[kWalkBlock * kRedPitch + orow] - m_use) * kLog2e);
+        l = fmaf(r[kWalkBlock * kRedPitch + kWalkBlock + orow], f, l);
+        const float4 a = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od);
+        const float4 c = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od + 4);
         o0.x = fmaf(a.x, f, o0.x); o0.y = fmaf(a.y, f, o0.y); o0.z = fmaf(a.z, f, o0.z); o0.w = fmaf(a.w, f, o0.w);
         o1.x = fmaf(c.x, f, o1.x); o1.y = fmaf(c.y, f, o1.y); o1.z = fmaf(c.z, f, o1.z); o1.w = fmaf(c.w, f, o1.w);
     }
@@ -163,13 +163,13 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
 }  // namespace
 
 hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, hipStream_t st) {
-    const int row_blocks = (max_tile_rows + kF32Block - 1) / kF32Block;
-    for (int i0 = 0; i0 < n_items; i0 += kF32LaunchItems) {         // a grid holds fewer than 2^32 threads
+    const int row_blocks = (max_tile_rows + kWalkBlock - 1) / kWalkBlock;
+    for (int i0 = 0; i0 < n_items; i0 += kLaunchItems) {         // a grid holds fewer than 2^32 threads
         FwdParams q = p;
         q.items += i0;
-        const int n = n_items - i0 < kF32LaunchItems ? n_items - i0 : kF32LaunchItems;
-        const int groups = (n + kF32Dies - 1) / kF32Dies;
-        hipLaunchKernelGGL(dfa_fwd_f32_kernel, dim3((unsigned)groups * kF32Dies * row_blocks), dim3(256), 0, st, q, n, row_blocks);
+        const int n = n_items - i0 < kLaunchItems ? n_items - i0 : kLaunchItems;
+        const int groups = (n + kDies - 1) / kDies;
+        hipLaunchKernelGGL(dfa_fwd_f32_kernel, dim3((unsigned)groups * kDies * row_blocks), dim3(256), 0, st, q, n, row_blocks);
     }
     return hipGetLastError();
 }

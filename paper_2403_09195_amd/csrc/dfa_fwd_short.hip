@@ -1,0 +1,283 @@
+// Fused dilated flash attention forward, bf16, for launches that do not fill the chip (one image, small images; the rule is
+// short_plan's).
+//
+// Same arithmetic as dfa_fwd_bf16.hip, whose beat it runs (reference exponent moved only when a block's sums ask for it,
+// probabilities rounded to bf16, row sums over the rounded values on the matrix cores), another split of the work: a
+// workgroup owns 64 query rows and its four waves walk a quarter of the tile's 32-key blocks each (wave w takes blocks w,
+// w + 4, ...), every wave with an online softmax of its own; the four partial results are merged through LDS in fp32, and
+// nothing but out and lse is written.
+//
+// Bound: latency.  Such a launch is as long as one workgroup's start, walk and end, so the walk is cut by four where the rows
+// are, not by more workgroups that have to meet in memory (partial rows written, read back and merged by a second launch).
+// A wave copies its own blocks and waits for nobody until the merge.  The list comes cut into blocks: one record each, all of a
+// wave's records read in one trip to memory at the start and kept in LDS.  Two workgroups to a CU (registers); a beat takes
+// 0.65 us then and as much with one, which is what the copies of its 8 KB take (20 bytes per clock and CU), and the
+// reason for short_plan's limit on the number of workgroups.  Eight waves that share the copies of a block for 128 rows
+// need a barrier per beat and were slower (one image of 2500 tokens, 12 heads: 32.5 against 23.0 us).
+// Measured, us against 256-row tiles with split walks: three images of 1500 tokens, 6 heads 18.2 / 25.7; one of 2500, 12
+// heads 23.0 / 27.2; one of 4096, 6 heads 19.6 / 26.4.
+#include "dfa_blocks.h"
+#include "dfa_fwd_beat.h"
+
+namespace dfa {
+
+namespace {
+
+constexpr int kBuffers = 4;                // 32-key blocks in a wave's LDS: two of K, two of V
+
+// One 32-key block of a wave's share of the list.  Wave-uniform, in scalar registers.
+struct Block {
+    int32_t key0;
+    int32_t stride_count;      // stride | count << 24; count 0: past the share's end, a copy of its last block without a valid key
+    float log2_mult[2];        // of the keys' multiplicity for either 32-row block of the tile; -inf: they are skipped
+    __device__ __forceinline__ int stride() const { return stride_count & 0xffffff; }
+    __device__ __forceinline__ int count() const { return stride_count >> 24; }
+};
+
+// Lane L's record of the wave's share.
+__device__ __forceinline__ u32x4 load_record(const FwdParams& p, const Tile& tile, int wave, int lane) {
+    const int i = wave + kWalkWaves * lane, last = tile.nseg - 1;
+    const int x = tile.seg_begin + (i <= last ? i : last >= wave ? last - ((last - wave) & (kWalkWaves - 1)) : 0);
+    const KeySeg r = p.segs[x];
+    const float2 m = *reinterpret_cast<const float2*>(p.block_mult + (int64_t)kTileBlocks * x);
+    return u32x4{(uint32_t)r.key0, (uint32_t)(r.stride | ((i <= last ? r.count : 0) << 24)), __builtin_bit_cast(uint32_t, m.x),
+                 __builtin_bit_cast(uint32_t, m.y)};
+}
+__device__ __forceinline__ Block read_block(const u32x4* records, int t) {
+    const u32x4 r = records[min(t, 63)];
+    Block b;
+    b.key0 = __builtin_amdgcn_readfirstlane(r[0]);
+    b.stride_count = __builtin_amdgcn_readfirstlane(r[1]);
+    b.log2_mult[0] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(r[2]));
+    b.log2_mult[1] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(r[3]));
+    return b;
+}
+
+// Copies of one block of a tensor into the wave's own LDS; rows past the end of the block re-read its last one.  kIsK: rows
+// permuted by sigma and swizzled as the scores read them, else in list order.  In a whole block the four copies differ in
+// their scalar base alone (K: and in one bit of the chunk).  The lane number comes in opaque, so that nothing derived from
+// it is kept in registers across the walk.
+template <bool kIsK>
+__device__ __forceinline__ void issue_block_rows(const uint16_t* base, int64_t sn, const Block& b, uint32_t lds_addr, int lane) {
+    const uint16_t* const first = base + (int64_t)b.key0 * sn;
+    const int64_t pitch = (int64_t)b.stride() * sn;               // elements
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int r = ln >> 3;
+    const int pos = kIsK ? (r & 3) | ((r & 4) << 1) : r;
+    const uint32_t chunk = 16u * (kIsK ? (ln & 7) ^ (r >> 1) : ln & 7);
+    if (b.count() == kWalkBlock) {
+        const uint32_t off = (uint32_t)pos * (uint32_t)(pitch * 2);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int row = kIsK ? ((u & 1) << 2) | ((u & 2) << 3) : 8 * u;
+            copy16_to_lds(uniform_ptr(first + row * pitch), off + (kIsK ? chunk ^ (64u * (u & 1)) : chunk), lds_addr + 1024u * u);
+        }
+    } else {
+        const int room = max(b.count() - 1, 0);
+        const void* const ub = uniform_ptr(first);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int row = kIsK ? ((u & 1) << 2) | ((u & 2) << 3) : 8 * u;
+            copy16_to_lds(ub, (uint32_t)min(pos + row, room) * (uint32_t)(pitch * 2) + (kIsK ? chunk ^ (64u * (u & 1)) : chunk), lds_addr + 1024u * u);
+        }
+    }
+}
+
+__global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void dfa_fwd_short_kernel(const FwdParams p) {
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[kWalkWaves][kBuffers * kBlockElems];     // per wave: K, K, V, V
+    __shared__ u32x4 records_all[kWalkWaves][64];
+
+    const Item item = load_item(p.items, blockIdx.x);
+    if (item.tile < 0) return;
+    const Tile tile = item.t;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const int h = tile.h, b = item.b;
+    const int32_t* const rows = p.rows + tile.row_begin;
+
+    uint16_t* const out = static_cast<uint16_t*>(p.out) + ((int64_t)b * p.N * p.H + h) * kD;     // row n adds n * H * D
+    float* const lse = p.lse ? p.lse + ((int64_t)b * p.H + h) * p.N : nullptr;
+
+    if (tile.nseg == 0) {                      // rows that no branch keeps (such tiles hold no filler slots)
+        for (int x = tid; x < tile.nrows * 8; x += 64 * kWalkWaves)
+            *reinterpret_cast<u32x4*>(out + (int64_t)rows[x >> 3] * p.H * kD + 8 * (x & 7)) = u32x4{0u, 0u, 0u, 0u};
+        if (lse && tid < tile.nrows) lse[rows[tid]] = -INFINITY;
+        return;
+    }
+
+    const uint16_t* const kp = static_cast<const uint16_t*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
+    const uint16_t* const vp = static_cast<const uint16_t*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
+    const uint32_t k_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, lds[wave]));
+    const uint32_t v_addr = k_addr + 2 * kBlockBytes;
+
+    // the share's records and the rows of the Q fragments in one trip to memory, the fragments and the first blocks in the next
+    u32x4* const records = records_all[wave];
+    const u32x4 my_record = load_record(p, tile, wave, lane);
+    // a filler slot of a packed tile holds ~n of a row n of its group: loaded like any row, never stored
+    int32_t q_row[2] = {rows[min(j, tile.nrows - 1)], rows[min(kWalkBlock + j, tile.nrows - 1)]};
+    q_row[0] ^= q_row[0] >> 31;
+    q_row[1] ^= q_row[1] >> 31;
+    // Q fragments: B operand of S^T, lane (j, g) holds Q[row j][16*kk + 8*g .. +7]
+    bf16x8 qf[2][4];
+    {
+        const uint16_t* const qp = static_cast<const uint16_t*>(p.q) + (int64_t)b * p.sqb + (int64_t)h * p.sqh;
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) qf[qb][kk] = *reinterpret_cast<const bf16x8*>(qp + (int64_t)q_row[qb] * p.sqn + 16 * kk + 8 * g);
+    }
+    records[lane] = my_record;                 // read back by this wave alone
+    // blocks are walked in pairs: a wave with an odd number of them, or none, ends on a block that is masked as a whole
+    const int n_pairs = max((tile.nseg - wave + 2 * kWalkWaves - 1) / (2 * kWalkWaves), 1);
+    Block blk[3];                              // blocks t, t + 1 and t + 2 of the walk
+#pragma unroll
+    for (int x = 0; x < 3; ++x) blk[x] = read_block(records, x);
+    auto issue_k = [&](const Block& b, int buf) { issue_block_rows<true>(kp, p.skn, b, k_addr + buf * kBlockBytes, lane); };
+    auto issue_v = [&](const Block& b, int buf) { issue_block_rows<false>(vp, p.svn, b, v_addr + buf * kBlockBytes, lane); };
+    issue_k(blk[0], 0);
+    issue_k(blk[1], 1);
+
+    const FragLane fl = frag_lane(lane);
+    const bf16x8 sel = row_sum_selector(lane);
+    const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, p.scale * kLog2e)));
+
+    floatx16 oacc[2][2];                       // [d block][query block], O^T layout
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) oacc[db][qb][v] = 0.f;
+    // Per 32-row block: the reference exponent less log2 m of the keys in hand (a key that counts m times adds log2 m to
+    // its score); while the block skips its keys, m_ref is +inf (every numerator an exact 0) and the reference waits in m_kept.
+    float m_ref[2] = {kRefStart, kRefStart}, m_kept[2] = {kRefStart, kRefStart}, bias_cur[2] = {0.f, 0.f}, l_run[2] = {0.f, 0.f};
+
+    // pinned: the compiler waits for the Q loads here and places no vector-memory wait of its own in the walk (it does
+    // not see the copies, and a wait sized for these loads would drain them)
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qf[qb][kk]));
+
+    // Beat t turns block t's scores into numerators, scores block t + 1 and accumulates block t - 1; buffers go by the
+    // parity of the block (odd = t & 1), left = blocks from t on.
+    int count = kWalkBlock;                    // valid keys of block t - 1
+    // rows past the end of a block become zeros in its V buffer, so that the weights 0 they get meet finite values
+    auto zero_tail = [&](int buf, int valid) {
+        for (int x = lane; x < (kWalkBlock - valid) * 8; x += 64)
+            *reinterpret_cast<u32x4*>(lds[wave] + buf * kBlockElems + valid * kRowElems + 8 * x) = u32x4{0u, 0u, 0u, 0u};
+    };
+    auto before = [&](int t, int odd, int left, floatx16 (&s)[2]) {
+        lds_reads_done();                      // K of block t and V of block t - 2 have been read
+        if (left > 2) issue_k(blk[2], odd);
+        issue_v(blk[0], odd);
+        const Block cur = blk[0];
+        const int prev_count = count;
+        count = cur.count();
+        blk[0] = blk[1];
+        blk[1] = blk[2];
+        blk[2] = read_block(records, t + 3);
+        if (left > 2) copies_left<8>(); else copies_left<4>();       // K of block t + 1 and V of block t - 1 are there
+        if (prev_count < kWalkBlock) zero_tail(odd ? 2 : 3, prev_count);
+        if (count < kWalkBlock) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            mask_block(s, ln >> 5, count);
+        }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            const float now = cur.log2_mult[qb];
+            if (now != bias_cur[qb]) {         // wave-uniform
+                const float ref = bias_cur[qb] > -INFINITY ? m_ref[qb] + bias_cur[qb] : m_kept[qb];
+                if (now > -INFINITY) {
+                    m_ref[qb] = ref - now;
+                } else {
+                    m_kept[qb] = ref;
+                    m_ref[qb] = INFINITY;
+                }
+                bias_cur[qb] = now;
+            }
+        }
+    };
+    const uint16_t* const k0 = lds[wave];
+    const uint16_t* const k1 = k0 + kBlockElems;
+    const uint16_t* const v0 = k0 + 2 * kBlockElems;
+    const uint16_t* const v1 = k0 + 3 * kBlockElems;
+
+    floatx16 s_a[2], s_b[2];
+    u32x4 p_a[2][2], p_b[2][2];
+    float psum[2];
+    copies_left<4>();                          // K of block 0
+    scores_block(k0, fl, qf, s_a);
+    before(0, 0, 2 * n_pairs, s_a);
+    beat<true, false>(k1, v1, fl, qf, s_a, s_b, p_b, p_a, oacc, c, m_ref, psum, sel);
+    settle<true>(s_a, p_a, c, m_ref, l_run, oacc, psum);
+    for (int s = 0; s + 1 < n_pairs; ++s) {
+        before(2 * s + 1, 1, 3, s_b);
+        beat<true, true>(k0, v0, fl, qf, s_b, s_a, p_a, p_b, oacc, c, m_ref, psum, sel);
+        settle<true>(s_b, p_b, c, m_ref, l_run, oacc, psum);
+        before(2 * s + 2, 0, 2 * (n_pairs - s) - 2, s_a);
+        beat<true, true>(k1, v1, fl, qf, s_a, s_b, p_b, p_a, oacc, c, m_ref, psum, sel);
+        settle<true>(s_a, p_a, c, m_ref, l_run, oacc, psum);
+    }
+    before(2 * n_pairs - 1, 1, 1, s_b);
+    beat<false, true>(k0, v0, fl, qf, s_b, s_a, p_a, p_b, oacc, c, m_ref, psum, sel);
+    settle<true>(s_b, p_b, c, m_ref, l_run, oacc, psum);
+    copies_left<0>();
+    if (count < kWalkBlock) zero_tail(3, count);
+    accumulate_block(v1, fl, p_b, oacc);
+    lds_reads_done();
+
+    // Merge of the four waves, one 32-row block after the other: a wave without a key for a row has a row sum and an
+    // accumulator of zeros under the start exponent, whose weight is an exact 0.
+    static_assert(sizeof(lds[0]) >= (kWalkBlock * kRedPitch + 2 * kWalkBlock) * 4, "a wave's results fit its buffers");
+    float* const red = reinterpret_cast<float*>(lds[wave]);
+    const int orow = tid >> 3, od = (tid & 7) * 8;        // eight threads a row, 16 bytes each
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        if (qb * kWalkBlock >= tile.nrows) break;         // uniform for the workgroup
+        if (qb > 0) __syncthreads();                      // everyone has read the first block
+        const floatx16 mine[2] = {oacc[0][qb], oacc[1][qb]};
+        result_to_lds(mine, red, lane);
+        if (g == 0) {
+            red[kWalkBlock * kRedPitch + j] = bias_cur[qb] > -INFINITY ? m_ref[qb] + bias_cur[qb] : m_kept[qb];
+            red[kWalkBlock * kRedPitch + kWalkBlock + j] = l_run[qb];
+        }
+        __syncthreads();
+        const int slot = qb * kWalkBlock + orow;
+        const int32_t n_out = rows[min(slot, tile.nrows - 1)];
+        if (slot >= tile.nrows || n_out < 0) continue;
+        float m = kRefStart;
+#pragma unroll
+        for (int x = 0; x < kWalkWaves; ++x) m = fmaxf(m, reinterpret_cast<const float*>(lds[x])[kWalkBlock * kRedPitch + orow]);
+        float l = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < kWalkWaves; ++x) {
+            const float* const r = reinterpret_cast<const float*>(lds[x]);
+            const float f = __builtin_amdgcn_exp2f(r[kWalkBlock * kRedPitch + orow] - m);
+            l = fmaf(r[kWalkBlock * kRedPitch + kWalkBlock + orow], f, l);
+            const float4 lo = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od);
+            const float4 hi = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od + 4);
+            const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = fmaf(a[e], f, o[e]);
+        }
+        const float inv = 1.0f / l;
+        bf16x8 ob;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ob[e] = (__bf16)(o[e] * inv);
+        *reinterpret_cast<bf16x8*>(out + (int64_t)n_out * p.H * kD + od) = ob;
+        if (lse && od == 0) lse[n_out] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_fwd_short(const FwdParams& p, int n_items, hipStream_t st) {
+    hipLaunchKernelGGL(dfa_fwd_short_kernel, dim3(n_items), dim3(64 * kWalkWaves), 0, st, p);
+    return hipGetLastError();
+}
+
+}  // namespace dfa

@@ -163,7 +163,8 @@ int check_branches(int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, con
 }
 
 void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb,
-                const int32_t* offsets, int order_mode, const ChipShape& chip, bool pack, HostPlan* plan) {
+                const int32_t* offsets, int order_mode, const ChipShape& chip, bool pack, HostPlan* plan,
+                int tile_blocks) {
     const int kNumXcd = std::max(chip.dies, 1);
     const int kSlotsPerDie = std::max(chip.fwd_slots_per_die(), 1);
     plan->tiles.clear();
@@ -173,6 +174,7 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     plan->block_mult.clear();
     plan->items.clear();
     plan->packed_tiles = false;
+    const size_t tile_rows = (size_t)tile_blocks * kBlockRows;
 
     std::vector<int64_t> tile_cost;   // (query, key) pairs of each tile
     // appends a key list; block_group[w] = which entry of a progression's multiplicities the rows of block w take (-1: none)
@@ -258,20 +260,20 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
             if (done[i]) continue;
             done[i] = 1;
             const RowGroup& g = *groups[i];
-            const bool small = pack && !g.plain.empty() && blocks_of(g) < kTileBlocks;
+            const bool small = pack && !g.plain.empty() && blocks_of(g) < tile_blocks;
             std::vector<const RowGroup*> members = {&g};
             std::vector<KeySeg> list = g.list;
             std::vector<MultVec> list_mult = g.list_mult;
             int blocks = blocks_of(g);
             int64_t key_lo = g.key_lo, key_hi = g.key_hi;
-            while (small && blocks < kTileBlocks) {
+            while (small && blocks < tile_blocks) {
                 int64_t best = -1, best_saved = 0;
                 std::vector<KeySeg> best_list;
                 std::vector<MultVec> best_mult;
                 const int64_t have = steps_of(list);
                 for (size_t j = i + 1; j < std::min(G, i + 1 + kPackWindow); ++j) {
                     const RowGroup& c = *groups[j];
-                    if (done[j] || c.plain.empty() || blocks + blocks_of(c) > kTileBlocks) continue;
+                    if (done[j] || c.plain.empty() || blocks + blocks_of(c) > tile_blocks) continue;
                     if (c.key_hi < key_lo || key_hi < c.key_lo) continue;      // no key in common: nothing to save
                     std::vector<const RowGroup*> trial = members;
                     trial.push_back(&c);
@@ -301,8 +303,8 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
                 const int32_t seg_begin = add_list(list, list_mult, block_group);
                 int64_t keys = 0;
                 for (const KeySeg& sg : list) keys += sg.count;
-                for (size_t lo = 0; lo < g.rows.size(); lo += kTileRows) {
-                    const int32_t cnt = (int32_t)std::min<size_t>(kTileRows, g.rows.size() - lo);
+                for (size_t lo = 0; lo < g.rows.size(); lo += tile_rows) {
+                    const int32_t cnt = (int32_t)std::min<size_t>(tile_rows, g.rows.size() - lo);
                     Tile t{h, (int32_t)plan->rows.size(), cnt, seg_begin, nseg, (int32_t)steps_of(list)};
                     plan->rows.insert(plan->rows.end(), g.rows.begin() + lo, g.rows.begin() + lo + cnt);
                     plan->tiles.push_back(t);
@@ -460,6 +462,50 @@ void split_plan(HostPlan* plan, const ChipShape& chip) {
         plan->item_parts[i] = ItemParts{(int32_t)plan->split_wgs.size(), parts[i]};
         for (int32_t x = 0; x < parts[i]; ++x) plan->split_wgs.push_back(SplitWg{(int32_t)i, x | (parts[i] << 16)});
     }
+}
+
+void cut_blocks(HostPlan* plan) {
+    std::vector<KeySeg> segs;
+    std::vector<int32_t> mult, block_mult;
+    std::map<int32_t, std::pair<int32_t, int32_t>> cut;      // seg_begin -> first piece, number of pieces
+    auto cut_list = [&](Tile& t) {
+        if (t.nseg == 0) return;
+        auto it = cut.find(t.seg_begin);                     // tiles of one group share their list
+        if (it == cut.end()) {
+            const int32_t begin = (int32_t)segs.size();
+            for (int32_t x = t.seg_begin; x < t.seg_begin + t.nseg; ++x) {
+                const KeySeg& s = plan->segs[x];
+                for (int32_t k = 0; k < s.count; k += kWalkBlock) {
+                    const int32_t count = std::min(kWalkBlock, s.count - k);
+                    segs.push_back(KeySeg{s.key0 + s.stride * k, count > 1 ? s.stride : 0, count, s.log2_mult});
+                    mult.push_back(plan->seg_mult[x]);
+                    block_mult.insert(block_mult.end(), plan->block_mult.begin() + (size_t)x * kTileBlocks,
+                                      plan->block_mult.begin() + (size_t)(x + 1) * kTileBlocks);
+                }
+            }
+            it = cut.emplace(t.seg_begin, std::make_pair(begin, (int32_t)segs.size() - begin)).first;
+        }
+        t.seg_begin = it->second.first;
+        t.nseg = it->second.second;
+    };
+    for (Tile& t : plan->tiles) cut_list(t);
+    for (Item& i : plan->items)
+        if (i.tile >= 0) i.t = plan->tiles[i.tile];
+    plan->segs.swap(segs);
+    plan->seg_mult.swap(mult);
+    plan->block_mult.swap(block_mult);
+}
+
+bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
+                int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan) {
+    const size_t most = (size_t)chip.fwd_slots() * 9 / 8;
+    if (full.items.size() > most || N >= kMaxCutStride) return false;
+    build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, plan, kShortRows / kBlockRows);
+    if (plan->items.size() > most) return false;
+    cut_blocks(plan);
+    for (const Tile& t : plan->tiles)
+        if (t.nseg > kShortBlocks) return false;
+    return true;
 }
 
 }  // namespace dfa

@@ -15,7 +15,10 @@ namespace dfa {
 constexpr int kTileRows = 256;   // query rows per workgroup (4 waves x 64 rows)
 constexpr int kTileBlocks = 8;   // a wave's 64 rows are two blocks of 32, each with its own softmax state
 constexpr int kBlockRows = 32;
+constexpr int kWalkBlock = 32;   // keys per piece of a list cut into blocks (see cut_blocks)
+constexpr int kWalkWaves = 4;    // waves that share such a list
 constexpr int kPackWindow = 32;  // row groups (in signature order) after a group that are tried as its tile mates
+constexpr int kShortRows = 64;   // query rows per workgroup of the short-launch kernels
 constexpr int kFwdWorkgroupsPerCu = 2;   // workgroups of the bf16 forward kernel that fit one compute unit
 constexpr int kTailItemsPerDie = 96;     // launch order: items at the end of a die's list that go heaviest first
 constexpr int kMaxTileSegs = 32; // key progressions per tile (the kernels hold a tile's list in LDS)
@@ -95,8 +98,10 @@ inline int32_t head_offset(const int32_t* offsets, int32_t H, int32_t x, int32_t
 // order_mode: 3 = default (see dfa_plan.cpp), 0 to 2 are alternatives kept for measurement.
 // pack: row groups of fewer than eight 32-row blocks may share a tile (only the bf16 forward kernel reads such
 // tiles: it takes its multiplicities per block from block_mult).
+// tile_blocks: 32-row blocks of a tile, kTileBlocks or less.
 void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb,
-                const int32_t* offsets, int order_mode, const ChipShape& chip, bool pack, HostPlan* plan);
+                const int32_t* offsets, int order_mode, const ChipShape& chip, bool pack, HostPlan* plan,
+                int tile_blocks = kTileBlocks);
 
 // Launches of the bf16 forward kernel with fewer workgroups than half the chip's slots are as long as their longest
 // tile's walk.  There the walks are cut: every tile gets one workgroup, then the workgroup slots left over go one by
@@ -107,5 +112,24 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 // (two 1024^2 images: 54.7 us against 46.1 us).  Fills plan->split_wgs / item_parts, or
 // leaves them empty when the launch is not to be split.
 void split_plan(HostPlan* plan, const ChipShape& chip);
+
+// Cuts every progression into pieces of at most kWalkBlock keys, the form the kernels read whose waves walk blocks of a
+// list on their own: piece i of a tile is one 16-byte record at a known place, whatever the progressions' lengths.  A piece
+// of one key has stride 0, so that every stride is below the token count; those kernels keep strides in 24 bits.
+constexpr int32_t kMaxCutStride = 1 << 24;
+void cut_blocks(HostPlan* plan);
+
+// Launches that do not fill the chip are as long as one workgroup's start, walk and end.  The short-launch forward kernel cuts
+// the walk by four inside the workgroup and gives it a quarter of the rows, but copies every key block for 64 rows where the
+// other kernels copy it for 256, and its copies run at some 20 bytes per clock and CU.  It is taken when its
+// workgroups start (nearly) all at once, up to an eighth more than there are slots, and no list has more than kShortBlocks
+// blocks.  Measured, us, short against 256-row tiles (split where split_plan cuts them): 3 images of 1500 tokens, 6 heads
+// (540 workgroups) 18.2 / 25.7; one of 2500, 12 heads (528) 23.0 / 27.2; one of 4096, 6 heads (384) 19.6 / 26.4, 12 heads (768)
+// 38.1 / 34.1; one of 4096, 12 heads, windows of 512 only (768) 23.8 / 15.1; lists of 4096 keys (128 blocks), 1 head (64)
+// 29.4 / 27.1.  Builds the plan of such a launch (64-row tiles, lists cut into blocks) when it is to be taken; `full` is
+// the plan of 256-row tiles.
+constexpr int kShortBlocks = 64;
+bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
+                int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan);
 
 }  // namespace dfa

@@ -1,0 +1,64 @@
+"""The short-launch forward kernel (64 rows per workgroup, four waves that take every fourth 32-key block of the list, two
+blocks at a time) at the edges of its tiles, blocks and shares, against the fp64 oracle.  Bars as everywhere on the bf16
+path (out 2e-2 / 2e-3, lse per row, see gpu_util)."""
+import numpy as np
+import pytest
+
+from gpu_util import check_lse_bf16, error_stats, make_qkv, to_f64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2403_09195_amd import binding
+    binding.lib()
+    return binding
+
+
+EDGES = [(n, [(n, 1)]) for n in (1, 31, 33, 64, 65, 96, 127, 129, 161, 256, 257, 2016, 2048)] + [
+    (2080, [(2080, 1)]),                           # one block more than the kernel takes: the general one
+    (130, [(65, 2)]),                              # one block and one row, uncovered rows
+    (384, [(96, 1), (192, 2), (384, 4)]),          # row groups that share a tile, skipping blocks, several multiplicities
+    (300, [(20, 1), (60, 3), (300, 5)]),           # many groups of a few rows, many progressions of a few keys
+]
+
+
+@pytest.mark.parametrize("N,branches", EDGES)
+@pytest.mark.parametrize("packed", [False, True])
+def test_edges(B, oracle, N, branches, packed):
+    import torch
+    (q, k, v), ex = make_qkv(1300 + N, 2, N, 3, 64, "bf16")
+    if packed:                                     # views of one buffer, row pitch 3 * H * D
+        q, k, v = torch.stack((q, k, v), dim=2).unbind(2)
+    out, lse = B.forward(q, k, v, branches, 0.125)
+    o_ref, l_ref = oracle.forward(*ex, branches, 0.125)
+    mx, mean = error_stats(to_f64(out), o_ref)
+    assert mx <= 2e-2 and mean <= 2e-3, (mx, mean)
+    check_lse_bf16(to_f64(lse), oracle, ex, branches, 0.125, l_ref)
+
+
+@pytest.mark.parametrize("N", [33, 96, 100, 160])
+def test_infinite_value_stays_in_its_column(B, N):
+    """A value row of infinities at the end of a list whose blocks, or whose shares, are not filled: its own column is
+    infinite, and the slots past the end make no NaN of it."""
+    import torch
+    (q, k, v), _ = make_qkv(78, 1, N, 1, 64, "bf16")
+    v[:, N - 1, :, 5] = float("inf")
+    out, lse = B.forward(q, k, v, [(N, 1)], 0.125)
+    assert bool(torch.isposinf(out[..., 5]).all())
+    rest = torch.cat((out[..., :5], out[..., 6:]), dim=-1)
+    assert bool(torch.isfinite(rest).all()) and bool(torch.isfinite(lse).all())
+
+
+def test_one_key_carries_the_row(B, oracle):
+    """Scores of very different size (scale 4): reference exponents that move late, waves whose share weighs nothing."""
+    (q, k, v), ex = make_qkv(1400, 1, 384, 2, 64, "bf16")
+    branches = [(96, 1), (384, 3)]
+    out, lse = B.forward(q, k, v, branches, 4.0)
+    o_ref, l_ref = oracle.forward(*ex, branches, 4.0)
+    # a weight is off by 2^-8 at most, an output by that times its two largest values (|v| <= 4.5) and its own rounding
+    assert np.abs(to_f64(out) - o_ref).max() <= 2.0 ** -8 * (2 * 4.5 + 4.5)
+    assert np.abs(to_f64(lse) - l_ref).max() <= 3.95e-3 + 4e-6 * np.abs(l_ref).max()
