@@ -122,17 +122,23 @@ def _branches(branches):
     return arr, len(branches)
 
 
-def _i32_array(values):
-    """Flattens nested ints into a C int32 array; None -> NULL."""
+def _flat(values):
+    """Nested ints as one list; None -> None."""
     if values is None:
         return None
     flat = []
     for row in values:
         if isinstance(row, (list, tuple)) or hasattr(row, "__iter__"):
-            flat.extend(int(x) for x in row)
+            flat.extend(map(int, row))
         else:
             flat.append(int(row))
-    return (ctypes.c_int32 * len(flat))(*flat)
+    return flat
+
+
+def _i32_array(values):
+    """Flattens nested ints into a C int32 array; None -> NULL."""
+    flat = _flat(values)
+    return None if flat is None else (ctypes.c_int32 * len(flat))(*flat)
 
 
 def _dtype_code(t):
@@ -152,8 +158,35 @@ def _strides(t):
 
 
 def _stream():
+    """Handle of the current device's current stream."""
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # the handle without a Stream object around it
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
+
+
+# What the C calls take besides pointers, scale and stream, marshalled once per combination of shape, strides, dtype,
+# branches and offsets.  Small calls wait for their host side: a forward call took 16.4 us on the host, with a table of offsets
+# 23.4, most of it for these ctypes objects (now 10.7 and 12.0).  Keyed by value throughout; no entry depends on a tensor's
+# memory, and entries are never written after they are made.
+_prepared = {}
+_MAX_PREPARED = 256
+
+
+def _prepare(q, k, v, branches, head_offsets):
+    """(strides of q, k, v, B, H, N, D, dtype code, branch array, their number, offset array, the key)."""
+    flat = _flat(head_offsets)
+    pairs = [(int(w), int(r)) for (w, r) in branches]
+    key = (q.shape, q.stride(), k.stride(), v.stride(), q.dtype, tuple(pairs), None if flat is None else tuple(flat))
+    hit = _prepared.get(key)
+    if hit is None:
+        B, N, H, D = q.shape
+        br, nb = _branches(pairs)
+        offs = None if flat is None else (ctypes.c_int32 * len(flat))(*flat)
+        hit = (_strides(q), _strides(k), _strides(v), B, H, N, D, _dtype_code(q), br, nb, offs, key)
+        if len(_prepared) >= _MAX_PREPARED:
+            _prepared.clear()
+        _prepared[key] = hit
+    return hit
 
 
 def _gpu(t, name):
@@ -183,38 +216,39 @@ _ws_bytes = {}
 
 def workspace_bytes(B, H, N, D, dtype_code, branches, head_offsets=None):
     """Bytes of workspace dfa_forward uses for this shape on the current device (0 = none)."""
-    offs = _i32_array(head_offsets)
-    key = (B, H, N, D, dtype_code, tuple(tuple(b) for b in branches), tuple(offs) if offs is not None else None)
+    flat = _flat(head_offsets)
+    key = (B, H, N, D, dtype_code, tuple(tuple(b) for b in branches), None if flat is None else tuple(flat))
     if key not in _ws_bytes:
         br, nb = _branches(branches)
-        _ws_bytes[key] = int(lib().dfa_workspace_bytes(B, H, N, D, dtype_code, br, nb, offs))
+        _ws_bytes[key] = int(lib().dfa_workspace_bytes(B, H, N, D, dtype_code, br, nb, _i32_array(flat)))
     return _ws_bytes[key]
 
 
-def _workspace(workspace, q, branches, head_offsets):
+def _workspace(workspace, q, prepared):
     """(pointer, bytes, keep-alive) of the workspace argument: a uint8 tensor, None (NULL: unsplit launch)
     or "auto" (a fresh tensor of the size the library asks for)."""
     import torch
     if isinstance(workspace, str) and workspace == "auto":
-        B, N, H, D = q.shape
-        need = workspace_bytes(B, H, N, D, _dtype_code(q), branches, head_offsets)
+        _, _, _, B, H, N, D, code, br, nb, offs, key = prepared
+        shape_key = (key[0], code, key[5], key[6])
+        need = _ws_bytes.get(shape_key)
+        if need is None:
+            need = _ws_bytes[shape_key] = int(lib().dfa_workspace_bytes(B, H, N, D, code, br, nb, offs))
         workspace = torch.empty((need,), dtype=torch.uint8, device=q.device) if need else None
     if workspace is None:
-        return ctypes.c_void_p(None), ctypes.c_size_t(0), None
+        return None, 0, None
     _gpu(workspace, "workspace")
-    return ctypes.c_void_p(workspace.data_ptr()), ctypes.c_size_t(workspace.numel() * workspace.element_size()), workspace
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size(), workspace
 
 
 def _fwd_args(q, k, v, branches, scale, head_offsets, out, lse, workspace):
     for t, nm in ((q, "q"), (k, "k"), (v, "v"), (out, "out")):
         _gpu(t, nm)
-    B, N, H, D = q.shape
-    br, nb = _branches(branches)
-    ws_ptr, ws_bytes, keep = _workspace(workspace, q, branches, head_offsets)
-    return [ctypes.c_void_p(q.data_ptr()), ctypes.c_void_p(k.data_ptr()), ctypes.c_void_p(v.data_ptr()),
-            _strides(q), _strides(k), _strides(v), B, H, N, D, _dtype_code(q), ctypes.c_float(scale),
-            br, nb, _i32_array(head_offsets), ctypes.c_void_p(out.data_ptr()),
-            ctypes.c_void_p(lse.data_ptr() if lse is not None else None), ws_ptr, ws_bytes, _stream()], keep
+    prepared = _prepare(q, k, v, branches, head_offsets)
+    sq, sk, sv, B, H, N, D, code, br, nb, offs, _ = prepared
+    ws_ptr, ws_bytes, keep = _workspace(workspace, q, prepared)
+    return [q.data_ptr(), k.data_ptr(), v.data_ptr(), sq, sk, sv, B, H, N, D, code, scale, br, nb, offs, out.data_ptr(),
+            lse.data_ptr() if lse is not None else None, ws_ptr, ws_bytes, _stream()], keep
 
 
 def forward(q, k, v, branches, scale, head_offsets=None, out=None, lse=None, want_lse=True, workspace="auto"):
@@ -228,8 +262,10 @@ def forward(q, k, v, branches, scale, head_offsets=None, out=None, lse=None, wan
         lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
     args, keep = _fwd_args(q, k, v, branches, scale, head_offsets, out, lse, workspace)
     _check(lib().dfa_forward(*args), "dfa_forward")
-    if keep is not None and hasattr(keep, "record_stream"):
-        keep.record_stream(torch.cuda.current_stream())     # the launch reads it after this function returns
+    if keep is workspace and hasattr(keep, "record_stream"):
+        # the launch reads it after this function returns.  (A fresh one was allocated on this stream: the allocator
+        # gives its memory to later work of this stream only.)
+        keep.record_stream(torch.cuda.current_stream())
     return out, lse
 
 
@@ -360,7 +396,9 @@ def encoder_stack(x, w_qkv, w_o, H, branches, scale, head_offsets=None, buffers=
     qkv, attn, y = buffers
     br, nb = _branches(branches)
     vp = ctypes.c_void_p
-    ws_ptr, ws_bytes, keep = _workspace(workspace, qkv[:, :, 0], branches, head_offsets)
+    q = qkv[:, :, 0]
+    prepared = _prepare(q, q, q, branches, head_offsets) if isinstance(workspace, str) else None
+    ws_ptr, ws_bytes, keep = _workspace(workspace, q, prepared)
     _check(lib().dfa_encoder_stack(vp(x.data_ptr()), vp(w_qkv.data_ptr()), vp(w_o.data_ptr()), layers, B, H, N, D,
                                    ctypes.c_float(scale), br, nb, _i32_array(head_offsets),
                                    vp(qkv.data_ptr()), vp(attn.data_ptr()), vp(y.data_ptr()), ws_ptr, ws_bytes,
@@ -381,15 +419,12 @@ def backward(q, k, v, out, lse, dout, branches, scale, head_offsets=None):
         raise ValueError("backward: out, dout and lse must be contiguous")
     if out.dtype != q.dtype or dout.dtype != q.dtype or lse.dtype != torch.float32:
         raise TypeError("backward: out and dout must have q's dtype, lse fp32")
-    br, nb = _branches(branches)
+    sq, sk, sv, _, _, _, _, code, br, nb, offs, _ = _prepare(q, k, v, branches, head_offsets)
     dq, dk, dv = (torch.empty((B, N, H, D), dtype=q.dtype, device=q.device) for _ in range(3))
     delta = torch.empty((2, B, H, N), dtype=torch.float32, device=q.device)
-    vp = ctypes.c_void_p
-    _check(lib().dfa_backward(vp(q.data_ptr()), vp(k.data_ptr()), vp(v.data_ptr()), vp(out.data_ptr()),
-                              vp(lse.data_ptr()), vp(dout.data_ptr()), _strides(q), _strides(k), _strides(v),
-                              B, H, N, D, _dtype_code(q), ctypes.c_float(scale), br, nb, _i32_array(head_offsets),
-                              vp(delta.data_ptr()), vp(dq.data_ptr()), vp(dk.data_ptr()), vp(dv.data_ptr()), _stream()),
-           "dfa_backward")
+    _check(lib().dfa_backward(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), dout.data_ptr(),
+                              sq, sk, sv, B, H, N, D, code, scale, br, nb, offs, delta.data_ptr(), dq.data_ptr(),
+                              dk.data_ptr(), dv.data_ptr(), _stream()), "dfa_backward")
     return dq, dk, dv
 
 
