@@ -89,10 +89,12 @@ size_t split_bytes(int32_t n_split_wgs) {
     return n_split_wgs > 0 ? align256((size_t)n_split_wgs * kSplitBlockBytes) : 0;
 }
 
-// packed: the plan of the bf16 forward kernel (row groups may share a tile, multiplicities per wave); the fp32 and
-// backward kernels read the plain one.
+// The plan of the bf16 forward (row groups may share a tile, multiplicities per 32-row block), that of the bf16 backward, and
+// the plain one that the fp32 kernels and the single branches read.
+enum class PlanKind : int32_t { kPlain, kForward, kBackward };
 int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
-              const ChipShape& chip, bool packed, PackedPlan* out) {
+              const ChipShape& chip, PlanKind kind, PackedPlan* out) {
+    const bool packed = kind == PlanKind::kForward;
     HostPlan hp;
     build_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, packed, &hp);
     if (hp.items.size() > (size_t)0x7fffffff) return DFA_ERR_TOO_LARGE;
@@ -101,6 +103,12 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
         out->n_split_wgs = (int32_t)hp.split_wgs.size();
         HostPlan sp;
         if (short_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, hp, &sp)) {
+            out->short_walk = true;
+            hp = std::move(sp);
+        }
+    } else if (kind == PlanKind::kBackward) {
+        HostPlan sp;
+        if (short_backward_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, hp, &sp)) {
             out->short_walk = true;
             hp = std::move(sp);
         }
@@ -153,9 +161,9 @@ void point_plan(DevicePlan* dp, void* base, const PackedPlan& pp, int device) {
     dp->max_tile_rows = pp.max_tile_rows;
 }
 
-std::vector<int32_t> plan_key(int device, bool packed, int32_t B, int32_t H, int32_t N, const dfa_branch_t* br,
+std::vector<int32_t> plan_key(int device, PlanKind kind, int32_t B, int32_t H, int32_t N, const dfa_branch_t* br,
                               int32_t nb, const int32_t* offsets) {
-    std::vector<int32_t> key = {device, packed ? 1 : 0, B, H, N, nb, offsets ? 1 : 0};
+    std::vector<int32_t> key = {device, (int32_t)kind, B, H, N, nb, offsets ? 1 : 0};
     for (int x = 0; x < nb; ++x) {
         key.push_back(br[x].w);
         key.push_back(br[x].r);
@@ -200,13 +208,13 @@ int current_chip(int* device, ChipShape* chip) {
 
 // Looks the plan of the current device up, building and uploading it on first use (the only device
 // allocation the library makes).  Plans pushed out of the cache are freed once no call holds them.
-int get_plan(bool packed, int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb,
+int get_plan(PlanKind kind, int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb,
              const int32_t* offsets, PlanRef* out) {
     int device = 0;
     ChipShape chip;
     int rc = current_chip(&device, &chip);
     if (rc != DFA_OK) return rc;
-    PlanKey key = plan_key(device, packed, B, H, N, br, nb, offsets);
+    PlanKey key = plan_key(device, kind, B, H, N, br, nb, offsets);
     {
         std::lock_guard<std::mutex> lock(g_mu);
         auto it = g_plans.find(key);
@@ -218,7 +226,7 @@ int get_plan(bool packed, int32_t B, int32_t H, int32_t N, const dfa_branch_t* b
     }
     // built outside the lock: two threads may both build a new shape, the second result replaces the first
     PackedPlan pp;
-    rc = pack_plan(B, H, N, br, nb, offsets, chip, packed, &pp);
+    rc = pack_plan(B, H, N, br, nb, offsets, chip, kind, &pp);
     if (rc != DFA_OK) return rc;
     auto dp = std::make_shared<DevicePlan>();
     void* base = nullptr;
@@ -364,7 +372,7 @@ int forward_impl(const void* q, const void* k, const void* v, dfa_strides_t sq, 
     if (workspace && reinterpret_cast<uintptr_t>(workspace) % 16) return DFA_ERR_ALIGN;
     PlanRef dp;
     // fp32 output from bf16 inputs is the unmerged single branch of dfa_forward_branch: the plain plan
-    rc = get_plan(dt == DFA_BF16 && !out_f32, B, H, N, branches, nb, head_offsets, &dp);
+    rc = get_plan(dt == DFA_BF16 && !out_f32 ? PlanKind::kForward : PlanKind::kPlain, B, H, N, branches, nb, head_offsets, &dp);
     if (rc != DFA_OK) return rc;
     float* split_ws = nullptr;
     if (workspace && dt == DFA_BF16 && !out_f32 && dp->n_split_wgs > 0) {
@@ -455,10 +463,11 @@ int dfa_forward_static(const void* q, const void* k, const void* v, dfa_strides_
             ss.ptr = static_cast<unsigned char*>(p);
             ss.plan.owned = false;
         }
-        PlanKey key = plan_key(device, dt == DFA_BF16, B, H, N, branches, nb, head_offsets);
+        const PlanKind kind = dt == DFA_BF16 ? PlanKind::kForward : PlanKind::kPlain;
+        PlanKey key = plan_key(device, kind, B, H, N, branches, nb, head_offsets);
         if (!ss.holds_plan || ss.key != key) {
             PackedPlan pp;
-            rc = pack_plan(B, H, N, branches, nb, head_offsets, chip, dt == DFA_BF16, &pp);
+            rc = pack_plan(B, H, N, branches, nb, head_offsets, chip, kind, &pp);
             if (rc != DFA_OK) return rc;
             const size_t plan_bytes = align256(pp.bytes.size());
             const size_t part_bytes = dt == DFA_BF16 ? split_bytes(pp.n_split_wgs) : 0;
@@ -570,7 +579,7 @@ int dfa_backward(const void* q, const void* k, const void* v, const void* out, c
     }
     try {
         PlanRef plan;
-        rc = get_plan(false, B, H, N, branches, nb, head_offsets, &plan);
+        rc = get_plan(dt == DFA_BF16 ? PlanKind::kBackward : PlanKind::kPlain, B, H, N, branches, nb, head_offsets, &plan);
         if (rc != DFA_OK) return rc;
         const DevicePlan& dp = *plan;
         BwdParams p;
@@ -581,6 +590,8 @@ int dfa_backward(const void* q, const void* k, const void* v, const void* out, c
         p.lse = lse; p.ndelta = delta_ws; p.lse2 = delta_ws + (int64_t)B * H * N; p.dq = dq; p.dk = dk; p.dv = dv;
         p.rows = dp.rows; p.segs = dp.segs; p.items = dp.items;
         p.H = H; p.N = N; p.scale = scale;
+        if (dp.short_walk)
+            return launch_bwd_short(p, dp.n_items, static_cast<hipStream_t>(stream)) == hipSuccess ? DFA_OK : DFA_ERR_LAUNCH;
         return launch_bwd(p, dp.n_items, dp.max_tile_rows, B, dt == DFA_BF16, static_cast<hipStream_t>(stream)) == hipSuccess
                    ? DFA_OK : DFA_ERR_LAUNCH;
     } catch (const std::bad_alloc&) {
@@ -630,7 +641,7 @@ int dfa_encoder_stack(const void* x, const void* w_qkv, const void* w_o, int32_t
     if (workspace && reinterpret_cast<uintptr_t>(workspace) % 16) return DFA_ERR_ALIGN;
     try {
         PlanRef dp;
-        rc = get_plan(true, B, H, N, branches, nb, head_offsets, &dp);
+        rc = get_plan(PlanKind::kForward, B, H, N, branches, nb, head_offsets, &dp);
         if (rc != DFA_OK) return rc;
         if (workspace && dp->n_split_wgs > 0 && workspace_bytes < split_bytes(dp->n_split_wgs))
             return DFA_ERR_WORKSPACE;

@@ -70,15 +70,6 @@ struct BlockWalk {
     __device__ __forceinline__ int32_t first() const { return kept_row(seg.key0, seg.stride, t * kWalkBlock); }
 };
 
-// Record i of a list cut into blocks, through the constant address space: a scalar load.  (After the copies' memory
-// clobber the compiler takes a vector load instead, whose wait would drain the copies in flight.)
-__device__ __forceinline__ KeySeg load_block(const KeySeg* list, int i) {
-    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    const i32x4 x = *reinterpret_cast<const __attribute__((address_space(4))) i32x4*>(reinterpret_cast<uintptr_t>(list + i));
-    const int32_t mult = x[3];              // (the bit cast of an element in place would be that of element 0)
-    return KeySeg{x[0], x[1], x[2], __builtin_bit_cast(float, mult)};
-}
-
 // All LDS reads of this wave so far have returned; no memory access moves across.
 __device__ __forceinline__ void lds_reads_done() {
     __builtin_amdgcn_s_waitcnt(0xC07F);
@@ -119,18 +110,29 @@ __device__ __forceinline__ bf16x8 read_transposed(const uint16_t* rows16, const 
 }
 
 // Issues the copies of one bf16 block into a wave's own LDS: rows key0 + stride * i of a tensor with row pitch sn
-// (elements), permuted by sigma (swap bits 2 and 3) and swizzled like a stage; rows past the end of the list re-read its
-// last one.
+// (elements), permuted by sigma (swap bits 2 and 3) and swizzled like a stage; rows past the end of the block re-read its
+// last one.  In a whole block the four copies differ in their scalar base and one bit of the chunk alone.  The lane number
+// comes in opaque, so that nothing derived from it is kept in registers across the walk.
 __device__ __forceinline__ void issue_rows(const uint16_t* base, int64_t sn, const KeySeg& blk, uint32_t lds_addr, int lane) {
-    const void* const ub = uniform_ptr(base + (int64_t)blk.key0 * sn);
-    const uint32_t pitch = (uint32_t)(blk.stride * sn * 2);
-    const int room = blk.count - 1, r = lane >> 3;
-    const int pos = (r & 3) | ((r & 4) << 1);
-    const uint32_t chunk = 16u * ((lane & 7) ^ stage_swizzle(r));
+    const uint16_t* const first = base + (int64_t)blk.key0 * sn;
+    const int64_t pitch = (int64_t)blk.stride * sn;               // elements
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int r = ln >> 3, pos = (r & 3) | ((r & 4) << 1);
+    const uint32_t chunk = 16u * ((ln & 7) ^ stage_swizzle(r));
+    if (blk.count == kWalkBlock) {
+        const uint32_t off = (uint32_t)pos * (uint32_t)(pitch * 2);
 #pragma unroll
-    for (int u = 0; u < kBlockCopies; ++u)
-        copy16_to_lds(ub, (uint32_t)min(pos | ((u & 1) << 2) | ((u & 2) << 3), room) * pitch + (chunk ^ (16u * (u & 1))),
-                      lds_addr + 1024u * u);
+        for (int u = 0; u < kBlockCopies; ++u)
+            copy16_to_lds(uniform_ptr(first + (((u & 1) << 2) | ((u & 2) << 3)) * pitch), off + (chunk ^ (16u * (u & 1))), lds_addr + 1024u * u);
+    } else {
+        const int room = blk.count - 1;
+        const void* const ub = uniform_ptr(first);
+#pragma unroll
+        for (int u = 0; u < kBlockCopies; ++u)
+            copy16_to_lds(ub, (uint32_t)min(pos | ((u & 1) << 2) | ((u & 2) << 3), room) * (uint32_t)(pitch * 2) + (chunk ^ (16u * (u & 1))),
+                          lds_addr + 1024u * u);
+    }
 }
 
 // A wave's [32 rows][64 d] result, held transposed (lane (j, g), register v of half db: row j, d = 32*db + kappa(v, g)),

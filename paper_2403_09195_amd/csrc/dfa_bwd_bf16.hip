@@ -24,7 +24,7 @@
 // (~ marks the walked rows).  lse and delta of the walked queries travel with the rows as 4-byte
 // copies.  P is recomputed from lse; there is no online softmax and no rescaling here.
 #include "dfa_device.h"
-#include "dfa_blocks.h"
+#include "dfa_bwd_bf16.h"
 
 namespace dfa {
 
@@ -75,66 +75,6 @@ __device__ __forceinline__ void issue_scalars(const float* per_row, const KeyCur
     const int room = c.count - 1 - j0;
     const int64_t first = kept_row(c.key0, c.stride, j0);
     copy4_to_lds(uniform_ptr(per_row + first), (uint32_t)(min(lane, room) * c.stride * 4), lds_addr);
-}
-
-// Every value of a 32-row block at or past list position nvalid becomes -inf (its P is then 0).
-// Register v of lane (j, g) is block position 16*(v/8) + 8*g + v%8.
-__device__ __forceinline__ void mask_rows(floatx16& s, int g, int nvalid) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v)
-        if (16 * (v >> 3) + 8 * g + (v & 7) >= nvalid) s[v] = -INFINITY;
-}
-
-__device__ __forceinline__ floatx16 zero16() {
-    floatx16 z;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) z[v] = 0.f;
-    return z;
-}
-
-// packs 16 fp32 values into the two B operands (16-row steps) of the second product
-__device__ __forceinline__ void pack_block(const float (&x)[16], u32x4 (&pb)[2]) {
-#pragma unroll
-    for (int v = 0; v < 8; ++v) {
-        const bf16x2 pr = {(__bf16)x[2 * v], (__bf16)x[2 * v + 1]};
-        pb[v >> 2][v & 3] = __builtin_bit_cast(uint32_t, pr);
-    }
-}
-
-// P and dS of one 32 x 32 block of the dk/dv kernel.  lp: lse (base-2 units) of the walked queries in LDS;
-// register v of a lane is block position 16*(v/8) + 8*g + v%8, lp points at position 8*g.  dpd holds
-// dP - delta already (the accumulators of dP start from -delta).  kBias: the pairs of this step count m
-// times, log2 m = bias (see KeySeg).  The factor scale of dS goes onto the dk accumulator at the end.
-template <bool kBias>
-__device__ __forceinline__ void probs_block(const floatx16& s, const floatx16& dpd, const float* lp,
-                                            float c, float bias, float (&pr)[16], float (&ds)[16]) {
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-        for (int e = 0; e < 8; e += 4) {
-            const float4 l2 = *reinterpret_cast<const float4*>(lp + 16 * hf + e);
-            const float l2a[4] = {l2.x, l2.y, l2.z, l2.w};
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const int v = 8 * hf + e + x;
-                pr[v] = __builtin_amdgcn_exp2f(fmaf(s[v], c, kBias ? bias - l2a[x] : -l2a[x]));
-                ds[v] = pr[v] * dpd[v];
-            }
-        }
-}
-
-// -delta of the 32 walked queries of a block as the start value of the dP accumulators: register v of a
-// lane is block position 16*(v/8) + 8*g + v%8, dl points at position 8*g.
-__device__ __forceinline__ floatx16 load_ndelta(const float* dl) {
-    floatx16 r;
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-        for (int e = 0; e < 8; e += 4) {
-            const float4 d = *reinterpret_cast<const float4*>(dl + 16 * hf + e);
-            r[8 * hf + e] = d.x; r[8 * hf + e + 1] = d.y; r[8 * hf + e + 2] = d.z; r[8 * hf + e + 3] = d.w;
-        }
-    return r;
 }
 
 // dq of a tile: its rows are queries, the lists are walked as keys.  Four waves of 64 rows each.

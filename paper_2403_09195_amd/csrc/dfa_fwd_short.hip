@@ -88,7 +88,12 @@ __global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu
 void dfa_fwd_short_kernel(const FwdParams p) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[kWalkWaves][kBuffers * kBlockElems];     // per wave: K, K, V, V
     __shared__ u32x4 records_all[kWalkWaves][64];
+    __shared__ int32_t row_lds[kShortRows];
 
+    // the kernel arguments read in one go (the compiler puts each load where its value is first used: a trip to memory each)
+    asm volatile("" ::"s"(p.q), "s"(p.k), "s"(p.v), "s"(p.out), "s"(p.lse), "s"(p.rows), "s"(p.segs), "s"(p.items), "s"(p.block_mult));
+    asm volatile("" ::"s"(p.sqb), "s"(p.sqn), "s"(p.sqh), "s"(p.skb), "s"(p.skn), "s"(p.skh), "s"(p.svb), "s"(p.svn), "s"(p.svh), "s"(p.H), "s"(p.N),
+                 "s"(p.scale));
     const Item item = load_item(p.items, blockIdx.x);
     if (item.tile < 0) return;
     const Tile tile = item.t;
@@ -115,6 +120,7 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     // the share's records and the rows of the Q fragments in one trip to memory, the fragments and the first blocks in the next
     u32x4* const records = records_all[wave];
     const u32x4 my_record = load_record(p, tile, wave, lane);
+    if (tid < kShortRows) row_lds[tid] = rows[min(tid, tile.nrows - 1)];
     // a filler slot of a packed tile holds ~n of a row n of its group: loaded like any row, never stored
     int32_t q_row[2] = {rows[min(j, tile.nrows - 1)], rows[min(kWalkBlock + j, tile.nrows - 1)]};
     q_row[0] ^= q_row[0] >> 31;
@@ -247,7 +253,7 @@ void dfa_fwd_short_kernel(const FwdParams p) {
         }
         __syncthreads();
         const int slot = qb * kWalkBlock + orow;
-        const int32_t n_out = rows[min(slot, tile.nrows - 1)];
+        const int32_t n_out = row_lds[slot];
         if (slot >= tile.nrows || n_out < 0) continue;
         float m = kRefStart;
 #pragma unroll

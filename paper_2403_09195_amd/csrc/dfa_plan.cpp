@@ -508,4 +508,30 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     return true;
 }
 
+bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
+                         int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan) {
+    if (N >= kMaxCutStride) return false;
+    // us for the two launches on 256 CUs, see dfa_plan.h; `most`: a bound on what the short kernels may take
+    const double per_slot = 512.0 / chip.fwd_slots();
+    int64_t steps = 0;
+    int32_t longest = 0;
+    for (const Item& i : full.items)
+        if (i.tile >= 0) {
+            steps += i.t.n_steps;
+            longest = std::max(longest, i.t.n_steps);
+        }
+    const double full_us = 15.0 + std::max(3.2 * longest, 0.0164 * steps * per_slot);
+    if (full.items.size() * 0.029 * per_slot > full_us) return false;          // there are at least as many 64-row tiles
+    build_plan(B, H, N, br, nb, offsets, order_mode, chip, false, plan, kShortRows / kBlockRows);
+    cut_blocks(plan);
+    int64_t tiles = 0, blocks = 0;
+    for (const Item& i : plan->items)
+        if (i.tile >= 0) {
+            if (i.t.nseg > kShortBackwardBlocks) return false;
+            ++tiles;
+            blocks += i.t.nseg;
+        }
+    return 10.0 + (0.029 * tiles + 0.002 * blocks) * per_slot < full_us;
+}
+
 }  // namespace dfa

@@ -1,10 +1,12 @@
-"""The short-launch forward kernel (64 rows per workgroup, four waves that take every fourth 32-key block of the list, two
-blocks at a time) at the edges of its tiles, blocks and shares, against the fp64 oracle.  Bars as everywhere on the bf16
-path (out 2e-2 / 2e-3, lse per row, see gpu_util)."""
+"""The short-launch kernels (64 rows per workgroup, 32 for dk and dv; four waves that take every fourth 32-row block of the
+list, the forward two blocks at a time) at the edges of their tiles, blocks and shares, against the fp64 oracle.  Bars as
+everywhere on the bf16 path: out 2e-2 / 2e-3, lse per row (see gpu_util), gradients by the size of the terms an element is
+a sum of (the bound of the random problems in test_gpu_random_shapes)."""
 import numpy as np
 import pytest
 
-from gpu_util import check_lse_bf16, error_stats, make_qkv, to_f64
+import helpers
+from gpu_util import check_lse_bf16, error_stats, make_qkv, to_device, to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -30,6 +32,7 @@ EDGES = [(n, [(n, 1)]) for n in (1, 31, 33, 64, 65, 96, 127, 129, 161, 256, 257,
 @pytest.mark.parametrize("packed", [False, True])
 def test_edges(B, oracle, N, branches, packed):
     import torch
+    from paper_2403_09195_amd import synth
     (q, k, v), ex = make_qkv(1300 + N, 2, N, 3, 64, "bf16")
     if packed:                                     # views of one buffer, row pitch 3 * H * D
         q, k, v = torch.stack((q, k, v), dim=2).unbind(2)
@@ -38,6 +41,17 @@ def test_edges(B, oracle, N, branches, packed):
     mx, mean = error_stats(to_f64(out), o_ref)
     assert mx <= 2e-2 and mean <= 2e-3, (mx, mean)
     check_lse_bf16(to_f64(lse), oracle, ex, branches, 0.125, l_ref)
+    st, ge = synth.tensor(1300 + N, 7, (2, N, 3, 64), "bf16")
+    grads = B.backward(q, k, v, out, lse, to_device(st), branches, 0.125)
+    refs = oracle.backward(*ex, ge, branches, 0.125)
+    bounds = helpers.multiset_attention_backward(*ex, ge, 0.125, branches)[3:]
+    dead = np.isneginf(l_ref).transpose(0, 2, 1)
+    eps = 2.0 ** -9
+    for name, got, ref, absum in zip(("dq", "dk", "dv"), grads, refs, bounds):
+        d = np.abs(to_f64(got) - ref)
+        assert np.all(d <= 2.0 ** -8 * np.abs(ref) + 4 * eps * absum + 1e-6), name
+        assert d.mean() <= eps * absum.mean() + 1e-7, name
+        assert np.all(to_f64(got)[dead] == 0.0)
 
 
 @pytest.mark.parametrize("N", [33, 96, 100, 160])
