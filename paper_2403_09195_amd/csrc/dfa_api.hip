@@ -44,6 +44,7 @@ struct DevicePlan {
     // other launches with few workgroups walk their tiles with n_split_wgs workgroups in all (see split_plan and
     // launch_fwd_bf16_split) when the caller brings a workspace for their partial results; 0: never split
     const SplitWg* split_wgs = nullptr;
+    const Item* split_items = nullptr;
     const ItemParts* item_parts = nullptr;
     int32_t n_split_wgs = 0;
     bool owned = true;          // base came from hipMalloc and is freed with the plan
@@ -70,7 +71,7 @@ using PlanRef = std::shared_ptr<const DevicePlan>;
 // shares of a split launch, each part 256-byte aligned.
 struct PackedPlan {
     std::vector<char> bytes;
-    size_t off_segs = 0, off_items = 0, off_split_wgs = 0, off_item_parts = 0, off_block_mult = 0;
+    size_t off_segs = 0, off_items = 0, off_split_wgs = 0, off_split_items = 0, off_item_parts = 0, off_block_mult = 0;
     int32_t n_items = 0;
     int32_t n_split_wgs = 0;
     int32_t max_tile_rows = 1;
@@ -117,13 +118,15 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
     const size_t b_segs = align256(hp.segs.size() * sizeof(KeySeg) + sizeof(KeySeg));
     const size_t b_items = align256(hp.items.size() * sizeof(Item));
     const size_t b_wgs = align256(hp.split_wgs.size() * sizeof(SplitWg));
+    const size_t b_witems = align256(hp.split_wgs.size() * sizeof(Item));
     const size_t b_parts = align256(hp.item_parts.size() * sizeof(ItemParts));
     const size_t b_wmult = packed ? align256((hp.segs.size() + 1) * kTileBlocks * sizeof(float)) : 0;
-    out->bytes.assign(b_rows + b_segs + b_items + b_wgs + b_parts + b_wmult, 0);
+    out->bytes.assign(b_rows + b_segs + b_items + b_wgs + b_witems + b_parts + b_wmult, 0);
     out->off_segs = b_rows;
     out->off_items = b_rows + b_segs;
     out->off_split_wgs = out->off_items + b_items;
-    out->off_item_parts = out->off_split_wgs + b_wgs;
+    out->off_split_items = out->off_split_wgs + b_wgs;
+    out->off_item_parts = out->off_split_items + b_witems;
     out->off_block_mult = out->off_item_parts + b_parts;
     if (packed) {
         // log2 of the multiplicities, -inf where a block's rows skip the progression
@@ -135,6 +138,8 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
     if (!hp.items.empty()) std::memcpy(out->bytes.data() + b_rows + b_segs, hp.items.data(), hp.items.size() * sizeof(Item));
     if (!hp.split_wgs.empty()) {
         std::memcpy(out->bytes.data() + out->off_split_wgs, hp.split_wgs.data(), hp.split_wgs.size() * sizeof(SplitWg));
+        for (size_t g = 0; g < hp.split_wgs.size(); ++g)
+            std::memcpy(out->bytes.data() + out->off_split_items + g * sizeof(Item), &hp.items[hp.split_wgs[g].item], sizeof(Item));
         std::memcpy(out->bytes.data() + out->off_item_parts, hp.item_parts.data(), hp.item_parts.size() * sizeof(ItemParts));
     }
     out->n_items = (int32_t)hp.items.size();
@@ -153,6 +158,7 @@ void point_plan(DevicePlan* dp, void* base, const PackedPlan& pp, int device) {
     dp->device = device;
     dp->bytes = pp.bytes.size();
     dp->split_wgs = reinterpret_cast<const SplitWg*>(b + pp.off_split_wgs);
+    dp->split_items = reinterpret_cast<const Item*>(b + pp.off_split_items);
     dp->item_parts = reinterpret_cast<const ItemParts*>(b + pp.off_item_parts);
     dp->n_split_wgs = pp.n_split_wgs;
     dp->block_mult = reinterpret_cast<const float*>(b + pp.off_block_mult);
@@ -346,7 +352,7 @@ int launch_forward(const DevicePlan& dp, const void* q, const void* k, const voi
     p.out = out; p.lse = lse;
     p.rows = dp.rows; p.segs = dp.segs; p.items = dp.items; p.block_mult = dp.block_mult;
     p.H = H; p.N = N; p.scale = scale;
-    p.split_wgs = dp.split_wgs; p.item_parts = dp.item_parts; p.split_ws = split_ws;
+    p.split_wgs = dp.split_wgs; p.split_items = dp.split_items; p.item_parts = dp.item_parts; p.split_ws = split_ws;
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     if (dt == DFA_BF16 && !out_f32 && dp.short_walk) {

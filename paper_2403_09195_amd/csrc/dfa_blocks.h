@@ -22,14 +22,6 @@ __device__ __forceinline__ void item_of_part(int x, int parts, int& item, int& p
     part = rem / kDies;
 }
 
-// A launch item in one scalar load.
-__device__ __forceinline__ Item load_item(const Item* items, int i) {
-    typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
-    static_assert(sizeof(Item) == sizeof(i32x8), "a launch item is eight words");
-    const i32x8 x = *reinterpret_cast<const __attribute__((address_space(4))) i32x8*>(reinterpret_cast<uintptr_t>(items + i));
-    return Item{x[0], x[1], Tile{x[2], x[3], x[4], x[5], x[6], x[7]}};
-}
-
 // The 32-row blocks of a tile's progressions, counted through; wave w takes blocks w, w + 4, w + 8, ...
 struct BlockWalk {
     const KeySeg* segs;

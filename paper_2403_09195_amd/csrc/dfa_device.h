@@ -37,6 +37,7 @@ struct FwdParams {
     // 64-key steps that split_wgs[g] names and leaves its partial result in block g of split_ws;
     // launch_merge_split then writes out and lse.
     const SplitWg* split_wgs;
+    const Item* split_items;       // the launch item of every such workgroup
     const ItemParts* item_parts;
     float* split_ws;
 };

@@ -103,14 +103,17 @@ void dfa_fwd_bf16_kernel(const FwdParams p) {
     __shared__ KeySeg seg_all[kPacked ? 4 : 1][kMaxTileSegs];
     __shared__ float bias1_all[kPacked ? 4 : 1][kMaxTileSegs];   // kPacked: log2 m of the wave's second 32-row block
 
-    int part = 0, nparts = 1, item_index = blockIdx.x;
+    int part = 0, nparts = 1;
     if (kSplit) {
-        const SplitWg sw = p.split_wgs[blockIdx.x];
-        item_index = sw.item;
-        part = sw.part_nparts & 0xffff;
-        nparts = sw.part_nparts >> 16;
+        // such a launch is one round of workgroups, as long as its start is: arguments in one trip to memory, share and item
+        // in the next
+        hold_args(p);
+        asm volatile("" ::"s"(p.split_wgs), "s"(p.split_items), "s"(p.split_ws));
+        const int32_t part_nparts = p.split_wgs[blockIdx.x].part_nparts;
+        part = part_nparts & 0xffff;
+        nparts = part_nparts >> 16;
     }
-    const Item item = p.items[item_index];
+    const Item item = kSplit ? load_item(p.split_items, blockIdx.x) : p.items[blockIdx.x];
     if (item.tile < 0) return;
     const Tile tile = item.t;
     const int tid = threadIdx.x;
@@ -499,8 +502,10 @@ void dfa_fwd_bf16_kernel(const FwdParams p) {
 // features each.  The shares' blocks are addressed from the item's entry of item_parts alone, so their loads go out
 // together with that of the row's token (every block has all 256 rows, whatever the tile's count).
 __global__ __launch_bounds__(256) void merge_split_kernel(const FwdParams p) {
+    hold_args(p);
+    asm volatile("" ::"s"(p.item_parts), "s"(p.split_ws));
     const ItemParts ip = p.item_parts[blockIdx.x];
-    const Item item = p.items[blockIdx.x];
+    const Item item = load_item(p.items, blockIdx.x);
     if (ip.nparts <= 1) return;         // padding item, or a tile walked whole (its workgroup wrote the rows itself)
     const int r = blockIdx.y * 32 + (threadIdx.x >> 3), sub = threadIdx.x & 7;
     const char* blk0 = reinterpret_cast<const char*>(p.split_ws) + (int64_t)ip.first_wg * kSplitBlockBytes;

@@ -90,10 +90,7 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     __shared__ u32x4 records_all[kWalkWaves][64];
     __shared__ int32_t row_lds[kShortRows];
 
-    // the kernel arguments read in one go (the compiler puts each load where its value is first used: a trip to memory each)
-    asm volatile("" ::"s"(p.q), "s"(p.k), "s"(p.v), "s"(p.out), "s"(p.lse), "s"(p.rows), "s"(p.segs), "s"(p.items), "s"(p.block_mult));
-    asm volatile("" ::"s"(p.sqb), "s"(p.sqn), "s"(p.sqh), "s"(p.skb), "s"(p.skn), "s"(p.skh), "s"(p.svb), "s"(p.svn), "s"(p.svh), "s"(p.H), "s"(p.N),
-                 "s"(p.scale));
+    hold_args(p);
     const Item item = load_item(p.items, blockIdx.x);
     if (item.tile < 0) return;
     const Tile tile = item.t;

@@ -74,6 +74,22 @@ __device__ __forceinline__ void cursor_next(KeyCursor& c, const KeySeg* seg_lds,
     }
 }
 
+// A launch item in one scalar load.
+__device__ __forceinline__ Item load_item(const Item* items, int i) {
+    typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
+    static_assert(sizeof(Item) == sizeof(i32x8), "a launch item is eight words");
+    const i32x8 x = *reinterpret_cast<const __attribute__((address_space(4))) i32x8*>(reinterpret_cast<uintptr_t>(items + i));
+    return Item{x[0], x[1], Tile{x[2], x[3], x[4], x[5], x[6], x[7]}};
+}
+
+// The forward kernels' arguments read in one go, at the start (the compiler puts each load where its value is first used: a
+// trip to memory each).
+__device__ __forceinline__ void hold_args(const FwdParams& p) {
+    asm volatile("" ::"s"(p.q), "s"(p.k), "s"(p.v), "s"(p.out), "s"(p.lse), "s"(p.rows), "s"(p.segs), "s"(p.items), "s"(p.block_mult));
+    asm volatile("" ::"s"(p.sqb), "s"(p.sqn), "s"(p.sqh), "s"(p.skb), "s"(p.skn), "s"(p.skh), "s"(p.svb), "s"(p.svn), "s"(p.svh), "s"(p.H), "s"(p.N),
+                 "s"(p.scale));
+}
+
 // 16 bytes per lane from global memory straight into LDS.  gbase and lds_addr are
 // wave-uniform; lane L's bytes land at lds_addr + 16*L.  Issued as inline assembly so that the
 // compiler's wait-count insertion does not see it: it would otherwise drain the vector-memory
