@@ -101,29 +101,51 @@ __device__ __forceinline__ bf16x8 read_transposed(const uint16_t* rows16, const 
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// Issues the copies of one bf16 block into a wave's own LDS: rows key0 + stride * i of a tensor with row pitch sn
-// (elements), permuted by sigma (swap bits 2 and 3) and swizzled like a stage; rows past the end of the block re-read its
-// last one.  In a whole block the four copies differ in their scalar base and one bit of the chunk alone.  The lane number
-// comes in opaque, so that nothing derived from it is kept in registers across the walk.
-__device__ __forceinline__ void issue_rows(const uint16_t* base, int64_t sn, const KeySeg& blk, uint32_t lds_addr, int lane) {
-    const uint16_t* const first = base + (int64_t)blk.key0 * sn;
-    const int64_t pitch = (int64_t)blk.stride * sn;               // elements
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-    const int r = ln >> 3, pos = (r & 3) | ((r & 4) << 1);
-    const uint32_t chunk = 16u * ((ln & 7) ^ stage_swizzle(r));
-    if (blk.count == kWalkBlock) {
-        const uint32_t off = (uint32_t)pos * (uint32_t)(pitch * 2);
+// A tensor whose rows a wave copies block by block: rows n of one image and head start at base + n * pitch.  (The entry
+// points take no row pitch of 2^25 bytes or more, see check_forward_args.)
+struct BlockSource {
+    const char* base;
+    uint32_t pitch;
+};
+__device__ __forceinline__ BlockSource block_source(const uint16_t* base, int64_t sn) {
+    return BlockSource{reinterpret_cast<const char*>(base), (uint32_t)(sn * 2)};
+}
+
+// What a lane fetches of a block: copy u fills LDS rows 8*u .. +7, lane L lands at row 8*u + L/8, chunk L%8.
+struct BlockLane {
+    int pos;               // list position of the lane's row in copy 0
+    uint32_t chunk;        // byte offset of its 16-byte chunk
+};
+
+// Issues the copies of one bf16 block into a wave's own LDS: rows key0 + stride * i, permuted and swizzled as kOrder says;
+// rows past the end of the block re-read its last one (a block without a valid row: its first).
+// kWalked: rows permuted by sigma (swap bits 2 and 3), chunks by stage_swizzle: read back as rows or transposed;
+// kKeys, kValues: the layouts of the forward's beat (sigma and k_swizzle; list order, chunks in place).
+enum class BlockOrder { kWalked, kKeys, kValues };
+template <BlockOrder kOrder>
+__device__ __forceinline__ BlockLane block_lane(int lane) {
+    const int r = lane >> 3, c = lane & 7;
+    BlockLane l;
+    l.pos = kOrder == BlockOrder::kValues ? r : (r & 3) | ((r & 4) << 1);
+    l.chunk = 16u * (kOrder == BlockOrder::kValues ? c : c ^ (kOrder == BlockOrder::kKeys ? r >> 1 : stage_swizzle(r)));
+    return l;
+}
+template <BlockOrder kOrder>
+__device__ __forceinline__ void issue_block_rows(const BlockSource& src, int key0, int stride, int count, uint32_t lds_addr, const BlockLane& l) {
+    const void* const first = uniform_ptr(src.base + (uint64_t)(uint32_t)key0 * src.pitch);
+    const uint32_t pitch = (uint32_t)stride * src.pitch;
+    constexpr uint32_t kFlip = kOrder == BlockOrder::kValues ? 0u : kOrder == BlockOrder::kKeys ? 64u : 16u;     // swizzle bit of LDS row bit 3
+    auto row_of = [](int u) { return kOrder == BlockOrder::kValues ? 8 * u : ((u & 1) << 2) | ((u & 2) << 3); };
+    if (count == kWalkBlock) {
+        const uint32_t off = (uint32_t)l.pos * pitch;
 #pragma unroll
         for (int u = 0; u < kBlockCopies; ++u)
-            copy16_to_lds(uniform_ptr(first + (((u & 1) << 2) | ((u & 2) << 3)) * pitch), off + (chunk ^ (16u * (u & 1))), lds_addr + 1024u * u);
+            copy16_to_lds(first, off + (l.chunk ^ (kFlip * (u & 1))) + row_of(u) * pitch, lds_addr + 1024u * u);
     } else {
-        const int room = blk.count - 1;
-        const void* const ub = uniform_ptr(first);
+        const int room = max(count - 1, 0);
 #pragma unroll
         for (int u = 0; u < kBlockCopies; ++u)
-            copy16_to_lds(ub, (uint32_t)min(pos | ((u & 1) << 2) | ((u & 2) << 3), room) * (uint32_t)(pitch * 2) + (chunk ^ (16u * (u & 1))),
-                          lds_addr + 1024u * u);
+            copy16_to_lds(first, (uint32_t)min(l.pos + row_of(u), room) * pitch + (l.chunk ^ (kFlip * (u & 1))), lds_addr + 1024u * u);
     }
 }
 

@@ -6,8 +6,8 @@
 // time.  A wave copies its own blocks, two ahead, and waits for nobody until that sum; the list comes cut into blocks,
 // whose records a wave reads in one trip to memory at the start and keeps in LDS.
 //
-// Bound: latency (start, a quarter of the walk, sum) where the launch is one round of workgroups, and the copies, some
-// 20 bytes per clock and CU, where it is more.
+// Bound: latency.  With one wave on a SIMD a block's steps (fragments, first products, exponentials, second products) follow
+// one another; the second workgroup of the CU fills the gaps.
 #include "dfa_bwd_bf16.h"
 
 namespace dfa {
@@ -90,8 +90,9 @@ void bwd_dq_short_kernel(const BwdParams p) {
     }
 
     const uint16_t* const qp = static_cast<const uint16_t*>(p.q) + (int64_t)b * p.sqb + (int64_t)h * p.sqh;
-    const uint16_t* const kp = static_cast<const uint16_t*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
-    const uint16_t* const vp = static_cast<const uint16_t*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
+    const BlockSource k_src = block_source(static_cast<const uint16_t*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh, p.skn);
+    const BlockSource v_src = block_source(static_cast<const uint16_t*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh, p.svn);
+    const BlockLane cl = block_lane<BlockOrder::kWalked>(lane);
     const uint16_t* const gp = static_cast<const uint16_t*>(p.dout) + out_bh;
     const uint16_t* const op = static_cast<const uint16_t*>(p.out) + out_bh;
     const int64_t stat_bh = ((int64_t)b * p.H + h) * p.N;
@@ -106,8 +107,8 @@ void bwd_dq_short_kernel(const BwdParams p) {
     const int n = (tile.nseg - wave + kWalkWaves - 1) / kWalkWaves;
     const uint32_t addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, lds[wave]));
     auto issue = [&](const KeySeg& blk, int buf) {
-        issue_rows(kp, p.skn, blk, addr + buf * kPairBytes, lane);
-        issue_rows(vp, p.svn, blk, addr + buf * kPairBytes + kBlockBytes, lane);
+        issue_block_rows<BlockOrder::kWalked>(k_src, blk.key0, blk.stride, blk.count, addr + buf * kPairBytes, cl);
+        issue_block_rows<BlockOrder::kWalked>(v_src, blk.key0, blk.stride, blk.count, addr + buf * kPairBytes + kBlockBytes, cl);
     };
     KeySeg cur = read_record(records, 0), nx = read_record(records, 1);
     // -delta = -(dout . out) and lse in base-2 units: 16 rows a wave, 4 lanes a row
@@ -263,10 +264,11 @@ void bwd_dkdv_short_kernel(const BwdParams p, int n_items) {
         return;
     }
 
-    const uint16_t* const qp = static_cast<const uint16_t*>(p.q) + (int64_t)b * p.sqb + (int64_t)h * p.sqh;
+    const BlockSource q_src = block_source(static_cast<const uint16_t*>(p.q) + (int64_t)b * p.sqb + (int64_t)h * p.sqh, p.sqn);
+    const BlockSource g_src = block_source(static_cast<const uint16_t*>(p.dout) + out_bh, g_pitch);
+    const BlockLane cl = block_lane<BlockOrder::kWalked>(lane);
     const uint16_t* const kp = static_cast<const uint16_t*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
     const uint16_t* const vp = static_cast<const uint16_t*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
-    const uint16_t* const gp = static_cast<const uint16_t*>(p.dout) + out_bh;
     const int64_t stat_bh = ((int64_t)b * p.H + h) * p.N;
 
     KeySeg* const records = records_all[wave];
@@ -286,8 +288,8 @@ void bwd_dkdv_short_kernel(const BwdParams p, int n_items) {
     const uint32_t stat_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, stats[wave][0]));
     const float* const lane_stat = (g ? p.ndelta : p.lse2) + stat_bh;       // lanes 0 to 31 bring lse, 32 to 63 -delta
     auto issue = [&](const KeySeg& blk, int buf) {
-        issue_rows(qp, p.sqn, blk, addr + buf * kPairBytes, lane);
-        issue_rows(gp, g_pitch, blk, addr + buf * kPairBytes + kBlockBytes, lane);
+        issue_block_rows<BlockOrder::kWalked>(q_src, blk.key0, blk.stride, blk.count, addr + buf * kPairBytes, cl);
+        issue_block_rows<BlockOrder::kWalked>(g_src, blk.key0, blk.stride, blk.count, addr + buf * kPairBytes + kBlockBytes, cl);
         copy4_to_lds(lane_stat + (blk.key0 + (int64_t)blk.stride * min(j, blk.count - 1)), stat_addr + buf * (2 * kWalkBlock * 4));
     };
     constexpr int kCopies = 2 * kBlockCopies + 1;

@@ -53,37 +53,6 @@ __device__ __forceinline__ Block read_block(const u32x4* records, int t) {
     return b;
 }
 
-// Copies of one block of a tensor into the wave's own LDS; rows past the end of the block re-read its last one.  kIsK: rows
-// permuted by sigma and swizzled as the scores read them, else in list order.  In a whole block the four copies differ in
-// their scalar base alone (K: and in one bit of the chunk).  The lane number comes in opaque, so that nothing derived from
-// it is kept in registers across the walk.
-template <bool kIsK>
-__device__ __forceinline__ void issue_block_rows(const uint16_t* base, int64_t sn, const Block& b, uint32_t lds_addr, int lane) {
-    const uint16_t* const first = base + (int64_t)b.key0 * sn;
-    const int64_t pitch = (int64_t)b.stride() * sn;               // elements
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-    const int r = ln >> 3;
-    const int pos = kIsK ? (r & 3) | ((r & 4) << 1) : r;
-    const uint32_t chunk = 16u * (kIsK ? (ln & 7) ^ (r >> 1) : ln & 7);
-    if (b.count() == kWalkBlock) {
-        const uint32_t off = (uint32_t)pos * (uint32_t)(pitch * 2);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int row = kIsK ? ((u & 1) << 2) | ((u & 2) << 3) : 8 * u;
-            copy16_to_lds(uniform_ptr(first + row * pitch), off + (kIsK ? chunk ^ (64u * (u & 1)) : chunk), lds_addr + 1024u * u);
-        }
-    } else {
-        const int room = max(b.count() - 1, 0);
-        const void* const ub = uniform_ptr(first);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int row = kIsK ? ((u & 1) << 2) | ((u & 2) << 3) : 8 * u;
-            copy16_to_lds(ub, (uint32_t)min(pos + row, room) * (uint32_t)(pitch * 2) + (kIsK ? chunk ^ (64u * (u & 1)) : chunk), lds_addr + 1024u * u);
-        }
-    }
-}
-
 __global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dfa_fwd_short_kernel(const FwdParams p) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[kWalkWaves][kBuffers * kBlockElems];     // per wave: K, K, V, V
@@ -109,8 +78,9 @@ void dfa_fwd_short_kernel(const FwdParams p) {
         return;
     }
 
-    const uint16_t* const kp = static_cast<const uint16_t*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
-    const uint16_t* const vp = static_cast<const uint16_t*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
+    const BlockSource k_src = block_source(static_cast<const uint16_t*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh, p.skn);
+    const BlockSource v_src = block_source(static_cast<const uint16_t*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh, p.svn);
+    const BlockLane k_lane = block_lane<BlockOrder::kKeys>(lane), v_lane = block_lane<BlockOrder::kValues>(lane);
     const uint32_t k_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, lds[wave]));
     const uint32_t v_addr = k_addr + 2 * kBlockBytes;
 
@@ -137,8 +107,8 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     Block blk[3];                              // blocks t, t + 1 and t + 2 of the walk
 #pragma unroll
     for (int x = 0; x < 3; ++x) blk[x] = read_block(records, x);
-    auto issue_k = [&](const Block& b, int buf) { issue_block_rows<true>(kp, p.skn, b, k_addr + buf * kBlockBytes, lane); };
-    auto issue_v = [&](const Block& b, int buf) { issue_block_rows<false>(vp, p.svn, b, v_addr + buf * kBlockBytes, lane); };
+    auto issue_k = [&](const Block& b, int buf) { issue_block_rows<BlockOrder::kKeys>(k_src, b.key0, b.stride(), b.count(), k_addr + buf * kBlockBytes, k_lane); };
+    auto issue_v = [&](const Block& b, int buf) { issue_block_rows<BlockOrder::kValues>(v_src, b.key0, b.stride(), b.count(), v_addr + buf * kBlockBytes, v_lane); };
     issue_k(blk[0], 0);
     issue_k(blk[1], 1);
 
