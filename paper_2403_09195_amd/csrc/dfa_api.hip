@@ -90,9 +90,9 @@ size_t split_bytes(int32_t n_split_wgs) {
     return n_split_wgs > 0 ? align256((size_t)n_split_wgs * kSplitBlockBytes) : 0;
 }
 
-// The plan of the bf16 forward (row groups may share a tile, multiplicities per 32-row block), that of the bf16 backward, and
-// the plain one that the fp32 kernels and the single branches read.
-enum class PlanKind : int32_t { kPlain, kForward, kBackward };
+// The plan of the bf16 forward (row groups may share a tile, multiplicities per 32-row block), that of the bf16 backward, that
+// of the fp32 kernels (plain, lists cut into blocks), and the plain one that single branches of bf16 inputs read.
+enum class PlanKind : int32_t { kPlain, kForward, kBackward, kBlocks };
 int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
               const ChipShape& chip, PlanKind kind, PackedPlan* out) {
     const bool packed = kind == PlanKind::kForward;
@@ -114,6 +114,7 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
             hp = std::move(sp);
         }
     }
+    if (kind == PlanKind::kBlocks) cut_blocks(&hp);
     const size_t b_rows = align256(hp.rows.size() * sizeof(int32_t));
     const size_t b_segs = align256(hp.segs.size() * sizeof(KeySeg) + sizeof(KeySeg));
     const size_t b_items = align256(hp.items.size() * sizeof(Item));
@@ -378,7 +379,7 @@ int forward_impl(const void* q, const void* k, const void* v, dfa_strides_t sq, 
     if (workspace && reinterpret_cast<uintptr_t>(workspace) % 16) return DFA_ERR_ALIGN;
     PlanRef dp;
     // fp32 output from bf16 inputs is the unmerged single branch of dfa_forward_branch: the plain plan
-    rc = get_plan(dt == DFA_BF16 && !out_f32 ? PlanKind::kForward : PlanKind::kPlain, B, H, N, branches, nb, head_offsets, &dp);
+    rc = get_plan(dt == DFA_F32 ? PlanKind::kBlocks : out_f32 ? PlanKind::kPlain : PlanKind::kForward, B, H, N, branches, nb, head_offsets, &dp);
     if (rc != DFA_OK) return rc;
     float* split_ws = nullptr;
     if (workspace && dt == DFA_BF16 && !out_f32 && dp->n_split_wgs > 0) {
@@ -469,7 +470,7 @@ int dfa_forward_static(const void* q, const void* k, const void* v, dfa_strides_
             ss.ptr = static_cast<unsigned char*>(p);
             ss.plan.owned = false;
         }
-        const PlanKind kind = dt == DFA_BF16 ? PlanKind::kForward : PlanKind::kPlain;
+        const PlanKind kind = dt == DFA_BF16 ? PlanKind::kForward : PlanKind::kBlocks;
         PlanKey key = plan_key(device, kind, B, H, N, branches, nb, head_offsets);
         if (!ss.holds_plan || ss.key != key) {
             PackedPlan pp;
@@ -585,7 +586,7 @@ int dfa_backward(const void* q, const void* k, const void* v, const void* out, c
     }
     try {
         PlanRef plan;
-        rc = get_plan(dt == DFA_BF16 ? PlanKind::kBackward : PlanKind::kPlain, B, H, N, branches, nb, head_offsets, &plan);
+        rc = get_plan(dt == DFA_BF16 ? PlanKind::kBackward : PlanKind::kBlocks, B, H, N, branches, nb, head_offsets, &plan);
         if (rc != DFA_OK) return rc;
         const DevicePlan& dp = *plan;
         BwdParams p;

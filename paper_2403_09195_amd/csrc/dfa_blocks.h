@@ -22,44 +22,44 @@ __device__ __forceinline__ void item_of_part(int x, int parts, int& item, int& p
     part = rem / kDies;
 }
 
-// The 32-row blocks of a tile's progressions, counted through; wave w takes blocks w, w + 4, w + 8, ...
+// A wave's share of a list cut into blocks: blocks wave, wave + 4, ...  Their records come 64 at a time in one trip to
+// memory (a lane each) and wait in LDS of the wave's own; the one in hand is held in scalar registers.
+constexpr int kWalkRecords = 64;
 struct BlockWalk {
-    const KeySeg* segs;
-    int nseg, s, t;              // progression, block within it
+    const KeySeg* list;
+    KeySeg* records;
+    int nseg, i;                 // block in hand
+    int t;                       // its place in `records`
     KeySeg seg;
 
-    // through the constant address space: a scalar load.  (After the copies' memory clobber the compiler takes a vector
-    // load instead, whose wait would drain the copies in flight.)
-    __device__ __forceinline__ void load() {
-        typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-        const i32x4 x = *reinterpret_cast<const __attribute__((address_space(4))) i32x4*>(reinterpret_cast<uintptr_t>(segs + s));
-        seg.key0 = x[0];
-        seg.stride = x[1];
-        seg.count = x[2];
-        const int32_t mult = x[3];          // (the bit cast of an element in place would be that of element 0)
-        seg.log2_mult = __builtin_bit_cast(float, mult);
+    __device__ __forceinline__ void fetch() { records[threadIdx.x & 63] = list[min(i + kWalkWaves * (int)(threadIdx.x & 63), nseg - 1)]; }
+    __device__ __forceinline__ void read() {
+        const KeySeg r = records[t];
+        seg.key0 = __builtin_amdgcn_readfirstlane(r.key0);
+        seg.stride = __builtin_amdgcn_readfirstlane(r.stride);
+        seg.count = __builtin_amdgcn_readfirstlane(r.count);
+        seg.log2_mult = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, r.log2_mult)));
     }
-    __device__ __forceinline__ void settle() {
-        while (s < nseg && t * kWalkBlock >= seg.count) {
-            t -= (seg.count + kWalkBlock - 1) / kWalkBlock;
-            if (++s < nseg) load();
-        }
-    }
-    __device__ __forceinline__ void start(const KeySeg* list, int n, int wave) {
-        segs = list;
+    __device__ __forceinline__ void start(const KeySeg* l, int n, int wave, KeySeg* lds) {
+        list = l;
+        records = lds;
         nseg = n;
-        s = 0;
-        t = wave;
-        load();
-        settle();
+        i = wave;
+        t = 0;
+        fetch();
+        read();
     }
     __device__ __forceinline__ void next() {
-        t += kWalkWaves;
-        settle();
+        i += kWalkWaves;
+        if (++t == kWalkRecords) {
+            t = 0;
+            if (i < nseg) fetch();
+        }
+        read();
     }
-    __device__ __forceinline__ bool valid() const { return s < nseg; }
-    __device__ __forceinline__ int rows() const { return min(kWalkBlock, seg.count - t * kWalkBlock); }
-    __device__ __forceinline__ int32_t first() const { return kept_row(seg.key0, seg.stride, t * kWalkBlock); }
+    __device__ __forceinline__ bool valid() const { return i < nseg; }
+    __device__ __forceinline__ int rows() const { return seg.count; }
+    __device__ __forceinline__ int32_t first() const { return seg.key0; }
 };
 
 // All LDS reads of this wave so far have returned; no memory access moves across.

@@ -60,6 +60,7 @@ struct BwdBlock {
     Tile tile;
     int b, h, nrows;
     const int32_t* rows;
+    KeySeg* records;             // LDS, kWalkRecords per wave
 };
 
 // Sum of the four waves' [32][64] results, written to rows of a contiguous [B, N, H, D] tensor.  Every wave has
@@ -96,6 +97,8 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
     const uint32_t v_addr = k_addr + kF32BlockBytes;
 
     const int64_t n = k.rows[min(j, k.nrows - 1)];
+    BlockWalk w;
+    w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave, k.records + wave * kWalkRecords);
     float4 q[8], go[8];
     load_chunks(static_cast<const float*>(p.q) + (int64_t)k.b * p.sqb + n * p.sqn + (int64_t)k.h * p.sqh, g, q);
     load_chunks(static_cast<const float*>(p.dout) + (((int64_t)k.b * p.N + n) * p.H + k.h) * kD, g, go);
@@ -106,8 +109,6 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
 
-    BlockWalk w;
-    w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave);
     if (w.valid()) {
         issue_block(vb, p.svn, w, v_addr, lane);
         issue_block(kb, p.skn, w, k_addr, lane);
@@ -165,6 +166,8 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
     const float* const my_stat = (g == 0 ? p.lse2 : p.ndelta) + ((int64_t)k.b * p.H + k.h) * p.N;
 
     const int64_t n = k.rows[min(j, k.nrows - 1)];
+    BlockWalk w;
+    w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave, k.records + wave * kWalkRecords);
     float4 kr[8], vr[8];
     load_chunks(static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + n * p.skn + (int64_t)k.h * p.skh, g, kr);
     load_chunks(static_cast<const float*>(p.v) + (int64_t)k.b * p.svb + n * p.svn + (int64_t)k.h * p.svh, g, vr);
@@ -177,8 +180,6 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
         issue_block(qb, p.sqn, w, q_addr, lane);
         copy4_to_lds(my_stat + (w.first() + w.seg.stride * min(j, w.rows() - 1)), stat_addr);
     };
-    BlockWalk w;
-    w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave);
     if (w.valid()) {
         issue_block(gb, gpitch, w, g_addr, lane);
         issue_q(w);
@@ -233,12 +234,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void bwd_f32_kernel(const BwdParams p, int n_items, int row_blocks) {
     __shared__ __attribute__((aligned(1024))) float lds[kWalkWaves][2 * kF32BlockElems];
     __shared__ __attribute__((aligned(256))) float stat_lds[kWalkWaves][64];
+    __shared__ KeySeg records[kWalkWaves][kWalkRecords];
 
+    hold_args(p);
     int item_index, part;
     item_of_part(blockIdx.x, 2 * row_blocks, item_index, part);
     if (item_index >= n_items) return;
     const int sub = part >> 1;
-    const Item item = p.items[item_index];
+    const Item item = load_item(p.items, item_index);
     if (item.tile < 0 || sub * kWalkBlock >= item.t.nrows) return;
     const int tid = threadIdx.x;
     BwdBlock k;
@@ -246,6 +249,7 @@ void bwd_f32_kernel(const BwdParams p, int n_items, int row_blocks) {
     k.b = item.b;
     k.h = item.t.h;
     k.nrows = min(kWalkBlock, item.t.nrows - sub * kWalkBlock);
+    k.records = records[0];
     k.rows = p.rows + item.t.row_begin + sub * kWalkBlock;
 
     if (item.t.nseg == 0) {                  // rows that no branch keeps take and give no gradient

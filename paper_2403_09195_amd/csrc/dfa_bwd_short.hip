@@ -19,15 +19,6 @@ constexpr int kPairElems = 2 * kBlockElems;        // one block of both tensors
 constexpr int kPairBytes = kPairElems * 2;
 constexpr int kMostBlocks = 64;                    // of one wave's share
 
-// The kernel arguments read in one go, at the start (the compiler puts each load where its value is first used: a trip to
-// memory each).
-__device__ __forceinline__ void hold_args(const BwdParams& p) {
-    asm volatile("" ::"s"(p.q), "s"(p.k), "s"(p.v), "s"(p.out), "s"(p.dout), "s"(p.lse), "s"(p.rows), "s"(p.segs), "s"(p.items));
-    asm volatile("" ::"s"(p.sqb), "s"(p.sqn), "s"(p.sqh), "s"(p.skb), "s"(p.skn), "s"(p.skh), "s"(p.svb), "s"(p.svn), "s"(p.svh), "s"(p.H), "s"(p.N),
-                 "s"(p.scale));
-    asm volatile("" ::"s"(p.ndelta), "s"(p.lse2), "s"(p.dq), "s"(p.dk), "s"(p.dv));
-}
-
 __device__ __forceinline__ KeySeg read_record(const KeySeg* records, int t) {
     const KeySeg r = records[min(t, kMostBlocks - 1)];
     KeySeg k;

@@ -27,11 +27,14 @@ namespace {
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
     __shared__ __attribute__((aligned(1024))) float lds[kWalkWaves][2 * kF32BlockElems];     // per wave: K block, V block
+    __shared__ KeySeg records[kWalkWaves][kWalkRecords];
+
+    hold_args(p);
 
     int item_index, sub;
     item_of_part(blockIdx.x, row_blocks, item_index, sub);
     if (item_index >= n_items) return;
-    const Item item = p.items[item_index];
+    const Item item = load_item(p.items, item_index);
     const Tile tile = item.t;
     if (item.tile < 0 || sub * kWalkBlock >= tile.nrows) return;
     const int tid = threadIdx.x;
@@ -62,16 +65,17 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
     const uint32_t k_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, k_lds));
     const uint32_t v_addr = k_addr + kF32BlockBytes;
 
+    const int64_t qn = rows[min(j, nrows - 1)];
+    BlockWalk w;
+    w.start(p.segs + tile.seg_begin, tile.nseg, wave, records[wave]);
     float4 q[8];
-    load_chunks(static_cast<const float*>(p.q) + (int64_t)b * p.sqb + (int64_t)rows[min(j, nrows - 1)] * p.sqn + (int64_t)h * p.sqh, g, q);
+    load_chunks(static_cast<const float*>(p.q) + (int64_t)b * p.sqb + qn * p.sqn + (int64_t)h * p.sqh, g, q);
 
     floatx16 acc[2];
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;      // l_run: over the lane's own 16 keys of every block
 
-    BlockWalk w;
-    w.start(p.segs + tile.seg_begin, tile.nseg, wave);
     if (w.valid()) {
         issue_block(kp, p.skn, w, k_addr, lane);
         issue_block(vp, p.svn, w, v_addr, lane);

@@ -82,12 +82,19 @@ __device__ __forceinline__ Item load_item(const Item* items, int i) {
     return Item{x[0], x[1], Tile{x[2], x[3], x[4], x[5], x[6], x[7]}};
 }
 
-// The forward kernels' arguments read in one go, at the start (the compiler puts each load where its value is first used: a
+// The kernels' arguments read in one go, at the start (the compiler puts each load where its value is first used: a
 // trip to memory each).
 __device__ __forceinline__ void hold_args(const FwdParams& p) {
     asm volatile("" ::"s"(p.q), "s"(p.k), "s"(p.v), "s"(p.out), "s"(p.lse), "s"(p.rows), "s"(p.segs), "s"(p.items), "s"(p.block_mult));
     asm volatile("" ::"s"(p.sqb), "s"(p.sqn), "s"(p.sqh), "s"(p.skb), "s"(p.skn), "s"(p.skh), "s"(p.svb), "s"(p.svn), "s"(p.svh), "s"(p.H), "s"(p.N),
                  "s"(p.scale));
+}
+
+__device__ __forceinline__ void hold_args(const BwdParams& p) {
+    asm volatile("" ::"s"(p.q), "s"(p.k), "s"(p.v), "s"(p.out), "s"(p.dout), "s"(p.lse), "s"(p.rows), "s"(p.segs), "s"(p.items));
+    asm volatile("" ::"s"(p.sqb), "s"(p.sqn), "s"(p.sqh), "s"(p.skb), "s"(p.skn), "s"(p.skh), "s"(p.svb), "s"(p.svn), "s"(p.svh), "s"(p.H), "s"(p.N),
+                 "s"(p.scale));
+    asm volatile("" ::"s"(p.ndelta), "s"(p.lse2), "s"(p.dq), "s"(p.dk), "s"(p.dv));
 }
 
 // 16 bytes per lane from global memory straight into LDS.  gbase and lds_addr are

@@ -29,15 +29,21 @@ __device__ __forceinline__ int f32_swizzle(int rho) { return ((rho & 4) << 1) | 
 // Issues the copies of one block: rows first() + stride * i of a tensor with row pitch sn (elements); rows past the end
 // of the list re-read its last one.
 __device__ __forceinline__ void issue_block(const float* base, int64_t sn, const BlockWalk& w, uint32_t lds_addr, int lane) {
-    const void* const ub = uniform_ptr(base + (int64_t)w.first() * sn);
-    const uint32_t pitch = (uint32_t)(w.seg.stride * sn * 4);
-    const int room = w.rows() - 1;
+    const uint32_t row_pitch = (uint32_t)(sn * 4);          // below 2^25, see check_forward_args
+    const void* const ub = uniform_ptr(reinterpret_cast<const char*>(base) + (uint64_t)(uint32_t)w.first() * row_pitch);
+    const uint32_t pitch = (uint32_t)w.seg.stride * row_pitch;
     const int chunk0 = (lane & 15) ^ (lane >> 4);
+    if (w.rows() == kWalkBlock) {
+        const uint32_t off = (uint32_t)(lane >> 4) * pitch;
 #pragma unroll
-    for (int u = 0; u < kF32Copies; ++u) {
-        const int row = 4 * u + (lane >> 4);
-        const int chunk = chunk0 ^ (((u & 1) << 3) | ((u & 2) << 1));
-        copy16_to_lds(ub, (uint32_t)min(row, room) * pitch + 16u * chunk, lds_addr + 1024u * u);
+        for (int u = 0; u < kF32Copies; ++u)
+            copy16_to_lds(ub, off + 16u * (chunk0 ^ (((u & 1) << 3) | ((u & 2) << 1))) + 4 * u * pitch, lds_addr + 1024u * u);
+    } else {
+        const int room = w.rows() - 1;
+#pragma unroll
+        for (int u = 0; u < kF32Copies; ++u)
+            copy16_to_lds(ub, (uint32_t)min(4 * u + (lane >> 4), room) * pitch + 16u * (chunk0 ^ (((u & 1) << 3) | ((u & 2) << 1))),
+                          lds_addr + 1024u * u);
     }
 }
 
