@@ -35,7 +35,8 @@ struct DevicePlan {
     const KeySeg* segs = nullptr;
     const Item* items = nullptr;
     const float* block_mult = nullptr;   // plans of the bf16 forward only
-    bool short_walk = false;            // bf16 forward: the plan of short_plan, walked by launch_fwd_short
+    bool short_walk = false;            // bf16: the plan of short_plan or short_backward_plan, walked by the short-launch kernels
+    bool cut = false;                   // fp32: the lists are cut into blocks
     bool packed_tiles = false;          // some tile packs several row groups: the kernel variant that reads block_mult
     int32_t n_items = 0;
     int32_t max_tile_rows = 1;     // most rows of any tile
@@ -76,6 +77,7 @@ struct PackedPlan {
     int32_t n_split_wgs = 0;
     int32_t max_tile_rows = 1;
     bool short_walk = false;
+    bool cut = false;
     bool packed_tiles = false;
 };
 
@@ -91,7 +93,7 @@ size_t split_bytes(int32_t n_split_wgs) {
 }
 
 // The plan of the bf16 forward (row groups may share a tile, multiplicities per 32-row block), that of the bf16 backward, that
-// of the fp32 kernels (plain, lists cut into blocks), and the plain one that single branches of bf16 inputs read.
+// of the fp32 kernels (plain, lists cut into blocks where that is affordable), and the plain one that single branches of bf16 inputs read.
 enum class PlanKind : int32_t { kPlain, kForward, kBackward, kBlocks };
 int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
               const ChipShape& chip, PlanKind kind, PackedPlan* out) {
@@ -114,7 +116,10 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
             hp = std::move(sp);
         }
     }
-    if (kind == PlanKind::kBlocks) cut_blocks(&hp);
+    if (kind == PlanKind::kBlocks && cut_size(hp).records <= kMaxCutRecords) {
+        out->cut = true;
+        cut_blocks(&hp);
+    }
     const size_t b_rows = align256(hp.rows.size() * sizeof(int32_t));
     const size_t b_segs = align256(hp.segs.size() * sizeof(KeySeg) + sizeof(KeySeg));
     const size_t b_items = align256(hp.items.size() * sizeof(Item));
@@ -165,6 +170,7 @@ void point_plan(DevicePlan* dp, void* base, const PackedPlan& pp, int device) {
     dp->block_mult = reinterpret_cast<const float*>(b + pp.off_block_mult);
     dp->packed_tiles = pp.packed_tiles;
     dp->short_walk = pp.short_walk;
+    dp->cut = pp.cut;
     dp->max_tile_rows = pp.max_tile_rows;
 }
 
@@ -365,7 +371,7 @@ int launch_forward(const DevicePlan& dp, const void* q, const void* k, const voi
     } else if (dt == DFA_BF16) {
         e = launch_fwd_bf16(p, dp.n_items, out_f32, dp.packed_tiles, st);
     } else {
-        e = launch_fwd_f32(p, dp.n_items, dp.max_tile_rows, st);         // fp32 inputs always give fp32 output
+        e = launch_fwd_f32(p, dp.n_items, dp.max_tile_rows, dp.cut, st);         // fp32 inputs always give fp32 output
     }
     return e == hipSuccess ? DFA_OK : DFA_ERR_LAUNCH;
 }
@@ -476,6 +482,11 @@ int dfa_forward_static(const void* q, const void* k, const void* v, dfa_strides_
             PackedPlan pp;
             rc = pack_plan(B, H, N, branches, nb, head_offsets, chip, kind, &pp);
             if (rc != DFA_OK) return rc;
+            if (kind == PlanKind::kBlocks && align256(pp.bytes.size()) > kStaticScratchBytes) {
+                pp = PackedPlan();             // the cut lists may be what does not fit
+                rc = pack_plan(B, H, N, branches, nb, head_offsets, chip, PlanKind::kPlain, &pp);
+                if (rc != DFA_OK) return rc;
+            }
             const size_t plan_bytes = align256(pp.bytes.size());
             const size_t part_bytes = dt == DFA_BF16 ? split_bytes(pp.n_split_wgs) : 0;
             if (plan_bytes + part_bytes > kStaticScratchBytes) return DFA_ERR_WORKSPACE;
@@ -599,7 +610,7 @@ int dfa_backward(const void* q, const void* k, const void* v, const void* out, c
         p.H = H; p.N = N; p.scale = scale;
         if (dp.short_walk)
             return launch_bwd_short(p, dp.n_items, static_cast<hipStream_t>(stream)) == hipSuccess ? DFA_OK : DFA_ERR_LAUNCH;
-        return launch_bwd(p, dp.n_items, dp.max_tile_rows, B, dt == DFA_BF16, static_cast<hipStream_t>(stream)) == hipSuccess
+        return launch_bwd(p, dp.n_items, dp.max_tile_rows, dp.cut, B, dt == DFA_BF16, static_cast<hipStream_t>(stream)) == hipSuccess
                    ? DFA_OK : DFA_ERR_LAUNCH;
     } catch (const std::bad_alloc&) {
         return DFA_ERR_LAUNCH;

@@ -22,10 +22,15 @@ __device__ __forceinline__ void item_of_part(int x, int parts, int& item, int& p
     part = rem / kDies;
 }
 
-// A wave's share of a list cut into blocks: blocks wave, wave + 4, ...  Their records come 64 at a time in one trip to
-// memory (a lane each) and wait in LDS of the wave's own; the one in hand is held in scalar registers.
+// A wave's share of a list: its 32-row blocks wave, wave + 4, ..., the one in hand in scalar registers.
+// kCut: the list is cut into blocks.  Their records come 64 at a time in one trip to memory (a lane each) and wait in LDS of
+// the wave's own.  Otherwise the blocks are counted through the list's progressions, read one by one: plans whose cut lists
+// would take too much memory (kMaxCutRecords).
 constexpr int kWalkRecords = 64;
-struct BlockWalk {
+template <bool kCut>
+struct BlockWalk;
+template <>
+struct BlockWalk<true> {
     const KeySeg* list;
     KeySeg* records;
     int nseg, i;                 // block in hand
@@ -60,6 +65,45 @@ struct BlockWalk {
     __device__ __forceinline__ bool valid() const { return i < nseg; }
     __device__ __forceinline__ int rows() const { return seg.count; }
     __device__ __forceinline__ int32_t first() const { return seg.key0; }
+};
+template <>
+struct BlockWalk<false> {
+    const KeySeg* segs;
+    int nseg, s, t;              // progression, block within it
+    KeySeg seg;
+
+    // through the constant address space: a scalar load.  (After the copies' memory clobber the compiler takes a vector
+    // load instead, whose wait would drain the copies in flight.)
+    __device__ __forceinline__ void load() {
+        typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+        const i32x4 x = *reinterpret_cast<const __attribute__((address_space(4))) i32x4*>(reinterpret_cast<uintptr_t>(segs + s));
+        seg.key0 = x[0];
+        seg.stride = x[1];
+        seg.count = x[2];
+        const int32_t mult = x[3];          // (the bit cast of an element in place would be that of element 0)
+        seg.log2_mult = __builtin_bit_cast(float, mult);
+    }
+    __device__ __forceinline__ void settle() {
+        while (s < nseg && t * kWalkBlock >= seg.count) {
+            t -= (seg.count + kWalkBlock - 1) / kWalkBlock;
+            if (++s < nseg) load();
+        }
+    }
+    __device__ __forceinline__ void start(const KeySeg* list, int n, int wave, KeySeg*) {
+        segs = list;
+        nseg = n;
+        s = 0;
+        t = wave;
+        load();
+        settle();
+    }
+    __device__ __forceinline__ void next() {
+        t += kWalkWaves;
+        settle();
+    }
+    __device__ __forceinline__ bool valid() const { return s < nseg; }
+    __device__ __forceinline__ int rows() const { return min(kWalkBlock, seg.count - t * kWalkBlock); }
+    __device__ __forceinline__ int32_t first() const { return kept_row(seg.key0, seg.stride, t * kWalkBlock); }
 };
 
 // All LDS reads of this wave so far have returned; no memory access moves across.

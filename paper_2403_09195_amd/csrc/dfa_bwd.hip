@@ -87,6 +87,7 @@ __device__ __forceinline__ void write_sum(const BwdParams& p, const BwdBlock& k,
 }
 
 // dq of the block's rows: they are queries, the lists are walked as keys.
+template <bool kCut>
 __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems], int tid) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
     const float* const kb = static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + (int64_t)k.h * p.skh;
@@ -97,7 +98,7 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
     const uint32_t v_addr = k_addr + kF32BlockBytes;
 
     const int64_t n = k.rows[min(j, k.nrows - 1)];
-    BlockWalk w;
+    BlockWalk<kCut> w;
     w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave, k.records + wave * kWalkRecords);
     float4 q[8], go[8];
     load_chunks(static_cast<const float*>(p.q) + (int64_t)k.b * p.sqb + n * p.sqn + (int64_t)k.h * p.sqh, g, q);
@@ -117,7 +118,7 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
     pin(go);
     asm volatile("" : "+v"(my_l), "+v"(my_d));
     while (w.valid()) {
-        BlockWalk nx = w;
+        BlockWalk<kCut> nx = w;
         nx.next();
         const bool more = nx.valid();
         const int nvalid = w.rows();
@@ -151,6 +152,7 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
 }
 
 // dk and dv of the block's rows: they are keys, the lists are walked as queries.
+template <bool kCut>
 __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems],
                                            float (*stat_lds)[64], int tid) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
@@ -166,7 +168,7 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
     const float* const my_stat = (g == 0 ? p.lse2 : p.ndelta) + ((int64_t)k.b * p.H + k.h) * p.N;
 
     const int64_t n = k.rows[min(j, k.nrows - 1)];
-    BlockWalk w;
+    BlockWalk<kCut> w;
     w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave, k.records + wave * kWalkRecords);
     float4 kr[8], vr[8];
     load_chunks(static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + n * p.skn + (int64_t)k.h * p.skh, g, kr);
@@ -176,7 +178,7 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
 #pragma unroll
     for (int v = 0; v < 16; ++v) dk[0][v] = dk[1][v] = dv[0][v] = dv[1][v] = 0.f;
 
-    auto issue_q = [&](const BlockWalk& w) {             // 9 copies
+    auto issue_q = [&](const BlockWalk<kCut>& w) {             // 9 copies
         issue_block(qb, p.sqn, w, q_addr, lane);
         copy4_to_lds(my_stat + (w.first() + w.seg.stride * min(j, w.rows() - 1)), stat_addr);
     };
@@ -187,7 +189,7 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
     pin(kr);
     pin(vr);
     while (w.valid()) {
-        BlockWalk nx = w;
+        BlockWalk<kCut> nx = w;
         nx.next();
         const bool more = nx.valid();
         const int nvalid = w.rows();
@@ -230,6 +232,7 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
     write_sum(p, k, lds, tid, dk, p.dk);
 }
 
+template <bool kCut>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void bwd_f32_kernel(const BwdParams p, int n_items, int row_blocks) {
     __shared__ __attribute__((aligned(1024))) float lds[kWalkWaves][2 * kF32BlockElems];
@@ -263,15 +266,15 @@ void bwd_f32_kernel(const BwdParams p, int n_items, int row_blocks) {
         }
         return;
     }
-    if (part & 1) dq_block(p, k, lds, tid);
-    else dkdv_block(p, k, lds, stat_lds, tid);
+    if (part & 1) dq_block<kCut>(p, k, lds, tid);
+    else dkdv_block<kCut>(p, k, lds, stat_lds, tid);
 }
 
 }  // namespace
 
 // fp32 operands: the per-row preparation, then both gradient kernels in one launch.  bf16 operands go to the
 // matrix-core kernels of dfa_bwd_bf16.hip, whose dq kernel prepares the per-row values itself.
-hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, int32_t B, bool bf16, hipStream_t st) {
+hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, bool cut, int32_t B, bool bf16, hipStream_t st) {
     if (bf16) return launch_bwd_bf16(p, n_items, st);
     hipLaunchKernelGGL(bwd_delta_kernel, dim3((unsigned)(((int64_t)p.N * p.H * 16 + 255) / 256), B), dim3(256), 0, st,
                        static_cast<const float*>(p.out), static_cast<const float*>(p.dout), p.lse, p.ndelta, p.lse2, p.H, p.N);
@@ -281,7 +284,7 @@ hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, int32_
         q.items += i0;
         const int n = n_items - i0 < kLaunchItems ? n_items - i0 : kLaunchItems;
         const int groups = (n + kDies - 1) / kDies;
-        hipLaunchKernelGGL(bwd_f32_kernel, dim3((unsigned)groups * kDies * 2 * row_blocks), dim3(256), 0, st, q, n, row_blocks);
+        hipLaunchKernelGGL(cut ? bwd_f32_kernel<true> : bwd_f32_kernel<false>, dim3((unsigned)groups * kDies * 2 * row_blocks), dim3(256), 0, st, q, n, row_blocks);
     }
     return hipGetLastError();
 }

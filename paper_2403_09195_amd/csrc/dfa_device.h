@@ -87,11 +87,11 @@ __device__ __forceinline__ int32_t segment_first(int32_t i, int32_t w, int32_t o
 hipError_t launch_fwd_bf16(const FwdParams& p, int n_items, bool out_f32, bool packed, hipStream_t st);
 hipError_t launch_fwd_bf16_split(const FwdParams& p, int n_split_wgs, bool packed, hipStream_t st);
 hipError_t launch_merge_split(const FwdParams& p, int n_items, hipStream_t st);
-// plans of 128-row tiles with their lists cut into blocks
+// plans of 64-row tiles with their lists cut into blocks
 hipError_t launch_fwd_short(const FwdParams& p, int n_items, hipStream_t st);
-// max_tile_rows: most rows of any tile of the plan
-hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, hipStream_t st);
-hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, int32_t B, bool bf16, hipStream_t st);
+// max_tile_rows: most rows of any tile of the plan; cut: its lists are cut into blocks
+hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, bool cut, hipStream_t st);
+hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, bool cut, int32_t B, bool bf16, hipStream_t st);
 hipError_t launch_bwd_bf16(const BwdParams& p, int n_items, hipStream_t st);
 // plans of plain 64-row tiles with their lists cut into blocks
 hipError_t launch_bwd_short(const BwdParams& p, int n_items, hipStream_t st);

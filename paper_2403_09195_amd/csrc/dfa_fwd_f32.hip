@@ -24,6 +24,7 @@ namespace dfa {
 
 namespace {
 
+template <bool kCut>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
     __shared__ __attribute__((aligned(1024))) float lds[kWalkWaves][2 * kF32BlockElems];     // per wave: K block, V block
@@ -66,7 +67,7 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
     const uint32_t v_addr = k_addr + kF32BlockBytes;
 
     const int64_t qn = rows[min(j, nrows - 1)];
-    BlockWalk w;
+    BlockWalk<kCut> w;
     w.start(p.segs + tile.seg_begin, tile.nseg, wave, records[wave]);
     float4 q[8];
     load_chunks(static_cast<const float*>(p.q) + (int64_t)b * p.sqb + qn * p.sqn + (int64_t)h * p.sqh, g, q);
@@ -82,7 +83,7 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
     }
     pin(q);
     while (w.valid()) {
-        BlockWalk nx = w;
+        BlockWalk<kCut> nx = w;
         nx.next();
         const bool more = nx.valid();
         const int nvalid = w.rows();
@@ -166,14 +167,14 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
 
 }  // namespace
 
-hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, hipStream_t st) {
+hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, bool cut, hipStream_t st) {
     const int row_blocks = (max_tile_rows + kWalkBlock - 1) / kWalkBlock;
     for (int i0 = 0; i0 < n_items; i0 += kLaunchItems) {         // a grid holds fewer than 2^32 threads
         FwdParams q = p;
         q.items += i0;
         const int n = n_items - i0 < kLaunchItems ? n_items - i0 : kLaunchItems;
         const int groups = (n + kDies - 1) / kDies;
-        hipLaunchKernelGGL(dfa_fwd_f32_kernel, dim3((unsigned)groups * kDies * row_blocks), dim3(256), 0, st, q, n, row_blocks);
+        hipLaunchKernelGGL(cut ? dfa_fwd_f32_kernel<true> : dfa_fwd_f32_kernel<false>, dim3((unsigned)groups * kDies * row_blocks), dim3(256), 0, st, q, n, row_blocks);
     }
     return hipGetLastError();
 }

@@ -28,7 +28,8 @@ __device__ __forceinline__ int f32_swizzle(int rho) { return ((rho & 4) << 1) | 
 
 // Issues the copies of one block: rows first() + stride * i of a tensor with row pitch sn (elements); rows past the end
 // of the list re-read its last one.
-__device__ __forceinline__ void issue_block(const float* base, int64_t sn, const BlockWalk& w, uint32_t lds_addr, int lane) {
+template <class Walk>
+__device__ __forceinline__ void issue_block(const float* base, int64_t sn, const Walk& w, uint32_t lds_addr, int lane) {
     const uint32_t row_pitch = (uint32_t)(sn * 4);          // below 2^25, see check_forward_args
     const void* const ub = uniform_ptr(reinterpret_cast<const char*>(base) + (uint64_t)(uint32_t)w.first() * row_pitch);
     const uint32_t pitch = (uint32_t)w.seg.stride * row_pitch;

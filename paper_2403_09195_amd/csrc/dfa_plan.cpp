@@ -464,6 +464,20 @@ void split_plan(HostPlan* plan, const ChipShape& chip) {
     }
 }
 
+CutSize cut_size(const HostPlan& plan) {
+    CutSize size;
+    std::vector<char> seen(plan.segs.size() + 1, 0);
+    for (const Tile& t : plan.tiles) {
+        if (t.nseg == 0 || seen[t.seg_begin]) continue;      // tiles of one group share their list
+        seen[t.seg_begin] = 1;
+        int64_t records = 0;
+        for (int32_t x = t.seg_begin; x < t.seg_begin + t.nseg; ++x) records += ((int64_t)plan.segs[x].count + kWalkBlock - 1) / kWalkBlock;
+        size.records += records;
+        size.longest = std::max(size.longest, records);
+    }
+    return size;
+}
+
 void cut_blocks(HostPlan* plan) {
     std::vector<KeySeg> segs;
     std::vector<int32_t> mult, block_mult;
@@ -501,10 +515,8 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     const size_t most = (size_t)chip.fwd_slots() * 9 / 8;
     if (full.items.size() > most || N >= kMaxCutStride) return false;
     build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, plan, kShortRows / kBlockRows);
-    if (plan->items.size() > most) return false;
+    if (plan->items.size() > most || cut_size(*plan).longest > kShortBlocks) return false;
     cut_blocks(plan);
-    for (const Tile& t : plan->tiles)
-        if (t.nseg > kShortBlocks) return false;
     return true;
 }
 
@@ -523,11 +535,12 @@ bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br
     const double full_us = 15.0 + std::max(3.2 * longest, 0.0164 * steps * per_slot);
     if (full.items.size() * 0.029 * per_slot > full_us) return false;          // there are at least as many 64-row tiles
     build_plan(B, H, N, br, nb, offsets, order_mode, chip, false, plan, kShortRows / kBlockRows);
+    const CutSize size = cut_size(*plan);
+    if (size.longest > kShortBackwardBlocks || size.records > kMaxCutRecords) return false;
     cut_blocks(plan);
     int64_t tiles = 0, blocks = 0;
     for (const Item& i : plan->items)
         if (i.tile >= 0) {
-            if (i.t.nseg > kShortBackwardBlocks) return false;
             ++tiles;
             blocks += i.t.nseg;
         }

@@ -119,6 +119,17 @@ void split_plan(HostPlan* plan, const ChipShape& chip);
 constexpr int32_t kMaxCutStride = 1 << 24;
 void cut_blocks(HostPlan* plan);
 
+// What cut_blocks would make of a plan: records of all its lists, and of the longest one.
+struct CutSize {
+    int64_t records = 0;
+    int64_t longest = 0;
+};
+CutSize cut_size(const HostPlan& plan);
+// A cut list takes 16 bytes per 32 keys where a progression took 16 bytes in all, and a plan has a list per row group: many
+// small groups with long lists (a branch over the whole image beside narrow windows) would take gigabytes at
+// some 100 000 tokens.  Plans past this many records (4 MB) keep their lists whole; such launches are long and lose nothing by it.
+constexpr int64_t kMaxCutRecords = 1 << 18;
+
 // Launches that do not fill the chip are as long as one workgroup's start, walk and end.  The short-launch forward kernel cuts
 // the walk by four inside the workgroup and gives it a quarter of the rows, but copies every key block for 64 rows where the
 // other kernels copy it for 256, and its copies run at some 20 bytes per clock and CU.  It is taken when its

@@ -82,3 +82,41 @@ def test_f32_launch_of_more_than_one_slice(B):
     assert torch.equal(out, v)
     ref = (q.double() * k.double()).sum(-1).mul(0.125).transpose(1, 2)
     assert float((lse.double() - ref).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("window,cut", [(16, False), (64, True)])
+def test_f32_lists_whole_and_cut(B, window, cut):
+    """Many row groups with long lists: past 2^18 blocks of lists (4 MB of records) the plan keeps them whole, and the
+    kernels count through the progressions instead.  Against fp64 by the definition: keys of the row's own window count
+    twice.  Sums of 16384 products, 1e-5 as above for out (of size 1e-2); gradients 2e-5 of the largest."""
+    import torch
+    N, br = 16384, [(16384, 1), (window, 1)]
+    plan = B.plan_describe(1, 1, N, br)
+    tiles, segs = plan["tiles"], plan["segs"]
+    blocks = sum(-(-int(segs[x][2]) // 32) for begin, n in {(int(t[3]), int(t[4])) for t in tiles} for x in range(begin, begin + n))
+    assert (blocks <= 1 << 18) == cut
+    (q, k, v), _ = make_qkv(79, 1, N, 1, 64, "f32")
+    g = torch.empty_like(q).normal_(generator=torch.Generator(device="cuda").manual_seed(6))
+    out, lse = B.forward(q, k, v, br, 0.125)
+    grads = B.backward(q, k, v, out, lse, g, br, 0.125)
+    same, same_lse = B.forward_static(q, k, v, br, 0.125)
+    assert torch.equal(same, out) and torch.equal(same_lse, lse)
+
+    q6, k6, v6, g6 = (t[0, :, 0].double() for t in (q, k, v, g))
+    ref, ref_lse, dq = torch.empty_like(q6), torch.empty(N, dtype=torch.float64, device="cuda"), torch.empty_like(q6)
+    dk, dv = torch.zeros_like(q6), torch.zeros_like(q6)
+    own = torch.arange(N, device="cuda") // window
+    for n0 in range(0, N, 4096):
+        r = slice(n0, n0 + 4096)
+        s = 0.125 * (q6[r] @ k6.T.contiguous()) + torch.log((own[r, None] == own[None]).double() + 1.0)
+        ref_lse[r] = torch.logsumexp(s, 1)
+        p = torch.exp(s - ref_lse[r, None])
+        ref[r] = p @ v6
+        ds = p * (g6[r] @ v6.T.contiguous() - (g6[r] * ref[r]).sum(1, keepdim=True)) * 0.125
+        dq[r] = ds @ k6
+        dk += ds.T.contiguous() @ q6[r]
+        dv += p.T.contiguous() @ g6[r]
+    assert float((out[0, :, 0] - ref).abs().max()) <= 1e-5
+    assert float((lse[0, 0] - ref_lse).abs().max()) <= 1e-5 * float(ref_lse.abs().max())
+    for got, want in zip(grads, (dq, dk, dv)):
+        assert float((got[0, :, 0] - want).abs().max()) <= 2e-5 * max(1.0, float(want.abs().max()))
