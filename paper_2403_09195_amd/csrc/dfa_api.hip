@@ -609,7 +609,7 @@ int dfa_backward(const void* q, const void* k, const void* v, const void* out, c
         p.rows = dp.rows; p.segs = dp.segs; p.items = dp.items;
         p.H = H; p.N = N; p.scale = scale;
         if (dp.short_walk)
-            return launch_bwd_short(p, dp.n_items, static_cast<hipStream_t>(stream)) == hipSuccess ? DFA_OK : DFA_ERR_LAUNCH;
+            return launch_bwd_short(p, dp.n_items, B, static_cast<hipStream_t>(stream)) == hipSuccess ? DFA_OK : DFA_ERR_LAUNCH;
         return launch_bwd(p, dp.n_items, dp.max_tile_rows, dp.cut, B, dt == DFA_BF16, static_cast<hipStream_t>(stream)) == hipSuccess
                    ? DFA_OK : DFA_ERR_LAUNCH;
     } catch (const std::bad_alloc&) {

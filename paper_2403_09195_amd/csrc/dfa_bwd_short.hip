@@ -1,13 +1,17 @@
 // Backward of the fused dilated attention for bf16 operands, for launches that do not fill the chip (the rule is
 // short_backward_plan's).  Formulas and operand layouts are those of dfa_bwd_bf16.hip.
 //
-// A workgroup owns 64 rows of dq, or 32 rows of dk and dv, and its four waves walk a quarter of the tile's 32-row blocks
+// A small launch leaves -delta and lse in base-2 units of every row in the workspace, one more works out all gradients: a
+// workgroup owns 64 rows of dq, or 32 rows of dk and dv, and its four waves walk a quarter of the tile's 32-row blocks
 // each (wave w takes blocks w, w + 4, ...); the four partial sums are added through LDS in fp32, in the same order every
 // time.  A wave copies its own blocks, two ahead, and waits for nobody until that sum; the list comes cut into blocks,
 // whose records a wave reads in one trip to memory at the start and keeps in LDS.
 //
 // Bound: latency.  With one wave on a SIMD a block's steps (fragments, first products, exponentials, second products) follow
-// one another; the second workgroup of the CU fills the gaps.
+// one another; the second workgroup of the CU fills the gaps.  Two workgroups to a CU are 512 slots, and a launch per gradient
+// (dq working out delta) ended each on a round of its own that was nearly empty: one image of 2500 tokens, 12 heads has 528 dq
+// and 1056 dk/dv workgroups.  Forward and backward of that image 81.7 -> 73.7 us in one launch for all gradients, of four images
+// of 1024 tokens, 6 heads 37.6 -> 34.9 us.
 #include "dfa_bwd_bf16.h"
 
 namespace dfa {
@@ -53,18 +57,46 @@ __device__ __forceinline__ void write_sum(const floatx16 (&acc)[2], uint16_t (*l
     }
 }
 
-// dq of 64 rows: they are queries, the lists are walked as keys.  Also leaves -delta and lse in base-2 units of its rows in
-// the workspace.
-__global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void bwd_dq_short_kernel(const BwdParams p) {
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[kWalkWaves][kBuffers * kPairElems];
-    __shared__ KeySeg records_all[kWalkWaves][kMostBlocks];
-    __shared__ float stats[2][kShortRows];             // lse in base-2 units and -delta of the rows
-    __shared__ int32_t row_lds[kShortRows];
-    static_assert(sizeof(lds[0]) >= kWalkBlock * kRedPitch * 4, "a wave's results fit its blocks");
+// What a workgroup keeps in LDS: two of them fit a CU.
+struct ShortLds {
+    uint16_t blocks[kWalkWaves][kBuffers * kPairElems];
+    float stats[kWalkWaves][kBuffers][2 * kWalkBlock];         // dk/dv: lse and -delta of a block
+    KeySeg records[kWalkWaves][kMostBlocks];
+    int32_t rows[kShortRows];
+};
+static_assert(sizeof(ShortLds) <= 80 * 1024, "two workgroups to a CU");
+static_assert(sizeof(ShortLds::blocks) / kWalkWaves >= kWalkBlock * kRedPitch * 4, "a wave's results fit its blocks");
 
-    hold_args(p);
-    const Item item = load_item(p.items, blockIdx.x);
+// -delta = -(dout . out) and lse in base-2 units of every row: 8 lanes a row, 16 bytes each.  grid = (8 * rows of one image /
+// 256, B): one image is indexed with 32-bit arithmetic.
+__global__ __launch_bounds__(256)
+void bwd_rows_short_kernel(const BwdParams p) {
+    const uint32_t x = blockIdx.x * 256u + threadIdx.x, t = x >> 3;      // t = n * H + h
+    const bool in = t < (uint32_t)p.N * (uint32_t)p.H;
+    const uint32_t h = t % (uint32_t)p.H, n = t / (uint32_t)p.H;
+    const int64_t stat = ((int64_t)blockIdx.y * p.H + h) * p.N + n;
+    float part = 0.f, lse = 0.f;
+    if (in) {
+        const int64_t at = ((int64_t)blockIdx.y * p.N * p.H + t) * kD + 8 * (x & 7u);
+        const bf16x8 go = *reinterpret_cast<const bf16x8*>(static_cast<const uint16_t*>(p.dout) + at);
+        const bf16x8 oo = *reinterpret_cast<const bf16x8*>(static_cast<const uint16_t*>(p.out) + at);
+        if ((x & 7u) == 0) lse = p.lse[stat];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) part = fmaf((float)go[e], (float)oo[e], part);
+    }
+    part += __shfl_xor(part, 1, 8);
+    part += __shfl_xor(part, 2, 8);
+    part += __shfl_xor(part, 4, 8);
+    if (in && (x & 7u) == 0) {
+        p.lse2[stat] = lse * kLog2e;
+        p.ndelta[stat] = -part;
+    }
+}
+
+// dq of 64 rows: they are queries, the lists are walked as keys.
+__device__ __forceinline__ void dq_short(const BwdParams& p, ShortLds& mem, const Item& item) {
+    uint16_t (*const lds)[kBuffers * kPairElems] = mem.blocks;
+    int32_t* const row_lds = mem.rows;
     if (item.tile < 0) return;
     const Tile tile = item.t;
     const int tid = threadIdx.x;
@@ -85,15 +117,13 @@ void bwd_dq_short_kernel(const BwdParams p) {
     const BlockSource v_src = block_source(static_cast<const uint16_t*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh, p.svn);
     const BlockLane cl = block_lane<BlockOrder::kWalked>(lane);
     const uint16_t* const gp = static_cast<const uint16_t*>(p.dout) + out_bh;
-    const uint16_t* const op = static_cast<const uint16_t*>(p.out) + out_bh;
     const int64_t stat_bh = ((int64_t)b * p.H + h) * p.N;
 
     // one trip to memory for the records and the row numbers, one for everything these lead to
-    KeySeg* const records = records_all[wave];
-    const int srow = 16 * wave + (lane >> 2), sd = 16 * (lane & 3);     // the row whose delta this lane's quad works out
+    KeySeg* const records = mem.records[wave];
     const KeySeg my_record = p.segs[tile.seg_begin + min(wave + kWalkWaves * lane, tile.nseg - 1)];
     const int32_t row[2] = {rows[min(j, tile.nrows - 1)], rows[min(kWalkBlock + j, tile.nrows - 1)]};
-    const int32_t stat_row = rows[min(srow, tile.nrows - 1)];
+    if (tid < kShortRows) row_lds[tid] = rows[min(tid, tile.nrows - 1)];
     records[lane] = my_record;                         // read back by this wave alone
     const int n = (tile.nseg - wave + kWalkWaves - 1) / kWalkWaves;
     const uint32_t addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, lds[wave]));
@@ -102,13 +132,11 @@ void bwd_dq_short_kernel(const BwdParams p) {
         issue_block_rows<BlockOrder::kWalked>(v_src, blk.key0, blk.stride, blk.count, addr + buf * kPairBytes + kBlockBytes, cl);
     };
     KeySeg cur = read_record(records, 0), nx = read_record(records, 1);
-    // -delta = -(dout . out) and lse in base-2 units: 16 rows a wave, 4 lanes a row
-    const float stat_lse = p.lse[stat_bh + stat_row];
-    bf16x8 go[2], oo[2];
+    float my_l2[2], my_nd[2];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        go[x] = *reinterpret_cast<const bf16x8*>(gp + stat_row * g_pitch + sd + 8 * x);
-        oo[x] = *reinterpret_cast<const bf16x8*>(op + stat_row * g_pitch + sd + 8 * x);
+    for (int blk = 0; blk < 2; ++blk) {
+        my_l2[blk] = p.lse2[stat_bh + row[blk]];
+        my_nd[blk] = p.ndelta[stat_bh + row[blk]];
     }
     // the tile's own rows as B operands (16 d x 32 rows): lane (j, g) holds row j, d 16*kk + 8*g .. +7
     bf16x8 qf[2][4], gf[2][4];
@@ -121,31 +149,6 @@ void bwd_dq_short_kernel(const BwdParams p) {
         }
     if (n > 0) issue(cur, 0);
     if (n > 1) issue(nx, 1);
-    {
-        float part = 0.f;
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int t = 0; t < 8; ++t) part = fmaf((float)go[x][t], (float)oo[x][t], part);
-        part += __shfl_xor(part, 1, 4);
-        part += __shfl_xor(part, 2, 4);
-        if ((lane & 3) == 0) {
-            stats[0][srow] = stat_lse * kLog2e;
-            stats[1][srow] = -part;
-            row_lds[srow] = stat_row;
-            if (srow < tile.nrows) {
-                p.lse2[stat_bh + stat_row] = stat_lse * kLog2e;
-                p.ndelta[stat_bh + stat_row] = -part;
-            }
-        }
-    }
-    __syncthreads();
-    float my_l2[2], my_nd[2];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-        my_l2[blk] = stats[0][blk * kWalkBlock + j];
-        my_nd[blk] = stats[1][blk * kWalkBlock + j];
-    }
 
     const int frag = j * kRowElems + 8 * (g ^ stage_swizzle(j));
     const TransposedLane tl = transposed_lane(lane);
@@ -222,19 +225,11 @@ void bwd_dq_short_kernel(const BwdParams p) {
     }
 }
 
-// dk and dv of 32 rows: they are keys, the lists are walked as the queries that see them.
-__global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void bwd_dkdv_short_kernel(const BwdParams p, int n_items) {
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[kWalkWaves][kBuffers * kPairElems];
-    __shared__ __attribute__((aligned(256))) float stats[kWalkWaves][kBuffers][2 * kWalkBlock];     // lse and -delta of a block
-    __shared__ KeySeg records_all[kWalkWaves][kMostBlocks];
-    __shared__ int32_t row_lds[kWalkBlock];
-
-    hold_args(p);
-    int item_index, sub;
-    item_of_part(blockIdx.x, kShortRows / kWalkBlock, item_index, sub);
-    if (item_index >= n_items) return;
-    const Item item = load_item(p.items, item_index);
+// dk and dv of 32 rows, half `sub` of the tile: they are keys, the lists are walked as the queries that see them.
+__device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, const Item& item, int sub) {
+    uint16_t (*const lds)[kBuffers * kPairElems] = mem.blocks;
+    float (*const stats)[kBuffers][2 * kWalkBlock] = mem.stats;
+    int32_t* const row_lds = mem.rows;
     if (item.tile < 0 || sub * kWalkBlock >= item.t.nrows) return;
     const Tile tile = item.t;
     const int tid = threadIdx.x;
@@ -262,7 +257,7 @@ void bwd_dkdv_short_kernel(const BwdParams p, int n_items) {
     const uint16_t* const vp = static_cast<const uint16_t*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
     const int64_t stat_bh = ((int64_t)b * p.H + h) * p.N;
 
-    KeySeg* const records = records_all[wave];
+    KeySeg* const records = mem.records[wave];
     const KeySeg my_record = p.segs[tile.seg_begin + min(wave + kWalkWaves * lane, tile.nseg - 1)];
     const int64_t row = rows[min(j, nrows - 1)];
     if (tid < kWalkBlock) row_lds[tid] = (int32_t)row;
@@ -342,12 +337,28 @@ void bwd_dkdv_short_kernel(const BwdParams p, int n_items) {
     write_sum(dv_acc, lds, tid, row_lds, nrows, grad_v, g_pitch, 1.0f);
 }
 
+// The dq workgroups (an item each, padded to a multiple of the dies), then the dk/dv workgroups: the longer ones start first.
+constexpr int kDkdvParts = kShortRows / kWalkBlock;
+__global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void bwd_short_kernel(const BwdParams p, int n_items, int n_dq) {
+    __shared__ __attribute__((aligned(1024))) ShortLds mem;
+    hold_args(p);
+    if ((int)blockIdx.x < n_dq) {
+        if ((int)blockIdx.x < n_items) dq_short(p, mem, load_item(p.items, blockIdx.x));
+        return;
+    }
+    int item_index, sub;
+    item_of_part((int)blockIdx.x - n_dq, kDkdvParts, item_index, sub);
+    if (item_index < n_items) dkdv_short(p, mem, load_item(p.items, item_index), sub);
+}
+
 }  // namespace
 
-hipError_t launch_bwd_short(const BwdParams& p, int n_items, hipStream_t st) {
-    constexpr int kParts = kShortRows / kWalkBlock;
-    hipLaunchKernelGGL(bwd_dq_short_kernel, dim3(n_items), dim3(64 * kWalkWaves), 0, st, p);
-    hipLaunchKernelGGL(bwd_dkdv_short_kernel, dim3((n_items + kDies - 1) / kDies * kDies * kParts), dim3(64 * kWalkWaves), 0, st, p, n_items);
+hipError_t launch_bwd_short(const BwdParams& p, int n_items, int32_t B, hipStream_t st) {
+    const int64_t lanes = (int64_t)p.N * p.H * 8;
+    const int n_dq = (n_items + kDies - 1) / kDies * kDies;
+    hipLaunchKernelGGL(bwd_rows_short_kernel, dim3((unsigned)((lanes + 255) / 256), B), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(bwd_short_kernel, dim3(n_dq * (1 + kDkdvParts)), dim3(64 * kWalkWaves), 0, st, p, n_items, n_dq);
     return hipGetLastError();
 }
 
