@@ -116,6 +116,8 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
             hp = std::move(sp);
         }
     }
+    if (kind == PlanKind::kBlocks && wants_row_tiles(hp))
+        build_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, false, &hp, kWalkBlock / kBlockRows);
     if (kind == PlanKind::kBlocks && cut_size(hp).records <= kMaxCutRecords) {
         out->cut = true;
         cut_blocks(&hp);

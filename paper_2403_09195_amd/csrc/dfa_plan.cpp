@@ -510,6 +510,19 @@ void cut_blocks(HostPlan* plan) {
     plan->block_mult.swap(block_mult);
 }
 
+bool wants_row_tiles(const HostPlan& plan) {
+    if (plan.items.size() > kMaxRowTiles / kTileBlocks) return false;
+    int64_t tiles = 0, filled = 0, most = 0;           // 32-row blocks: with rows, and of the largest tile
+    for (const Item& i : plan.items)
+        if (i.tile >= 0) {
+            const int64_t blocks = (i.t.nrows + kBlockRows - 1) / kBlockRows;
+            ++tiles;
+            filled += blocks;
+            most = std::max(most, blocks);
+        }
+    return tiles * most > filled;
+}
+
 bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                 int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan) {
     const size_t most = (size_t)chip.fwd_slots() * 9 / 8;
@@ -523,7 +536,7 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                          int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan) {
     if (N >= kMaxCutStride) return false;
-    // us for the two launches on 256 CUs, see dfa_plan.h; `most`: a bound on what the short kernels may take
+    // us for the call on 256 CUs, see dfa_plan.h; `most`: a bound on what the short kernels may take
     const double per_slot = 512.0 / chip.fwd_slots();
     int64_t steps = 0;
     int32_t longest = 0;

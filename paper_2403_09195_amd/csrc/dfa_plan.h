@@ -129,6 +129,14 @@ CutSize cut_size(const HostPlan& plan);
 // small groups with long lists (a branch over the whole image beside narrow windows) would take gigabytes at
 // some 100 000 tokens.  Plans past this many records (4 MB) keep their lists whole; such launches are long and lose nothing by it.
 constexpr int64_t kMaxCutRecords = 1 << 18;
+// The fp32 kernels give a workgroup 32 rows, every tile as many workgroups as the largest has.  A launch with part-filled tiles
+// would start workgroups without rows and deal the others unevenly to the CUs; it takes a plan of 32-row tiles, unless it
+// is long anyway (such a plan holds 32 bytes per workgroup).  Measured, us, forward / backward, 32-row tiles against 256-row ones: two
+// images of 1024 tokens, 6 heads 19.8 / 55.2 against 31.1 / 56.3, four 31.3 / 86.4 against 42.8 / 90.9, one of 2500, 12 heads
+// 74.1 / 239.8 against 99.7 / 268.4, 16 of 1024, 12 heads 289.6 / 643.8 against 289.5 / 642.3; tiles that are all full: one of
+// 4096, 12 heads 162.3 / 545.0 against 160.2 / 543.4.  `plan`: the plain plan of 256-row tiles.
+constexpr size_t kMaxRowTiles = 1 << 14;
+bool wants_row_tiles(const HostPlan& plan);
 
 // Launches that do not fill the chip are as long as one workgroup's start, walk and end.  The short-launch forward kernel cuts
 // the walk by four inside the workgroup and gives it a quarter of the rows, but copies every key block for 64 rows where the
