@@ -546,7 +546,7 @@ bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br
             longest = std::max(longest, i.t.n_steps);
         }
     const double full_us = 15.0 + std::max(3.2 * longest, 0.0164 * steps * per_slot);
-    if (full.items.size() * 0.029 * per_slot > full_us) return false;          // there are at least as many 64-row tiles
+    if (full.items.size() * 0.024 * per_slot > full_us) return false;          // there are at least as many 64-row tiles
     build_plan(B, H, N, br, nb, offsets, order_mode, chip, false, plan, kShortRows / kBlockRows);
     const CutSize size = cut_size(*plan);
     if (size.longest > kShortBackwardBlocks || size.records > kMaxCutRecords) return false;
@@ -555,9 +555,9 @@ bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br
     for (const Item& i : plan->items)
         if (i.tile >= 0) {
             ++tiles;
-            blocks += i.t.nseg;
+            blocks += (int64_t)i.t.nseg * ((i.t.nrows + kBlockRows - 1) / kBlockRows);
         }
-    return 10.0 + (0.029 * tiles + 0.002 * blocks) * per_slot < full_us;
+    return 10.0 + (0.024 * tiles + 0.00105 * blocks) * per_slot < full_us;
 }
 
 }  // namespace dfa

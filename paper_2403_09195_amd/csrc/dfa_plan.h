@@ -154,9 +154,10 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 // The same for the backward.  The kernels of dfa_bwd_bf16.hip walk a tile's whole list in one workgroup and spend as much on
 // a part-filled tile as on a full one; those of dfa_bwd_short.hip cut the walk by four and have 64-row tiles, but copy a block
 // for 64 (dq) or 32 rows (dk, dv).  Both times, in us, are linear in the plan: 15 + the larger of 3.2 per step of the longest
-// list and 0.0164 per step of all tiles, against 10 + 0.029 per 64-row tile + 0.002 per 32-row block of all tiles.  Measured,
-// short against full: 4 images of 1024 tokens, 6 heads 28.4 / 43.8; 16 of 1024, 12 heads 147 / 227; one of 2500 62.7 / 88.0;
-// one of 4096 107 / 118, two 188 / 149; windows of 512 only, one image of 4096 58.9 / 45.0.
+// list and 0.0164 per step of all tiles, against 10 + 0.024 per 64-row tile + 0.00105 per 32 x 32 block of pairs.  Measured,
+// short against full: 4 images of 1024 tokens, 6 heads 24.1 / 43.2; 16 of 1024, 12 heads 145 / 227, of 256 66.4 / 97.8; one
+// of 2500 51.7 / 88.1, three 136 / 145; one of 4096 97.6 / 117, two 173 / 150; windows of 512 only, one image of 4096
+// 53.6 / 44.7.
 // `full` is the plain plan of 256-row tiles.
 constexpr int kShortBackwardBlocks = 256;
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
