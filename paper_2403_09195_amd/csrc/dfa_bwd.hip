@@ -20,7 +20,7 @@
 // (small images are what fp32 training runs on: 12 heads of 1024 rows are 384 workgroups for either gradient kernel).
 // The dq and the dk/dv workgroups ride in one launch, so that together they fill the chip.  Buffers are refilled
 // as soon as a block's last product with them is through, each landing under a product with the other one.
-// Measured, forward and backward of two 512^2 images (6 heads x 1024 tokens): 88 us (one lane per row on the vector units,
+// Measured, forward and backward of two 512^2 images (6 heads x 1024 tokens): 74 us (one lane per row on the vector units,
 // a launch per gradient: 1554 us), error of the gradients against fp64 4.2e-7 of their 2-norm (5.6e-7).
 #include "dfa_device.h"
 #include "dfa_mfma_f32.h"
