@@ -218,9 +218,10 @@ int dfa_scatter(const void *og, int32_t B, int32_t H, int32_t N, int32_t D, dfa_
                 dfa_branch_t br, const int32_t *head_offsets, void *out, void *stream);
 
 /*
- * Host-side view of the launch plan of the fp32 forward kernel and of dfa_backward (no GPU needed;
- * the bf16 dfa_forward refines it, see dfa_plan_describe_forward): the query
- * rows of each head are grouped by the set of (branch, segment) pairs that keep them and
+ * Host-side view of the launch plan of plain 256-row tiles (no GPU needed).  Large launches of the bf16 dfa_backward run
+ * it as it stands.  The others refine it: the fp32 kernels walk its lists cut into blocks, small launches of either take
+ * smaller tiles (dfa_launch_describe in dfa_bench.h gives the plan of a call), the bf16 dfa_forward packs tiles
+ * (dfa_plan_describe_forward).  The query rows of each head are grouped by the set of (branch, segment) pairs that keep them and
  * cut into tiles; every tile carries its keys as arithmetic progressions: one per member
  * branch, or, where the member branches keep some keys more than once, the multiset union of
  * those cut into progressions of one multiplicity each (a key kept by m branches is visited
@@ -239,7 +240,8 @@ int dfa_plan_describe(int32_t B, int32_t H, int32_t N, const dfa_branch_t *branc
                       int32_t *segs, int32_t *items);
 
 /*
- * The same view of the plan the bf16 dfa_forward launches.  It differs where row groups fill only part of a
+ * The same view of the plan of 256-row tiles of the bf16 dfa_forward (launches that do not fill the chip may run 64-row
+ * tiles instead, see dfa_launch_describe in dfa_bench.h).  It differs from the plain one where row groups fill only part of a
  * 256-row tile (small images: the rows of one window of the narrowest branch fall into several groups by which
  * dilated branches also keep them): groups that share most of their keys are packed into one tile, each group
  * on 32-row blocks of its own (half a wave: the unit with its own softmax state), and the tile walks the union of

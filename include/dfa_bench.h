@@ -42,6 +42,29 @@ int dfa_dense_unfused(const void *q, const void *k, const void *v,
                       void *out, float *lse, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * Which kernels a call launches for a shape, and with which plan (no GPU needed).  The library picks the form by its
+ * own estimate of the times, so this is what tests and benchmarks ask when they mean one form in particular.
+ *   backward   0: dfa_forward (dfa_forward_static, dfa_encoder_stack), 1: dfa_backward
+ *   launch     out, host
+ *   tiles, rows, segs, block_mult, items   out, host, NULL to skip: as dfa_plan_describe_forward, of the plan that is
+ *              launched.  Where launch->cut is set every entry of segs is a block of at most 32 keys (one of a single key
+ *              has stride 0).
+ */
+#define DFA_FORM_TILES 0    /* bf16: tiles of 256 rows; fp32: tiles of 256 or of 32 rows */
+#define DFA_FORM_SHORT 1    /* bf16: tiles of 64 rows, whose walk is shared out inside the workgroup */
+#define DFA_FORM_SPLIT 2    /* bf16 forward: tiles of 256 rows, walks shared out over workgroups (DFA_FORM_TILES without a workspace) */
+typedef struct {
+    int32_t form;           /* DFA_FORM_* */
+    int32_t packed;         /* some tile packs several row groups */
+    int32_t cut;            /* the key lists are cut into blocks */
+    int32_t n_tiles, n_rows, n_segs, n_items;
+    int64_t threads;        /* of the call's largest kernel launch (a grid holds fewer than 2^32) */
+} dfa_launch_t;
+int dfa_launch_describe(int32_t backward, dfa_dtype_t dt, int32_t B, int32_t H, int32_t N,
+                        const dfa_branch_t *branches, int32_t nb, const int32_t *head_offsets, dfa_launch_t *launch,
+                        int32_t *tiles, int32_t *rows, int32_t *segs, int32_t *block_mult, int32_t *items);
+
+/*
  * Measurement aid (no part of the operator): what the matrix cores sustain on their own, the
  * ceiling that the kernels' MFMA rooflines are also quoted against.  Runs a loop of
  * independent v_mfma_f32_32x32x16_bf16 on the whole chip (two waves per SIMD, no memory

@@ -23,7 +23,7 @@ EXPORTS = [
     "dfa_forward_branch", "dfa_merge", "dfa_gather", "dfa_scatter", "dfa_plan_describe", "dfa_plan_describe_forward",
     "dfa_release_plans", "dfa_linear", "dfa_encoder_stack", "dfa_backward",
 ]
-BENCH_EXPORTS = ["dfa_forward_timed", "dfa_mfma_peak", "dfa_dense_unfused", "dfa_dense_unfused_workspace_bytes"]
+BENCH_EXPORTS = ["dfa_launch_describe", "dfa_forward_timed", "dfa_mfma_peak", "dfa_dense_unfused", "dfa_dense_unfused_workspace_bytes"]
 
 
 class Branch(ctypes.Structure):
@@ -32,6 +32,13 @@ class Branch(ctypes.Structure):
 
 class Strides(ctypes.Structure):
     _fields_ = [("b", ctypes.c_int64), ("n", ctypes.c_int64), ("h", ctypes.c_int64)]
+
+
+FORM_TILES, FORM_SHORT, FORM_SPLIT = 0, 1, 2
+
+
+class Launch(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("form", "packed", "cut", "n_tiles", "n_rows", "n_segs", "n_items")] + [("threads", ctypes.c_int64)]
 
 
 class DfaError(RuntimeError):
@@ -85,6 +92,8 @@ def lib():
                                         _i32p, _i32p, _i32p, _i32p, _i32p, _i32p, _i32p, _i32p]
         L.dfa_plan_describe_forward.argtypes = [i32, i32, i32, ctypes.POINTER(Branch), i32, _i32p,
                                                 _i32p, _i32p, _i32p, _i32p, _i32p, _i32p, _i32p, _i32p, _i32p]
+        L.dfa_launch_describe.argtypes = [i32, ctypes.c_int, i32, i32, i32, ctypes.POINTER(Branch), i32, _i32p,
+                                          ctypes.POINTER(Launch), _i32p, _i32p, _i32p, _i32p, _i32p]
         i64 = ctypes.c_int64
         L.dfa_linear.argtypes = [vp, vp, vp, i64, i32, i32, i64, i64, i64, vp]
         L.dfa_encoder_stack.argtypes = [vp, vp, vp, i32, i32, i32, i32, i32, f32, ctypes.POINTER(Branch), i32,
@@ -497,6 +506,25 @@ def plan_describe_forward(B, H, N, branches, head_offsets=None):
     _check(lib().dfa_plan_describe_forward(B, H, N, br, nb, off, *refs, p(tiles), p(rows), p(segs), p(block_mult), p(items)),
            "dfa_plan_describe_forward")
     return dict(tiles=tiles, rows=rows, segs=segs[:ns], block_mult=block_mult[:ns], items=items)
+
+
+def launch_describe(B, H, N, branches, head_offsets=None, dtype_code=DFA_BF16, backward=False, arrays=False):
+    """Which kernel form a call launches: dict of form (FORM_*), packed, cut, threads of the largest launch; with `arrays` the
+    launched plan's tiles, rows, segs, block_mult and items too (as plan_describe_forward)."""
+    import numpy as np
+    br, nb = _branches(branches)
+    off = _i32_array(head_offsets)
+    info = Launch()
+    call = lambda *ptrs: _check(lib().dfa_launch_describe(int(backward), dtype_code, B, H, N, br, nb, off, ctypes.byref(info), *ptrs),
+                                "dfa_launch_describe")
+    call(None, None, None, None, None)
+    res = dict(form=info.form, packed=bool(info.packed), cut=bool(info.cut), n_items=info.n_items, threads=info.threads)
+    if arrays:
+        shapes = dict(tiles=(info.n_tiles, 6), rows=(info.n_rows,), segs=(info.n_segs, 4), block_mult=(info.n_segs, 8), items=(info.n_items, 2))
+        out = {k: np.zeros((max(s[0], 1),) + s[1:], dtype=np.int32) for k, s in shapes.items()}
+        call(*(a.ctypes.data_as(_i32p) for a in out.values()))
+        res.update({k: out[k][:s[0]] for k, s in shapes.items()})
+    return res
 
 
 def release_plans():

@@ -95,33 +95,45 @@ size_t split_bytes(int32_t n_split_wgs) {
 // The plan of the bf16 forward (row groups may share a tile, multiplicities per 32-row block), that of the bf16 backward, that
 // of the fp32 kernels (plain, lists cut into blocks where that is affordable), and the plain one that single branches of bf16 inputs read.
 enum class PlanKind : int32_t { kPlain, kForward, kBackward, kBlocks };
+
+// The plan a call of this kind launches: *hp, and of *out what the launch needs to know besides.
+int choose_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
+                const ChipShape& chip, PlanKind kind, HostPlan* hp, PackedPlan* out) {
+    build_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, kind == PlanKind::kForward, hp);
+    if (hp->items.size() > (size_t)0x7fffffff) return DFA_ERR_TOO_LARGE;
+    if (kind == PlanKind::kForward) {
+        split_plan(hp, chip);
+        out->n_split_wgs = (int32_t)hp->split_wgs.size();
+        HostPlan sp;
+        if (short_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, *hp, &sp)) {
+            out->short_walk = true;
+            *hp = std::move(sp);
+        }
+    } else if (kind == PlanKind::kBackward) {
+        HostPlan sp;
+        if (short_backward_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, *hp, &sp)) {
+            out->short_walk = true;
+            *hp = std::move(sp);
+        }
+    }
+    if (kind == PlanKind::kBlocks && wants_row_tiles(*hp))
+        build_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, false, hp, kWalkBlock / kBlockRows);
+    if (kind == PlanKind::kBlocks && cut_size(*hp).records <= kMaxCutRecords) {
+        out->cut = true;
+        cut_blocks(hp);
+    }
+    out->n_items = (int32_t)hp->items.size();
+    out->packed_tiles = hp->packed_tiles;
+    for (const Tile& t : hp->tiles) out->max_tile_rows = std::max(out->max_tile_rows, t.nrows);
+    return DFA_OK;
+}
+
 int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
               const ChipShape& chip, PlanKind kind, PackedPlan* out) {
     const bool packed = kind == PlanKind::kForward;
     HostPlan hp;
-    build_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, packed, &hp);
-    if (hp.items.size() > (size_t)0x7fffffff) return DFA_ERR_TOO_LARGE;
-    if (packed) {
-        split_plan(&hp, chip);
-        out->n_split_wgs = (int32_t)hp.split_wgs.size();
-        HostPlan sp;
-        if (short_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, hp, &sp)) {
-            out->short_walk = true;
-            hp = std::move(sp);
-        }
-    } else if (kind == PlanKind::kBackward) {
-        HostPlan sp;
-        if (short_backward_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, hp, &sp)) {
-            out->short_walk = true;
-            hp = std::move(sp);
-        }
-    }
-    if (kind == PlanKind::kBlocks && wants_row_tiles(hp))
-        build_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, false, &hp, kWalkBlock / kBlockRows);
-    if (kind == PlanKind::kBlocks && cut_size(hp).records <= kMaxCutRecords) {
-        out->cut = true;
-        cut_blocks(&hp);
-    }
+    const int rc = choose_plan(B, H, N, br, nb, offsets, chip, kind, &hp, out);
+    if (rc != DFA_OK) return rc;
     const size_t b_rows = align256(hp.rows.size() * sizeof(int32_t));
     const size_t b_segs = align256(hp.segs.size() * sizeof(KeySeg) + sizeof(KeySeg));
     const size_t b_items = align256(hp.items.size() * sizeof(Item));
@@ -150,9 +162,6 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
             std::memcpy(out->bytes.data() + out->off_split_items + g * sizeof(Item), &hp.items[hp.split_wgs[g].item], sizeof(Item));
         std::memcpy(out->bytes.data() + out->off_item_parts, hp.item_parts.data(), hp.item_parts.size() * sizeof(ItemParts));
     }
-    out->n_items = (int32_t)hp.items.size();
-    out->packed_tiles = hp.packed_tiles;
-    for (const Tile& t : hp.tiles) out->max_tile_rows = std::max(out->max_tile_rows, t.nrows);
     return DFA_OK;
 }
 
@@ -700,6 +709,30 @@ size_t dfa_workspace_bytes(int32_t B, int32_t H, int32_t N, int32_t D, dfa_dtype
 
 namespace {
 
+// A plan's arrays as the descriptors hand them out; each may be NULL.
+void copy_plan(const HostPlan& hp, int32_t* tiles, int32_t* rows, int32_t* segs, int32_t* block_mult, int32_t* items) {
+    if (tiles)
+        for (size_t t = 0; t < hp.tiles.size(); ++t) {
+            const Tile& x = hp.tiles[t];
+            const int32_t rec[6] = {x.h, x.row_begin, x.nrows, x.seg_begin, x.nseg, x.n_steps};
+            std::memcpy(tiles + 6 * t, rec, sizeof(rec));
+        }
+    if (rows) std::memcpy(rows, hp.rows.data(), hp.rows.size() * sizeof(int32_t));
+    if (segs)
+        for (size_t s = 0; s < hp.segs.size(); ++s) {
+            segs[4 * s] = hp.segs[s].key0;
+            segs[4 * s + 1] = hp.segs[s].stride;
+            segs[4 * s + 2] = hp.segs[s].count;
+            segs[4 * s + 3] = hp.seg_mult[s];
+        }
+    if (block_mult) std::memcpy(block_mult, hp.block_mult.data(), hp.block_mult.size() * sizeof(int32_t));
+    if (items)
+        for (size_t i = 0; i < hp.items.size(); ++i) {
+            items[2 * i] = hp.items[i].tile;
+            items[2 * i + 1] = hp.items[i].b;
+        }
+}
+
 int describe_plan(bool packed, int32_t B, int32_t H, int32_t N, const dfa_branch_t* branches, int32_t nb,
                   const int32_t* head_offsets, int32_t* n_tiles, int32_t* n_rows, int32_t* n_segs,
                   int32_t* n_items, int32_t* tiles, int32_t* rows, int32_t* segs, int32_t* block_mult, int32_t* items) {
@@ -714,26 +747,7 @@ int describe_plan(bool packed, int32_t B, int32_t H, int32_t N, const dfa_branch
         *n_rows = (int32_t)hp.rows.size();
         *n_segs = (int32_t)hp.segs.size();
         *n_items = (int32_t)hp.items.size();
-        if (tiles)
-            for (size_t t = 0; t < hp.tiles.size(); ++t) {
-                const Tile& x = hp.tiles[t];
-                const int32_t rec[6] = {x.h, x.row_begin, x.nrows, x.seg_begin, x.nseg, x.n_steps};
-                std::memcpy(tiles + 6 * t, rec, sizeof(rec));
-            }
-        if (rows) std::memcpy(rows, hp.rows.data(), hp.rows.size() * sizeof(int32_t));
-        if (segs)
-            for (size_t s = 0; s < hp.segs.size(); ++s) {
-                segs[4 * s] = hp.segs[s].key0;
-                segs[4 * s + 1] = hp.segs[s].stride;
-                segs[4 * s + 2] = hp.segs[s].count;
-                segs[4 * s + 3] = hp.seg_mult[s];
-            }
-        if (block_mult) std::memcpy(block_mult, hp.block_mult.data(), hp.block_mult.size() * sizeof(int32_t));
-        if (items)
-            for (size_t i = 0; i < hp.items.size(); ++i) {
-                items[2 * i] = hp.items[i].tile;
-                items[2 * i + 1] = hp.items[i].b;
-            }
+        copy_plan(hp, tiles, rows, segs, block_mult, items);
     } catch (const std::bad_alloc&) {
         return DFA_ERR_LAUNCH;
     }
@@ -755,6 +769,50 @@ int dfa_plan_describe_forward(int32_t B, int32_t H, int32_t N, const dfa_branch_
                               int32_t* items) {
     return describe_plan(true, B, H, N, branches, nb, head_offsets, n_tiles, n_rows, n_segs, n_items, tiles, rows, segs,
                          block_mult, items);
+}
+
+int dfa_launch_describe(int32_t backward, dfa_dtype_t dt, int32_t B, int32_t H, int32_t N, const dfa_branch_t* branches, int32_t nb,
+                        const int32_t* head_offsets, dfa_launch_t* launch, int32_t* tiles, int32_t* rows, int32_t* segs,
+                        int32_t* block_mult, int32_t* items) {
+    if (!launch) return DFA_ERR_NULL;
+    int rc = check_common(B, H, N, DFA_HEAD_DIM, dt);
+    if (rc != DFA_OK) return rc;
+    rc = check_branches(H, N, branches, nb, head_offsets);
+    if (rc != DFA_OK) return rc;
+    try {
+        int device = 0;
+        ChipShape chip;                    // the MI355X when no device can be asked
+        if (current_chip(&device, &chip) != DFA_OK) (void)hipGetLastError();
+        const PlanKind kind = dt == DFA_F32 ? PlanKind::kBlocks : backward ? PlanKind::kBackward : PlanKind::kForward;
+        HostPlan hp;
+        PackedPlan choice;
+        rc = choose_plan(B, H, N, branches, nb, head_offsets, chip, kind, &hp, &choice);
+        if (rc != DFA_OK) return rc;
+        launch->form = choice.short_walk ? DFA_FORM_SHORT : choice.n_split_wgs > 0 ? DFA_FORM_SPLIT : DFA_FORM_TILES;
+        launch->packed = choice.packed_tiles;
+        launch->cut = choice.short_walk || choice.cut;
+        launch->n_tiles = (int32_t)hp.tiles.size();
+        launch->n_rows = (int32_t)hp.rows.size();
+        launch->n_segs = (int32_t)hp.segs.size();
+        launch->n_items = choice.n_items;
+        // the largest of the call's kernel launches, as the launchers of each form size it
+        int64_t workgroups = choice.n_items;
+        if (choice.short_walk) {
+            if (backward) workgroups = short_backward_workgroups(choice.n_items);
+        } else if (kind == PlanKind::kBlocks) {
+            const int parts = (backward ? 2 : 1) * ((choice.max_tile_rows + kWalkBlock - 1) / kWalkBlock);
+            workgroups = (int64_t)std::min(choice.n_items, kLaunchItems) * parts;
+        } else if (backward) {
+            workgroups = (int64_t)choice.n_items * kDkdvParts;
+        } else if (choice.n_split_wgs > 0) {
+            workgroups = choice.n_split_wgs;
+        }
+        launch->threads = 256 * workgroups;
+        copy_plan(hp, tiles, rows, segs, block_mult, items);
+    } catch (const std::bad_alloc&) {
+        return DFA_ERR_LAUNCH;
+    }
+    return DFA_OK;
 }
 
 int dfa_release_plans(void) {

@@ -6,10 +6,6 @@
 
 namespace dfa {
 
-constexpr int kDies = 8;                   // launch order of a plan: item i on die i mod 8
-constexpr int kLaunchItems = 1 << 19;      // most items of one launch (at most 16 workgroups of 256 threads each: a grid
-                                           // holds fewer than 2^32 threads)
-
 constexpr int kRedPitch = kD + 4;          // row pitch of the per-wave results in LDS (floats)
 constexpr int kBlockElems = kWalkBlock * kRowElems;      // one bf16 block of one tensor in LDS: 4 KB
 constexpr int kBlockBytes = kBlockElems * 2;

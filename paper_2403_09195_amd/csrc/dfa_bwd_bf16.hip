@@ -31,8 +31,6 @@ namespace dfa {
 namespace {
 
 constexpr int kDqStages = 4, kDkdvStages = 4;      // 64-row stages in LDS; all but one of them in flight or in use
-constexpr int kDkdvRows = 128;                     // rows of a dk/dv workgroup: a tile is up to kDkdvParts of them
-constexpr int kDkdvParts = kTileRows / kDkdvRows;
 
 // 4 bytes per lane from global memory straight into LDS: lane L's word lands at lds_addr + 4*L.
 __device__ __forceinline__ void copy4_to_lds(const void* gbase, uint32_t lane_byte_offset, uint32_t lds_addr) {

@@ -338,7 +338,6 @@ __device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, co
 }
 
 // The dq workgroups (an item each, padded to a multiple of the dies), then the dk/dv workgroups: the longer ones start first.
-constexpr int kDkdvParts = kShortRows / kWalkBlock;
 __global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void bwd_short_kernel(const BwdParams p, int n_items, int n_dq) {
     __shared__ __attribute__((aligned(1024))) ShortLds mem;
@@ -348,7 +347,7 @@ void bwd_short_kernel(const BwdParams p, int n_items, int n_dq) {
         return;
     }
     int item_index, sub;
-    item_of_part((int)blockIdx.x - n_dq, kDkdvParts, item_index, sub);
+    item_of_part((int)blockIdx.x - n_dq, kShortDkdvParts, item_index, sub);
     if (item_index < n_items) dkdv_short(p, mem, load_item(p.items, item_index), sub);
 }
 
@@ -358,7 +357,7 @@ hipError_t launch_bwd_short(const BwdParams& p, int n_items, int32_t B, hipStrea
     const int64_t lanes = (int64_t)p.N * p.H * 8;
     const int n_dq = (n_items + kDies - 1) / kDies * kDies;
     hipLaunchKernelGGL(bwd_rows_short_kernel, dim3((unsigned)((lanes + 255) / 256), B), dim3(256), 0, st, p);
-    hipLaunchKernelGGL(bwd_short_kernel, dim3(n_dq * (1 + kDkdvParts)), dim3(64 * kWalkWaves), 0, st, p, n_items, n_dq);
+    hipLaunchKernelGGL(bwd_short_kernel, dim3((unsigned)short_backward_workgroups(n_items)), dim3(64 * kWalkWaves), 0, st, p, n_items, n_dq);
     return hipGetLastError();
 }
 

@@ -19,6 +19,12 @@ constexpr int kWalkBlock = 32;   // keys per piece of a list cut into blocks (se
 constexpr int kWalkWaves = 4;    // waves that share such a list
 constexpr int kPackWindow = 32;  // row groups (in signature order) after a group that are tried as its tile mates
 constexpr int kShortRows = 64;   // query rows per workgroup of the short-launch kernels
+constexpr int kDies = 8;         // launch order of a plan: item i on die i mod 8
+constexpr int kLaunchItems = 1 << 19;    // most items of one launch (at most 16 workgroups of 256 threads each: a grid
+                                         // holds fewer than 2^32 threads)
+constexpr int kDkdvRows = 128;   // bf16 backward, full tiles: rows of a dk/dv workgroup; a tile is up to kDkdvParts of them
+constexpr int kDkdvParts = kTileRows / kDkdvRows;
+constexpr int kShortDkdvParts = kShortRows / kWalkBlock;     // bf16 backward, short launches: dk/dv workgroups of a tile
 constexpr int kFwdWorkgroupsPerCu = 2;   // workgroups of the bf16 forward kernel that fit one compute unit
 constexpr int kTailItemsPerDie = 96;     // launch order: items at the end of a die's list that go heaviest first
 constexpr int kMaxTileSegs = 32; // key progressions per tile (the kernels hold a tile's list in LDS)
@@ -160,6 +166,8 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 // 53.6 / 44.7.
 // `full` is the plain plan of 256-row tiles.
 constexpr int kShortBackwardBlocks = 256;
+// workgroups of the launch that works out all gradients of n_items launch items: dq ones, padded to whole rounds of the dies, then dk/dv ones
+inline int64_t short_backward_workgroups(int64_t n_items) { return (n_items + kDies - 1) / kDies * kDies * (1 + kShortDkdvParts); }
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                          int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan);
 

@@ -1,0 +1,101 @@
+"""Which kernel form a call takes, and the plan it is launched with, through dfa_launch_describe: 64-row tiles of the
+short launches, 32-row tiles and cut lists of the fp32 kernels, split and packed launches, all against the operator's
+definition.  Host code only: nothing here launches a kernel."""
+import os
+
+import numpy as np
+import pytest
+
+import helpers
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2403_09195_amd import binding, build
+    if not os.path.exists(build.LIB_PATH):
+        build.build()
+    binding.lib()
+    return binding
+
+
+def _check_launched_plan(B, Bsz, H, N, branches, offs, dtype_code, backward):
+    """Every row is stored by one slot of one tile, and the multiplicities of the keys its 32-row block walks are those of
+    the definition; blocks, tiles and items are within what the form's kernels take."""
+    p = B.launch_describe(Bsz, H, N, branches, offs, dtype_code, backward, arrays=True)
+    rows, segs, bm = p["rows"], p["segs"], p["block_mult"]
+    short = p["form"] == B.FORM_SHORT
+    assert p["threads"] < 2 ** 32
+    forward_bf16 = dtype_code == B.DFA_BF16 and not backward
+    most_blocks = None if not short else 64 if forward_bf16 else 256
+    mult = [helpers.multiplicity_matrix(N, h, branches, offs) for h in range(H)]
+    seen = np.zeros((H, N), dtype=np.int32)
+    for (h, rb, nr, sb, ns, _) in p["tiles"]:
+        assert 1 <= nr <= (64 if short else 256)
+        if p["cut"]:
+            assert most_blocks is None or ns <= most_blocks
+            lst = segs[sb:sb + ns]
+            assert np.all((lst[:, 2] >= 1) & (lst[:, 2] <= 32)) and np.all(lst[lst[:, 2] == 1, 1] == 0)
+        tile_rows = rows[rb:rb + nr]
+        assert forward_bf16 or np.all(tile_rows >= 0)                # only the bf16 forward packs tiles
+        for blk in range((nr + 31) // 32):
+            mine = np.zeros(N, dtype=np.int64)
+            for s in range(sb, sb + ns):
+                key0, stride, count, m = (int(x) for x in segs[s])
+                m = int(bm[s, blk]) if forward_bf16 else m
+                assert 0 <= key0 and key0 + stride * (count - 1) < N
+                mine[key0 + stride * np.arange(count)] += m
+            slots = tile_rows[32 * blk:32 * blk + 32]
+            real = slots[slots >= 0]
+            seen[h, real] += 1
+            assert np.all(mult[h][np.where(slots < 0, ~slots, slots)] == mine)
+    assert np.all(seen == 1)
+    live = p["items"][p["items"][:, 0] >= 0]
+    assert len(p["items"]) % 8 == 0 and len(set(map(tuple, live.tolist()))) == len(live) == len(p["tiles"]) * Bsz
+    return p
+
+
+PROBLEMS = [
+    (1, 12, 256, [(64, 1), (128, 2), (256, 4)], None),
+    (3, 6, 1500, [(400, 1), (750, 3), (1500, 5)], [[(3 * h + x + 1) % r for h in range(6)] for x, r in enumerate((1, 3, 5))]),
+    (1, 3, 1000, [(625, 1), (1250, 2), (2500, 4)], None),
+    (2, 2, 130, [(65, 2)], None),                                    # uncovered rows
+    (40, 2, 96, [(32, 4), (96, 1)], None),
+    (2, 3, 50, [(16, 3), (7, 2), (64, 5)], None),
+    (1, 2, 1025, [(1024, 1), (300, 7)], [[0, 0], [6, 2]]),
+    (1, 2, 512, [(256, 2), (256, 2), (512, 1)], None),               # keys that count double
+    (600, 1, 64, [(64, 1)], None),
+    (1, 1, 2100, [(2100, 1)], None),                                 # a list of 66 blocks
+]
+
+
+@pytest.mark.parametrize("Bsz,H,N,branches,offs", PROBLEMS)
+@pytest.mark.parametrize("dtype,backward", [("bf16", False), ("bf16", True), ("f32", False)])
+def test_launched_plan_covers_the_definition(B, Bsz, H, N, branches, offs, dtype, backward):
+    _check_launched_plan(B, Bsz, H, N, branches, offs, B.DFA_BF16 if dtype == "bf16" else B.DFA_F32, backward)
+
+
+@pytest.mark.parametrize("seed", range(16))
+def test_launched_plans_of_random_problems(B, seed):
+    rng = np.random.default_rng(250 + seed)
+    Bsz, H, N, nb = int(rng.integers(1, 40)), int(rng.integers(1, 7)), int(rng.integers(1, 500)), int(rng.integers(1, 6))
+    branches, offs = [], []
+    for _ in range(nb):
+        r = int(rng.integers(1, 8))
+        branches.append((int(rng.integers(1, 2 * N + 1)), r))
+        offs.append([int(rng.integers(0, r)) for _ in range(H)])
+    for code, backward in ((B.DFA_BF16, False), (B.DFA_BF16, True), (B.DFA_F32, False)):
+        _check_launched_plan(B, Bsz, H, N, branches, offs if seed % 2 else None, code, backward)
+
+
+def test_each_form_is_taken_where_it_should_be(B):
+    """One shape per form, far from where the library's estimates meet."""
+    sam = [(1024, 1), (2048, 2), (4096, 4)]
+    form = lambda *a, **k: B.launch_describe(*a, **k)["form"]
+    assert form(16, 12, 4096, sam) == B.FORM_TILES and form(16, 12, 4096, sam, backward=True) == B.FORM_TILES
+    assert form(1, 12, 4096, sam) == B.FORM_SPLIT
+    assert form(1, 6, 4096, sam) == B.FORM_SHORT and form(1, 6, 4096, sam, backward=True) == B.FORM_SHORT
+    small = B.launch_describe(2, 6, 1024, [(256, 1), (512, 2), (1024, 4)], dtype_code=B.DFA_F32, arrays=True)
+    assert small["cut"] and int(small["tiles"][:, 2].max()) == 32            # part-filled 256-row tiles: 32-row tiles
+    one = B.launch_describe(1, 12, 4096, sam, dtype_code=B.DFA_F32, arrays=True)
+    assert one["cut"] and int(one["tiles"][:, 2].max()) == 256
+    assert not B.launch_describe(1, 1, 16384, [(16384, 1), (16, 1)], dtype_code=B.DFA_F32)["cut"]     # 2^19 blocks of lists
