@@ -523,6 +523,30 @@ bool wants_row_tiles(const HostPlan& plan) {
     return tiles * most > filled;
 }
 
+namespace {
+
+// us of a short forward launch and of a launch of whole 256-row tiles, see dfa_plan.h
+double short_forward_us(const HostPlan& plan, const ChipShape& chip) {
+    int64_t live = 0;                                   // a workgroup of rows that no branch keeps is over at once
+    int32_t longest = 0;
+    for (const Item& i : plan.items)
+        if (i.tile >= 0 && i.t.nseg > 0) {
+            ++live;
+            longest = std::max(longest, i.t.nseg);
+        }
+    if (live <= chip.fwd_slots() / kFwdWorkgroupsPerCu) return 6.5 + 0.18 * longest;
+    if (live <= chip.fwd_slots()) return 8.5 + 0.25 * longest;
+    return 12.5 + 0.26 * longest;
+}
+double whole_forward_us(const HostPlan& plan) {
+    int32_t longest = 0;
+    for (const Item& i : plan.items)
+        if (i.tile >= 0) longest = std::max(longest, i.t.n_steps);
+    return plan.packed_tiles ? 7.1 + 1.3 * longest : 4.6 + 1.2 * longest;
+}
+
+}  // namespace
+
 bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                 int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan) {
     const size_t most = (size_t)chip.fwd_slots() * 9 / 8;
@@ -530,7 +554,7 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, plan, kShortRows / kBlockRows);
     if (plan->items.size() > most || cut_size(*plan).longest > kShortBlocks) return false;
     cut_blocks(plan);
-    return true;
+    return !full.split_wgs.empty() || short_forward_us(*plan, chip) < whole_forward_us(full);
 }
 
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,

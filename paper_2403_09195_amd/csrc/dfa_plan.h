@@ -146,13 +146,20 @@ bool wants_row_tiles(const HostPlan& plan);
 
 // Launches that do not fill the chip are as long as one workgroup's start, walk and end.  The short-launch forward kernel cuts
 // the walk by four inside the workgroup and gives it a quarter of the rows, but copies every key block for 64 rows where the
-// other kernels copy it for 256, and its copies run at some 20 bytes per clock and CU.  It is taken when its
+// other kernels copy it for 256, and its copies run at some 20 bytes per clock and CU.  It is considered where its
 // workgroups start (nearly) all at once, up to an eighth more than there are slots, and no list has more than kShortBlocks
-// blocks.  Measured, us, short against 256-row tiles (split where split_plan cuts them): 3 images of 1500 tokens, 6 heads
-// (540 workgroups) 18.2 / 25.7; one of 2500, 12 heads (528) 23.0 / 27.2; one of 4096, 6 heads (384) 19.6 / 26.4, 12 heads (768)
-// 38.1 / 34.1; one of 4096, 12 heads, windows of 512 only (768) 23.8 / 15.1; lists of 4096 keys (128 blocks), 1 head (64)
-// 29.4 / 27.1.  Builds the plan of such a launch (64-row tiles, lists cut into blocks) when it is to be taken; `full` is
-// the plan of 256-row tiles.
+// blocks.  There it takes the place of every split launch; against whole tiles both times, in us, go by the longest list: 4.6 +
+// 1.2 per 64-key step of a 256-row tile (7.1 + 1.3 where tiles pack several row groups), against 6.5 + 0.18 per 32-key block
+// with one workgroup to a CU, 8.5 + 0.25 with two, 12.5 + 0.26 where some CUs run a second round.  Over 271 shapes (1 to 24
+// heads, 100 to 8192 tokens, 1 to 16 images, plain windows, single dilated branches, two to four branches) the choice is
+// within 1 % of the faster form but for four, the worst two 14 % (8 images of 784 tokens, 3 heads, windows of 392 at rate 3, short
+// 9.5 / 8.4) and 12 % (2 of 2614, 3 heads, windows of 201, whole tiles 8.7 / 9.8).
+// Measured, us, short against split: 3 images of 1500 tokens, 6 heads (540 workgroups) 19.3 / 26.4; one of 2500, 12 heads (528)
+// 24.3 / 28.6; one of 4096, 6 heads (384) 20.7 / 28.3, past the range 12 heads (768) 38.4 / 35.3; lists of 4096 keys (128
+// blocks), 1 head (64) 29.4 / 27.1.  Against whole tiles: windows of 512, 9 heads (576) 20.0 / 14.9; windows of 50, 8 images of
+// 200 tokens, 16 heads (512) 10.3 / 6.3; windows of 512, 2 images of 2048, 5 heads (320) 11.7 / 14.2; one of 256 tokens, 12
+// heads, four branches (192) 6.9 / 16.5.  Builds the plan of such a launch (64-row tiles, lists cut into blocks) when it is to
+// be taken; `full` is the plan of 256-row tiles, split where split_plan cuts it.
 constexpr int kShortBlocks = 64;
 bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                 int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan);
