@@ -525,24 +525,21 @@ bool wants_row_tiles(const HostPlan& plan) {
 
 namespace {
 
-// us of a short forward launch and of a launch of whole 256-row tiles, see dfa_plan.h
-double short_forward_us(const HostPlan& plan, const ChipShape& chip) {
-    int64_t live = 0;                                   // a workgroup of rows that no branch keeps is over at once
-    int32_t longest = 0;
+// What short_plan estimates the times by: workgroups with keys (one of rows that no branch keeps is over at once), and blocks
+// (cut lists) or steps (whole ones) of the longest list.
+struct LaunchSize {
+    int64_t live = 0;
+    int32_t blocks = 0, steps = 0;
+};
+LaunchSize launch_size(const HostPlan& plan) {
+    LaunchSize size;
     for (const Item& i : plan.items)
         if (i.tile >= 0 && i.t.nseg > 0) {
-            ++live;
-            longest = std::max(longest, i.t.nseg);
+            ++size.live;
+            size.blocks = std::max(size.blocks, i.t.nseg);
+            size.steps = std::max(size.steps, i.t.n_steps);
         }
-    if (live <= chip.fwd_slots() / kFwdWorkgroupsPerCu) return 6.5 + 0.18 * longest;
-    if (live <= chip.fwd_slots()) return 8.5 + 0.25 * longest;
-    return 12.5 + 0.26 * longest;
-}
-double whole_forward_us(const HostPlan& plan) {
-    int32_t longest = 0;
-    for (const Item& i : plan.items)
-        if (i.tile >= 0) longest = std::max(longest, i.t.n_steps);
-    return plan.packed_tiles ? 7.1 + 1.3 * longest : 4.6 + 1.2 * longest;
+    return size;
 }
 
 }  // namespace
@@ -554,7 +551,13 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, plan, kShortRows / kBlockRows);
     if (plan->items.size() > most || cut_size(*plan).longest > kShortBlocks) return false;
     cut_blocks(plan);
-    return !full.split_wgs.empty() || short_forward_us(*plan, chip) < whole_forward_us(full);
+    if (!full.split_wgs.empty()) return true;
+    const LaunchSize size = launch_size(*plan);
+    const bool one_to_a_cu = size.live <= chip.fwd_slots() / kFwdWorkgroupsPerCu;
+    if (one_to_a_cu && std::any_of(full.segs.begin(), full.segs.end(), [](const KeySeg& s) { return s.count % 64 != 0; })) return true;
+    const double short_us = one_to_a_cu ? 6.5 + 0.18 * size.blocks : size.live <= chip.fwd_slots() ? 8.5 + 0.25 * size.blocks : 12.5 + 0.26 * size.blocks;
+    const int32_t steps = launch_size(full).steps;
+    return short_us < (full.packed_tiles ? 7.1 + 1.3 * steps : 4.6 + 1.2 * steps);
 }
 
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,

@@ -150,10 +150,13 @@ bool wants_row_tiles(const HostPlan& plan);
 // workgroups start (nearly) all at once, up to an eighth more than there are slots, and no list has more than kShortBlocks
 // blocks.  There it takes the place of every split launch; against whole tiles both times, in us, go by the longest list: 4.6 +
 // 1.2 per 64-key step of a 256-row tile (7.1 + 1.3 where tiles pack several row groups), against 6.5 + 0.18 per 32-key block
-// with one workgroup to a CU, 8.5 + 0.25 with two, 12.5 + 0.26 where some CUs run a second round.  Over 271 shapes (1 to 24
-// heads, 100 to 8192 tokens, 1 to 16 images, plain windows, single dilated branches, two to four branches) the choice is
-// within 1 % of the faster form but for four, the worst two 14 % (8 images of 784 tokens, 3 heads, windows of 392 at rate 3, short
-// 9.5 / 8.4) and 12 % (2 of 2614, 3 heads, windows of 201, whole tiles 8.7 / 9.8).
+// with one workgroup to a CU, 8.5 + 0.25 with two, 12.5 + 0.26 where some CUs run a second round.  With one to a CU, lists that do
+// not fill their last step stay with the short kernel whatever the times: it clears the rows past a list's end, where the
+// 256-row kernel gives them weight 0, which makes NaN of an infinite value, and its start outweighs the walk by 2 us at most
+// (whole tiles 5.7 against 7.7), less than the host takes for the call.  Over 271 shapes (1
+// to 24 heads, 100 to 8192 tokens, 1 to 16 images, plain windows, single dilated branches, two to four branches) the choice by times
+// is within 1 % of the faster form but for four, the worst two 14 % (8 images of 784 tokens, 3 heads, windows of 392 at rate 3,
+// short 9.5 / 8.4) and 12 % (2 of 2614, 3 heads, windows of 201, whole tiles 8.7 / 9.8).
 // Measured, us, short against split: 3 images of 1500 tokens, 6 heads (540 workgroups) 19.3 / 26.4; one of 2500, 12 heads (528)
 // 24.3 / 28.6; one of 4096, 6 heads (384) 20.7 / 28.3, past the range 12 heads (768) 38.4 / 35.3; lists of 4096 keys (128
 // blocks), 1 head (64) 29.4 / 27.1.  Against whole tiles: windows of 512, 9 heads (576) 20.0 / 14.9; windows of 50, 8 images of

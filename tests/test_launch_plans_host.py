@@ -106,7 +106,7 @@ def test_each_form_is_taken_where_it_should_be(B):
     (6, 4, 1500, [(512, 1)]),
     (8, 16, 200, [(50, 1)]),             # 512 workgroups, lists of two blocks
     (3, 9, 1024, [(128, 1)]),            # lists of four
-    (8, 10, 256, [(85, 3)]),             # a single dilated branch
+    (8, 2, 1024, [(256, 4)]),            # a single dilated branch, lists of one whole step
 ])
 def test_short_lists_in_whole_tiles_keep_them(B, Bsz, H, N, branches):
     """Launches whose 256-row tiles walk a few steps and are done before the short form has merged its shares (measured
@@ -120,6 +120,8 @@ def test_short_lists_in_whole_tiles_keep_them(B, Bsz, H, N, branches):
     (2, 5, 2048, [(512, 1)]),
     (1, 12, 256, [(64, 1), (128, 2), (256, 4)]),
     (2, 2, 512, [(512, 1)]),
+    (1, 1, 33, [(33, 1)]),               # one workgroup to a CU, lists that do not fill their last 64-key step
+    (2, 7, 550, [(55, 1)]),
 ])
-def test_launches_the_short_form_is_faster_for(B, Bsz, H, N, branches):
+def test_launches_that_stay_with_the_short_form(B, Bsz, H, N, branches):
     assert B.launch_describe(Bsz, H, N, branches)["form"] == B.FORM_SHORT
