@@ -798,7 +798,7 @@ int dfa_launch_describe(int32_t backward, dfa_dtype_t dt, int32_t B, int32_t H, 
         // the largest of the call's kernel launches, as the launchers of each form size it
         int64_t workgroups = choice.n_items;
         if (choice.short_walk) {
-            if (backward) workgroups = short_backward_workgroups(choice.n_items);
+            if (backward) workgroups = short_backward_workgroups(std::min(choice.n_items, kLaunchItems));
         } else if (kind == PlanKind::kBlocks) {
             const int parts = (backward ? 2 : 1) * ((choice.max_tile_rows + kWalkBlock - 1) / kWalkBlock);
             workgroups = (int64_t)std::min(choice.n_items, kLaunchItems) * parts;

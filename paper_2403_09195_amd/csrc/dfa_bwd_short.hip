@@ -355,9 +355,14 @@ void bwd_short_kernel(const BwdParams p, int n_items, int n_dq) {
 
 hipError_t launch_bwd_short(const BwdParams& p, int n_items, int32_t B, hipStream_t st) {
     const int64_t lanes = (int64_t)p.N * p.H * 8;
-    const int n_dq = (n_items + kDies - 1) / kDies * kDies;
     hipLaunchKernelGGL(bwd_rows_short_kernel, dim3((unsigned)((lanes + 255) / 256), B), dim3(256), 0, st, p);
-    hipLaunchKernelGGL(bwd_short_kernel, dim3((unsigned)short_backward_workgroups(n_items)), dim3(64 * kWalkWaves), 0, st, p, n_items, n_dq);
+    for (int i0 = 0; i0 < n_items; i0 += kLaunchItems) {         // a grid holds fewer than 2^32 threads
+        BwdParams q = p;
+        q.items += i0;
+        const int n = n_items - i0 < kLaunchItems ? n_items - i0 : kLaunchItems;
+        const int n_dq = (n + kDies - 1) / kDies * kDies;
+        hipLaunchKernelGGL(bwd_short_kernel, dim3((unsigned)short_backward_workgroups(n)), dim3(64 * kWalkWaves), 0, st, q, n, n_dq);
+    }
     return hipGetLastError();
 }
 

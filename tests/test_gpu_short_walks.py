@@ -76,3 +76,22 @@ def test_one_key_carries_the_row(B, oracle):
     # a weight is off by 2^-8 at most, an output by that times its two largest values (|v| <= 4.5) and its own rounding
     assert np.abs(to_f64(out) - o_ref).max() <= 2.0 ** -8 * (2 * 4.5 + 4.5)
     assert np.abs(to_f64(lse) - l_ref).max() <= 3.95e-3 + 4e-6 * np.abs(l_ref).max()
+
+
+def test_backward_launch_of_more_than_one_slice(B):
+    """More tiles than one slice of the launch takes (2^19): every gradient as from four calls of a quarter of the images,
+    bit for bit (a tile's arithmetic does not depend on the launch around it)."""
+    import torch
+    Bsz, N, H, branches = 5600, 1024, 3, [(32, 1), (1024, 1)]
+    whole = B.launch_describe(Bsz, H, N, branches, backward=True)
+    quarter = B.launch_describe(Bsz // 4, H, N, branches, backward=True)
+    assert whole["form"] == quarter["form"] == B.FORM_SHORT and whole["n_items"] > 2 ** 19 > quarter["n_items"]
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    q, k, v, g = (torch.empty((Bsz, N, H, 64), dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(4))
+    out, lse = B.forward(q, k, v, branches, 0.125)
+    grads = B.backward(q, k, v, out, lse, g, branches, 0.125)
+    for b in range(0, Bsz, Bsz // 4):
+        sl = slice(b, b + Bsz // 4)
+        for got, ref in zip(grads, B.backward(q[sl], k[sl], v[sl], out[sl], lse[sl], g[sl], branches, 0.125)):
+            assert torch.equal(got[sl], ref), b
+    assert all(bool(torch.isfinite(t[-1].float()).all()) for t in grads)

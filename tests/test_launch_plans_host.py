@@ -125,3 +125,11 @@ def test_short_lists_in_whole_tiles_keep_them(B, Bsz, H, N, branches):
 ])
 def test_launches_that_stay_with_the_short_form(B, Bsz, H, N, branches):
     assert B.launch_describe(Bsz, H, N, branches)["form"] == B.FORM_SHORT
+
+
+def test_short_backward_of_millions_of_tiles_stays_within_a_grid(B):
+    """60 000 images of 96 short tiles each, three workgroups of 256 threads per tile: more threads than one grid holds,
+    so the launch has to come in slices."""
+    d = B.launch_describe(60000, 3, 1024, [(32, 1), (1024, 1)], backward=True)
+    assert d["form"] == B.FORM_SHORT and 3 * 256 * d["n_items"] >= 2 ** 32
+    assert d["threads"] < 2 ** 32
