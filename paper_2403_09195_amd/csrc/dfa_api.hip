@@ -107,6 +107,7 @@ int choose_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
         HostPlan sp;
         if (short_plan(B, H, N, br, nb, offsets, kPlanOrder, chip, *hp, &sp)) {
             out->short_walk = true;
+            out->n_split_wgs = 0;              // nor a workspace for partial results
             *hp = std::move(sp);
         }
     } else if (kind == PlanKind::kBackward) {
@@ -699,9 +700,9 @@ size_t dfa_workspace_bytes(int32_t B, int32_t H, int32_t N, int32_t D, dfa_dtype
         ChipShape chip;                    // the MI355X when no device can be asked
         if (current_chip(&device, &chip) != DFA_OK) (void)hipGetLastError();
         HostPlan hp;
-        build_plan(B, H, N, branches, nb, head_offsets, kPlanOrder, chip, true, &hp);
-        split_plan(&hp, chip);
-        return split_bytes((int32_t)hp.split_wgs.size());
+        PackedPlan choice;
+        if (choose_plan(B, H, N, branches, nb, head_offsets, chip, PlanKind::kForward, &hp, &choice) != DFA_OK) return 0;
+        return split_bytes(choice.n_split_wgs);
     } catch (const std::bad_alloc&) {
         return 0;
     }

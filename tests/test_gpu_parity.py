@@ -130,25 +130,28 @@ def test_bf16_small_multi_tile(B, oracle):
     assert bool((out2 == out).all()) and bool((lse2 == lse).all())
 
 
-@pytest.mark.parametrize("Bsz,N,H,branches,split", [
-    (2, 256, 6, [(64, 1), (128, 2), (256, 4)], False),       # 256^2 image: groups of 32, 16, 16 rows, filler slots between them
-    (3, 1024, 12, [(256, 1), (512, 2), (1024, 4)], False),   # 512^2 image: groups of 128, 64, 64 rows fill a tile exactly
-    (1, 2048, 4, [(512, 1), (1024, 2), (2048, 4)], True),    # two groups of 128 rows share a tile whose walk is split over workgroups
-    (2, 600, 3, [(100, 1), (300, 2), (600, 3), (50, 1)], False),   # ragged groups, rates 2 and 3
+@pytest.mark.parametrize("Bsz,N,H,branches,form", [
+    (2, 256, 6, [(64, 1), (128, 2), (256, 4)], "short"),     # 256^2 image, 64-row tiles: groups of 32 and 16 rows, filler slots between them
+    (40, 256, 12, [(64, 1), (128, 2), (256, 4)], "tiles"),   # the same in 256-row tiles of six groups
+    (3, 1024, 12, [(256, 1), (512, 2), (1024, 4)], "tiles"), # 512^2 image: groups of 128, 64, 64 rows fill a tile exactly
+    (1, 2048, 20, [(512, 1), (1024, 2), (2048, 4)], "split"),  # two groups of 128 rows share a tile whose walk is split over workgroups
+    (1, 2200, 2, [(2200, 1), (150, 2), (300, 4)], "split"),  # ragged groups in split tiles
+    (2, 600, 3, [(100, 1), (300, 2), (600, 3), (50, 1)], "short"),   # ragged groups, rates 2 and 3
+    (40, 600, 3, [(100, 1), (300, 2), (600, 3), (50, 1)], "tiles"),
 ])
-def test_bf16_tiles_that_pack_several_row_groups(B, oracle, Bsz, N, H, branches, split):
-    """Row groups that fill only part of a tile share one (each on waves of its own, the tile walking the union of
-    their key lists, a wave masking the progressions its rows do not attend to): results as from the definition."""
-    plan = B.plan_describe_forward(Bsz, H, N, branches)
-    plain = B.plan_describe(Bsz, H, N, branches)
-    assert len(plan["tiles"]) < len(plain["tiles"]) and int((plan["block_mult"] == 0).sum()) > 0
-    assert (B.workspace_bytes(Bsz, H, N, 64, B.DFA_BF16, branches) > 0) == split
+def test_bf16_tiles_that_pack_several_row_groups(B, oracle, Bsz, N, H, branches, form):
+    """Row groups that fill only part of a tile share one (each on 32-row blocks of its own, the tile walking the union of
+    their key lists, a block masking the progressions its rows do not attend to): results as from the definition."""
+    plan = B.launch_describe(Bsz, H, N, branches, arrays=True)
+    assert plan["packed"] and int((plan["block_mult"] == 0).sum()) > 0
+    assert plan["form"] == {"tiles": B.FORM_TILES, "short": B.FORM_SHORT, "split": B.FORM_SPLIT}[form]
     (q, k, v), ex = make_qkv(110 + N, Bsz, N, H, 64, "bf16")
     out, lse = B.forward(q, k, v, branches, 0.125)
     o_ref, l_ref = oracle.forward(*ex, branches, 0.125)
     _check_bf16(out, lse, o_ref, l_ref, f"bf16 packed N={N}", rows=(oracle, ex, branches, 0.125, None))
-    if split:
+    if form == "split":
         out_u, lse_u = B.forward(q, k, v, branches, 0.125, workspace=None)      # the same tiles walked whole
+        assert not bool((out_u == out).all())                                   # (by another kernel)
         _check_bf16(out_u, lse_u, o_ref, l_ref, f"bf16 packed unsplit N={N}", rows=(oracle, ex, branches, 0.125, None))
 
 
@@ -313,11 +316,15 @@ def test_bf16_side_stream_and_plan_release(B, oracle):
     assert bool((out4 == out0).all())
 
 
-@pytest.mark.parametrize("Bsz,N,H", [(4, 1024, 6), (1, 2048, 3)])
-def test_forward_and_backward_replay_from_a_captured_graph(B, Bsz, N, H):
+@pytest.mark.parametrize("Bsz,N,H,form,backward", [
+    (4, 1024, 6, "short", "short"), (1, 2048, 3, "short", "short"),
+    (1, 4224, 2, "split", "short"),            # the split launch and its merge
+    (2, 4096, 12, "tiles", "tiles"),
+])
+def test_forward_and_backward_replay_from_a_captured_graph(B, Bsz, N, H, form, backward):
     """Once a shape's plan exists the calls only enqueue kernels, so they can be captured in a HIP graph: the
     graph is replayed on fresh inputs, with eager work and synchronisations in between, and every replay must
-    equal the eager call on the same inputs bit for bit (the second shape takes the split launch and its merge)."""
+    equal the eager call on the same inputs bit for bit."""
     import torch
     from paper_2403_09195_amd import synth
     branches = [(N // 4, 1), (N // 2, 2), (N, 4)]
@@ -326,8 +333,10 @@ def test_forward_and_backward_replay_from_a_captured_graph(B, Bsz, N, H):
     g = to_device(synth.tensor(900, 7, (Bsz, N, H, 64), "bf16")[0])
     out, lse = B.forward(q, k, v, branches, 0.125)                     # builds the plan
     dq, dk, dv = B.backward(q, k, v, out, lse, g, branches, 0.125)
+    forms = {"tiles": B.FORM_TILES, "short": B.FORM_SHORT, "split": B.FORM_SPLIT}
+    assert B.launch_describe(Bsz, H, N, branches)["form"] == forms[form]
+    assert B.launch_describe(Bsz, H, N, branches, backward=True)["form"] == forms[backward]
     need = B.workspace_bytes(Bsz, H, N, 64, B.DFA_BF16, branches)
-    assert (need > 0) == (Bsz == 1)
     ws = torch.empty((max(need, 16),), dtype=torch.uint8, device="cuda")   # the caller's workspace: allocated before the capture
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()

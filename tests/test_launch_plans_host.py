@@ -133,3 +133,17 @@ def test_short_backward_of_millions_of_tiles_stays_within_a_grid(B):
     d = B.launch_describe(60000, 3, 1024, [(32, 1), (1024, 1)], backward=True)
     assert d["form"] == B.FORM_SHORT and 3 * 256 * d["n_items"] >= 2 ** 32
     assert d["threads"] < 2 ** 32
+
+
+@pytest.mark.parametrize("Bsz,H,N,branches,offs", PROBLEMS + [
+    (1, 4, 2048, [(512, 1), (1024, 2), (2048, 4)], None),            # walks long enough to split, taken by the short form
+    (3, 6, 1500, [(400, 1), (750, 3), (1500, 5)], None),
+    (1, 20, 2048, [(512, 1), (1024, 2), (2048, 4)], None),           # split
+    (1, 2, 4224, [(1056, 1), (2112, 2), (4224, 4)], None),
+    (1, 12, 4096, [(1024, 1), (2048, 2), (4096, 4)], None),
+])
+def test_only_split_launches_ask_for_a_workspace(B, Bsz, H, N, branches, offs):
+    """Partial results are written by split launches alone: no other form asks for room for them."""
+    d = B.launch_describe(Bsz, H, N, branches, offs)
+    need = B.workspace_bytes(Bsz, H, N, 64, B.DFA_BF16, branches, offs)
+    assert need == (d["threads"] // 256 * 256 * (64 * 2 + 8) if d["form"] == B.FORM_SPLIT else 0)

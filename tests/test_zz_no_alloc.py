@@ -39,10 +39,10 @@ def test_static_scratch_matches_dfa_forward_on_consecutive_calls(B, oracle):
     assert mx <= 2e-2 and mean <= 2e-3
     check_lse_bf16(to_f64(got1[1]), oracle, ex, SAM_BRANCHES, 0.125, l_ref)
 
-    # 2: straight after it a smaller input (also split: half the tokens, fewer heads, ragged tiles of 250 rows)
-    small_br = [(500, 1), (1000, 2), (2000, 4)]
-    (q2, k2, v2), ex2 = make_qkv(951, 1, 2000, 5, 64, "bf16")
-    assert B.workspace_bytes(1, 5, 2000, 64, B.DFA_BF16, small_br) > 0
+    # 2: straight after it a smaller input (also split: fewer heads, ragged tiles)
+    small_br = [(1050, 1), (2100, 2), (4200, 4)]
+    (q2, k2, v2), ex2 = make_qkv(951, 1, 4200, 3, 64, "bf16")
+    assert B.launch_describe(1, 3, 4200, small_br)["form"] == B.FORM_SPLIT
     got2 = B.forward_static(q2, k2, v2, small_br, 0.125)
     ref2 = B.forward(q2, k2, v2, small_br, 0.125)
     torch.cuda.synchronize()
@@ -64,9 +64,11 @@ def test_static_scratch_matches_dfa_forward_on_consecutive_calls(B, oracle):
         assert got3[0] is out and _same(got3, ref3)
         out.fill_(float("nan")); lse.fill_(float("nan"))
 
-    # 4: a launch that is not split (a batch that fills the chip) and the fp32 path, rows kept by no branch included
+    # 4: launches that are not split (a small one of 64-row tiles, a batch that fills the chip) and the fp32 path, rows kept by no branch included
     (q4, k4, v4), _ = make_qkv(953, 16, 1024, 12, 64, "bf16")
     br4 = [(256, 1), (512, 2), (1024, 4)]
+    assert B.launch_describe(1, 12, 1024, br4)["form"] == B.FORM_SHORT
+    assert _same(B.forward_static(q4[:1], k4[:1], v4[:1], br4, 0.125), B.forward(q4[:1], k4[:1], v4[:1], br4, 0.125))
     assert B.workspace_bytes(16, 12, 1024, 64, B.DFA_BF16, br4) == 0
     assert _same(B.forward_static(q4, k4, v4, br4, 0.125), B.forward(q4, k4, v4, br4, 0.125))
     (q5, k5, v5), _ = make_qkv(954, 1, 256, 1, 64, "f32")
