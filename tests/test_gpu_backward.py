@@ -202,7 +202,8 @@ def test_backward_bf16_full_size_locality_on_every_row(B):
 @pytest.mark.parametrize("count", [1, 31, 33, 64, 65, 129])
 def test_backward_bf16_list_lengths_around_the_block_sizes(B, oracle, count):
     """Lists of `count` rows: one row (P = 1, dq = dk = 0, dv = dout), and lengths just below, at and
-    above the 32-row block and the 64-row stage the kernels walk in."""
+    above the 32-row block that a wave of the short launches walks in (the 64-row stages of the general kernels:
+    test_gpu_forms)."""
     w, r = 2 * count, 2
     N, H = 3 * w, 2
     branches = [(w, r), (N, 1)]

@@ -82,6 +82,13 @@ def test_f32_launch_of_more_than_one_slice(B):
     assert torch.equal(out, v)
     ref = (q.double() * k.double()).sum(-1).mul(0.125).transpose(1, 2)
     assert float((lse.double() - ref).abs().max()) <= 1e-5
+    # the backward likewise: P is 1, dv is dout; dq and dk are scale times a key or query (below 6) times dP - delta, which is the
+    # rounding of two sums of 64 products (terms below 100 in all: 64 * 2^-24 * 100 at worst), where a wrong row gives about 1
+    g = torch.empty_like(q).normal_(generator=gen)
+    dq, dk, dv = B.backward(q, k, v, out, lse, g, [(1, 1)], 0.125)
+    assert float((dv - g).abs().max()) <= 1e-5 * float(g.abs().max())
+    bar = 0.125 * 6 * 2 * 64 * 2.0 ** -24 * 100
+    assert float(dq.abs().max()) <= bar and float(dk.abs().max()) <= bar
 
 
 @pytest.mark.parametrize("window,cut", [(16, False), (64, True)])

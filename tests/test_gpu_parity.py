@@ -160,8 +160,8 @@ def test_bf16_packed_plan_of_many_workgroups(B, oracle):
     image, 8192 workgroups of six row groups each."""
     Bsz, N, H = 128, 256, 32
     branches = [(64, 1), (128, 2), (256, 4)]
-    plan = B.plan_describe_forward(Bsz, H, N, branches)
-    assert int((plan["items"][:, 0] >= 0).sum()) == 8192 and int((plan["block_mult"] == 0).sum()) > 0
+    plan = B.launch_describe(Bsz, H, N, branches, arrays=True)
+    assert plan["form"] == B.FORM_TILES and int((plan["items"][:, 0] >= 0).sum()) == 8192 and int((plan["block_mult"] == 0).sum()) > 0
     (q, k, v), ex = make_qkv(140, Bsz, N, H, 64, "bf16")
     out, lse = B.forward(q, k, v, branches, 0.125)
     o_ref, l_ref = oracle.forward(*ex, branches, 0.125)
@@ -203,8 +203,8 @@ def test_bf16_eight_branches_and_no_lse(B, oracle):
                                      (95, 1), (96, 2), (97, 1), (128, 1), (129, 2), (257, 1)])
 def test_bf16_key_counts_around_the_pipeline_beats(B, oracle, count, r):
     """Segments of `count` kept keys: one key (a row attends only itself), and counts just below,
-    at and above the 32-key beat and the 64-key stage of the kernel's pipeline, with a second,
-    coarser branch on top so that two key lists of ragged length are walked back to back."""
+    at and above the 32-key beat of the short launches' pipeline (the 64-key stages of the 256-row tiles: test_gpu_forms),
+    with a second, coarser branch on top so that two key lists of ragged length are walked back to back."""
     w = count * r
     N, H = 4 * w, 3
     branches = [(w, r), (2 * w, 2 * r)]

@@ -21,7 +21,8 @@ def B():
 
 
 EDGES = [(n, [(n, 1)]) for n in (1, 31, 33, 64, 65, 96, 127, 129, 161, 256, 257, 2016, 2048)] + [
-    (2080, [(2080, 1)]),                           # one block more than the kernel takes: the general one
+    (2080, [(2080, 1)]),                           # one block more than the forward takes: the split launch
+    (128, [(64, 1), (96, 1)]),                     # a full block or two for some rows, more for others
     (130, [(65, 2)]),                              # one block and one row, uncovered rows
     (384, [(96, 1), (192, 2), (384, 4)]),          # row groups that share a tile, skipping blocks, several multiplicities
     (300, [(20, 1), (60, 3), (300, 5)]),           # many groups of a few rows, many progressions of a few keys
@@ -33,6 +34,10 @@ EDGES = [(n, [(n, 1)]) for n in (1, 31, 33, 64, 65, 96, 127, 129, 161, 256, 257,
 def test_edges(B, oracle, N, branches, packed):
     import torch
     from paper_2403_09195_amd import synth
+    # one full step is a short walk in 256-row tiles too, and faster there
+    forward = {64: B.FORM_TILES, 2080: B.FORM_SPLIT}.get(N, B.FORM_SHORT)
+    assert B.launch_describe(2, 3, N, branches)["form"] == forward
+    assert B.launch_describe(2, 3, N, branches, backward=True)["form"] == B.FORM_SHORT
     (q, k, v), ex = make_qkv(1300 + N, 2, N, 3, 64, "bf16")
     if packed:                                     # views of one buffer, row pitch 3 * H * D
         q, k, v = torch.stack((q, k, v), dim=2).unbind(2)
@@ -59,6 +64,7 @@ def test_infinite_value_stays_in_its_column(B, N):
     """A value row of infinities at the end of a list whose blocks, or whose shares, are not filled: its own column is
     infinite, and the slots past the end make no NaN of it."""
     import torch
+    assert B.launch_describe(1, 1, N, [(N, 1)])["form"] == B.FORM_SHORT
     (q, k, v), _ = make_qkv(78, 1, N, 1, 64, "bf16")
     v[:, N - 1, :, 5] = float("inf")
     out, lse = B.forward(q, k, v, [(N, 1)], 0.125)
@@ -71,11 +77,37 @@ def test_one_key_carries_the_row(B, oracle):
     """Scores of very different size (scale 4): reference exponents that move late, waves whose share weighs nothing."""
     (q, k, v), ex = make_qkv(1400, 1, 384, 2, 64, "bf16")
     branches = [(96, 1), (384, 3)]
+    assert B.launch_describe(1, 2, 384, branches)["form"] == B.FORM_SHORT
     out, lse = B.forward(q, k, v, branches, 4.0)
     o_ref, l_ref = oracle.forward(*ex, branches, 4.0)
     # a weight is off by 2^-8 at most, an output by that times its two largest values (|v| <= 4.5) and its own rounding
     assert np.abs(to_f64(out) - o_ref).max() <= 2.0 ** -8 * (2 * 4.5 + 4.5)
     assert np.abs(to_f64(lse) - l_ref).max() <= 3.95e-3 + 4e-6 * np.abs(l_ref).max()
+
+
+@pytest.mark.parametrize("N,form", [(8133, "short"), (8160, "short"), (8192, "short"), (8193, "tiles"), (8224, "tiles")])
+def test_backward_of_the_longest_lists(B, N, form):
+    """255 and 256 blocks, the most a short launch takes (64 records a wave), and 257, which go to the general kernels:
+    against fp64 by the definition, bounds as in test_edges."""
+    import torch
+    assert B.launch_describe(1, 1, N, [(N, 1)], backward=True)["form"] == {"short": B.FORM_SHORT, "tiles": B.FORM_TILES}[form]
+    (q, k, v), _ = make_qkv(1500, 1, N, 1, 64, "bf16")
+    g = torch.empty_like(q).normal_(generator=torch.Generator(device="cuda").manual_seed(8))
+    out, lse = B.forward(q, k, v, [(N, 1)], 0.125)
+    grads = B.backward(q, k, v, out, lse, g, [(N, 1)], 0.125)
+    q6, k6, v6, g6 = (t[0, :, 0].double() for t in (q, k, v, g))
+    p = torch.softmax(0.125 * (q6 @ k6.T.contiguous()), 1)
+    go = g6 * (p @ v6)
+    dp = g6 @ v6.T.contiguous()
+    ds = 0.125 * p * (dp - go.sum(1, keepdim=True))
+    w = 0.125 * p * (dp.abs() + go.abs().sum(1, keepdim=True))
+    refs = (ds @ k6, ds.T.contiguous() @ q6, p.T.contiguous() @ g6)
+    sums = (w @ k6.abs(), w.T.contiguous() @ q6.abs(), p.T.contiguous() @ g6.abs())
+    eps = 2.0 ** -9
+    for name, got, ref, absum in zip(("dq", "dk", "dv"), grads, refs, sums):
+        d = (got[0, :, 0].double() - ref).abs()
+        assert bool((d <= 2.0 ** -8 * ref.abs() + 4 * eps * absum + 1e-6).all()), name
+        assert float(d.mean()) <= eps * float(absum.mean()) + 1e-7, name
 
 
 def test_backward_launch_of_more_than_one_slice(B):
