@@ -43,11 +43,12 @@
  *     a plan is shared and never written after its upload.
  *   - Workspace.  A bf16 dfa_forward with fewer workgroups than the chip has room for (a single
  *     image, say) is faster when the long key walks are shared out over several workgroups
- *     whose partial results (out in fp16 with a scale per row, lse in fp32) are merged afterwards
- *     (the smallest launches cut the walk inside the workgroup instead and leave the workspace
- *     alone).  Those partial results live in a workspace that the caller owns: dfa_workspace_bytes() says how much the shape needs (0 = none), and each call that
- *     may overlap another one needs a workspace of its own.  With workspace == NULL the call
- *     runs unsplit: same results to within rounding, slower for such shapes.
+ *     whose partial results (out in fp16 with a scale per row, lse in fp32) are merged afterwards.
+ *     Those partial results live in a workspace that the caller owns: dfa_workspace_bytes() says
+ *     how much the shape needs (0 = none; the smallest launches cut the walk inside the workgroup
+ *     instead), and each call that may overlap another one needs a workspace of its own.  With
+ *     workspace == NULL the call runs unsplit: same results to within rounding, slower for such
+ *     shapes.
  */
 #ifndef DFA_H
 #define DFA_H

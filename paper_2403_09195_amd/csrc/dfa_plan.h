@@ -121,7 +121,8 @@ void split_plan(HostPlan* plan, const ChipShape& chip);
 
 // Cuts every progression into pieces of at most kWalkBlock keys, the form the kernels read whose waves walk blocks of a
 // list on their own: piece i of a tile is one 16-byte record at a known place, whatever the progressions' lengths.  A piece
-// of one key has stride 0, so that every stride is below the token count; those kernels keep strides in 24 bits.
+// of one key has stride 0, so that every stride is below the token count.  The short forward keeps strides in 24 bits;
+// short_backward_plan takes the same bound, which its kernels do not need: past it a launch is long.
 constexpr int32_t kMaxCutStride = 1 << 24;
 void cut_blocks(HostPlan* plan);
 
