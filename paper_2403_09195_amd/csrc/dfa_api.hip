@@ -513,8 +513,6 @@ int dfa_forward_static(const void* q, const void* k, const void* v, dfa_strides_
             ss.plan_bytes = plan_bytes;
             ss.key = std::move(key);
             ss.holds_plan = true;
-        } else if (dt == DFA_BF16 && ss.plan_bytes + split_bytes(ss.plan.n_split_wgs) > kStaticScratchBytes) {
-            return DFA_ERR_WORKSPACE;      // the plan was left by a call in the other precision, which needs no partial results
         }
         // the partial results of a split launch are written in full by that launch before its merge reads them:
         // nothing in the scratch has to start at zero
