@@ -182,21 +182,24 @@ __device__ __forceinline__ bool res_item(int die, int j, int per_die, int wide_p
     return true;
 }
 
-// The copies of k-step ks of the tile at (m0, n0), `bn` features wide, into stage `stage`.
+// Copy u of a k-step (4 of x, BN / 64 of w per wave) into stage `stage`; xb, wb: the tile's operands at that k-step.
 template <int BN>
-__device__ __forceinline__ void res_issue(const uint16_t* x, const uint16_t* w, int64_t ldx, int64_t ldw, int64_t m0,
-                                          int64_t n0, int ks, int stage, int wave, uint32_t x_off, uint32_t w_off,
-                                          uint32_t lds_addr) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
+__device__ __forceinline__ void res_copy(int u, const uint16_t* xb, const uint16_t* wb, int64_t ldx, int64_t ldw, int stage,
+                                         int wave, uint32_t x_off, uint32_t w_off, uint32_t lds_addr) {
+    if (u < 4) {
         const int row = 32 * wave + 8 * u;
-        copy16_to_lds(uniform_ptr(x + (m0 + row) * ldx + (int64_t)ks * kLinBK), x_off, lds_addr + stage * kResXStage + row * 128);
+        copy16_to_lds(uniform_ptr(xb + (int64_t)row * ldx), x_off, lds_addr + stage * kResXStage + row * 128);
+    } else {
+        const int row = (BN / 8) * wave + 8 * (u - 4);
+        copy16_to_lds(uniform_ptr(wb + (int64_t)row * ldw), w_off, lds_addr + kResWBase + stage * kResWStage + row * 128);
     }
+}
+// All copies of the first k-step of the tile at (m0, n0).
+template <int BN>
+__device__ __forceinline__ void res_first(const uint16_t* x, const uint16_t* w, int64_t ldx, int64_t ldw, int64_t m0, int64_t n0,
+                                          int stage, int wave, uint32_t x_off, uint32_t w_off, uint32_t lds_addr) {
 #pragma unroll
-    for (int u = 0; u < BN / 64; ++u) {
-        const int row = (BN / 8) * wave + 8 * u;
-        copy16_to_lds(uniform_ptr(w + (n0 + row) * ldw + (int64_t)ks * kLinBK), w_off, lds_addr + kResWBase + stage * kResWStage + row * 128);
-    }
+    for (int u = 0; u < 4 + BN / 64; ++u) res_copy<BN>(u, x + m0 * ldx, w + n0 * ldw, ldx, ldw, stage, wave, x_off, w_off, lds_addr);
 }
 
 // All k-steps and the write-out of one tile whose first k-step is already on its way into stage `stage`
@@ -227,11 +230,16 @@ __device__ __forceinline__ void res_tile(const uint16_t* __restrict__ x, const u
     for (int ks = 0; ks < n_k; ++ks) {
         wait_vmcnt<0>();           // this wave's share of stage ks has landed (and the stores of the tile before have left)
         __syncthreads();           // everyone's has, and everyone is done reading the other stage
-        if (ks + 1 < n_k) {
-            res_issue<BN>(x, w, ldx, ldw, cur.m0, cur.n0, ks + 1, stage ^ 1, wave, x_off, w_off, lds_addr);
-        } else if (have_next) {    // the next tile's first k-step, under this tile's last one and its write-out
-            if (next.wide) res_issue<256>(x, w, ldx, ldw, next.m0, next.n0, 0, stage ^ 1, wave, x_off, w_off, lds_addr);
-            else res_issue<128>(x, w, ldx, ldw, next.m0, next.n0, 0, stage ^ 1, wave, x_off, w_off, lds_addr);
+        // The copies of the next k-step: half of them here, half a quarter of a step later.  Behind the other waves' in the
+        // vector-memory queue a copy holds up its wave's MFMAs; too late, and the next step waits for it.  (32768 x 2304 x 768: all
+        // here 118.9 us, in halves 114.4, over three quarters of the step 117.6, over all of it 119.1.)
+        const bool inner = ks + 1 < n_k;
+        const uint16_t* const xb = x + cur.m0 * ldx + (int64_t)(ks + 1) * kLinBK;
+        const uint16_t* const wb = w + cur.n0 * ldw + (int64_t)(ks + 1) * kLinBK;
+        constexpr int kCopies = 4 + BN / 64;
+        if (!inner && have_next) { // the next tile's first k-step, under this tile's last one and its write-out
+            if (next.wide) res_first<256>(x, w, ldx, ldw, next.m0, next.n0, stage ^ 1, wave, x_off, w_off, lds_addr);
+            else res_first<128>(x, w, ldx, ldw, next.m0, next.n0, stage ^ 1, wave, x_off, w_off, lds_addr);
         }
         const uint16_t* xs = reinterpret_cast<const uint16_t*>(lds + stage * kResXStage) + x_rows * kLinBK;
         const uint16_t* ws = reinterpret_cast<const uint16_t*>(lds + kResWBase + stage * kResWStage) + w_rows * kLinBK;
@@ -243,6 +251,11 @@ __device__ __forceinline__ void res_tile(const uint16_t* __restrict__ x, const u
                 wf[nt] = *reinterpret_cast<const bf16x8*>(ws + 16 * nt * kLinBK + (frag ^ (32 * kh)));
 #pragma unroll
             for (int mh = 0; mh < 2; ++mh) {
+                if (kh == 0 && inner) {
+#pragma unroll
+                    for (int u = mh * kCopies / 2; u < (mh + 1) * kCopies / 2; ++u)
+                        res_copy<BN>(u, xb, wb, ldx, ldw, stage ^ 1, wave, x_off, w_off, lds_addr);
+                }
                 bf16x8 xf[4];
 #pragma unroll
                 for (int m4 = 0; m4 < 4; ++m4)
@@ -307,8 +320,8 @@ void linear_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restri
         const int chunk = (lane & 7) ^ lin_swizzle(r8);
         const uint32_t x_off = (uint32_t)(r8 * ldx * 2 + 16 * chunk), w_off = (uint32_t)(r8 * ldw * 2 + 16 * chunk);
         const uint32_t lds_addr = (uint32_t)(uintptr_t)DFA_LDS_PTR(void, &lds[0]);
-        if (cur.wide) res_issue<256>(x, w, ldx, ldw, cur.m0, cur.n0, 0, 0, wave, x_off, w_off, lds_addr);
-        else res_issue<128>(x, w, ldx, ldw, cur.m0, cur.n0, 0, 0, wave, x_off, w_off, lds_addr);
+        if (cur.wide) res_first<256>(x, w, ldx, ldw, cur.m0, cur.n0, 0, wave, x_off, w_off, lds_addr);
+        else res_first<128>(x, w, ldx, ldw, cur.m0, cur.n0, 0, wave, x_off, w_off, lds_addr);
     }
     int stage = 0;
     for (;;) {                     // ends: j grows by cus_per_die >= 1 every trip, res_item fails past the die's list
@@ -321,32 +334,58 @@ void linear_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restri
     }
 }
 
-// ---- the resident form for launches that 256-row tiles do not fill -----------------------------------------------
-// 128 x BN tiles (BN = 128, 96 or 64; launch_linear_bf16 says when).  A workgroup of 4 waves stays for the whole launch and
-// works through its CU's tiles one after the other, as one stream of 64-k steps: stage i + S of the ring is fetched as
-// soon as every wave has stage i in registers, whichever tile it belongs to, so neither the first trip to memory of a tile
-// nor the write-out of the one before it stops the copies.  A wave (one per SIMD) computes 64 rows x BN/2 features.  Its
-// fragments are double-buffered in registers: while the MFMAs of one 32-k half run, the fragments of the next half are
-// read, also across the one barrier of a step.
-// Bound: with all CUs at it the L2's byte rate (28 KB per step of a 128 x 96 tile in 0.46 us and CU, 15 TB/s over the chip;
-// alone on the chip a workgroup takes 0.21 us).  One 1024^2 image: output projection (256 tiles) 13.0 -> 9.6 us, QKV
-// projection (768 tiles) 25.4 -> 22.5 us.
-// (512 threads in the launch bounds keep the compiler within 256 registers: above that it moves the accumulators through the
-// second half of the register file, two copies per product.)
+// ---- the resident form of 128-row tiles ---------------------------------------------------------------------------
+// 128 x BN tiles (launch_linear_bf16 says when).  A workgroup of 4 waves, one per SIMD, stays for the whole launch and works
+// through its CU's tiles one after the other, as one stream of 64-k steps: stage i + S of the ring is fetched as soon as every
+// wave has stage i in registers, whichever tile it belongs to, so neither the first trip to memory of a tile nor the write-out
+// of the one before it stops the copies.  A wave computes 64 rows x BN/2 features, one 16-feature block against its four
+// 16-row blocks at a time (a group: one weight fragment, four MFMAs of 16 cycles).  Weight fragments are read kAhead groups
+// before their use, the x fragments of a 32-k half as far before the half starts, also across the one barrier of a step,
+// which therefore stands kAhead groups before the step's end; the copies into the freed slot follow it.
+// The results leave straight from the registers: two lane-group exchanges give every lane 16 contiguous bytes of a row.
+// Bound, with all CUs at it: the copies (40 to 57 bytes per clock and CU) beside the MFMAs (whose power takes the clock to some
+// 2 GHz).  A 64-k step of a 128 x 288 tile takes 0.90 us: its MFMAs alone 0.71, its copies alone 0.57.  A copy waits in the
+// vector-memory queue behind the other waves' and its wave's MFMAs with it, so the copies of the wide tiles are spread over a whole
+// step (0.97 us with all of them behind the barrier); the narrow ones need theirs early.  The k-steps' addresses are
+// counted along: a division by the number of feature tiles in every step cost up to 0.08 us.
+// One 1024^2 image: QKV projection 21.5 (256 x 256 tiles on 144 CUs) -> 19.0 us (256 128 x 288 tiles).
 constexpr int kStreamBM = 128;
 template <int BN> constexpr uint32_t kStreamStageBytes = (kStreamBM + BN) * kLinBK * 2;
-template <int BN> constexpr int kStreamStages = BN == 128 ? 4 : BN == 96 ? 5 : 6;      // 128, 140 and 144 KB
-template <int BN> constexpr int kStreamOutPitch = BN + 16;      // bytes: BN / 2 features of one row, padded
+template <int BN> constexpr int kStreamStages = BN == 288 ? 3 : BN >= 128 ? 4 : BN == 96 ? 5 : 6;      // 160, 163, 131, 143 and 147 KB
+// fragments in flight: at most half a step's groups; the ring's length divides a step's groups
+template <int NT> constexpr int kStreamAhead = NT == 9 ? 4 : NT >= 3 ? 3 : 2;
+template <int NT> constexpr int kStreamRing = NT == 9 || NT == 3 ? 6 : 4;
 
+// Rows (16-lane groups) 1 and 3 of `a` change places with rows 0 and 2 of `b`.
+__device__ __forceinline__ void swap_lane_rows(uint32_t& a, uint32_t& b) {
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
+
+// Two 16 x 16 results, lane (g4, r16) with features 4*g4 .. +3 of row r16 of either, as 16 bytes: lane groups 0 and 2 receive
+// features 0 .. 7 and 8 .. 15 of `a`'s row r16, groups 1 and 3 those of `b`'s.
+__device__ __forceinline__ u32x4 pack_pair(const floatx4& a, const floatx4& b) {
+    const bf16x2 a0 = {(__bf16)a[0], (__bf16)a[1]}, a1 = {(__bf16)a[2], (__bf16)a[3]};
+    const bf16x2 b0 = {(__bf16)b[0], (__bf16)b[1]}, b1 = {(__bf16)b[2], (__bf16)b[3]};
+    uint32_t x0 = __builtin_bit_cast(uint32_t, a0), x1 = __builtin_bit_cast(uint32_t, a1);
+    uint32_t y0 = __builtin_bit_cast(uint32_t, b0), y1 = __builtin_bit_cast(uint32_t, b1);
+    swap_lane_rows(x0, y0);
+    swap_lane_rows(x1, y1);
+    return u32x4{x0, x1, y0, y1};
+}
+
+// (512 threads in the launch bounds keep the compiler within 256 registers: above that it moves the accumulators through the
+// second half of the register file, two copies per product.)
 template <int BN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void linear_stream_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, uint16_t* __restrict__ y,
-                          int K, int64_t ldx, int64_t ldw, int64_t ldy, int tiles, int tiles_n, int dies, int cus_per_die) {
-    constexpr int BM = kStreamBM, S = kStreamStages<BN>, MT = BM / 32, NT = BN / 32;              // 16-row / 16-feature blocks per wave
-    constexpr int kCopies = MT + NT;                                                  // copies per wave and stage
+                          int K, int64_t ldx, int64_t ldw, int64_t ldy, int tiles_m, int tiles_n, int parts, int dies, int cus_per_die) {
+    constexpr int BM = kStreamBM, S = kStreamStages<BN>, MT = 4, NT = BN / 32;        // 16-row / 16-feature blocks per wave
+    constexpr int kXCopies = BM / 32, kCopies = kXCopies + BN / 32;                   // copies per wave and stage
     constexpr uint32_t kStage = kStreamStageBytes<BN>, kWBase = BM * kLinBK * 2;
-    constexpr int kPitch = kStreamOutPitch<BN>;
-    __shared__ __attribute__((aligned(1024))) char lds[S * kStage + 4 * 16 * kPitch];
+    constexpr int kAhead = kStreamAhead<NT>, kRing = kStreamRing<NT>, kGroups = 2 * NT;
+    constexpr int kSpread = BN >= 192 ? kGroups : kAhead;                            // groups that a stage's copies are spread over
+    static_assert(kGroups % kRing == 0 && kAhead < kRing && kAhead <= NT, "a fragment's place in the ring is its group's, in every step");
+    __shared__ __attribute__((aligned(1024))) char lds[S * kStage];
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
@@ -357,11 +396,12 @@ void linear_stream_kernel(const uint16_t* __restrict__ x, const uint16_t* __rest
     const uint32_t w_off = (uint32_t)(((BN / 4) * wave + r8) * ldw * 2) + 16u * chunk;
     const uint32_t lds_addr = (uint32_t)(uintptr_t)DFA_LDS_PTR(void, &lds[0]);
     const int wm = wave >> 1, wn = wave & 1;
-    const int frag = r16 * kLinBK + 8 * (g4 ^ lin_swizzle(r16));
 
-    // this workgroup's tiles: first, first + cus_per_die, ... of its die's list
-    const int die = blockIdx.x % dies, per_die = (tiles + dies - 1) / dies;
-    const int die_first = die * per_die, die_tiles = min(per_die, tiles - die_first);
+    // this workgroup's tiles: first, first + cus_per_die, ... of its die's list.  A group of `parts` dies has a run of the tiles
+    // (numbered band by band), each die of it a share of the features.
+    const int die = blockIdx.x % dies, part_n = tiles_n / parts, tile_n0 = die % parts * part_n;
+    const int per_die = (tiles_m * part_n * parts + dies - 1) / dies;
+    const int die_first = die / parts * per_die, die_tiles = min(per_die, tiles_m * part_n - die_first);
     const int first = blockIdx.x / dies;
     if (first >= die_tiles) return;
     const int n_k = K / kLinBK;
@@ -369,16 +409,21 @@ void linear_stream_kernel(const uint16_t* __restrict__ x, const uint16_t* __rest
 
     // the stream of copies
     int ij = first, iks = 0, issued = 0;
-    auto issue = [&](int slot) {
+    const uint16_t *xt, *wt;                                                          // the tile in hand at k-step iks
+    auto tile_start = [&]() {
         const int t = die_first + ij;
-        const void* const xb = uniform_ptr(x + (int64_t)(t / tiles_n) * BM * ldx + (int64_t)iks * kLinBK);
-        const void* const wb = uniform_ptr(w + (int64_t)(t % tiles_n) * BN * ldw + (int64_t)iks * kLinBK);
-        const uint32_t at = lds_addr + slot * kStage;
-#pragma unroll
-        for (int u = 0; u < MT; ++u) copy16_to_lds(xb, x_off + u * x_step, at + ((BM / 4) * wave + 8 * u) * 128);
-#pragma unroll
-        for (int u = 0; u < NT; ++u) copy16_to_lds(wb, w_off + u * w_step, at + kWBase + ((BN / 4) * wave + 8 * u) * 128);
-        if (++iks == n_k) { iks = 0; ij += cus_per_die; }
+        xt = x + (int64_t)(t / part_n) * BM * ldx;
+        wt = w + (int64_t)(tile_n0 + t % part_n) * BN * ldw;
+    };
+    tile_start();
+    auto copy = [&](int u, uint32_t at) {
+        if (u < kXCopies) copy16_to_lds(uniform_ptr(xt), x_off + u * x_step, at + ((BM / 4) * wave + 8 * u) * 128);
+        else copy16_to_lds(uniform_ptr(wt), w_off + (u - kXCopies) * w_step, at + kWBase + ((BN / 4) * wave + 8 * (u - kXCopies)) * 128);
+    };
+    auto stage_issued = [&]() {
+        xt += kLinBK;
+        wt += kLinBK;
+        if (++iks == n_k) { iks = 0; ij += cus_per_die; tile_start(); }
         ++issued;
     };
     // waits until all but the youngest `ahead` stages of this wave's copies have landed (stores of a tile before count as
@@ -391,80 +436,79 @@ void linear_stream_kernel(const uint16_t* __restrict__ x, const uint16_t* __rest
         else if (S > 2 && ahead >= 1) wait_vmcnt<kCopies>();
         else wait_vmcnt<0>();
     };
-    struct Frags { bf16x8 w[NT], x[MT]; };
-    auto read = [&](Frags& f, int slot, int kh) {
-        const uint16_t* xs = reinterpret_cast<const uint16_t*>(lds + slot * kStage) + (BM / 2) * wm * kLinBK + (frag ^ (32 * kh));
-        const uint16_t* ws = reinterpret_cast<const uint16_t*>(lds + slot * kStage + kWBase) + (BN / 2) * wn * kLinBK + (frag ^ (32 * kh));
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) f.w[nt] = *reinterpret_cast<const bf16x8*>(ws + 16 * nt * kLinBK);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) f.x[mt] = *reinterpret_cast<const bf16x8*>(xs + 16 * mt * kLinBK);
+
+    // fragments: row r16 of a 16-row block, chunk (4 * half + g4) ^ swizzle
+    const int frag = r16 * kLinBK + 8 * (g4 ^ lin_swizzle(r16));
+    bf16x8 wf[kRing], xf[2][MT];
+    auto read_w = [&](const uint16_t* st, int i) {         // fragment of group i of a step
+        wf[i % kRing] = *reinterpret_cast<const bf16x8*>(st + kWBase / 2 + ((BN / 2) * wn + 16 * (i % NT)) * kLinBK + (frag ^ (32 * (i / NT))));
     };
+    auto read_x = [&](const uint16_t* st, int half) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) xf[half][mt] = *reinterpret_cast<const bf16x8*>(st + ((BM / 2) * wm + 16 * mt) * kLinBK + (frag ^ (32 * half)));
+    };
+    auto stage = [&](int slot) { return reinterpret_cast<const uint16_t*>(lds + slot * kStage); };
+
+    for (int s = 0; s < S && s < total; ++s) {
+#pragma unroll
+        for (int u = 0; u < kCopies; ++u) copy(u, lds_addr + s * kStage);
+        stage_issued();
+    }
+    landed(issued - 1);
+    asm volatile("s_barrier" ::: "memory");
+    read_x(stage(0), 0);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) read_w(stage(0), i);
 
     floatx4 acc[NT][MT];                   // [16-feature block][16-row block], as in linear_tile
-    auto multiply = [&](const Frags& f) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.x[mt], acc[nt][mt], 0, 0, 0);
-    };
-    // the reads of one half spread over the MFMAs of the other
-    auto weave = [&]() {
-#pragma unroll
-        for (int i = 0; i < MT + NT; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, MT * NT / (MT + NT), 0);
-        }
-    };
-
-    for (int s = 0; s < S && s < total; ++s) issue(s);
-    landed(issued - 1);
-    __syncthreads();
-    Frags f0, f1;
-    read(f0, 0, 0);
-    int step = 0, slot = 0;
+    int step = 0, slot = 0, fill = 0;
+    bool more = false;                     // a stage is being fetched into slot `fill`
     for (int j = first; j < die_tiles; j += cus_per_die) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
         for (int ks = 0; ks < n_k; ++ks, ++step) {
-            read(f1, slot, 1);
-            multiply(f0);
-            weave();
             const int next_slot = slot + 1 == S ? 0 : slot + 1;
-            // every wave has the whole of this slot in registers, and stage step + 1 has landed for every wave
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            landed(issued - step - 2);
-            __syncthreads();
-            if (issued < total) issue(slot);
-            read(f0, next_slot, 0);        // past the last step: an old slot, not used
-            multiply(f1);
-            weave();
+#pragma unroll
+            for (int i = 0; i < kGroups; ++i) {
+                constexpr int kMeet = kGroups - kAhead;
+                if (i == kMeet) {
+                    // every wave has the whole of this slot in registers, and stage step + 1 has landed for every wave
+                    if (more) stage_issued();
+                    landed(issued - step - 2);
+                    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                    more = issued < total;
+                    fill = slot;
+                }
+                // past the last step: an old slot, not used
+                const int r = i + kAhead;
+                if (i % NT == NT - kAhead) read_x(stage(i < NT ? slot : next_slot), i < NT ? 1 : 0);
+                read_w(stage(r < kGroups ? slot : next_slot), r % kGroups);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[i % NT][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i % kRing], xf[i / NT][mt], acc[i % NT][mt], 0, 0, 0);
+                const int g = (i + kGroups - kMeet) % kGroups;
+                if (g < kSpread && more) {
+#pragma unroll
+                    for (int u = g * kCopies / kSpread; u < (g + 1) * kCopies / kSpread; ++u) copy(u, lds_addr + fill * kStage);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
             slot = next_slot;
         }
-        // write-out: 16 rows of the wave's tile at a time through its own piece of LDS.  No barrier: the piece belongs to
-        // this wave alone, and LDS operations of a wave complete in order.
+        // write-out: pairs of feature blocks, 64 contiguous bytes of every row per store; a last single one by pairs of row blocks
         const int t = die_first + j;
-        const int64_t m0 = (int64_t)(t / tiles_n) * BM + (BM / 2) * wm, n0 = (int64_t)(t % tiles_n) * BN + (BN / 2) * wn;
-        constexpr int kLanesPerRow = BN / 16, kChunks = 16 * kLanesPerRow;             // 16-byte pieces of BN / 2 features
-        char* const mine = lds + S * kStage + wave * (16 * kPitch);
+        uint16_t* const yt = y + ((int64_t)(t / part_n) * BM + (BM / 2) * wm + r16) * ldy + (tile_n0 + t % part_n) * BN + (BN / 2) * wn + 8 * (g4 >> 1);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const floatx4& a = acc[nt][mt];
-                const bf16x4 o = {(__bf16)a[0], (__bf16)a[1], (__bf16)a[2], (__bf16)a[3]};
-                *reinterpret_cast<bf16x4*>(mine + r16 * kPitch + (16 * nt + 4 * g4) * 2) = o;
-            }
+            for (int nt = 0; nt + 1 < NT; nt += 2)
+                *reinterpret_cast<u32x4*>(yt + (int64_t)16 * mt * ldy + 16 * (nt + (g4 & 1))) = pack_pair(acc[nt][mt], acc[nt + 1][mt]);
+        if (NT % 2 != 0) {
 #pragma unroll
-            for (int c0 = 0; c0 < kChunks; c0 += 64) {
-                const int c = c0 + lane, row = c / kLanesPerRow, ch = c % kLanesPerRow;
-                if (kChunks % 64 == 0 || c < kChunks)
-                    *reinterpret_cast<u32x4*>(y + (m0 + 16 * mt + row) * ldy + n0 + 8 * ch) =
-                        *reinterpret_cast<const u32x4*>(mine + row * kPitch + 16 * ch);
-            }
+            for (int mt = 0; mt < MT; mt += 2)
+                *reinterpret_cast<u32x4*>(yt + (int64_t)16 * (mt + (g4 & 1)) * ldy + 16 * (NT - 1)) = pack_pair(acc[NT - 1][mt], acc[NT - 1][mt + 1]);
         }
     }
 }
@@ -473,10 +517,14 @@ template <int BN>
 hipError_t launch_stream(const void* x, const void* w, void* y, int64_t M, int32_t N, int32_t K,
                          int64_t ldx, int64_t ldw, int64_t ldy, const ChipShape& chip, hipStream_t st) {
     const int dies = chip.dies > 0 ? chip.dies : 1, cus_per_die = chip.cus / dies > 0 ? chip.cus / dies : 1;
-    const int tiles_n = N / BN, tiles = (int)(M / kStreamBM) * tiles_n, per_die = (tiles + dies - 1) / dies;
+    const int tiles_n = N / BN, tiles_m = (int)(M / kStreamBM);
+    // Two dies with half the feature tiles each fetch less, and keep it more easily, than each with all (8192 x 2304 x 768 34.3 ->
+    // 31.9 us, 4096 x 2304 x 768 18.7 -> 18.5), where that deals the dies the same number of tiles.
+    const int parts = tiles_n % 2 == 0 && dies % 2 == 0 && tiles_m % (dies / 2) == 0 ? 2 : 1;
+    const int per_die = (tiles_m * tiles_n + dies - 1) / dies;
     hipLaunchKernelGGL((linear_stream_kernel<BN>), dim3((per_die < cus_per_die ? per_die : cus_per_die) * dies), dim3(256), 0, st,
                        static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), static_cast<uint16_t*>(y),
-                       K, ldx, ldw, ldy, tiles, tiles_n, dies, cus_per_die);
+                       K, ldx, ldw, ldy, tiles_m, tiles_n, parts, dies, cus_per_die);
     return hipGetLastError();
 }
 
@@ -514,12 +562,15 @@ hipError_t launch_tiles(const void* x, const void* w, void* y, int64_t M, int32_
 
 hipError_t launch_linear_bf16(const void* x, const void* w, void* y, int64_t M, int32_t N, int32_t K,
                               int64_t ldx, int64_t ldw, int64_t ldy, const ChipShape& chip, hipStream_t st) {
-    // One workgroup per CU at a time, so a launch lasts as long as the CU with most tiles.  A round of tiles costs about as
-    // much as the bytes it fetches, 64 (BM + BN) per k-step and CU, a round of 256 x 256 tiles 1.28 times that (its MFMAs
-    // show): measured over 256 to 32768 rows and 384 to 2304 features (K = 384 and 768), the least estimate is the fastest
-    // form or within 2 % of it.  Rows x features, us, 256 x 256 / 256 x 128 / 128 x 96 / 128 x 64 tiles at K = 768:
-    // 2048 x 768 13.0 / 12.5 / 9.6 / 9.4, 4096 x 768 13.4 / 13.0 / 9.6 / 13.1, 2048 x 2304 15.0 / 14.1 / 15.6 / 18.5,
-    // 4096 x 2304 22.7 / 25.4 / 22.5 / 28.5, 8192 x 2304 34.0 / 38.0 / 41.9 / 48.6.
+    // One workgroup per CU at a time, so a launch lasts as long as the CU with most tiles.  Per round of tiles the small forms
+    // cost about as much as the bytes they fetch, 64 (BM + BN) per k-step and CU; 256 x 256, 128 x 288 and 128 x 192 tiles
+    // more (their MFMAs show), 128 x 192 ones less where K is long enough to make up for their start.  Fitted over 2048 to 32768
+    // rows and 384 to 2304 features (K = 384 and 768): the least estimate is the fastest form or within 4 % of it.
+    // Rows x features x K, us, 256 x 256 / 256 x 128 / 128 x 288 / 128 x 192 / 128 x 128 / 128 x 96 / 128 x 64 tiles:
+    // 2048 x 2304 x 768 14.9 / 14.3 / 16.4 / 13.3 / 17.2 / 15.0 / 16.7, 4096 x 2304 x 768 21.4 / 25.8 / 19.0 / 22.5 / 24.1 / 21.3 / 25.1,
+    // 8192 x 2304 x 768 34.5 / 39.3 / 33.2 / 34.4 / 38.3 / 37.9 / 42.6, 16384 x 2304 x 768 57.3 / 65.3 / 60.7 / 64.0 / 67.6 / 73.6 / 80.9,
+    // 4096 x 768 x 768 13.9 / 13.2 / - / 12.7 / 10.2 / 9.5 / 12.3, 6144 x 768 x 768 14.5 / 13.9 / - / 13.3 / 17.2 / 15.1 / 16.5,
+    // 5120 x 1152 x 384 - / 9.6 / 11.8 / 10.3 / 11.8 / 10.8 / 11.5, 8192 x 1152 x 384 - / 16.2 / 13.1 / 15.4 / 15.8 / 14.2 / 16.4.
     const int64_t dies = chip.dies > 0 ? chip.dies : 1, cus = chip.cus / dies > 0 ? chip.cus / dies : 1;
     auto per_die = [&](int bm, int bn) { return ((M / bm) * (N / bn) + dies - 1) / dies; };
     auto rounds = [&](int bm, int bn) { return (per_die(bm, bn) + cus - 1) / cus; };
@@ -533,13 +584,17 @@ hipError_t launch_linear_bf16(const void* x, const void* w, void* y, int64_t M, 
         const int64_t rem = per_die(256, 256) % cus, halves = rem > 0 && 2 * rem <= cus;
         consider(256, (rounds(256, 256) - halves) * 655 + halves * (256 + 128));
     }
-    // its copy lanes address 128 rows with 32-bit byte offsets
+    // their copy lanes address up to 288 rows with 32-bit byte offsets
     if (ldx < (1 << 22) && ldw < (1 << 22)) {
+        if (N % 288 == 0) consider(288, rounds(128, 288) * 515);
+        if (N % 192 == 0) consider(192, rounds(128, 192) * (K >= 512 ? 375 : 400));
         consider(128, rounds(128, 128) * (128 + 128));
         if (N % 96 == 0) consider(96, rounds(128, 96) * (128 + 96));
         consider(64, rounds(128, 64) * (128 + 64));
     }
     switch (form) {
+        case 288: return launch_stream<288>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
+        case 192: return launch_stream<192>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
         case 256: return launch_tiles<256>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
         case 128: return launch_stream<128>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);
         case 96: return launch_stream<96>(x, w, y, M, N, K, ldx, ldw, ldy, chip, st);

@@ -80,6 +80,19 @@ def test_linear_tile_forms(B, oracle, M, N, K):
     assert np.all(err <= _linear_bar(xe, we[:, :K], ref))
 
 
+# the wide 128-row tiles: 128 x 288 (fewer k-steps than stages, as many, more; one tile per workgroup, two whose k-steps follow one
+# another in the ring), 128 x 192 (one tile per workgroup, two); feature tiles shared by two dies and, with a number
+# of row bands that four does not divide, not
+@pytest.mark.parametrize("M,N,K", [(4096, 2304, 64), (4096, 2304, 192), (8192, 1152, 320), (8192, 2304, 64), (8192, 2304, 256),
+                                   (3840, 2304, 128), (2048, 2304, 512), (6144, 1920, 512)])
+def test_linear_wide_tile_forms(B, oracle, M, N, K):
+    x, xe = _bf16(407, 3, (M, K))
+    wide, we = _bf16(407, 10, (N, K + 8), std=0.02)
+    y = B.linear(x, wide[:, :K])
+    ref = oracle.linear(xe, we[:, :K])
+    assert np.all(np.abs(to_f64(y) - ref) <= _linear_bar(xe, we[:, :K], ref))
+
+
 def test_linear_rejects_bad_shapes(B):
     import torch
     x = torch.zeros((256, 64), dtype=torch.bfloat16, device="cuda")
