@@ -10,20 +10,23 @@
 // above is linear in P).
 //
 // This file: the per-row preparation of the fp32 path (delta, and lse in base-2 units; the bf16 path does it in
-// its dq kernel) and the fp32 path on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: full fp32 products and sums).
-// bf16 operands go to the kernels of dfa_bwd_bf16.hip.  In a segment the kept rows are queries and keys alike, so a
-// tile's key lists are also the lists of queries that see its rows as keys: the dq workgroups walk them as keys, the
-// dk/dv workgroups walk them as queries, and no gradient needs an atomic or a second pass over partial sums.
+// its dq kernel) and the fp32 path, whose products run on the bf16 matrix cores with every operand as the sum of three bf16
+// numbers (see dfa_mfma_f32.h).  bf16 operands go to the kernels of dfa_bwd_bf16.hip.  In a segment the kept rows are queries
+// and keys alike, so a tile's key lists are also the lists of queries that see its rows as keys: the dq workgroups walk them as
+// keys, the dk/dv workgroups walk them as queries, and no gradient needs an atomic or a second pass over partial sums.
 //
-// Bound: the fp32 matrix cores (a 32 x 32 block of pairs takes 96 MFMAs of 64 cycles for dq and 128 for dk and dv).
-// As in the forward a workgroup owns 32 rows of a tile and its four waves a quarter of the walked 32-row blocks each
-// (small images are what fp32 training runs on: 12 heads of 1024 rows are 384 workgroups for either gradient kernel).
-// The dq and the dk/dv workgroups ride in one launch, so that together they fill the chip.  Buffers are refilled
-// as soon as a block's last product with them is through, each landing under a product with the other one.
-// Measured, forward and backward of two 512^2 images (6 heads x 1024 tokens): 74 us (one lane per row on the vector units,
-// a launch per gradient: 1554 us), error of the gradients against fp64 4.2e-7 of their 2-norm (5.6e-7).
+// Bound: the matrix cores and the vector unit together (a 32 x 32 block of pairs takes 72 MFMAs of 32 cycles for dq and 96 for
+// dk and dv, and as much again to split the operands).  As in the forward a workgroup owns 32 rows of a tile and its four waves a
+// quarter of the walked 32-row blocks each (small images are what fp32 training runs on: 12 heads of 1024 rows are 384 workgroups
+// for either gradient kernel).  The dq and the dk/dv workgroups ride in one launch, so that together they fill the chip.
+// Buffers are refilled as soon as a block's last product with them is through, each landing under a product with the other
+// one.  The dk/dv workgroups hold 64 registers of split tile rows and the low parts in LDS, where the four waves share them: with all of
+// them in registers the walk spills.
+// Measured, forward and backward of two 512^2 images (6 heads x 1024 tokens): 60 us (fp32 matrix cores 74 us), error of the gradients
+// against fp64 3.6e-7 of their 2-norm (4.3e-7).
 #include "dfa_device.h"
 #include "dfa_mfma_f32.h"
+#include <type_traits>
 
 namespace dfa {
 
@@ -64,12 +67,13 @@ struct BwdBlock {
 };
 
 // Sum of the four waves' [32][64] results, written to rows of a contiguous [B, N, H, D] tensor.  Every wave has
-// finished with its own region of LDS.
-__device__ __forceinline__ void write_sum(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems], int tid,
+// finished with its own region of LDS.  Returns whether a value of this thread's is suspect.
+__device__ __forceinline__ bool write_sum(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems], int tid,
                                           const floatx16 (&acc)[2], void* grad) {
     result_to_lds(acc, lds[tid >> 6], tid & 63);
     __syncthreads();
     const int row = tid >> 3, d = (tid & 7) * 8;
+    bool odd = false;
     if (row < k.nrows) {
         float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
 #pragma unroll
@@ -83,12 +87,14 @@ __device__ __forceinline__ void write_sum(const BwdParams& p, const BwdBlock& k,
                                                       (((int64_t)k.b * p.N + k.rows[row]) * p.H + k.h) * kD + d);
         dst[0] = a;
         dst[1] = c;
+        odd = suspect(a.x) | suspect(a.y) | suspect(a.z) | suspect(a.w) | suspect(c.x) | suspect(c.y) | suspect(c.z) | suspect(c.w);
     }
+    return odd;
 }
 
 // dq of the block's rows: they are queries, the lists are walked as keys.
-template <bool kCut>
-__device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems], int tid) {
+template <class Rows, class Sum, bool kCut>
+__device__ __forceinline__ bool dq_block(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems], int tid) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
     const float* const kb = static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + (int64_t)k.h * p.skh;
     const float* const vb = static_cast<const float*>(p.v) + (int64_t)k.b * p.svb + (int64_t)k.h * p.svh;
@@ -100,15 +106,14 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
     const int64_t n = k.rows[min(j, k.nrows - 1)];
     BlockWalk<kCut> w;
     w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave, k.records + wave * kWalkRecords);
-    float4 q[8], go[8];
-    load_chunks(static_cast<const float*>(p.q) + (int64_t)k.b * p.sqb + n * p.sqn + (int64_t)k.h * p.sqh, g, q);
-    load_chunks(static_cast<const float*>(p.dout) + (((int64_t)k.b * p.N + n) * p.H + k.h) * kD, g, go);
+    Rows q, go;
+    load_rows(static_cast<const float*>(p.q) + (int64_t)k.b * p.sqb + n * p.sqn + (int64_t)k.h * p.sqh, g, q);
+    load_rows(static_cast<const float*>(p.dout) + (((int64_t)k.b * p.N + n) * p.H + k.h) * kD, g, go);
     const int64_t at = ((int64_t)k.b * p.H + k.h) * p.N + n;
     float my_l = p.lse2[at], my_d = p.ndelta[at];
 
-    floatx16 acc[2];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+    Sum acc;
+    acc.clear();
 
     if (w.valid()) {
         issue_block(vb, p.svn, w, v_addr, lane);
@@ -125,13 +130,13 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
         const float bias = w.seg.log2_mult;
 
         copies_left<kF32Copies>();                       // V is there
-        const floatx16 dp = rows_product(v_lds, go, lane);
+        const floatx16 dp = rows_product(read_rows(v_lds, go, lane), go, lane);
         lds_reads_done();
         if (more) issue_block(vb, p.svn, nx, v_addr, lane);
         if (more) copies_left<kF32Copies>();             // K is there
         else copies_left<0>();
         if (nvalid < kWalkBlock) zero_tail(k_lds, nvalid, lane);
-        const floatx16 s = rows_product(k_lds, q, lane);
+        const floatx16 s = rows_product(read_rows(k_lds, q, lane), q, lane);
         float ds[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -143,18 +148,20 @@ __device__ __forceinline__ void dq_block(const BwdParams& p, const BwdBlock& k, 
             for (int v = 0; v < 16; ++v)
                 if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) ds[v] = 0.f;
         }
-        cols_product(k_lds, ds, acc, lane);              // dq += scale ds k
+        cols_product(read_cols(k_lds, lane), ds, acc);   // dq += scale ds k
         lds_reads_done();
         if (more) issue_block(kb, p.skn, nx, k_addr, lane);
         w = nx;
     }
-    write_sum(p, k, lds, tid, acc, p.dq);
+    floatx16 sum[2];
+    acc.total(sum);
+    return write_sum(p, k, lds, tid, sum, p.dq);
 }
 
 // dk and dv of the block's rows: they are keys, the lists are walked as queries.
-template <bool kCut>
-__device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems],
-                                           float (*stat_lds)[64], int tid) {
+template <class Rows, class Sum, bool kCut>
+__device__ __forceinline__ bool dkdv_block(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems],
+                                           float (*stat_lds)[64], bf16x8 (*low_lds)[kLowParts], int tid) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
     const float* const qb = static_cast<const float*>(p.q) + (int64_t)k.b * p.sqb + (int64_t)k.h * p.sqh;
     const float* const gb = static_cast<const float*>(p.dout) + ((int64_t)k.b * p.N * p.H + k.h) * kD;   // row n at n * H * D
@@ -170,13 +177,17 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
     const int64_t n = k.rows[min(j, k.nrows - 1)];
     BlockWalk<kCut> w;
     w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave, k.records + wave * kWalkRecords);
-    float4 kr[8], vr[8];
-    load_chunks(static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + n * p.skn + (int64_t)k.h * p.skh, g, kr);
-    load_chunks(static_cast<const float*>(p.v) + (int64_t)k.b * p.svb + n * p.svn + (int64_t)k.h * p.svh, g, vr);
+    Rows kr, vr;
+    if constexpr (std::is_same<Rows, LeanRows>::value) {
+        kr.low = low_lds[0];
+        vr.low = low_lds[1];
+    }
+    load_rows(static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + n * p.skn + (int64_t)k.h * p.skh, g, kr);
+    load_rows(static_cast<const float*>(p.v) + (int64_t)k.b * p.svb + n * p.svn + (int64_t)k.h * p.svh, g, vr);
 
-    floatx16 dk[2], dv[2];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) dk[0][v] = dk[1][v] = dv[0][v] = dv[1][v] = 0.f;
+    Sum dk, dv;
+    dk.clear();
+    dv.clear();
 
     auto issue_q = [&](const BlockWalk<kCut>& w) {             // 9 copies
         issue_block(qb, p.sqn, w, q_addr, lane);
@@ -188,6 +199,7 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
     }
     pin(kr);
     pin(vr);
+    __syncthreads();                                     // the low parts are there
     while (w.valid()) {
         BlockWalk<kCut> nx = w;
         nx.next();
@@ -197,10 +209,10 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
 
         copies_left<kF32Copies + 1>();                   // dout is there
         if (nvalid < kWalkBlock) zero_tail(g_lds, nvalid, lane);
-        const floatx16 dp = rows_product(g_lds, vr, lane);
+        const floatx16 dp = rows_product(read_rows(g_lds, vr, lane), vr, lane);
         copies_left<0>();                                // q and the row statistics are there
         if (nvalid < kWalkBlock) zero_tail(q_lds, nvalid, lane);
-        const floatx16 s = rows_product(q_lds, kr, lane);
+        const floatx16 s = rows_product(read_rows(q_lds, kr, lane), kr, lane);
         float pr[16], ds[16];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -219,17 +231,20 @@ __device__ __forceinline__ void dkdv_block(const BwdParams& p, const BwdBlock& k
             for (int v = 0; v < 16; ++v)
                 if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) pr[v] = ds[v] = 0.f;
         }
-        cols_product(g_lds, pr, dv, lane);               // dv += P dout
+        cols_product(read_cols(g_lds, lane), pr, dv);    // dv += P dout
         lds_reads_done();
         if (more) issue_block(gb, gpitch, nx, g_addr, lane);
-        cols_product(q_lds, ds, dk, lane);               // dk += scale ds q
+        cols_product(read_cols(q_lds, lane), ds, dk);    // dk += scale ds q
         lds_reads_done();
         if (more) issue_q(nx);
         w = nx;
     }
-    write_sum(p, k, lds, tid, dv, p.dv);
+    floatx16 sum[2];
+    dv.total(sum);
+    const bool odd = write_sum(p, k, lds, tid, sum, p.dv);
     __syncthreads();
-    write_sum(p, k, lds, tid, dk, p.dk);
+    dk.total(sum);
+    return odd | write_sum(p, k, lds, tid, sum, p.dk);
 }
 
 template <bool kCut>
@@ -238,6 +253,8 @@ void bwd_f32_kernel(const BwdParams p, int n_items, int row_blocks) {
     __shared__ __attribute__((aligned(1024))) float lds[kWalkWaves][2 * kF32BlockElems];
     __shared__ __attribute__((aligned(256))) float stat_lds[kWalkWaves][64];
     __shared__ KeySeg records[kWalkWaves][kWalkRecords];
+    __shared__ bf16x8 low_lds[2][kLowParts];
+    __shared__ int odd_lds[kWalkWaves];
 
     hold_args(p);
     int item_index, part;
@@ -266,13 +283,19 @@ void bwd_f32_kernel(const BwdParams p, int n_items, int row_blocks) {
         }
         return;
     }
-    if (part & 1) dq_block<kCut>(p, k, lds, tid);
-    else dkdv_block<kCut>(p, k, lds, stat_lds, tid);
+    // a result that the split products may not have got right: the same with fp32 products
+    const bool odd = part & 1 ? dq_block<SplitRows, ChainSum, kCut>(p, k, lds, tid) : dkdv_block<LeanRows, ChainSum, kCut>(p, k, lds, stat_lds, low_lds, tid);
+    const bool wave_odd = __ballot(odd) != 0ull;
+    if ((tid & 63) == 0) odd_lds[tid >> 6] = wave_odd;
+    __syncthreads();                         // everyone has read the partial sums as well
+    if (!(odd_lds[0] | odd_lds[1] | odd_lds[2] | odd_lds[3])) return;
+    if (part & 1) dq_block<PlainRows, PlainSum, kCut>(p, k, lds, tid);
+    else dkdv_block<PlainRows, PlainSum, kCut>(p, k, lds, stat_lds, low_lds, tid);
 }
 
 }  // namespace
 
-// fp32 operands: the per-row preparation, then both gradient kernels in one launch.  bf16 operands go to the
+// fp32 operands: the per-row preparation, then both gradients' workgroups in one launch.  bf16 operands go to the
 // matrix-core kernels of dfa_bwd_bf16.hip, whose dq kernel prepares the per-row values itself.
 hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, bool cut, int32_t B, bool bf16, hipStream_t st) {
     if (bf16) return launch_bwd_bf16(p, n_items, st);

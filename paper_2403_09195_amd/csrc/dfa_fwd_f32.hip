@@ -1,22 +1,19 @@
-// Fused dilated flash attention forward in fp32, on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: full fp32
-// products and sums).
+// Fused dilated flash attention forward in fp32.  The products run on the bf16 matrix cores, every operand as the sum of three bf16
+// numbers (see dfa_mfma_f32.h), sums in fp32.
 //
 // Same plan and the same single online-softmax state per query row across all member branches as the bf16 kernel.
 // A workgroup owns 32 query rows of a tile; its four waves walk the tile's key lists in blocks of 32 keys, wave w
 // taking blocks w, w + 4, ..., each with an online softmax of its own, and merge their four partial results through
-// LDS by their maxima and sums at the end.
+// LDS by their reference exponents and sums at the end.
 //
-// Bound: the fp32 matrix cores (64 FLOP per cycle and SIMD; 64 MFMAs of 64 cycles per 32 x 32 block of pairs beside
-// some 1000 cycles of vector work, which the second wave of the SIMD covers).  One query block per workgroup gives a
-// single 1024^2 image 1536 workgroups, enough to even out walks of 1024 to 2048 keys over 256 CUs; every operand read
-// from LDS feeds one MFMA of 64 cycles, so LDS bandwidth is no issue and sharing a staged block between waves would save
-// nothing but L2 reads.  A wave copies its own blocks global -> LDS, K and V into one buffer each: a buffer is
-// refilled as soon as its product is through and has the other product's 2048 cycles to land, so no barrier and no
-// second stage is needed.
+// Bound: the matrix cores and the vector unit together.  A 32 x 32 block of pairs takes 48 MFMAs of 32 cycles and some 400 vector
+// instructions, two thirds of them to split K, V and the weights (of which the subtractions take turns with the MFMAs); with fp32
+// MFMAs the block took 64 of 64 cycles.  One query block per workgroup gives a single 1024^2 image 1536 workgroups, enough to even out
+// walks of 1024 to 2048 keys over 256 CUs.  A wave copies its own blocks global -> LDS, K and V into one buffer each: a buffer is
+// refilled as soon as its block is in registers and has the rest of the beat to land, so no barrier and no second stage is needed.
 //
-// Measured, one 1024^2 image (12 heads x 4096 tokens, three branches): 160 us = 111 TFLOP/s of the distinct pairs, 70 % of
-// the matrix cores' fp32 rate (one lane per query row on the vector units: 1048 us); error against fp64 2.3e-7 of the
-// output's 2-norm (8.5e-7): a block's sums are added up on their own, so no chain of roundings is longer than 48.
+// Measured, one 1024^2 image (12 heads x 4096 tokens, three branches): 126 us = 141 TFLOP/s of the distinct pairs (160 us on the fp32
+// matrix cores, whose rate is 157 TFLOP/s); error against fp64 1.8e-7 of the output's 2-norm (2.3e-7), of lse 3.3e-8 (3.4e-8).
 #include "dfa_device.h"
 #include "dfa_mfma_f32.h"
 
@@ -24,11 +21,117 @@ namespace dfa {
 
 namespace {
 
+// Natural logarithm of 2^m l: the exponent of l goes to m, a = m + exponent with its rounding error e, so that what is left for
+// the hardware's logarithm is below 1 in magnitude; ln 2 to twice fp32's digits.
+__device__ __forceinline__ float log_sum(float m, float l) {
+    const float k = (float)__builtin_amdgcn_frexp_expf(l), b = __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(l));
+    const float a = m + k, kk = a - m, e = (m - (a - kk)) + (k - kk);
+    if (!(fabsf(a) <= 3.4028234e38f) || !(fabsf(b) <= 3.4028234e38f)) return m + b;      // no key, or nothing that a number holds
+    constexpr float kLn2Rest = 0.6931471805599453094 - (double)kLn2;
+    return fmaf(a, kLn2, fmaf(a, kLn2Rest, (e + b) * kLn2));
+}
+
+// How far, in powers of two, a block's weights may pass the reference exponent before it is moved up (walks with fp32 products: not at
+// all, so that values next to fp32's largest do not overflow for it).
+template <class Rows> constexpr float kHeadroom = Rows::kPlain ? 0.f : 8.f;
+
+// The walk of one wave over its share of the lists; its partial result (rows, maxima, sums) goes into its region of LDS.
+// Rows, Sum: how the products are taken.
+template <class Rows, class Sum, bool kCut>
+__device__ __forceinline__ void walk(const FwdParams& p, const Tile& tile, int b, int64_t qn, float* k_lds, KeySeg* records, int wave, int lane) {
+    const int j = lane & 31, g = lane >> 5, h = tile.h;
+    const float* const kp = static_cast<const float*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
+    const float* const vp = static_cast<const float*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
+    float* const v_lds = k_lds + kF32BlockElems;
+    const uint32_t k_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, k_lds));
+    const uint32_t v_addr = k_addr + kF32BlockBytes;
+
+    BlockWalk<kCut> w;
+    w.start(p.segs + tile.seg_begin, tile.nseg, wave, records);
+    Rows q;
+    load_rows(static_cast<const float*>(p.q) + (int64_t)b * p.sqb + qn * p.sqn + (int64_t)h * p.sqh, g, q);
+
+    Sum acc;
+    acc.clear();
+    const float c = p.scale * kLog2e;          // scores in base-2 units (scale > 0)
+    float m_ref = -INFINITY, l_run = 0.f;      // l_run: over the lane's own 16 keys of every block
+
+    if (w.valid()) {
+        issue_block(kp, p.skn, w, k_addr, lane);
+        issue_block(vp, p.svn, w, v_addr, lane);
+    }
+    pin(q);
+    while (w.valid()) {
+        BlockWalk<kCut> nx = w;
+        nx.next();
+        const bool more = nx.valid();
+        const int nvalid = w.rows();
+        const float mult = rintf(__builtin_amdgcn_exp2f(w.seg.log2_mult));         // a key that counts m times has weight m exp2(t)
+
+        copies_left<kF32Copies>();                      // K is there, V may be on its way
+        const BlockRows kr = read_rows(k_lds, q, lane);
+        lds_reads_done();
+        if (more) issue_block(kp, p.skn, nx, k_addr, lane);
+        floatx16 s = rows_product(kr, q, lane);
+
+        if (nvalid < kWalkBlock) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) s[v] = -INFINITY;
+        }
+        // (rounded to fp32 before the reference is taken off: the largest score then has weight 1 exactly)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] *= c;
+        float t_max = s[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) t_max = fmaxf(t_max, s[v]);
+        t_max = wave_half_max(t_max);
+        // The reference exponent moves only where weights would pass 2^kHeadroom: fp32 holds them as exactly as those below 1.
+        if (__ballot(!(t_max <= m_ref + kHeadroom<Rows>)) != 0ull) {
+            const float m_new = fmaxf(m_ref, t_max);
+            const float alpha = m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref - m_new);
+            m_ref = m_new;
+            l_run *= alpha;
+            acc.scale(alpha);
+        }
+        const float ref = m_ref == -INFINITY ? 0.f : m_ref;        // nothing but masked or infinitely low scores so far
+        float pr[16], l0 = 0.f, l1 = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) pr[v] = __builtin_amdgcn_exp2f(s[v] - ref);
+        if (mult != 1.f) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) pr[v] *= mult;
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) (v & 1 ? l1 : l0) += pr[v];
+        l_run += l0 + l1;
+
+        if (more) copies_left<kF32Copies>();            // V is there, the next K may be on its way
+        else copies_left<0>();
+        if (nvalid < kWalkBlock) zero_tail(v_lds, nvalid, lane);
+        const BlockCols vc = read_cols(v_lds, lane);
+        lds_reads_done();
+        if (more) issue_block(vp, p.svn, nx, v_addr, lane);
+        cols_product(vc, pr, acc);
+        w = nx;
+    }
+
+    l_run = wave_half_sum(l_run);
+    floatx16 sum[2];
+    acc.total(sum);
+    result_to_lds(sum, k_lds, lane);
+    if (g == 0) {
+        k_lds[kWalkBlock * kRedPitch + j] = m_ref;
+        k_lds[kWalkBlock * kRedPitch + kWalkBlock + j] = l_run;
+    }
+}
+
 template <bool kCut>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
     __shared__ __attribute__((aligned(1024))) float lds[kWalkWaves][2 * kF32BlockElems];     // per wave: K block, V block
     __shared__ KeySeg records[kWalkWaves][kWalkRecords];
+    __shared__ int odd_lds[kWalkWaves];
 
     hold_args(p);
 
@@ -39,7 +142,7 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
     const Tile tile = item.t;
     if (item.tile < 0 || sub * kWalkBlock >= tile.nrows) return;
     const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31;
     const int h = tile.h, b = item.b;
     const int32_t* const rows = p.rows + tile.row_begin + sub * kWalkBlock;
     const int nrows = min(kWalkBlock, tile.nrows - sub * kWalkBlock);
@@ -59,110 +162,49 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
         return;
     }
 
-    const float* const kp = static_cast<const float*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
-    const float* const vp = static_cast<const float*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
-    float* const k_lds = lds[wave];
-    float* const v_lds = k_lds + kF32BlockElems;
-    const uint32_t k_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, k_lds));
-    const uint32_t v_addr = k_addr + kF32BlockBytes;
-
     const int64_t qn = rows[min(j, nrows - 1)];
-    BlockWalk<kCut> w;
-    w.start(p.segs + tile.seg_begin, tile.nseg, wave, records[wave]);
-    float4 q[8];
-    load_chunks(static_cast<const float*>(p.q) + (int64_t)b * p.sqb + qn * p.sqn + (int64_t)h * p.sqh, g, q);
-
-    floatx16 acc[2];
+    // merge of the four waves: a wave without a block has m = -inf, l = 0 and an accumulator of zeros.  Returns whether a
+    // result of this thread's is suspect.
+    auto merge = [&]() {
+        __syncthreads();
+        bool odd = false;
+        if (orow < nrows) {
+            float m = -INFINITY;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;      // l_run: over the lane's own 16 keys of every block
-
-    if (w.valid()) {
-        issue_block(kp, p.skn, w, k_addr, lane);
-        issue_block(vp, p.svn, w, v_addr, lane);
-    }
-    pin(q);
-    while (w.valid()) {
-        BlockWalk<kCut> nx = w;
-        nx.next();
-        const bool more = nx.valid();
-        const int nvalid = w.rows();
-        const float ln_mult = w.seg.log2_mult * kLn2;   // a key that counts m times: weight m exp(s) = exp(s + ln m)
-
-        copies_left<kF32Copies>();                      // K is there, V may be on its way
-        floatx16 s = rows_product(k_lds, q, lane);
-        lds_reads_done();
-        if (more) issue_block(kp, p.skn, nx, k_addr, lane);
-
-        float mx = -INFINITY;
+            for (int x = 0; x < kWalkWaves; ++x) m = fmaxf(m, lds[x][kWalkBlock * kRedPitch + orow]);
+            const float m_use = m == -INFINITY ? 0.f : m;
+            float l = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = fmaf(s[v], p.scale, ln_mult);
-        if (nvalid < kWalkBlock) {
+            for (int x = 0; x < kWalkWaves; ++x) {
+                const float* const r = lds[x];
+                const float f = __builtin_amdgcn_exp2f(r[kWalkBlock * kRedPitch + orow] - m_use);
+                l = fmaf(r[kWalkBlock * kRedPitch + kWalkBlock + orow], f, l);
+                const float4 lo = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od);
+                const float4 hi = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od + 4);
+                const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) s[v] = -INFINITY;
+                for (int e = 0; e < 8; ++e) o[e] = fmaf(a[e], f, o[e]);
+            }
+            const float inv = 1.0f / l, row_lse = log_sum(m, l);
+            odd = !(fabsf(row_lse) <= 3.4028234e38f);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                o[e] *= inv;
+                odd |= suspect(o[e]);
+            }
+            reinterpret_cast<float4*>(out)[0] = make_float4(o[0], o[1], o[2], o[3]);
+            reinterpret_cast<float4*>(out)[1] = make_float4(o[4], o[5], o[6], o[7]);
+            if (lse && od == 0) *lse = row_lse;
         }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[v]);
-        const float m_new = fmaxf(m_run, wave_half_max(mx));
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;       // nothing but masked scores so far
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_use) * kLog2e);
-        m_run = m_new;
-        float pr[16], l0 = 0.f, l1 = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            pr[v] = __builtin_amdgcn_exp2f((s[v] - m_use) * kLog2e);
-            (v & 1 ? l1 : l0) += pr[v];
-        }
-        l_run = fmaf(l_run, alpha, l0 + l1);
-
-        if (more) copies_left<kF32Copies>();            // V is there, the next K may be on its way
-        else copies_left<0>();
-        if (nvalid < kWalkBlock) zero_tail(v_lds, nvalid, lane);
-        // the block's sums on their own, added to the running ones once: shorter chains of roundings
-        floatx16 blk[2];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) blk[0][v] = blk[1][v] = 0.f;
-        cols_product(v_lds, pr, blk, lane);
-        lds_reads_done();
-        if (more) issue_block(vp, p.svn, nx, v_addr, lane);
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[db][v] = fmaf(acc[db][v], alpha, blk[db][v]);
-        w = nx;
-    }
-
-    // merge of the four waves: a wave without a block has m = -inf, l = 0 and an accumulator of zeros
-    l_run = wave_half_sum(l_run);
-    float* const red = lds[wave];
-    result_to_lds(acc, red, lane);
-    if (g == 0) {
-        red[kWalkBlock * kRedPitch + j] = m_run;
-        red[kWalkBlock * kRedPitch + kWalkBlock + j] = l_run;
-    }
-    __syncthreads();
-    if (orow >= nrows) return;
-    float m = -INFINITY;
-#pragma unroll
-    for (int x = 0; x < kWalkWaves; ++x) m = fmaxf(m, lds[x][kWalkBlock * kRedPitch + orow]);
-    const float m_use = m == -INFINITY ? 0.f : m;
-    float l = 0.f;
-    float4 o0 = make_float4(0.f, 0.f, 0.f, 0.f), o1 = o0;
-#pragma unroll
-    for (int x = 0; x < kWalkWaves; ++x) {
-        const float* const r = lds[x];
-        const float f = __builtin_amdgcn_exp2f((r[kWalkBlock * kRedPitch + orow] - m_use) * kLog2e);
-        l = fmaf(r[kWalkBlock * kRedPitch + kWalkBlock + orow], f, l);
-        const float4 a = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od);
-        const float4 c = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od + 4);
-        o0.x = fmaf(a.x, f, o0.x); o0.y = fmaf(a.y, f, o0.y); o0.z = fmaf(a.z, f, o0.z); o0.w = fmaf(a.w, f, o0.w);
-        o1.x = fmaf(c.x, f, o1.x); o1.y = fmaf(c.y, f, o1.y); o1.z = fmaf(c.z, f, o1.z); o1.w = fmaf(c.w, f, o1.w);
-    }
-    const float inv = 1.0f / l;
-    reinterpret_cast<float4*>(out)[0] = make_float4(o0.x * inv, o0.y * inv, o0.z * inv, o0.w * inv);
-    reinterpret_cast<float4*>(out)[1] = make_float4(o1.x * inv, o1.y * inv, o1.z * inv, o1.w * inv);
-    if (lse && od == 0) *lse = m + __builtin_amdgcn_logf(l) * kLn2;
+        return odd;
+    };
+    walk<SplitRows, SplitSum, kCut>(p, tile, b, qn, lds[wave], records[wave], wave, lane);
+    const bool wave_odd = __ballot(merge()) != 0ull;
+    if (lane == 0) odd_lds[wave] = wave_odd;
+    __syncthreads();                                      // everyone has read the partial results as well
+    if (!(odd_lds[0] | odd_lds[1] | odd_lds[2] | odd_lds[3])) return;
+    walk<PlainRows, PlainSum, kCut>(p, tile, b, qn, lds[wave], records[wave], wave, lane);
+    merge();
 }
 
 }  // namespace

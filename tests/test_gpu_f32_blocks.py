@@ -127,3 +127,58 @@ def test_f32_lists_whole_and_cut(B, window, cut):
     assert float((lse[0, 0] - ref_lse).abs().max()) <= 1e-5 * float(ref_lse.abs().max())
     for got, want in zip(grads, (dq, dk, dv)):
         assert float((got[0, :, 0] - want).abs().max()) <= 2e-5 * max(1.0, float(want.abs().max()))
+
+
+# The products of the fp32 path are sums of bf16 products of the operands' parts; operands that parts cannot hold take fp32
+# products.  Values so small that their low parts are not normal bf16 numbers (1e-37 is 2^-123), small and large ones that parts do
+# hold, and ones that round up to 2^128 in bf16: everything is linear in v (forward) and in dout (backward), so the bars are
+# those of ordinary values times the factor.
+@pytest.mark.parametrize("factor", [2.0 ** -121, 2.0 ** -100, 2.0 ** -60, 2.0 ** 90])
+def test_f32_range_of_values(B, oracle, factor):
+    N, branches = 200, [(50, 1), (100, 2), (200, 4)]
+    (q, k, v), ex = make_qkv(311, 2, N, 3, 64, "f32")
+    from paper_2403_09195_amd import synth
+    st, ge = synth.tensor(311, 7, (2, N, 3, 64), "f32")
+    out, lse = B.forward(q, k, v * factor, branches, 0.125)
+    o_ref, l_ref = oracle.forward(*ex, branches, 0.125)
+    assert np.abs(to_f64(out) / factor - o_ref).max() <= 1e-5
+    check_lse(to_f64(lse), l_ref, atol=1e-5, rtol=1e-5)
+    out, lse = B.forward(q, k, v, branches, 0.125)
+    grads = B.backward(q, k, v, out, lse, to_device(st) * factor, branches, 0.125)
+    for got, ref in zip(grads, oracle.backward(*ex, ge, branches, 0.125)):
+        assert np.abs(to_f64(got) / factor - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
+
+
+def test_f32_values_next_to_the_largest(B, oracle):
+    """A value at fp32's largest: bf16 rounds it up to infinity, its share of every weighted mean is finite."""
+    N, top = 96, float(np.finfo(np.float32).max)
+    (q, k, v), ex = make_qkv(312, 1, N, 2, 64, "f32")
+    v[:, 50, :, 9] = top
+    ex[2][:, 50, :, 9] = top
+    out, _ = B.forward(q, k, v, [(N, 1)], 0.125)
+    o_ref, _ = oracle.forward(*ex, [(N, 1)], 0.125)
+    scale = np.where(np.arange(64) == 9, top, 1.0)
+    assert np.abs(to_f64(out) / scale - o_ref / scale).max() <= 1e-5
+
+
+def test_f32_infinities_and_nan(B):
+    """An infinite key component makes the scores of its key infinite: NaN rows where the score is +inf, weight 0 where it is
+    -inf.  A NaN value row is NaN in its column only."""
+    import torch
+    N = 70
+    (q, k, v), _ = make_qkv(313, 1, N, 1, 64, "f32")
+    k2 = k.clone()
+    k2[:, 40, :, 3] = float("inf")
+    out, lse = B.forward(q, k2, v, [(N, 1)], 0.125)
+    up = q[0, :, 0, 3] > 0                          # rows whose score with key 40 is +inf
+    assert bool(torch.isnan(out[0, up]).all())
+    keep = [n for n in range(N) if n != 40]
+    o_ref, l_ref = B.forward(q[:, keep].contiguous(), k[:, keep].contiguous(), v[:, keep].contiguous(), [(N - 1, 1)], 0.125)
+    down = torch.tensor([n for n in keep if not bool(up[n])])
+    at = torch.tensor([keep.index(int(n)) for n in down])
+    assert float((out[0, down.cuda()] - o_ref[0, at.cuda()]).abs().max()) <= 1e-5
+    assert float((lse[0, 0, down.cuda()] - l_ref[0, 0, at.cuda()]).abs().max()) <= 1e-5
+    v2 = v.clone()
+    v2[:, 11, :, 60] = float("nan")
+    out, lse = B.forward(q, k, v2, [(N, 1)], 0.125)
+    assert bool(torch.isnan(out[..., 60]).all()) and bool(torch.isfinite(out[..., :60]).all()) and bool(torch.isfinite(lse).all())
