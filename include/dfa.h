@@ -133,13 +133,26 @@ size_t dfa_workspace_bytes(int32_t B, int32_t H, int32_t N, int32_t D, dfa_dtype
  * bf16.  The softmax denominator is the fp32 sum of those rounded probabilities, so out is
  * their exact weighted mean of V rows, and lse is within 2^-8 (3.9e-3) of the exact value
  * in the worst case (one key carrying the row), a few 1e-4 when many keys share the
- * weight.  dt = DFA_F32: fp32 throughout.
+ * weight.  dt = DFA_F32: fp32 throughout (products of exact three-part splits of the operands, within 2^-24 of each
+ * product, accumulated in fp32; operands that the parts cannot hold take plain fp32 products).
  */
 int dfa_forward(const void *q, const void *k, const void *v,
                 dfa_strides_t sq, dfa_strides_t sk, dfa_strides_t sv,
                 int32_t B, int32_t H, int32_t N, int32_t D, dfa_dtype_t dt, float scale,
                 const dfa_branch_t *branches, int32_t nb, const int32_t *head_offsets,
                 void *out, float *lse, void *workspace, size_t workspace_bytes, void *stream);
+
+/*
+ * dfa_forward with a workspace that is asked for only when the call turns out to need one: alloc(context, bytes) is called at
+ * most once, on the calling thread, before anything is enqueued, and returns 16-byte aligned device memory that stays valid for
+ * this call's launches, or NULL (the call then runs unsplit).  alloc == NULL: no workspace.  alloc must not throw.
+ */
+typedef void *(*dfa_alloc_t)(void *context, size_t bytes);
+int dfa_forward_alloc(const void *q, const void *k, const void *v,
+                      dfa_strides_t sq, dfa_strides_t sk, dfa_strides_t sv,
+                      int32_t B, int32_t H, int32_t N, int32_t D, dfa_dtype_t dt, float scale,
+                      const dfa_branch_t *branches, int32_t nb, const int32_t *head_offsets,
+                      void *out, float *lse, dfa_alloc_t alloc, void *context, void *stream);
 
 /*
  * dfa_forward for callers that cannot allocate device memory (code under HIP graph capture set-up rules,

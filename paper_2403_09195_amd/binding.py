@@ -1,7 +1,7 @@
 """ctypes binding of libdfa.so: same names as the C ABI in include/dfa.h.
 
-Argument marshalling only.  Tensors are torch tensors on the GPU (torch is used for
-device memory and streams); data pointers, element strides and the current HIP stream are
+Argument marshalling only (the ordinary forward call's in native code, csrc/dfa_torch.cpp).  Tensors are torch tensors on the
+GPU (torch is used for device memory and streams); data pointers, element strides and the current HIP stream are
 passed to the library, which runs every step of the path in its own kernels.  There is no
 fallback: a missing library raises.
 """
@@ -19,7 +19,7 @@ DFA_ERR_WORKSPACE = -8
 # include/dfa.h (the operator) and include/dfa_bench.h (measurement aids)
 EXPORTS = [
     "dfa_version", "dfa_error_string", "dfa_index_map", "dfa_index_map_device", "dfa_workspace_bytes", "dfa_forward",
-    "dfa_forward_static",
+    "dfa_forward_alloc", "dfa_forward_static",
     "dfa_forward_branch", "dfa_merge", "dfa_gather", "dfa_scatter", "dfa_plan_describe", "dfa_plan_describe_forward",
     "dfa_release_plans", "dfa_linear", "dfa_encoder_stack", "dfa_backward",
 ]
@@ -48,6 +48,7 @@ class DfaError(RuntimeError):
 
 
 _lib = None
+_native_forward = None       # the ordinary forward call in native code (csrc/dfa_torch.cpp), set by lib()
 _i32p = ctypes.POINTER(ctypes.c_int32)
 
 
@@ -107,6 +108,10 @@ def lib():
         for name in EXPORTS + BENCH_EXPORTS:
             if name not in ("dfa_error_string", "dfa_workspace_bytes", "dfa_dense_unfused_workspace_bytes"):
                 getattr(L, name).restype = ctypes.c_int
+        from . import _dfa_torch
+        _dfa_torch.bind(ctypes.cast(L.dfa_forward_alloc, ctypes.c_void_p).value)
+        global _native_forward
+        _native_forward = _dfa_torch.forward
         L.dfa_workspace_bytes.restype = ctypes.c_size_t
         L.dfa_dense_unfused_workspace_bytes.restype = ctypes.c_size_t
         _lib = L
@@ -174,8 +179,8 @@ def _stream():
 
 
 # What the C calls take besides pointers, scale and stream, marshalled once per combination of shape, strides, dtype,
-# branches and offsets.  Small calls wait for their host side: a forward call took 16.4 us on the host, with a table of offsets
-# 23.4, most of it for these ctypes objects (now 10.7 and 12.0).  Keyed by value throughout; no entry depends on a tensor's
+# branches and offsets.  Small calls wait for their host side: a forward call that made these ctypes objects every time took 16.4 us
+# on the host, with a table of offsets 23.4, this way 10.9 and 12.0 (and 5.7 in native code).  Keyed by value throughout; no entry depends on a tensor's
 # memory, and entries are never written after they are made.
 _prepared = {}
 _MAX_PREPARED = 256
@@ -263,6 +268,14 @@ def _fwd_args(q, k, v, branches, scale, head_offsets, out, lse, workspace):
 def forward(q, k, v, branches, scale, head_offsets=None, out=None, lse=None, want_lse=True, workspace="auto"):
     """Fused dilated attention.  q, k, v [B, N, H, D] (may be strided views) -> (out, lse).
     workspace: uint8 GPU tensor of workspace_bytes(...), None for no workspace, "auto" to allocate one."""
+    if out is None and lse is None and want_lse and isinstance(workspace, str) and workspace == "auto":
+        if _native_forward is None:
+            lib()
+        res = _native_forward(q, k, v, branches, scale, head_offsets)
+        if type(res) is tuple:
+            return res
+        if res is not None:
+            raise DfaError(res, "dfa_forward")
     import torch
     B, N, H, D = q.shape
     if out is None:

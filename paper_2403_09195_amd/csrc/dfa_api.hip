@@ -391,7 +391,8 @@ int launch_forward(const DevicePlan& dp, const void* q, const void* k, const voi
 int forward_impl(const void* q, const void* k, const void* v, dfa_strides_t sq, dfa_strides_t sk,
                  dfa_strides_t sv, int32_t B, int32_t H, int32_t N, int32_t D, dfa_dtype_t dt,
                  float scale, const dfa_branch_t* branches, int32_t nb, const int32_t* head_offsets,
-                 void* out, bool out_f32, float* lse, void* workspace, size_t workspace_bytes, void* stream) {
+                 void* out, bool out_f32, float* lse, void* workspace, size_t workspace_bytes, void* stream,
+                 dfa_alloc_t alloc = nullptr, void* context = nullptr) {
     int rc = check_forward_args(q, k, v, sq, sk, sv, B, H, N, D, dt, scale, branches, nb, head_offsets, out, lse);
     if (rc != DFA_OK) return rc;
     if (workspace && reinterpret_cast<uintptr_t>(workspace) % 16) return DFA_ERR_ALIGN;
@@ -400,7 +401,12 @@ int forward_impl(const void* q, const void* k, const void* v, dfa_strides_t sq, 
     rc = get_plan(dt == DFA_F32 ? PlanKind::kBlocks : out_f32 ? PlanKind::kPlain : PlanKind::kForward, B, H, N, branches, nb, head_offsets, &dp);
     if (rc != DFA_OK) return rc;
     float* split_ws = nullptr;
-    if (workspace && dt == DFA_BF16 && !out_f32 && dp->n_split_wgs > 0) {
+    const bool splits = dt == DFA_BF16 && !out_f32 && dp->n_split_wgs > 0;
+    if (splits && alloc) {
+        workspace = alloc(context, split_bytes(dp->n_split_wgs));
+        if (reinterpret_cast<uintptr_t>(workspace) % 16) return DFA_ERR_ALIGN;
+        split_ws = static_cast<float*>(workspace);
+    } else if (splits && workspace) {
         if (workspace_bytes < split_bytes(dp->n_split_wgs)) return DFA_ERR_WORKSPACE;
         split_ws = static_cast<float*>(workspace);
     }
@@ -460,6 +466,18 @@ int dfa_forward(const void* q, const void* k, const void* v, dfa_strides_t sq, d
     try {
         return forward_impl(q, k, v, sq, sk, sv, B, H, N, D, dt, scale, branches, nb, head_offsets,
                             out, dt == DFA_F32, lse, workspace, workspace_bytes, stream);
+    } catch (const std::bad_alloc&) {
+        return DFA_ERR_LAUNCH;
+    }
+}
+
+int dfa_forward_alloc(const void* q, const void* k, const void* v, dfa_strides_t sq, dfa_strides_t sk,
+                dfa_strides_t sv, int32_t B, int32_t H, int32_t N, int32_t D, dfa_dtype_t dt, float scale,
+                const dfa_branch_t* branches, int32_t nb, const int32_t* head_offsets,
+                void* out, float* lse, dfa_alloc_t alloc, void* context, void* stream) {
+    try {
+        return forward_impl(q, k, v, sq, sk, sv, B, H, N, D, dt, scale, branches, nb, head_offsets,
+                            out, dt == DFA_F32, lse, nullptr, 0, stream, alloc, context);
     } catch (const std::bad_alloc&) {
         return DFA_ERR_LAUNCH;
     }

@@ -1,0 +1,84 @@
+"""The forward call in native code (csrc/dfa_torch.cpp) against the one that Python marshals: the same results bit for bit from the
+same kernels, whichever of them a call's arguments lead to, and the same refusals."""
+import numpy as np
+import pytest
+
+from gpu_util import make_qkv
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2403_09195_amd import binding
+    binding.lib()
+    return binding
+
+
+def _python(B, monkeypatch, *args, **kw):
+    with monkeypatch.context() as m:
+        m.setattr(B, "_native_forward", lambda *a: None)
+        return B.forward(*args, **kw)
+
+
+# short, split (its workspace comes from the callback) and whole-tile launches, fp32; packed strides; a table of offsets
+@pytest.mark.parametrize("N,branches,table", [(200, [(50, 1), (200, 4)], False), (4096, [(1024, 1), (2048, 2), (4096, 4)], False),
+                                              (4096, [(4096, 1)], False), (300, [(100, 1), (150, 3)], True)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_same_results(B, monkeypatch, N, branches, table, dtype):
+    import torch
+    (q, k, v), _ = make_qkv(21, 1, N, 4, 64, dtype)
+    q, k, v = torch.stack((q, k, v), dim=2).unbind(2)
+    offsets = [[(h + x) % r for h in range(4)] for x, (_, r) in enumerate(branches)] if table else None
+    native = B._native_forward(q, k, v, branches, 0.125, offsets)
+    assert type(native) is tuple
+    for other in (_python(B, monkeypatch, q, k, v, branches, 0.125, head_offsets=offsets),
+                  B.forward(q, k, v, tuple(branches), 0.125, head_offsets=offsets)):
+        assert all(torch.equal(a, b) and a.dtype == b.dtype and a.shape == b.shape and a.is_contiguous() for a, b in zip(native, other))
+
+
+def test_calls_left_to_python(B):
+    import torch
+    (q, k, v), _ = make_qkv(22, 1, 64, 2, 64, "bf16")
+    ref = B.forward(q, k, v, [(64, 1)], 0.125)
+    for branches, scale, offsets in (([(np.int64(64), 1)], 0.125, None), ([(64, 1)], np.float32(0.125), None),
+                                     ([(64, 1)], 0.125, np.zeros((1, 2), dtype=np.int32))):
+        assert B._native_forward(q, k, v, branches, scale, offsets) is None
+        assert all(torch.equal(a, b) for a, b in zip(ref, B.forward(q, k, v, branches, scale, head_offsets=offsets)))
+    out, lse = B.forward(q, k, v, [(64, 1)], 0.125, want_lse=False)
+    assert lse is None and torch.equal(out, ref[0])
+
+
+def test_refusals(B):
+    import torch
+    (q, k, v), _ = make_qkv(23, 1, 64, 2, 64, "bf16")
+    for bad, code in (([(64, 0)], -2), ([(0, 1)], -2)):
+        with pytest.raises(B.DfaError) as e:
+            B.forward(q, k, v, bad, 0.125)
+        assert e.value.code == code
+    with pytest.raises(B.DfaError):
+        B.forward(q, k, v, [(64, 1)] * 9, 0.125)
+    with pytest.raises(B.DfaError):
+        B.forward(q, k, v, [(64, 1)], 0.0)
+    with pytest.raises(B.DfaError):
+        B.forward(q.half(), k.half(), v.half(), [(64, 1)], 0.125)
+    with pytest.raises(RuntimeError):
+        B.forward(q.cpu(), k, v, [(64, 1)], 0.125)
+    with pytest.raises(B.DfaError):
+        B.forward(q.transpose(2, 3), k, v, [(64, 1)], 0.125)
+
+
+def test_side_stream(B):
+    """The launch goes to the current stream."""
+    import torch
+    (q, k, v), _ = make_qkv(24, 1, 1024, 4, 64, "bf16")
+    ref = B.forward(q, k, v, [(256, 1)], 0.125)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        q2 = q.clone()
+        out, lse = B.forward(q2, k, v, [(256, 1)], 0.125)
+    side.synchronize()
+    assert torch.equal(out, ref[0]) and torch.equal(lse, ref[1])
