@@ -1,6 +1,7 @@
 #include "dfa_plan.h"
 
 #include <algorithm>
+#include <deque>
 #include <array>
 #include <cmath>
 #include <map>
@@ -164,7 +165,7 @@ int check_branches(int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, con
 
 void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb,
                 const int32_t* offsets, int order_mode, const ChipShape& chip, bool pack, HostPlan* plan,
-                int tile_blocks) {
+                int tile_blocks, bool pack_tails) {
     const int kNumXcd = std::max(chip.dies, 1);
     const int kSlotsPerDie = std::max(chip.fwd_slots_per_die(), 1);
     plan->tiles.clear();
@@ -246,6 +247,22 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
             // keys that several member branches keep are visited once, weighted by how many keep them
             if (!g.plain.empty()) tile_list({&g}, &g.list, &g.list_mult);
             groups.push_back(&g);
+        }
+
+        // The rows past a group's last full tile as a group of their own (same lists), which may share a tile like any other.
+        std::deque<RowGroup> tails;
+        if (pack_tails) {
+            std::vector<RowGroup*> cut;
+            for (RowGroup* g : groups) {
+                cut.push_back(g);
+                const size_t rest = g->rows.size() % tile_rows;
+                if (g->plain.empty() || g->rows.size() < tile_rows || rest == 0) continue;
+                tails.push_back(*g);
+                tails.back().rows.assign(g->rows.end() - rest, g->rows.end());
+                g->rows.resize(g->rows.size() - rest);
+                cut.push_back(&tails.back());
+            }
+            groups.swap(cut);
         }
 
         // Row groups that fill only part of a tile.  Where such groups attend to many of the same keys (rows of one
@@ -525,18 +542,18 @@ bool wants_row_tiles(const HostPlan& plan) {
 
 namespace {
 
-// What short_plan estimates the times by: workgroups with keys (one of rows that no branch keeps is over at once), and blocks
-// (cut lists) or steps (whole ones) of the longest list.
+// What short_plan estimates the times by: workgroups with keys (one of rows that no branch keeps is over at once), the 32-key blocks
+// of all their lists, and the 64-key steps of the longest one.
 struct LaunchSize {
-    int64_t live = 0;
-    int32_t blocks = 0, steps = 0;
+    int64_t live = 0, blocks = 0;
+    int32_t steps = 0;
 };
 LaunchSize launch_size(const HostPlan& plan) {
     LaunchSize size;
     for (const Item& i : plan.items)
         if (i.tile >= 0 && i.t.nseg > 0) {
             ++size.live;
-            size.blocks = std::max(size.blocks, i.t.nseg);
+            for (int32_t x = 0; x < i.t.nseg; ++x) size.blocks += (plan.segs[i.t.seg_begin + x].count + kWalkBlock - 1) / kWalkBlock;
             size.steps = std::max(size.steps, i.t.n_steps);
         }
     return size;
@@ -549,13 +566,31 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     const size_t most = (size_t)chip.fwd_slots() * 9 / 8;
     if (full.items.size() > most || N >= kMaxCutStride) return false;
     build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, plan, kShortRows / kBlockRows);
+    auto estimate = [&](const HostPlan& p) {
+        const LaunchSize size = launch_size(p);
+        const double blocks = (double)cut_size(p).longest;
+        return size.live <= chip.fwd_slots() / kFwdWorkgroupsPerCu ? 6.5 + 0.18 * blocks : size.live <= chip.fwd_slots() ? 8.5 + 0.25 * blocks : 12.5 + 0.26 * blocks;
+    };
+    // A little more than one round of workgroups, or than one to a CU: fewer of them where the rests of row groups share tiles (see
+    // kTailBlocks).
+    const int64_t slots = chip.fwd_slots(), one = slots / kFwdWorkgroupsPerCu;
+    const LaunchSize apart = launch_size(*plan);
+    if ((apart.live > one && apart.live <= one * 5 / 4) || (apart.live > slots && apart.live <= slots * 5 / 4)) {
+        HostPlan shared;
+        build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, &shared, kShortRows / kBlockRows, true);
+        const int64_t live = launch_size(shared).live, bound = apart.live > slots ? slots : one;
+        const int64_t longest = cut_size(shared).longest;
+        if (longest <= kShortBlocks && ((apart.blocks >= kTailBlocks * apart.live && 25 * live <= 24 * apart.live) || plan->items.size() > most ||
+                                        (live <= bound && longest <= cut_size(*plan).longest)))
+            *plan = std::move(shared);
+    }
     if (plan->items.size() > most || cut_size(*plan).longest > kShortBlocks) return false;
+    const double short_us = estimate(*plan);
     cut_blocks(plan);
     if (!full.split_wgs.empty()) return true;
     const LaunchSize size = launch_size(*plan);
     const bool one_to_a_cu = size.live <= chip.fwd_slots() / kFwdWorkgroupsPerCu;
     if (one_to_a_cu && std::any_of(full.segs.begin(), full.segs.end(), [](const KeySeg& s) { return s.count % 64 != 0; })) return true;
-    const double short_us = one_to_a_cu ? 6.5 + 0.18 * size.blocks : size.live <= chip.fwd_slots() ? 8.5 + 0.25 * size.blocks : 12.5 + 0.26 * size.blocks;
     const int32_t steps = launch_size(full).steps;
     return short_us < (full.packed_tiles ? 7.1 + 1.3 * steps : 4.6 + 1.2 * steps);
 }

@@ -105,9 +105,10 @@ inline int32_t head_offset(const int32_t* offsets, int32_t H, int32_t x, int32_t
 // pack: row groups of fewer than eight 32-row blocks may share a tile (only the bf16 forward kernel reads such
 // tiles: it takes its multiplicities per block from block_mult).
 // tile_blocks: 32-row blocks of a tile, kTileBlocks or less.
+// pack_tails: the rows past a group's last full tile may share a tile too (they then walk the union of two lists).
 void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb,
                 const int32_t* offsets, int order_mode, const ChipShape& chip, bool pack, HostPlan* plan,
-                int tile_blocks = kTileBlocks);
+                int tile_blocks = kTileBlocks, bool pack_tails = false);
 
 // Launches of the bf16 forward kernel with fewer workgroups than half the chip's slots are as long as their longest
 // tile's walk.  There the walks are cut: every tile gets one workgroup, then the workgroup slots left over go one by
@@ -148,7 +149,7 @@ bool wants_row_tiles(const HostPlan& plan);
 // Launches that do not fill the chip are as long as one workgroup's start, walk and end.  The short-launch forward kernel cuts
 // the walk by four inside the workgroup and gives it a quarter of the rows, but copies every key block for 64 rows where the
 // other kernels copy it for 256, and its copies run at some 20 bytes per clock and CU.  It is considered where its
-// workgroups start (nearly) all at once, up to an eighth more than there are slots, and no list has more than kShortBlocks
+// workgroups start (nearly) all at once, up to an eighth more than there are slots (see kTailBlocks for how they are counted), and no list has more than kShortBlocks
 // blocks.  There it takes the place of every split launch; against whole tiles both times, in us, go by the longest list: 4.6 +
 // 1.2 per 64-key step of a 256-row tile (7.1 + 1.3 where tiles pack several row groups), against 6.5 + 0.18 per 32-key block
 // with one workgroup to a CU, 8.5 + 0.25 with two, 12.5 + 0.26 where some CUs run a second round.  With one to a CU, lists that do
@@ -165,6 +166,15 @@ bool wants_row_tiles(const HostPlan& plan);
 // heads, four branches (192) 6.9 / 16.5.  Builds the plan of such a launch (64-row tiles, lists cut into blocks) when it is to
 // be taken; `full` is the plan of 256-row tiles, split where split_plan cuts it.
 constexpr int kShortBlocks = 64;
+// Plans of up to a quarter more workgroups than start at once, or than there are CUs, are tried with the rests of row groups sharing
+// tiles: fewer workgroups, some of which walk the union of two lists.  That is taken where the lists have kTailBlocks blocks or
+// more on average and the workgroups become 4 % fewer (then they are worth more than some longer walks), where there are too many workgroups for
+// the form otherwise, or where it brings them within the bound and no list gets longer.  Measured over 80 such shapes (in the mean 1.25
+// times faster, three slower by 3 to 5 % and one by 11), us, apart / sharing:
+// one image of 2312 tokens, 12 heads (528 / 480 workgroups) 22.6 / 18.5, of 2219 (560 / 520) 27.0 / 21.9, one of 2332, 6 heads
+// (264 / 240) 15.8 / 13.6, one of 2229, 12 heads, in whole tiles before, (528) 36.5 / 20.9; short lists that get longer: one of 1386, 16
+// heads, four branches (552 / 504, 12 blocks on average) 14.9 / 17.0, one of 654, 16 heads (288 / 256, 9 blocks) 9.9 / 11.2.
+constexpr int kTailBlocks = 19;
 bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                 int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan);
 

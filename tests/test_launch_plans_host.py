@@ -68,6 +68,18 @@ PROBLEMS = [
 ]
 
 
+# A little more than one round of 64-row workgroups: the rests of row groups share tiles where that saves the second round
+# (six 800^2 images of two heads: 528 -> 480 workgroups; three of 1500 tokens: 540 -> at most 512), or than one workgroup to a CU.
+@pytest.mark.parametrize("Bsz,H,N,branches,offs,most", [
+    (6, 2, 2500, [(625, 1), (1250, 2), (2500, 4)], None, 512),
+    (3, 6, 1500, [(400, 1), (750, 3), (1500, 5)], [[(3 * h + x + 1) % r for h in range(6)] for x, r in enumerate((1, 3, 5))], 512),
+    (3, 2, 2500, [(625, 1), (1250, 2), (2500, 4)], None, 256),
+])
+def test_rests_of_row_groups_share_tiles(B, Bsz, H, N, branches, offs, most):
+    p = _check_launched_plan(B, Bsz, H, N, branches, offs, B.DFA_BF16, False)
+    assert p["form"] == B.FORM_SHORT and p["packed"] and p["n_items"] <= most
+
+
 @pytest.mark.parametrize("Bsz,H,N,branches,offs", PROBLEMS)
 @pytest.mark.parametrize("dtype,backward", [("bf16", False), ("bf16", True), ("f32", False)])
 def test_launched_plan_covers_the_definition(B, Bsz, H, N, branches, offs, dtype, backward):
