@@ -11,8 +11,8 @@
 // are, not by more workgroups that have to meet in memory (partial rows written, read back and merged by a second launch).
 // A wave copies its own blocks and waits for nobody until the merge.  The list comes cut into blocks: one record each, all of a
 // wave's records read in one trip to memory at the start and kept in LDS.  Two workgroups to a CU (registers); a beat takes
-// 0.65 us then and as much with one, which is what the copies of its 8 KB take (20 bytes per clock and CU), and the
-// reason for short_plan's limit on the number of workgroups.  Eight waves that share the copies of a block for 128 rows
+// 0.65 us then and as much with one: a wave's own chain of wait, products and exponentials, not the rate of the copies (four
+// waves' 32 KB in that time are 23 bytes per clock and CU; copies from L2 alone reach 52 to 57).  Eight waves that share the copies of a block for 128 rows
 // need a barrier per beat and were slower (one image of 2500 tokens, 12 heads: 32.5 against 23.0 us).
 // Measured, us against 256-row tiles with split walks: three images of 1500 tokens, 6 heads 18.2 / 25.7; one of 2500, 12
 // heads 23.0 / 27.2; one of 4096, 6 heads 19.6 / 26.4.

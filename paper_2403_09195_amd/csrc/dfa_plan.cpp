@@ -543,10 +543,10 @@ bool wants_row_tiles(const HostPlan& plan) {
 namespace {
 
 // What short_plan estimates the times by: workgroups with keys (one of rows that no branch keeps is over at once), the 32-key blocks
-// of all their lists, and the 64-key steps of the longest one.
+// and 64-key steps of all their lists, and the steps of the longest one.
 struct LaunchSize {
-    int64_t live = 0, blocks = 0;
-    int32_t steps = 0;
+    int64_t live = 0, blocks = 0, steps = 0;
+    int32_t longest = 0;
 };
 LaunchSize launch_size(const HostPlan& plan) {
     LaunchSize size;
@@ -554,7 +554,8 @@ LaunchSize launch_size(const HostPlan& plan) {
         if (i.tile >= 0 && i.t.nseg > 0) {
             ++size.live;
             for (int32_t x = 0; x < i.t.nseg; ++x) size.blocks += (plan.segs[i.t.seg_begin + x].count + kWalkBlock - 1) / kWalkBlock;
-            size.steps = std::max(size.steps, i.t.n_steps);
+            size.steps += i.t.n_steps;
+            size.longest = std::max(size.longest, i.t.n_steps);
         }
     return size;
 }
@@ -563,8 +564,9 @@ LaunchSize launch_size(const HostPlan& plan) {
 
 bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                 int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan) {
-    const size_t most = (size_t)chip.fwd_slots() * 9 / 8;
-    if (full.items.size() > most || N >= kMaxCutStride) return false;
+    const size_t near = (size_t)chip.fwd_slots() * 9 / 8, most = (size_t)chip.fwd_slots() * 9 / 4;
+    // 64 rows to a workgroup: more rows than this cannot fit
+    if ((uint64_t)B * H * N > (uint64_t)most * kShortRows || full.items.size() > most || N >= kMaxCutStride) return false;
     build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, plan, kShortRows / kBlockRows);
     auto estimate = [&](const HostPlan& p) {
         const LaunchSize size = launch_size(p);
@@ -575,24 +577,38 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     // kTailBlocks).
     const int64_t slots = chip.fwd_slots(), one = slots / kFwdWorkgroupsPerCu;
     const LaunchSize apart = launch_size(*plan);
-    if ((apart.live > one && apart.live <= one * 5 / 4) || (apart.live > slots && apart.live <= slots * 5 / 4)) {
+    if ((apart.live > one && apart.live <= one * 5 / 4) || apart.live > slots) {
         HostPlan shared;
         build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, &shared, kShortRows / kBlockRows, true);
         const int64_t live = launch_size(shared).live, bound = apart.live > slots ? slots : one;
         const int64_t longest = cut_size(shared).longest;
-        if (longest <= kShortBlocks && ((apart.blocks >= kTailBlocks * apart.live && 25 * live <= 24 * apart.live) || plan->items.size() > most ||
+        if (longest <= kShortBlocks && ((apart.blocks >= kTailBlocks * apart.live && 25 * live <= 24 * apart.live) ||
+                                        (plan->items.size() > near && shared.items.size() <= near) ||
                                         (live <= bound && longest <= cut_size(*plan).longest)))
             *plan = std::move(shared);
     }
     if (plan->items.size() > most || cut_size(*plan).longest > kShortBlocks) return false;
+    const LaunchSize whole = launch_size(full);
+    if (plan->items.size() > near) {
+        // two rounds and more: see kManyMargin
+        const bool split = !full.split_wgs.empty();
+        if (split ? plan->items.size() <= (size_t)chip.fwd_slots() * 11 / 8 : full.packed_tiles && whole.longest < kManySteps) return false;
+        const double per_slot = 512.0 / chip.fwd_slots();
+        const double short_us = 7.1 + per_slot * (0.0046 * plan->items.size() + 0.00078 * launch_size(*plan).blocks);
+        const double other_us = split               ? 16.2 + per_slot * 0.0034 * whole.steps + 0.13 * whole.longest
+                                : full.packed_tiles ? 3.6 + per_slot * (0.0174 * full.items.size() + 0.0011 * whole.steps) + 1.18 * whole.longest
+                                                    : 3.6 + per_slot * (0.0066 * full.items.size() + 0.00215 * whole.steps) + 0.925 * whole.longest;
+        if (short_us * kManyMargin >= other_us) return false;
+        cut_blocks(plan);
+        return true;
+    }
     const double short_us = estimate(*plan);
+    const LaunchSize size = launch_size(*plan);
     cut_blocks(plan);
     if (!full.split_wgs.empty()) return true;
-    const LaunchSize size = launch_size(*plan);
     const bool one_to_a_cu = size.live <= chip.fwd_slots() / kFwdWorkgroupsPerCu;
     if (one_to_a_cu && std::any_of(full.segs.begin(), full.segs.end(), [](const KeySeg& s) { return s.count % 64 != 0; })) return true;
-    const int32_t steps = launch_size(full).steps;
-    return short_us < (full.packed_tiles ? 7.1 + 1.3 * steps : 4.6 + 1.2 * steps);
+    return short_us < (full.packed_tiles ? 7.1 + 1.3 * whole.longest : 4.6 + 1.2 * whole.longest);
 }
 
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,

@@ -148,9 +148,8 @@ bool wants_row_tiles(const HostPlan& plan);
 
 // Launches that do not fill the chip are as long as one workgroup's start, walk and end.  The short-launch forward kernel cuts
 // the walk by four inside the workgroup and gives it a quarter of the rows, but copies every key block for 64 rows where the
-// other kernels copy it for 256, and its copies run at some 20 bytes per clock and CU.  It is considered where its
-// workgroups start (nearly) all at once, up to an eighth more than there are slots (see kTailBlocks for how they are counted), and no list has more than kShortBlocks
-// blocks.  There it takes the place of every split launch; against whole tiles both times, in us, go by the longest list: 4.6 +
+// other kernels copy it for 256.  It is considered where its workgroups start (nearly) all at once, up to an eighth more than there are
+// slots (see kTailBlocks for how they are counted, kManyMargin for launches past that), and no list has more than kShortBlocks blocks.  There it takes the place of every split launch; against whole tiles both times, in us, go by the longest list: 4.6 +
 // 1.2 per 64-key step of a 256-row tile (7.1 + 1.3 where tiles pack several row groups), against 6.5 + 0.18 per 32-key block
 // with one workgroup to a CU, 8.5 + 0.25 with two, 12.5 + 0.26 where some CUs run a second round.  With one to a CU, lists that do
 // not fill their last step stay with the short kernel whatever the times: it clears the rows past a list's end, where the
@@ -166,7 +165,7 @@ bool wants_row_tiles(const HostPlan& plan);
 // heads, four branches (192) 6.9 / 16.5.  Builds the plan of such a launch (64-row tiles, lists cut into blocks) when it is to
 // be taken; `full` is the plan of 256-row tiles, split where split_plan cuts it.
 constexpr int kShortBlocks = 64;
-// Plans of up to a quarter more workgroups than start at once, or than there are CUs, are tried with the rests of row groups sharing
+// Plans of more workgroups than start at once, or of up to a quarter more than there are CUs, are tried with the rests of row groups sharing
 // tiles: fewer workgroups, some of which walk the union of two lists.  That is taken where the lists have kTailBlocks blocks or
 // more on average and the workgroups become 4 % fewer (then they are worth more than some longer walks), where there are too many workgroups for
 // the form otherwise, or where it brings them within the bound and no list gets longer.  Measured over 80 such shapes (in the mean 1.25
@@ -175,6 +174,18 @@ constexpr int kShortBlocks = 64;
 // (264 / 240) 15.8 / 13.6, one of 2229, 12 heads, in whole tiles before, (528) 36.5 / 20.9; short lists that get longer: one of 1386, 16
 // heads, four branches (552 / 504, 12 blocks on average) 14.9 / 17.0, one of 654, 16 heads (288 / 256, 9 blocks) 9.9 / 11.2.
 constexpr int kTailBlocks = 19;
+// From nine eighths of the slots up to twice that, the form takes the place of split launches and whole tiles where its estimate times
+// kManyMargin is the shorter one.  The estimates, us, are linear in the plan, fitted to 270 shapes (3 to 16 heads, 200 to 8000 tokens, 1 to 16
+// images, one to four branches) with residuals of 9 to 14 %: short 7.1 + 0.0046 per workgroup + 0.00078 per 32-key block; split 16.2 + 0.0034 per
+// 64-key step + 0.13 per step of the longest list; whole tiles 3.6 + 0.0066 per tile + 0.00215 per step + 0.925 per step of the longest list, where
+// tiles pack several row groups 3.6 + 0.0174 + 0.0011 + 1.18.  Two kinds stay, where the gain is small and the estimates are not that
+// sharp: split launches up to eleven eighths of the slots, whose second round would be nearly empty (one image of 5504 tokens, 6 heads,
+// four branches, 624 workgroups 31.5 / 33.5), and packed tiles whose longest list is under kManySteps steps (16 of 505, 8 heads
+// 19.9 / 23.8).  Over 95 other shapes that the estimates send here 1.40 times as fast in the mean, 1.00 to 2.17; us, before / now: 2 images
+// of 2107 tokens, 8 heads 60.2 / 24.9, one of 2170, 16 heads, four branches 38.2 / 23.5, 6 of 310, 16 heads 29.2 / 18.2; left as they are:
+// 3 of 1441, 8 heads, windows of 288 10.9 / 16.7, one of 4096, 12 heads 32.2 / 38.4.
+constexpr int kManySteps = 10;
+constexpr double kManyMargin = 1.15;
 bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                 int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan);
 

@@ -127,3 +127,19 @@ def test_backward_launch_of_more_than_one_slice(B):
         for got, ref in zip(grads, B.backward(q[sl], k[sl], v[sl], out[sl], lse[sl], g[sl], branches, 0.125)):
             assert torch.equal(got[sl], ref), b
     assert all(bool(torch.isfinite(t[-1].float()).all()) for t in grads)
+
+
+# launches of more than a round of workgroups: in place of whole tiles (ragged, offsets) and of a split launch
+@pytest.mark.parametrize("Bsz,H,N,branches,offs", [
+    (3, 6, 2053, [(511, 1), (1029, 3), (2053, 5)], [[(3 * h + x + 1) % r for h in range(6)] for x, r in enumerate((1, 3, 5))]),
+    (1, 16, 2170, [(271, 1), (542, 2), (1085, 4), (2170, 8)], None),
+])
+def test_two_rounds_of_row_groups(B, oracle, Bsz, H, N, branches, offs):
+    plan = B.launch_describe(Bsz, H, N, branches, offs, arrays=True)
+    assert plan["form"] == B.FORM_SHORT and plan["n_items"] > 576
+    (q, k, v), ex = make_qkv(1700 + N, Bsz, N, H, 64, "bf16")
+    out, lse = B.forward(q, k, v, branches, 0.125, offs)
+    o_ref, l_ref = oracle.forward(*ex, branches, 0.125, offs)
+    mx, mean = error_stats(to_f64(out), o_ref)
+    assert mx <= 2e-2 and mean <= 2e-3, (mx, mean)
+    check_lse_bf16(to_f64(lse), oracle, ex, branches, 0.125, l_ref, offs)

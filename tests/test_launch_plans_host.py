@@ -80,6 +80,24 @@ def test_rests_of_row_groups_share_tiles(B, Bsz, H, N, branches, offs, most):
     assert p["form"] == B.FORM_SHORT and p["packed"] and p["n_items"] <= most
 
 
+# Launches of 577 to 1152 workgroups of 64 rows: the short form where its estimate is the shorter one, the form of before elsewhere
+# (one image: split; windows: whole tiles; lists of few steps: packed tiles; one workgroup more than fits).
+@pytest.mark.parametrize("Bsz,H,N,branches,offs,form", [
+    (2, 8, 2107, [(526, 1), (1053, 2), (2107, 4)], None, "SHORT"),
+    (3, 6, 2053, [(511, 1), (1029, 3), (2053, 5)], [[(3 * h + x + 1) % r for h in range(6)] for x, r in enumerate((1, 3, 5))], "SHORT"),
+    (1, 12, 4096, [(1024, 1), (2048, 2), (4096, 4)], None, "SPLIT"), (1, 20, 2048, [(512, 1), (1024, 2), (2048, 4)], None, "SPLIT"),
+    (1, 16, 2170, [(271, 1), (542, 2), (1085, 4), (2170, 8)], None, "SHORT"),
+    (3, 8, 1441, [(288, 1)], None, "TILES"),
+    (16, 8, 505, [(126, 1), (252, 2), (505, 4)], None, "TILES"),
+    (1153, 1, 64, [(64, 1)], None, "TILES"),
+])
+def test_launches_of_two_rounds_of_row_groups(B, Bsz, H, N, branches, offs, form):
+    p = B.launch_describe(Bsz, H, N, branches, offs)
+    if N == 2053: _check_launched_plan(B, Bsz, H, N, branches, offs, B.DFA_BF16, False)
+    assert p["form"] == getattr(B, "FORM_" + form)
+    assert form != "SHORT" or 576 < p["n_items"] <= 1152
+
+
 @pytest.mark.parametrize("Bsz,H,N,branches,offs", PROBLEMS)
 @pytest.mark.parametrize("dtype,backward", [("bf16", False), ("bf16", True), ("f32", False)])
 def test_launched_plan_covers_the_definition(B, Bsz, H, N, branches, offs, dtype, backward):
