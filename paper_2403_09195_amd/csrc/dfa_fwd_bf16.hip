@@ -250,16 +250,12 @@ void dfa_fwd_bf16_kernel(const FwdParams p) {
     // the third behind the wait for the first: 64 KB less per CU before the first beat (one 1024^2 image 33.4 -> 32.8 us).
     cursor_load(pf, seg_lds);
     KeyCursor cur = pf;
-    auto issue_first = [&](int s) {
-        if (s >= n_steps) return;
-        issue_stage(p, kp, vp, pf, copy_lane(), wave, k_lds_addr + s * kStageBytes, v_lds_addr + s * kStageBytes);
-        cursor_next(pf, seg_lds, tile.nseg);
-    };
-    issue_first(0);
-    if (!kSplit) {
-        issue_first(1);
-        issue_first(2);
-    }
+#pragma unroll
+    for (int s = 0; s <= (kSplit ? 0 : 2); ++s)
+        if (s < n_steps) {
+            issue_stage(p, kp, vp, pf, copy_lane(), wave, k_lds_addr + s * kStageBytes, v_lds_addr + s * kStageBytes);
+            cursor_next(pf, seg_lds, tile.nseg);
+        }
 
     // pin the Q fragments here: the compiler then waits for their loads (and, as the counter is
     // shared and loads complete in order, for the stages issued after them) before the main loop and
@@ -271,8 +267,12 @@ void dfa_fwd_bf16_kernel(const FwdParams p) {
         for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qf[qb][kk]));
     wait_vmcnt<0>();           // all stages so far
     if (kSplit) {
-        issue_first(1);
-        issue_first(2);
+#pragma unroll
+        for (int s = 1; s <= 2; ++s)
+            if (s < n_steps) {
+                issue_stage(p, kp, vp, pf, copy_lane(), wave, k_lds_addr + s * kStageBytes, v_lds_addr + s * kStageBytes);
+                cursor_next(pf, seg_lds, tile.nseg);
+            }
     }
     __syncthreads();           // stage 0 (unsplit: 0 to 2) complete in LDS; from the first refill on, two stages are in flight at every wait
 
