@@ -427,7 +427,7 @@ def main():
         g = g.view(torch.bfloat16) if cfg["dtype"] == "bf16" else g
         if args.zero_inputs:
             g.zero_()
-        steps = max(1, args.steps if cfg["dtype"] == "bf16" else min(args.steps, 20))   # fp32 takes a sixteenth of bf16's matrix rate
+        steps = max(1, args.steps if cfg["dtype"] == "bf16" else min(args.steps, 20))   # an fp32 product is six bf16 ones
         if cfg["dtype"] == "bf16" and args.settle_ms > 0:
             settle(torch, lambda: binding.backward(q, k, v, out, lse, g, branches, scale), args.settle_ms)
         for _ in range(max(1, min(args.warmup, steps))):
@@ -443,7 +443,7 @@ def main():
         pairs = executed_pairs
         executed = pairs * 14 * D          # products of 2*D flops per pair: 3 for dq, 4 for dk and dv together
         mfma = cfg["dtype"] == "bf16"
-        peak = MFMA_BF16_PEAK_TFLOPS if mfma else 157.3
+        peak = MFMA_BF16_PEAK_TFLOPS / (1 if mfma else 6)            # an fp32 product is six bf16 ones (dfa_mfma_f32.h)
         print(json.dumps({"metric": "dfa_backward ms per step (dq, dk, dv)", "value": ms, "unit": "ms", "steps": steps,
                           "higher_is_better": False, "config": {"workload": args.workload},
                           "dtype": "bf16" if mfma else "f32", "data": "zeros" if args.zero_inputs else "synthetic",

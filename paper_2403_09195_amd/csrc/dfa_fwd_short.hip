@@ -15,7 +15,7 @@
 // waves' 32 KB in that time are 23 bytes per clock and CU; copies from L2 alone reach 52 to 57).  Eight waves that share the copies of a block for 128 rows
 // need a barrier per beat and were slower (one image of 2500 tokens, 12 heads: 32.5 against 23.0 us).
 // Measured, us against 256-row tiles with split walks: three images of 1500 tokens, 6 heads 18.2 / 25.7; one of 2500, 12
-// heads 23.0 / 27.2; one of 4096, 6 heads 19.6 / 26.4.
+// heads 23.0 / 27.2 (18.9 now that the rests of its row groups share tiles); one of 4096, 6 heads 19.6 / 26.4.
 #include "dfa_blocks.h"
 #include "dfa_fwd_beat.h"
 
