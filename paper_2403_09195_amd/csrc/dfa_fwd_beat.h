@@ -127,9 +127,9 @@ __device__ __forceinline__ void scores_block(const uint16_t* kblk, const FragLan
 }
 
 
-// Second product of one 32-key block on its own (pipeline epilogue).
+// Second product of one 32-key block on its own (pipeline epilogue), for the 32-row blocks that take part.
 __device__ __forceinline__ void accumulate_block(const uint16_t* vblk, const FragLane& fl, const u32x4 (&pb)[2][2],
-                                                 floatx16 (&oacc)[2][2]) {
+                                                 floatx16 (&oacc)[2][2], bool first = true, bool second = true) {
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -137,7 +137,8 @@ __device__ __forceinline__ void accumulate_block(const uint16_t* vblk, const Fra
             const bf16x8 vf = read_v_frag(vblk + fl.v + 16 * st * kRowElems + 32 * db);
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb)
-                oacc[db][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pb[qb][st]), oacc[db][qb], 0, 0, 0);
+                if (qb == 0 ? first : second)
+                    oacc[db][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pb[qb][st]), oacc[db][qb], 0, 0, 0);
         }
 }
 

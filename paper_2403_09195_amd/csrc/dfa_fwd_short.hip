@@ -53,11 +53,19 @@ __device__ __forceinline__ Block read_block(const u32x4* records, int t) {
     return b;
 }
 
+// The wave ends here if `any` is all zeros (the same in every lane).  In place: the compiler's own end of the kernel lies behind the code
+// that is skipped, and fetching it takes longer than the branch saves (one 256^2 image 6.7 us, 7.0 that way).
+__device__ __forceinline__ void end_unless(const u32x4& any) {
+    const uint32_t x = __builtin_amdgcn_readfirstlane(any[0] | any[1] | any[2] | any[3]);
+    asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 .Lgo_on%=\n\ts_endpgm\n.Lgo_on%=:" ::"s"(x) : "scc", "memory");
+}
+
 __global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dfa_fwd_short_kernel(const FwdParams p) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[kWalkWaves][kBuffers * kBlockElems];     // per wave: K, K, V, V
     __shared__ u32x4 records_all[kWalkWaves][64];
     __shared__ int32_t row_lds[kShortRows];
+    __shared__ __attribute__((aligned(16))) uint32_t skips_lds[kWalkWaves], odd_lds[kWalkWaves];
 
     hold_args(p);
     const Item item = load_item(p.items, blockIdx.x);
@@ -88,19 +96,20 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     u32x4* const records = records_all[wave];
     const u32x4 my_record = load_record(p, tile, wave, lane);
     if (tid < kShortRows) row_lds[tid] = rows[min(tid, tile.nrows - 1)];
-    // a filler slot of a packed tile holds ~n of a row n of its group: loaded like any row, never stored
-    int32_t q_row[2] = {rows[min(j, tile.nrows - 1)], rows[min(kWalkBlock + j, tile.nrows - 1)]};
-    q_row[0] ^= q_row[0] >> 31;
-    q_row[1] ^= q_row[1] >> 31;
     // Q fragments: B operand of S^T, lane (j, g) holds Q[row j][16*kk + 8*g .. +7]
     bf16x8 qf[2][4];
-    {
+    auto load_q = [&](int j, int g, int last) {
+        // a filler slot of a packed tile holds ~n of a row n of its group: loaded like any row, never stored
+        int32_t q_row[2] = {rows[min(j, last)], rows[min(kWalkBlock + j, last)]};
+        q_row[0] ^= q_row[0] >> 31;
+        q_row[1] ^= q_row[1] >> 31;
         const uint16_t* const qp = static_cast<const uint16_t*>(p.q) + (int64_t)b * p.sqb + (int64_t)h * p.sqh;
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) qf[qb][kk] = *reinterpret_cast<const bf16x8*>(qp + (int64_t)q_row[qb] * p.sqn + 16 * kk + 8 * g);
-    }
+    };
+    load_q(j, g, tile.nrows - 1);
     records[lane] = my_record;                 // read back by this wave alone
     // blocks are walked in pairs: a wave with an odd number of them, or none, ends on a block that is masked as a whole
     const int n_pairs = max((tile.nseg - wave + 2 * kWalkWaves - 1) / (2 * kWalkWaves), 1);
@@ -111,6 +120,10 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     auto issue_v = [&](const Block& b, int buf) { issue_block_rows<BlockOrder::kValues>(v_src, b.key0, b.stride(), b.count(), v_addr + buf * kBlockBytes, v_lane); };
     issue_k(blk[0], 0);
     issue_k(blk[1], 1);
+    // does either block skip a key of the share?
+    constexpr uint32_t kMinusInf = 0xff800000u;
+    const bool skips = __ballot(my_record[2] == kMinusInf || my_record[3] == kMinusInf) != 0ull;
+    if (lane == 0) skips_lds[wave] = skips;
 
     const FragLane fl = frag_lane(lane);
     const bf16x8 sel = row_sum_selector(lane);
@@ -139,7 +152,9 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     int count = kWalkBlock;                    // valid keys of block t - 1
     // rows past the end of a block become zeros in its V buffer, so that the weights 0 they get meet finite values
     auto zero_tail = [&](int buf, int valid) {
-        for (int x = lane; x < (kWalkBlock - valid) * 8; x += 64)
+        int ln = lane;                         // its address is worked out here, not kept in a register
+        asm volatile("" : "+v"(ln));
+        for (int x = ln; x < (kWalkBlock - valid) * 8; x += 64)
             *reinterpret_cast<u32x4*>(lds[wave] + buf * kBlockElems + valid * kRowElems + 8 * x) = u32x4{0u, 0u, 0u, 0u};
     };
     auto before = [&](int t, int odd, int left, floatx16 (&s)[2]) {
@@ -207,42 +222,99 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     // accumulator of zeros under the start exponent, whose weight is an exact 0.
     static_assert(sizeof(lds[0]) >= (kWalkBlock * kRedPitch + 2 * kWalkBlock) * 4, "a wave's results fit its buffers");
     float* const red = reinterpret_cast<float*>(lds[wave]);
-    const int orow = tid >> 3, od = (tid & 7) * 8;        // eight threads a row, 16 bytes each
+    // the lane's number worked out afresh: nothing that only this part needs is carried through the walk, which has no register left
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int orow = 8 * wave + (ln >> 3), od = (ln & 7) * 8;        // eight threads a row, 16 bytes each
+    for (int apart = 0;; apart = 1) {
+        u32x4 skips_any;
+        bool odd = false;                                     // a result of this thread's is not finite
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        if (qb * kWalkBlock >= tile.nrows) break;         // uniform for the workgroup
-        if (qb > 0) __syncthreads();                      // everyone has read the first block
-        const floatx16 mine[2] = {oacc[0][qb], oacc[1][qb]};
-        result_to_lds(mine, red, lane);
-        if (g == 0) {
-            red[kWalkBlock * kRedPitch + j] = bias_cur[qb] > -INFINITY ? m_ref[qb] + bias_cur[qb] : m_kept[qb];
-            red[kWalkBlock * kRedPitch + kWalkBlock + j] = l_run[qb];
+        for (int qb = 0; qb < 2; ++qb) {
+            if (qb * kWalkBlock >= tile.nrows) break;         // uniform for the workgroup
+            if (qb > 0) __syncthreads();                      // everyone has read the first block
+            const floatx16 mine[2] = {oacc[0][qb], oacc[1][qb]};
+            result_to_lds(mine, red, ln);
+            if (ln < kWalkBlock) {
+                red[kWalkBlock * kRedPitch + ln] = bias_cur[qb] > -INFINITY ? m_ref[qb] + bias_cur[qb] : m_kept[qb];
+                red[kWalkBlock * kRedPitch + kWalkBlock + ln] = l_run[qb];
+            }
+            __syncthreads();
+            if (qb == 0) skips_any = *reinterpret_cast<const u32x4*>(skips_lds);
+            const int slot = qb * kWalkBlock + orow;
+            const int32_t n_out = row_lds[slot];
+            if (slot >= tile.nrows || n_out < 0) continue;
+            float m = kRefStart;
+#pragma unroll
+            for (int x = 0; x < kWalkWaves; ++x) m = fmaxf(m, reinterpret_cast<const float*>(lds[x])[kWalkBlock * kRedPitch + orow]);
+            float l = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int x = 0; x < kWalkWaves; ++x) {
+                const float* const r = reinterpret_cast<const float*>(lds[x]);
+                const float f = __builtin_amdgcn_exp2f(r[kWalkBlock * kRedPitch + orow] - m);
+                l = fmaf(r[kWalkBlock * kRedPitch + kWalkBlock + orow], f, l);
+                const float4 lo = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od);
+                const float4 hi = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od + 4);
+                const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = fmaf(a[e], f, o[e]);
+            }
+            const float inv = 1.0f / l;
+            bf16x8 ob;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                ob[e] = (__bf16)(o[e] * inv);
+                odd |= !(fabsf(o[e]) <= 3.4028234e38f);
+            }
+            *reinterpret_cast<bf16x8*>(out + (int64_t)n_out * p.H * kD + od) = ob;
+            if (lse && od == 0) lse[n_out] = (m + __builtin_amdgcn_logf(l)) * kLn2;
         }
-        __syncthreads();
-        const int slot = qb * kWalkBlock + orow;
-        const int32_t n_out = row_lds[slot];
-        if (slot >= tile.nrows || n_out < 0) continue;
-        float m = kRefStart;
+
+        // A 32-row block that skips keys still scores them and multiplies their values by weights 0, which makes NaN of what is not
+        // finite.  A tile with such a result walks its list once more, one block of keys at a time and without the blocks that skip it.
+        // (No register and no time of the walk above: one 256^2 image 6.66 us with and without, one 800^2 image 17.4.)
+        if (apart) return;
+        end_unless(skips_any);
+        const bool wave_odd = __ballot(odd) != 0ull;
+        if (ln == 0) odd_lds[wave] = wave_odd;
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // everyone has read the partial results; the stores may be on their way
+        const u32x4 odd_any = *reinterpret_cast<const u32x4*>(odd_lds);
+        end_unless(odd_any);
+        int last = __builtin_amdgcn_readfirstlane(tile.nrows - 1);
+        asm volatile("" : "+s"(last));
+        load_q(ln & 31, ln >> 5, last);
 #pragma unroll
-        for (int x = 0; x < kWalkWaves; ++x) m = fmaxf(m, reinterpret_cast<const float*>(lds[x])[kWalkBlock * kRedPitch + orow]);
-        float l = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int qb = 0; qb < 2; ++qb) {
+            m_ref[qb] = kRefStart;
+            bias_cur[qb] = l_run[qb] = 0.f;
 #pragma unroll
-        for (int x = 0; x < kWalkWaves; ++x) {
-            const float* const r = reinterpret_cast<const float*>(lds[x]);
-            const float f = __builtin_amdgcn_exp2f(r[kWalkBlock * kRedPitch + orow] - m);
-            l = fmaf(r[kWalkBlock * kRedPitch + kWalkBlock + orow], f, l);
-            const float4 lo = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od);
-            const float4 hi = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od + 4);
-            const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = fmaf(a[e], f, o[e]);
+            for (int v = 0; v < 16; ++v) oacc[0][qb][v] = oacc[1][qb][v] = 0.f;
         }
-        const float inv = 1.0f / l;
-        bf16x8 ob;
+        for (int t = 0; wave + kWalkWaves * t < tile.nseg; ++t) {        // at most kShortBlocks / kWalkWaves: every block has its record
+            const Block cur = read_block(records, t);
+            issue_k(cur, 0);
+            issue_v(cur, 0);
+            copies_left<0>();
+            if (cur.count() < kWalkBlock) zero_tail(2, cur.count());
+            lds_reads_done();
+            scores_block(k0, fl, qf, s_a);
+            if (cur.count() < kWalkBlock) mask_block(s_a, ln >> 5, cur.count());
+            const bool on[2] = {cur.log2_mult[0] > -INFINITY, cur.log2_mult[1] > -INFINITY};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ob[e] = (__bf16)(o[e] * inv);
-        *reinterpret_cast<bf16x8*>(out + (int64_t)n_out * p.H * kD + od) = ob;
-        if (lse && od == 0) lse[n_out] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+            for (int qb = 0; qb < 2; ++qb) {
+                if (on[qb]) {
+                    m_ref[qb] += bias_cur[qb] - cur.log2_mult[qb];
+                    bias_cur[qb] = cur.log2_mult[qb];
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) s_a[qb][v] = -INFINITY;
+                }
+            }
+            exp_block(s_a, c, m_ref, p_a, psum);
+            settle<false>(s_a, p_a, c, m_ref, l_run, oacc, psum);
+            accumulate_block(v0, fl, p_a, oacc, on[0], on[1]);
+            lds_reads_done();
+        }
     }
 }
 

@@ -143,3 +143,51 @@ def test_two_rounds_of_row_groups(B, oracle, Bsz, H, N, branches, offs):
     mx, mean = error_stats(to_f64(out), o_ref)
     assert mx <= 2e-2 and mean <= 2e-3, (mx, mean)
     check_lse_bf16(to_f64(lse), oracle, ex, branches, 0.125, l_ref, offs)
+
+
+def _attends(N, H, branches, offs, t):
+    """[H, N]: does row n of head h hold token t as a key (the definition, branch by branch)?"""
+    n = np.arange(N)
+    res = np.zeros((H, N), dtype=bool)
+    for h in range(H):
+        for x, (w, r) in enumerate(branches):
+            o = offs[x][h] if offs else h % r
+            pos = n % w - o
+            kept = (pos >= 0) & (pos % r == 0)
+            if kept[t]:
+                res[h] |= kept & (n // w == t // w)
+    return res
+
+
+# Tiles whose 32-row blocks walk keys that only some of them attend to: the rests of row groups (an 800^2 image; ragged, offsets) and small
+# groups.  What is not finite at such a key reaches exactly the rows that hold it.
+@pytest.mark.parametrize("Bsz,H,N,branches,offs", [
+    (6, 2, 2500, [(625, 1), (1250, 2), (2500, 4)], None),
+    (3, 6, 1500, [(400, 1), (750, 3), (1500, 5)], [[(3 * h + x + 1) % r for h in range(6)] for x, r in enumerate((1, 3, 5))]),
+    (1, 4, 256, [(64, 1), (128, 2), (256, 4)], None),
+])
+def test_not_finite_stays_with_the_rows_that_hold_it(B, oracle, Bsz, H, N, branches, offs):
+    plan = B.launch_describe(Bsz, H, N, branches, offs, arrays=True)
+    assert plan["form"] == B.FORM_SHORT and plan["packed"]
+    skipped = [int(plan["segs"][s, 0]) for h, _, nrows, seg, nseg, _ in plan["tiles"] for s in range(seg, seg + nseg)
+               if any(plan["block_mult"][s, x] == 0 for x in range((nrows + 31) // 32))]
+    t = skipped[len(skipped) // 2]
+    (q, k, v), ex = make_qkv(1800 + N, Bsz, N, H, 64, "bf16")
+    o_ref, l_ref = oracle.forward(*ex, branches, 0.125, offs)
+    holds = _attends(N, H, branches, offs, t).T                       # [N, H]
+    assert holds.any() and not holds.all()
+    for value in (float("inf"), float("nan")):
+        bad = v.clone()
+        bad[:, t, :, 7] = value
+        out, lse = (to_f64(x) for x in B.forward(q, k, bad, branches, 0.125, offs))
+        check_lse_bf16(lse, oracle, ex, branches, 0.125, l_ref, offs)
+        d = np.abs(np.delete(out - o_ref, 7, axis=3))
+        assert d.max() <= 2e-2 and d.mean() <= 2e-3
+        assert np.abs((out - o_ref)[:, ~holds]).max() <= 2e-2 and not np.isfinite(out[:, holds][..., 7]).any()
+        bad = k.clone()
+        bad[:, t, :, 7] = value
+        out, lse = (to_f64(x) for x in B.forward(q, bad, v, branches, 0.125, offs))
+        assert np.abs((out - o_ref)[:, ~holds]).max() <= 2e-2
+        assert np.abs(lse - l_ref)[:, ~holds.T][np.isfinite(l_ref[:, ~holds.T])].max() <= 3.95e-3 + 4e-6 * np.abs(l_ref[np.isfinite(l_ref)]).max()
+        if value != value:
+            assert np.isnan(out[:, holds]).all() and np.isnan(lse[:, holds.T]).all()
