@@ -133,8 +133,9 @@ size_t dfa_workspace_bytes(int32_t B, int32_t H, int32_t N, int32_t D, dfa_dtype
  * bf16.  The softmax denominator is the fp32 sum of those rounded probabilities, so out is
  * their exact weighted mean of V rows, and lse is within 2^-8 (3.9e-3) of the exact value
  * in the worst case (one key carrying the row), a few 1e-4 when many keys share the
- * weight.  dt = DFA_F32: fp32 throughout (products of exact three-part splits of the operands, within 2^-24 of each
- * product, accumulated in fp32; operands that the parts cannot hold take plain fp32 products).
+ * weight.  dt = DFA_F32: fp32 throughout (products of exact three-part splits of the operands, within 2^-23 of each
+ * product, 2^-26.7 on average, accumulated in fp32; operands that the parts do not hold exactly, those with bits below 2^-133 and those
+ * that are not finite or round up to 2^128, take plain fp32 products; weights below 2^-109 of the row's largest are kept to 2^-133).
  */
 int dfa_forward(const void *q, const void *k, const void *v,
                 dfa_strides_t sq, dfa_strides_t sk, dfa_strides_t sv,

@@ -66,10 +66,22 @@ struct BwdBlock {
     KeySeg* records;             // LDS, kWalkRecords per wave
 };
 
-// Sum of the four waves' [32][64] results, written to rows of a contiguous [B, N, H, D] tensor.  Every wave has
-// finished with its own region of LDS.  Returns whether a value of this thread's is suspect.
+// dS of a pair, P times the difference of dP and delta.  As weights of split products they carry 2^60 in place of `scale`, so that their
+// parts hold what fp32 holds (small gradients, weights of exp2(-100)), and the sums are put right at the end; differences past
+// 2^67 overflow and go to fp32 products, which take `scale` at once.
+template <class Rows>
+__device__ __forceinline__ float score_grad(const BwdParams& p, float pr, float diff) {
+    return Rows::kPlain ? pr * diff * p.scale : pr * (diff * 0x1p60f);
+}
+template <class Rows>
+__device__ __forceinline__ float sum_factor(const BwdParams& p) { return Rows::kPlain ? 1.f : p.scale * 0x1p-60f; }
+constexpr float kLeastScale = 0x1p-60f;             // below it that factor would leave fp32's normal numbers: fp32 products
+
+// Sum of the four waves' [32][64] results times `factor`, written to rows of a contiguous [B, N, H, D] tensor.  Every wave has
+// finished with its own region of LDS.  Returns whether a value of this thread's is not finite.
 __device__ __forceinline__ bool write_sum(const BwdParams& p, const BwdBlock& k, float (*lds)[2 * kF32BlockElems], int tid,
-                                          const floatx16 (&acc)[2], void* grad) {
+                                          const floatx16 (&acc)[2], void* grad, float factor) {
+    asm volatile("" : "+v"(tid));                     // nothing of what follows is worked out before the walk and kept: its registers are full
     result_to_lds(acc, lds[tid >> 6], tid & 63);
     __syncthreads();
     const int row = tid >> 3, d = (tid & 7) * 8;
@@ -83,11 +95,13 @@ __device__ __forceinline__ bool write_sum(const BwdParams& p, const BwdBlock& k,
             a.x += u.x; a.y += u.y; a.z += u.z; a.w += u.w;
             c.x += v.x; c.y += v.y; c.z += v.z; c.w += v.w;
         }
+        a.x *= factor; a.y *= factor; a.z *= factor; a.w *= factor;
+        c.x *= factor; c.y *= factor; c.z *= factor; c.w *= factor;
         float4* const dst = reinterpret_cast<float4*>(static_cast<float*>(grad) +
                                                       (((int64_t)k.b * p.N + k.rows[row]) * p.H + k.h) * kD + d);
         dst[0] = a;
         dst[1] = c;
-        odd = suspect(a.x) | suspect(a.y) | suspect(a.z) | suspect(a.w) | suspect(c.x) | suspect(c.y) | suspect(c.z) | suspect(c.w);
+        odd = !(finite(a.x) & finite(a.y) & finite(a.z) & finite(a.w) & finite(c.x) & finite(c.y) & finite(c.z) & finite(c.w));
     }
     return odd;
 }
@@ -106,9 +120,11 @@ __device__ __forceinline__ bool dq_block(const BwdParams& p, const BwdBlock& k, 
     const int64_t n = k.rows[min(j, k.nrows - 1)];
     BlockWalk<kCut> w;
     w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave, k.records + wave * kWalkRecords);
+    LostAtOnce lost;
+    Unchecked checked;                                   // second products: their rows have gone through a first one
     Rows q, go;
-    load_rows(static_cast<const float*>(p.q) + (int64_t)k.b * p.sqb + n * p.sqn + (int64_t)k.h * p.sqh, g, q);
-    load_rows(static_cast<const float*>(p.dout) + (((int64_t)k.b * p.N + n) * p.H + k.h) * kD, g, go);
+    load_rows(static_cast<const float*>(p.q) + (int64_t)k.b * p.sqb + n * p.sqn + (int64_t)k.h * p.sqh, g, q, lost);
+    load_rows(static_cast<const float*>(p.dout) + (((int64_t)k.b * p.N + n) * p.H + k.h) * kD, g, go, lost);
     const int64_t at = ((int64_t)k.b * p.H + k.h) * p.N + n;
     float my_l = p.lse2[at], my_d = p.ndelta[at];
 
@@ -130,32 +146,32 @@ __device__ __forceinline__ bool dq_block(const BwdParams& p, const BwdBlock& k, 
         const float bias = w.seg.log2_mult;
 
         copies_left<kF32Copies>();                       // V is there
-        const floatx16 dp = rows_product(read_rows(v_lds, go, lane), go, lane);
+        const floatx16 dp = rows_product(read_rows(v_lds, go, lane), go, lane, lost);
         lds_reads_done();
         if (more) issue_block(vb, p.svn, nx, v_addr, lane);
         if (more) copies_left<kF32Copies>();             // K is there
         else copies_left<0>();
         if (nvalid < kWalkBlock) zero_tail(k_lds, nvalid, lane);
-        const floatx16 s = rows_product(read_rows(k_lds, q, lane), q, lane);
+        const floatx16 s = rows_product(read_rows(k_lds, q, lane), q, lane, lost);
         float ds[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float pr = __builtin_amdgcn_exp2f(fmaf(s[v] * p.scale, kLog2e, bias) - my_l);
-            ds[v] = pr * (dp[v] + my_d) * p.scale;
+            ds[v] = score_grad<Rows>(p, pr, dp[v] + my_d);
         }
         if (nvalid < kWalkBlock) {
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) ds[v] = 0.f;
         }
-        cols_product(read_cols(k_lds, lane), ds, acc);   // dq += scale ds k
+        cols_product(read_cols(k_lds, lane), ds, acc, checked);   // dq += ds k
         lds_reads_done();
         if (more) issue_block(kb, p.skn, nx, k_addr, lane);
         w = nx;
     }
     floatx16 sum[2];
     acc.total(sum);
-    return write_sum(p, k, lds, tid, sum, p.dq);
+    return write_sum(p, k, lds, tid, sum, p.dq, sum_factor<Rows>(p)) | lost.any() | !(p.scale >= kLeastScale);
 }
 
 // dk and dv of the block's rows: they are keys, the lists are walked as queries.
@@ -177,13 +193,15 @@ __device__ __forceinline__ bool dkdv_block(const BwdParams& p, const BwdBlock& k
     const int64_t n = k.rows[min(j, k.nrows - 1)];
     BlockWalk<kCut> w;
     w.start(p.segs + k.tile.seg_begin, k.tile.nseg, wave, k.records + wave * kWalkRecords);
+    LostAtOnce lost;
+    Unchecked checked;                                   // second products: their rows have gone through a first one
     Rows kr, vr;
     if constexpr (std::is_same<Rows, LeanRows>::value) {
         kr.low = low_lds[0];
         vr.low = low_lds[1];
     }
-    load_rows(static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + n * p.skn + (int64_t)k.h * p.skh, g, kr);
-    load_rows(static_cast<const float*>(p.v) + (int64_t)k.b * p.svb + n * p.svn + (int64_t)k.h * p.svh, g, vr);
+    load_rows(static_cast<const float*>(p.k) + (int64_t)k.b * p.skb + n * p.skn + (int64_t)k.h * p.skh, g, kr, lost);
+    load_rows(static_cast<const float*>(p.v) + (int64_t)k.b * p.svb + n * p.svn + (int64_t)k.h * p.svh, g, vr, lost);
 
     Sum dk, dv;
     dk.clear();
@@ -209,10 +227,10 @@ __device__ __forceinline__ bool dkdv_block(const BwdParams& p, const BwdBlock& k
 
         copies_left<kF32Copies + 1>();                   // dout is there
         if (nvalid < kWalkBlock) zero_tail(g_lds, nvalid, lane);
-        const floatx16 dp = rows_product(read_rows(g_lds, vr, lane), vr, lane);
+        const floatx16 dp = rows_product(read_rows(g_lds, vr, lane), vr, lane, lost);
         copies_left<0>();                                // q and the row statistics are there
         if (nvalid < kWalkBlock) zero_tail(q_lds, nvalid, lane);
-        const floatx16 s = rows_product(read_rows(q_lds, kr, lane), kr, lane);
+        const floatx16 s = rows_product(read_rows(q_lds, kr, lane), kr, lane, lost);
         float pr[16], ds[16];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -223,7 +241,7 @@ __device__ __forceinline__ bool dkdv_block(const BwdParams& p, const BwdBlock& k
             for (int e = 0; e < 4; ++e) {
                 const int v = 4 * t + e;
                 pr[v] = __builtin_amdgcn_exp2f(fmaf(s[v] * p.scale, kLog2e, bias) - lv[e]);
-                ds[v] = pr[v] * (dp[v] + dv4[e]) * p.scale;
+                ds[v] = score_grad<Rows>(p, pr[v], dp[v] + dv4[e]);
             }
         }
         if (nvalid < kWalkBlock) {
@@ -231,20 +249,20 @@ __device__ __forceinline__ bool dkdv_block(const BwdParams& p, const BwdBlock& k
             for (int v = 0; v < 16; ++v)
                 if (8 * (v >> 2) + 4 * g + (v & 3) >= nvalid) pr[v] = ds[v] = 0.f;
         }
-        cols_product(read_cols(g_lds, lane), pr, dv);    // dv += P dout
+        cols_product(read_cols(g_lds, lane), pr, dv, checked);    // dv += P dout
         lds_reads_done();
         if (more) issue_block(gb, gpitch, nx, g_addr, lane);
-        cols_product(read_cols(q_lds, lane), ds, dk);    // dk += scale ds q
+        cols_product(read_cols(q_lds, lane), ds, dk, checked);    // dk += ds q
         lds_reads_done();
         if (more) issue_q(nx);
         w = nx;
     }
     floatx16 sum[2];
     dv.total(sum);
-    const bool odd = write_sum(p, k, lds, tid, sum, p.dv);
+    const bool odd = write_sum(p, k, lds, tid, sum, p.dv, 1.f);
     __syncthreads();
     dk.total(sum);
-    return odd | write_sum(p, k, lds, tid, sum, p.dk);
+    return odd | write_sum(p, k, lds, tid, sum, p.dk, sum_factor<Rows>(p)) | lost.any() | !(p.scale >= kLeastScale);
 }
 
 template <bool kCut>
@@ -276,14 +294,14 @@ void bwd_f32_kernel(const BwdParams p, int n_items, int row_blocks) {
         floatx16 zero[2];
 #pragma unroll
         for (int v = 0; v < 16; ++v) zero[0][v] = zero[1][v] = 0.f;
-        write_sum(p, k, lds, tid, zero, part & 1 ? p.dq : p.dv);
+        write_sum(p, k, lds, tid, zero, part & 1 ? p.dq : p.dv, 1.f);
         if (!(part & 1)) {
             __syncthreads();
-            write_sum(p, k, lds, tid, zero, p.dk);
+            write_sum(p, k, lds, tid, zero, p.dk, 1.f);
         }
         return;
     }
-    // a result that the split products may not have got right: the same with fp32 products
+    // operands that parts do not hold, results that are not finite: the same with fp32 products
     const bool odd = part & 1 ? dq_block<SplitRows, ChainSum, kCut>(p, k, lds, tid) : dkdv_block<LeanRows, ChainSum, kCut>(p, k, lds, stat_lds, low_lds, tid);
     const bool wave_odd = __ballot(odd) != 0ull;
     if ((tid & 63) == 0) odd_lds[tid >> 6] = wave_odd;

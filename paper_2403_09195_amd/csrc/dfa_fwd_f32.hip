@@ -36,9 +36,9 @@ __device__ __forceinline__ float log_sum(float m, float l) {
 template <class Rows> constexpr float kHeadroom = Rows::kPlain ? 0.f : 8.f;
 
 // The walk of one wave over its share of the lists; its partial result (rows, maxima, sums) goes into its region of LDS.
-// Rows, Sum: how the products are taken.
+// Rows, Sum: how the products are taken.  Returns whether the parts of an operand of this lane's leave something out.
 template <class Rows, class Sum, bool kCut>
-__device__ __forceinline__ void walk(const FwdParams& p, const Tile& tile, int b, int64_t qn, float* k_lds, KeySeg* records, int wave, int lane) {
+__device__ __forceinline__ bool walk(const FwdParams& p, const Tile& tile, int b, int64_t qn, float* k_lds, KeySeg* records, int wave, int lane) {
     const int j = lane & 31, g = lane >> 5, h = tile.h;
     const float* const kp = static_cast<const float*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh;
     const float* const vp = static_cast<const float*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh;
@@ -48,8 +48,9 @@ __device__ __forceinline__ void walk(const FwdParams& p, const Tile& tile, int b
 
     BlockWalk<kCut> w;
     w.start(p.segs + tile.seg_begin, tile.nseg, wave, records);
+    Lost lost;
     Rows q;
-    load_rows(static_cast<const float*>(p.q) + (int64_t)b * p.sqb + qn * p.sqn + (int64_t)h * p.sqh, g, q);
+    load_rows(static_cast<const float*>(p.q) + (int64_t)b * p.sqb + qn * p.sqn + (int64_t)h * p.sqh, g, q, lost);
 
     Sum acc;
     acc.clear();
@@ -72,7 +73,7 @@ __device__ __forceinline__ void walk(const FwdParams& p, const Tile& tile, int b
         const BlockRows kr = read_rows(k_lds, q, lane);
         lds_reads_done();
         if (more) issue_block(kp, p.skn, nx, k_addr, lane);
-        floatx16 s = rows_product(kr, q, lane);
+        floatx16 s = rows_product(kr, q, lane, lost);
 
         if (nvalid < kWalkBlock) {
 #pragma unroll
@@ -112,7 +113,7 @@ __device__ __forceinline__ void walk(const FwdParams& p, const Tile& tile, int b
         const BlockCols vc = read_cols(v_lds, lane);
         lds_reads_done();
         if (more) issue_block(vp, p.svn, nx, v_addr, lane);
-        cols_product(vc, pr, acc);
+        cols_product(vc, pr, acc, lost);
         w = nx;
     }
 
@@ -124,6 +125,7 @@ __device__ __forceinline__ void walk(const FwdParams& p, const Tile& tile, int b
         k_lds[kWalkBlock * kRedPitch + j] = m_ref;
         k_lds[kWalkBlock * kRedPitch + kWalkBlock + j] = l_run;
     }
+    return lost.any();
 }
 
 template <bool kCut>
@@ -164,7 +166,7 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
 
     const int64_t qn = rows[min(j, nrows - 1)];
     // merge of the four waves: a wave without a block has m = -inf, l = 0 and an accumulator of zeros.  Returns whether a
-    // result of this thread's is suspect.
+    // result of this thread's is not finite.
     auto merge = [&]() {
         __syncthreads();
         bool odd = false;
@@ -186,11 +188,11 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
                 for (int e = 0; e < 8; ++e) o[e] = fmaf(a[e], f, o[e]);
             }
             const float inv = 1.0f / l, row_lse = log_sum(m, l);
-            odd = !(fabsf(row_lse) <= 3.4028234e38f);
+            odd = !finite(row_lse);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 o[e] *= inv;
-                odd |= suspect(o[e]);
+                odd |= !finite(o[e]);
             }
             reinterpret_cast<float4*>(out)[0] = make_float4(o[0], o[1], o[2], o[3]);
             reinterpret_cast<float4*>(out)[1] = make_float4(o[4], o[5], o[6], o[7]);
@@ -198,8 +200,8 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
         }
         return odd;
     };
-    walk<SplitRows, SplitSum, kCut>(p, tile, b, qn, lds[wave], records[wave], wave, lane);
-    const bool wave_odd = __ballot(merge()) != 0ull;
+    const bool lost = walk<SplitRows, SplitSum, kCut>(p, tile, b, qn, lds[wave], records[wave], wave, lane);
+    const bool wave_odd = __ballot(merge() | lost) != 0ull;
     if (lane == 0) odd_lds[wave] = wave_odd;
     __syncthreads();                                      // everyone has read the partial results as well
     if (!(odd_lds[0] | odd_lds[1] | odd_lds[2] | odd_lds[3])) return;

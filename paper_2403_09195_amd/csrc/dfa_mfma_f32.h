@@ -2,14 +2,16 @@
 // global->LDS copies of such a block and the two ways its rows are read back as MFMA operands.
 //
 // The products run on the bf16 matrix cores, whose rate is 16 times that of the fp32 ones: an fp32 number is the sum of three
-// bf16 numbers, x = h + m + l, exactly (8 bits of its 24 each, rounded to nearest, so that |m| <= 2^-8 |x| and |l| <= 2^-17 |x|), and of
-// the nine partial products of two numbers the six of h h, h m, m h, m m, h l, l h are taken; m l, l m and l l are below
-// 2^-24 of the product, 2^-26 on average.  Every partial product is exact in the fp32 accumulator's input, and a step of 16
-// contraction slots is one accumulation where the fp32 instruction takes eight, so the sums are rounded less often: the error of the
-// operator against fp64 is not larger than with v_mfma_f32_32x32x2_f32 (figures in the kernels).
-// What the split cannot hold (infinite and NaN operands, of which h - h makes NaN; numbers that round up to 2^128; parts below
-// bf16's normal numbers, from operands below 2^-109) shows in a result that is not finite or not zero and below 2^-80 in magnitude: the
-// kernels then walk the workgroup's lists again with fp32 products.
+// bf16 numbers, x = h + m + l, exactly (8 bits of its 24 each; h rounded to nearest, m and l cut off, so that |m| <= 2^-8 |x| and
+// |l| < 2^-16 |x|), and of the nine partial products of two numbers the six of h h, h m, m h, m m, h l, l h are taken; m l, l m and l l
+// together are below 2^-23 of the product, 2^-26.7 on average.  Every partial product is exact in the fp32 accumulator's input, and a
+// step of 16 contraction slots is one accumulation where the fp32 instruction takes eight, so the sums are rounded less often: the
+// error of the operator against fp64 is not larger than with v_mfma_f32_32x32x2_f32 (figures in the kernels).
+// Operands that three parts do not hold go to fp32 products: the kernels then walk the workgroup's lists again.  Bits below 2^-133
+// (bf16's least number; conversion, dot products and MFMAs of gfx950 keep numbers below 2^-126) are looked for in every operand as it is
+// split; infinite and NaN operands and numbers that round up to 2^128 make a NaN (h - h) that reaches the result.  The softmax
+// weights are not looked at: what theirs lose below 2^-133 is less than what the exponential does, which ends at 2^-126.
+// (Such a second walk makes a launch 2.2 times as long, backward 2.1.)
 //
 // Layouts (lane = 32*g + j).  v_mfma_f32_32x32x16_bf16: A is 32 x 16 with row j, slots 8*g .. +7 in lane (j, g), B 16 x 32 with the
 // same slots, column j; v_mfma_f32_32x32x2_f32: one slot g.  The result's register v of lane (j, g) is row kappa(v, g) = 8*(v/4) +
@@ -71,6 +73,24 @@ __device__ __forceinline__ uint32_t high_halves(float lo, float hi) {
     return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo), 0x07060302u);
 }
 
+// Whether a lane has split a number that its parts do not hold: what is left after m is cut off has then bits below 2^-133, in the
+// lower half of its word.  (One instruction for two numbers, not seen in any launch's time.)
+struct Lost {
+    uint32_t bits = 0u;
+    __device__ __forceinline__ void add(float a, float b) { bits |= __builtin_bit_cast(uint32_t, a) | __builtin_bit_cast(uint32_t, b); }
+    __device__ __forceinline__ bool any() const { return (bits & 0xffffu) != 0u; }
+};
+// The same where there is no register to put it off (the dk/dv walk spills then).
+struct LostAtOnce : Lost {
+    __device__ __forceinline__ void add(float a, float b) {
+        Lost::add(a, b);
+        asm volatile("" : "+v"(bits));
+    }
+};
+struct Unchecked {
+    __device__ __forceinline__ void add(float, float) {}
+};
+
 // 8 fp32 numbers as three bf16 operands.
 struct Split8 {
     bf16x8 h, m, l;
@@ -79,7 +99,8 @@ struct Split8 {
 // with the matrix cores, where other vector instructions run beside them, but are 4 instructions a pair where unpacking, masking
 // and subtracting are 8, and the vector unit is the busier one (forward and backward of two 512^2 images, 6 heads: 60.5 us, 64.1 with
 // the latter).  (The constants sit in scalar registers: as a literal operand the assembler's -1.0 is the pair (0, -1).)
-__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+template <class Check>
+__device__ __forceinline__ Split8 split8(const float (&x)[8], Check& lost) {
     uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;
     asm("" : "+s"(c0));
     asm("" : "+s"(c1));
@@ -94,7 +115,9 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
         const bf16x2 mp = __builtin_bit_cast(bf16x2, mw);
         m[e] = mw;
         h[e] = __builtin_bit_cast(uint32_t, hp);
-        l[e] = high_halves(__builtin_amdgcn_fdot2_f32_bf16(mp, n0, r0, false), __builtin_amdgcn_fdot2_f32_bf16(mp, n1, r1, false));
+        const float t0 = __builtin_amdgcn_fdot2_f32_bf16(mp, n0, r0, false), t1 = __builtin_amdgcn_fdot2_f32_bf16(mp, n1, r1, false);
+        l[e] = high_halves(t0, t1);
+        lost.add(t0, t1);
     }
     return Split8{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
 }
@@ -102,11 +125,7 @@ __device__ __forceinline__ floatx16 mfma_bf16(const bf16x8& a, const bf16x8& b, 
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// A result that the split products may not have got right (see above).
-__device__ __forceinline__ bool suspect(float x) {
-    const float a = fabsf(x);
-    return !(a <= 3.4028234e38f) || (a < 8.2718061e-25f && a != 0.f);
-}
+__device__ __forceinline__ bool finite(float x) { return fabsf(x) <= 3.4028234e38f; }
 
 // Tile rows held for the whole walk, as B operands of first products: row[16*kk + 8*g .. +7] split (LeanRows: the low parts in LDS,
 // shared by the workgroup's waves, whose tile rows are the same), or chunks 2*t + g as they are.
@@ -130,17 +149,19 @@ struct PlainRows {
     static constexpr bool kPlain = true;
     float4 c[8];
 };
-__device__ __forceinline__ void load_rows(const float* row, int g, SplitRows& x) {
+template <class Check>
+__device__ __forceinline__ void load_rows(const float* row, int g, SplitRows& x, Check& lost) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
         const float4 a = *reinterpret_cast<const float4*>(row + 16 * kk + 8 * g), b = *reinterpret_cast<const float4*>(row + 16 * kk + 8 * g + 4);
-        x.k[kk] = split8({a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w});
+        x.k[kk] = split8({a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}, lost);
     }
 }
 // Every wave writes the same low parts; they can be read after the next barrier.
-__device__ __forceinline__ void load_rows(const float* row, int g, LeanRows& x) {
+template <class Check>
+__device__ __forceinline__ void load_rows(const float* row, int g, LeanRows& x, Check& lost) {
     SplitRows r;
-    load_rows(row, g, r);
+    load_rows(row, g, r, lost);
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
         x.hi[kk] = r.k[kk].h;
@@ -148,7 +169,8 @@ __device__ __forceinline__ void load_rows(const float* row, int g, LeanRows& x) 
         x.low[64 * kk + (threadIdx.x & 63)] = r.k[kk].l;
     }
 }
-__device__ __forceinline__ void load_rows(const float* row, int g, PlainRows& x) {
+template <class Check>
+__device__ __forceinline__ void load_rows(const float* row, int g, PlainRows& x, Check&) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) x.c[t] = *reinterpret_cast<const float4*>(row + 8 * t + 4 * g);
 }
@@ -201,15 +223,15 @@ __device__ __forceinline__ BlockCols read_cols(const float* blk, int lane) {
 
 // First product of a block: its rows (A) against 32 tile rows (B).  The five small partial products have a sum of their
 // own, added to that of the large one at the end.
-template <class Rows>
-__device__ __forceinline__ floatx16 rows_product(const BlockRows& blk, const Rows& b, int lane) {
+template <class Rows, class Check>
+__device__ __forceinline__ floatx16 rows_product(const BlockRows& blk, const Rows& b, int lane, Check& lost) {
     floatx16 z, small, large;
 #pragma unroll
     for (int v = 0; v < 16; ++v) z[v] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
         const float4 x = blk.c[2 * kk], y = blk.c[2 * kk + 1];
-        const Split8 a = split8({x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w});
+        const Split8 a = split8({x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w}, lost);
         small = mfma_bf16(a.l, b.h(kk), kk == 0 ? z : small);
         large = mfma_bf16(a.h, b.h(kk), kk == 0 ? z : large);
         small = mfma_bf16(a.h, b.l(kk, lane), small);
@@ -284,22 +306,24 @@ __device__ __forceinline__ void add_products(const Split8& a, const Split8& b, C
     sum.acc[db] = mfma_bf16(a.h, b.m, sum.acc[db]);
     sum.acc[db] = mfma_bf16(a.h, b.h, sum.acc[db]);
 }
-template <class Sum>
-__device__ __forceinline__ void cols_product(const BlockCols& blk, const float (&w)[16], Sum& sum) {
+template <class Sum, class Check>
+__device__ __forceinline__ void cols_product(const BlockCols& blk, const float (&w)[16], Sum& sum, Check& lost) {
+    Unchecked weights;
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
-        const Split8 b = split8({w[8 * st], w[8 * st + 1], w[8 * st + 2], w[8 * st + 3], w[8 * st + 4], w[8 * st + 5], w[8 * st + 6], w[8 * st + 7]});
+        const Split8 b = split8({w[8 * st], w[8 * st + 1], w[8 * st + 2], w[8 * st + 3], w[8 * st + 4], w[8 * st + 5], w[8 * st + 6], w[8 * st + 7]}, weights);
 #pragma unroll
         for (int db = 0; db < 2; ++db) {
             const float* const x = blk.x[db] + 8 * st;
-            const Split8 a = split8({x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7]});
+            const Split8 a = split8({x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7]}, lost);
             add_products(a, b, sum, db);
         }
     }
 }
 
 // The same on the fp32 matrix cores.  Two chains in the first product: half the length of the sums.
-__device__ __forceinline__ floatx16 rows_product(const BlockRows& blk, const PlainRows& b, int) {
+template <class Check>
+__device__ __forceinline__ floatx16 rows_product(const BlockRows& blk, const PlainRows& b, int, Check&) {
     floatx16 z, s0, s1;
 #pragma unroll
     for (int v = 0; v < 16; ++v) z[v] = 0.f;
@@ -316,7 +340,8 @@ __device__ __forceinline__ floatx16 rows_product(const BlockRows& blk, const Pla
     for (int v = 0; v < 16; ++v) s0[v] += s1[v];
     return s0;
 }
-__device__ __forceinline__ void cols_product(const BlockCols& blk, const float (&w)[16], PlainSum& sum) {
+template <class Check>
+__device__ __forceinline__ void cols_product(const BlockCols& blk, const float (&w)[16], PlainSum& sum, Check&) {
 #pragma unroll
     for (int v = 0; v < 16; ++v)
 #pragma unroll

@@ -182,3 +182,50 @@ def test_f32_infinities_and_nan(B):
     v2[:, 11, :, 60] = float("nan")
     out, lse = B.forward(q, k, v2, [(N, 1)], 0.125)
     assert bool(torch.isnan(out[..., 60]).all()) and bool(torch.isfinite(out[..., :60]).all()) and bool(torch.isfinite(lse).all())
+
+
+# Small operands against large ones: the result is an ordinary number and says nothing of the low parts that 2^-120 has lost (scores; dP;
+# ds k and ds q).  Every gradient is its ordinary value times the powers of two of its operands.
+@pytest.mark.parametrize("e_q,e_v,e_g", [(-120, 0, 0), (120, 0, 0), (0, -121, 110), (0, 110, -121)])
+def test_f32_small_operands_against_large_ones(B, oracle, e_q, e_v, e_g):
+    N, branches = 200, [(50, 1), (100, 2), (200, 4)]
+    (q, k, v), ex = make_qkv(314, 1, N, 3, 64, "f32")
+    from paper_2403_09195_amd import synth
+    st, ge = synth.tensor(314, 7, (1, N, 3, 64), "f32")
+    q, k, v, g = q * 2.0 ** e_q, k * 2.0 ** -e_q, v * 2.0 ** e_v, to_device(st) * 2.0 ** e_g
+    out, lse = B.forward(q, k, v, branches, 0.125)
+    o_ref, l_ref = oracle.forward(*ex, branches, 0.125)
+    assert np.abs(to_f64(out) / 2.0 ** e_v - o_ref).max() <= 1e-5
+    check_lse(to_f64(lse), l_ref, atol=1e-5, rtol=1e-5)
+    grads = B.backward(q, k, v, out, lse, g, branches, 0.125)
+    for got, ref, e in zip(grads, oracle.backward(*ex, ge, branches, 0.125), (e_v + e_g - e_q, e_v + e_g + e_q, e_g)):
+        assert np.abs(to_f64(got) / 2.0 ** e - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
+
+
+def test_f32_one_small_operand(B, oracle):
+    """One walked row whose values parts do not hold, at weight 1 for its own segment: the other lists and tiles keep the split."""
+    N, w = 128, 64
+    (q, k, v), ex = make_qkv(315, 1, N, 2, 64, "f32")
+    v[:, :w] *= 2.0 ** -120
+    out, lse = B.forward(q, k, v, [(w, 1)], 0.125)
+    o_ref, l_ref = oracle.forward(*ex, [(w, 1)], 0.125)
+    got = to_f64(out)
+    got[:, :w] *= 2.0 ** 120
+    assert np.abs(got - o_ref).max() <= 1e-5
+    check_lse(to_f64(lse), l_ref, atol=1e-5, rtol=1e-5)
+
+
+def test_f32_small_scale(B, oracle):
+    """A scale whose product with 2^-60 is no normal number, against queries as much larger."""
+    N = 100
+    (q, k, v), ex = make_qkv(316, 1, N, 2, 64, "f32")
+    from paper_2403_09195_amd import synth
+    st, ge = synth.tensor(316, 7, (1, N, 2, 64), "f32")
+    for e in (-50, -80):
+        out, lse = B.forward(q * 2.0 ** -e, k, v, [(N, 1)], 0.125 * 2.0 ** e)
+        o_ref, l_ref = oracle.forward(*ex, [(N, 1)], 0.125)
+        assert np.abs(to_f64(out) - o_ref).max() <= 1e-5
+        check_lse(to_f64(lse), l_ref, atol=1e-5, rtol=1e-5)
+        grads = B.backward(q * 2.0 ** -e, k, v, out, lse, to_device(st), [(N, 1)], 0.125 * 2.0 ** e)
+        for got, ref, x in zip(grads, oracle.backward(*ex, ge, [(N, 1)], 0.125), (e, 0, 0)):
+            assert np.abs(to_f64(got) / 2.0 ** x - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
