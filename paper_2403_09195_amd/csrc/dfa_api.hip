@@ -37,6 +37,7 @@ struct DevicePlan {
     const float* block_mult = nullptr;   // plans of the bf16 forward only
     bool short_walk = false;            // bf16: the plan of short_plan or short_backward_plan, walked by the short-launch kernels
     bool cut = false;                   // fp32: the lists are cut into blocks
+    bool one_block = false;             // fp32: into one block each
     bool packed_tiles = false;          // some tile packs several row groups: the kernel variant that reads block_mult
     int32_t n_items = 0;
     int32_t max_tile_rows = 1;     // most rows of any tile
@@ -78,6 +79,7 @@ struct PackedPlan {
     int32_t max_tile_rows = 1;
     bool short_walk = false;
     bool cut = false;
+    bool one_block = false;
     bool packed_tiles = false;
 };
 
@@ -122,6 +124,7 @@ int choose_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     if (kind == PlanKind::kBlocks && cut_size(*hp).records <= kMaxCutRecords) {
         out->cut = true;
         cut_blocks(hp);
+        out->one_block = std::all_of(hp->tiles.begin(), hp->tiles.end(), [](const Tile& t) { return t.nseg <= 1; });
     }
     out->n_items = (int32_t)hp->items.size();
     out->packed_tiles = hp->packed_tiles;
@@ -183,6 +186,7 @@ void point_plan(DevicePlan* dp, void* base, const PackedPlan& pp, int device) {
     dp->packed_tiles = pp.packed_tiles;
     dp->short_walk = pp.short_walk;
     dp->cut = pp.cut;
+    dp->one_block = pp.one_block;
     dp->max_tile_rows = pp.max_tile_rows;
 }
 
@@ -383,7 +387,7 @@ int launch_forward(const DevicePlan& dp, const void* q, const void* k, const voi
     } else if (dt == DFA_BF16) {
         e = launch_fwd_bf16(p, dp.n_items, out_f32, dp.packed_tiles, st);
     } else {
-        e = launch_fwd_f32(p, dp.n_items, dp.max_tile_rows, dp.cut, st);         // fp32 inputs always give fp32 output
+        e = launch_fwd_f32(p, dp.n_items, dp.max_tile_rows, dp.cut, dp.one_block, st);         // fp32 inputs always give fp32 output
     }
     return e == hipSuccess ? DFA_OK : DFA_ERR_LAUNCH;
 }

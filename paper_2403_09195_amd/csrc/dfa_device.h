@@ -89,8 +89,8 @@ hipError_t launch_fwd_bf16_split(const FwdParams& p, int n_split_wgs, bool packe
 hipError_t launch_merge_split(const FwdParams& p, int n_items, hipStream_t st);
 // plans of 64-row tiles with their lists cut into blocks
 hipError_t launch_fwd_short(const FwdParams& p, int n_items, hipStream_t st);
-// max_tile_rows: most rows of any tile of the plan; cut: its lists are cut into blocks
-hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, bool cut, hipStream_t st);
+// max_tile_rows: most rows of any tile of the plan; cut: its lists are cut into blocks; one_block: into one each
+hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, bool cut, bool one_block, hipStream_t st);
 hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, bool cut, int32_t B, bool bf16, hipStream_t st);
 hipError_t launch_bwd_bf16(const BwdParams& p, int n_items, hipStream_t st);
 // plans of plain 64-row tiles with their lists cut into blocks

@@ -128,12 +128,14 @@ __device__ __forceinline__ bool walk(const FwdParams& p, const Tile& tile, int b
     return lost.any();
 }
 
-template <bool kCut>
+// kPlain: fp32 products from the start, for plans whose lists are one block each: a single block is not worth the code of both walks,
+// which a short launch has to fetch (windows of 32, four images of 256 tokens, 12 heads: 7.7 us, split 8.1; windows of 64 9.5 / 9.3).
+template <bool kCut, bool kPlain>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
     __shared__ __attribute__((aligned(1024))) float lds[kWalkWaves][2 * kF32BlockElems];     // per wave: K block, V block
     __shared__ KeySeg records[kWalkWaves][kWalkRecords];
-    __shared__ int odd_lds[kWalkWaves];
+    __shared__ __attribute__((aligned(16))) uint32_t odd_lds[kWalkWaves];
 
     hold_args(p);
 
@@ -200,25 +202,29 @@ void dfa_fwd_f32_kernel(const FwdParams p, int n_items, int row_blocks) {
         }
         return odd;
     };
-    const bool lost = walk<SplitRows, SplitSum, kCut>(p, tile, b, qn, lds[wave], records[wave], wave, lane);
-    const bool wave_odd = __ballot(merge() | lost) != 0ull;
-    if (lane == 0) odd_lds[wave] = wave_odd;
-    __syncthreads();                                      // everyone has read the partial results as well
-    if (!(odd_lds[0] | odd_lds[1] | odd_lds[2] | odd_lds[3])) return;
+    if constexpr (!kPlain) {
+        const bool lost = walk<SplitRows, SplitSum, kCut>(p, tile, b, qn, lds[wave], records[wave], wave, lane);
+        const bool wave_odd = __ballot(merge() | lost) != 0ull;
+        if (lane == 0) odd_lds[wave] = wave_odd;
+        __syncthreads();                                      // everyone has read the partial results as well
+        const u32x4 odd_any = *reinterpret_cast<const u32x4*>(odd_lds);
+        end_unless(odd_any[0] | odd_any[1] | odd_any[2] | odd_any[3]);
+    }
     walk<PlainRows, PlainSum, kCut>(p, tile, b, qn, lds[wave], records[wave], wave, lane);
     merge();
 }
 
 }  // namespace
 
-hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, bool cut, hipStream_t st) {
+hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, bool cut, bool one_block, hipStream_t st) {
     const int row_blocks = (max_tile_rows + kWalkBlock - 1) / kWalkBlock;
+    const auto kernel = one_block ? &dfa_fwd_f32_kernel<true, true> : cut ? &dfa_fwd_f32_kernel<true, false> : &dfa_fwd_f32_kernel<false, false>;
     for (int i0 = 0; i0 < n_items; i0 += kLaunchItems) {         // a grid holds fewer than 2^32 threads
         FwdParams q = p;
         q.items += i0;
         const int n = n_items - i0 < kLaunchItems ? n_items - i0 : kLaunchItems;
         const int groups = (n + kDies - 1) / kDies;
-        hipLaunchKernelGGL(cut ? dfa_fwd_f32_kernel<true> : dfa_fwd_f32_kernel<false>, dim3((unsigned)groups * kDies * row_blocks), dim3(256), 0, st, q, n, row_blocks);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)groups * kDies * row_blocks), dim3(256), 0, st, q, n, row_blocks);
     }
     return hipGetLastError();
 }

@@ -53,13 +53,6 @@ __device__ __forceinline__ Block read_block(const u32x4* records, int t) {
     return b;
 }
 
-// The wave ends here if `any` is all zeros (the same in every lane).  In place: the compiler's own end of the kernel lies behind the code
-// that is skipped, and fetching it takes longer than the branch saves (one 256^2 image 6.7 us, 7.0 that way).
-__device__ __forceinline__ void end_unless(const u32x4& any) {
-    const uint32_t x = __builtin_amdgcn_readfirstlane(any[0] | any[1] | any[2] | any[3]);
-    asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 .Lgo_on%=\n\ts_endpgm\n.Lgo_on%=:" ::"s"(x) : "scc", "memory");
-}
-
 __global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dfa_fwd_short_kernel(const FwdParams p) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[kWalkWaves][kBuffers * kBlockElems];     // per wave: K, K, V, V
@@ -274,12 +267,12 @@ void dfa_fwd_short_kernel(const FwdParams p) {
         // finite.  A tile with such a result walks its list once more, one block of keys at a time and without the blocks that skip it.
         // (No register and no time of the walk above: one 256^2 image 6.66 us with and without, one 800^2 image 17.4.)
         if (apart) return;
-        end_unless(skips_any);
+        end_unless(skips_any[0] | skips_any[1] | skips_any[2] | skips_any[3]);
         const bool wave_odd = __ballot(odd) != 0ull;
         if (ln == 0) odd_lds[wave] = wave_odd;
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // everyone has read the partial results; the stores may be on their way
         const u32x4 odd_any = *reinterpret_cast<const u32x4*>(odd_lds);
-        end_unless(odd_any);
+        end_unless(odd_any[0] | odd_any[1] | odd_any[2] | odd_any[3]);
         int last = __builtin_amdgcn_readfirstlane(tile.nrows - 1);
         asm volatile("" : "+s"(last));
         load_q(ln & 31, ln >> 5, last);

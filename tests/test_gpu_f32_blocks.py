@@ -229,3 +229,15 @@ def test_f32_small_scale(B, oracle):
         grads = B.backward(q * 2.0 ** -e, k, v, out, lse, to_device(st), [(N, 1)], 0.125 * 2.0 ** e)
         for got, ref, x in zip(grads, oracle.backward(*ex, ge, [(N, 1)], 0.125), (e, 0, 0)):
             assert np.abs(to_f64(got) / 2.0 ** x - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max())
+
+
+# lists of one block each: windows and dilated windows of up to 32 keys, a shorter last one, rows that no branch keeps; a window of 33 and
+# windows beside longer ones take the other form
+@pytest.mark.parametrize("N,branches", [(32, [(32, 1)]), (100, [(32, 1)]), (96, [(31, 1)]), (130, [(64, 2)]), (96, [(33, 1)]), (128, [(32, 1), (128, 2)])])
+def test_f32_lists_of_one_block(B, oracle, N, branches):
+    (q, k, v), ex = make_qkv(317 + N, 2, N, 3, 64, "f32")
+    out, lse = B.forward(q, k, v, branches, 0.125)
+    o_ref, l_ref = oracle.forward(*ex, branches, 0.125)
+    assert np.abs(to_f64(out) - o_ref).max() <= 1e-5
+    check_lse(to_f64(lse), l_ref, atol=1e-5, rtol=1e-5)
+    assert np.all(to_f64(out)[np.isneginf(l_ref).transpose(0, 2, 1)] == 0.0)
