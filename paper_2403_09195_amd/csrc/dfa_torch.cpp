@@ -5,6 +5,7 @@
 // Only the ordinary call goes this way: 4-d GPU tensors with contiguous last dimension, lists of Python integers.  Anything else
 // is handed back (None) to binding.forward, which converts it or names what is wrong with it.
 #include <Python.h>
+#include <pybind11/pybind11.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/ATen.h>
@@ -42,14 +43,14 @@ bool as_int32(PyObject* o, int32_t* out) {
 // What the workspace callback needs, and what it leaves: the tensor lives until the call has enqueued its launches.
 // (Allocated on the current stream: the allocator gives its memory to later work of this stream only.)
 struct Workspace {
-    const at::Tensor& like;
+    const at::TensorOptions options;
     at::Tensor tensor;
     std::exception_ptr error;
 };
 void* allocate(void* context, size_t bytes) {
     Workspace* w = static_cast<Workspace*>(context);
     try {
-        w->tensor = at::empty({(int64_t)bytes}, w->like.options().dtype(at::kByte));
+        w->tensor = at::empty({(int64_t)bytes}, w->options);
         return w->tensor.data_ptr();
     } catch (...) {
         w->error = std::current_exception();
@@ -99,11 +100,17 @@ PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
 
     at::Tensor out = at::empty({B, N, H, D}, q.options());
     at::Tensor lse = at::empty({B, H, N}, q.options().dtype(at::kFloat));
-    Workspace ws{q, at::Tensor(), nullptr};
-    const int rc = g_forward(q.data_ptr(), t[1]->data_ptr(), t[2]->data_ptr(), s[0], s[1], s[2], (int32_t)B, (int32_t)H, (int32_t)N,
-                             (int32_t)D, type == at::kFloat ? DFA_F32 : DFA_BF16, scale, branches, (int32_t)list.n,
-                             args[5] != Py_None ? table : nullptr, out.data_ptr(), lse.data_ptr<float>(), allocate, &ws,
-                             c10::hip::getCurrentHIPStream().stream());
+    Workspace ws{q.options().dtype(at::kByte), at::Tensor(), nullptr};
+    const void *const qp = q.data_ptr(), *const kp = t[1]->data_ptr(), *const vp = t[2]->data_ptr();
+    int rc;
+    {
+        // Other threads run meanwhile: a shape's first call builds and uploads its plan, a dropped plan waits for the device, a
+        // launch may wait for the queue.  (No Python object is touched; the workspace callback needs none either.)
+        pybind11::gil_scoped_release release;
+        rc = g_forward(qp, kp, vp, s[0], s[1], s[2], (int32_t)B, (int32_t)H, (int32_t)N, (int32_t)D, type == at::kFloat ? DFA_F32 : DFA_BF16,
+                       scale, branches, (int32_t)list.n, args[5] != Py_None ? table : nullptr, out.data_ptr(), lse.data_ptr<float>(), allocate,
+                       &ws, c10::hip::getCurrentHIPStream().stream());
+    }
     if (ws.error) std::rethrow_exception(ws.error);
     if (rc != DFA_OK) return PyLong_FromLong(rc);
     PyObject* const po = THPVariable_Wrap(std::move(out));

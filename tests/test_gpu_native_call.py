@@ -82,3 +82,35 @@ def test_side_stream(B):
         out, lse = B.forward(q2, k, v, [(256, 1)], 0.125)
     side.synchronize()
     assert torch.equal(out, ref[0]) and torch.equal(lse, ref[1])
+
+
+def test_other_threads_run_during_a_call(B):
+    """The first call of a shape builds its plan, about a second here: other threads are not held up by it."""
+    import threading
+    import time
+    import torch
+    q, k, v = torch.randn((3, 1, 65536, 4, 64), device="cuda").bfloat16().unbind(0)
+    branches = [(50, 1), (1000, 3), (65536, 5)]
+    torch.cuda.synchronize()
+    ticks, stop = [], threading.Event()
+
+    def tick():
+        while not stop.is_set():
+            ticks.append(time.monotonic())
+            time.sleep(0.001)
+
+    thread = threading.Thread(target=tick)
+    thread.start()
+    try:
+        while not ticks:
+            time.sleep(0.001)
+        B.release_plans()
+        t0 = time.monotonic()
+        assert type(B._native_forward(q, k, v, branches, 0.125, None)) is tuple
+        t1 = time.monotonic()
+    finally:
+        stop.set()
+        thread.join()
+    during = [t for t in ticks if t0 <= t <= t1]
+    assert t1 - t0 > 0.05, "the call was too short to tell"
+    assert len(during) > 10, (len(during), t1 - t0)
