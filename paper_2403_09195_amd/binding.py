@@ -178,6 +178,15 @@ def _stream():
     return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
+def _covers(q, k, v):
+    """Refuses k and v that are not of q's dtype or hold less than q's [B, N, H, D]: the kernels would read past their end."""
+    for t, name in ((k, "k"), (v, "v")):
+        if t.dtype != q.dtype:
+            raise DfaError(-4, f"{name} must have q's dtype")
+        if t.dim() != 4 or any(have < need for have, need in zip(t.shape, q.shape)):
+            raise DfaError(-2, f"{name} is smaller than q")
+
+
 # What the C calls take besides pointers, scale and stream, marshalled once per combination of shape, strides, dtype,
 # branches and offsets.  Small calls wait for their host side: a forward call that made these ctypes objects every time took 16.4 us
 # on the host, with a table of offsets 23.4, this way 10.9 and 12.0 (and 5.7 in native code).  Keyed by value throughout; no entry depends on a tensor's
@@ -190,10 +199,12 @@ def _prepare(q, k, v, branches, head_offsets):
     """(strides of q, k, v, B, H, N, D, dtype code, branch array, their number, offset array, the key)."""
     flat = _flat(head_offsets)
     pairs = [(int(w), int(r)) for (w, r) in branches]
-    key = (q.shape, q.stride(), k.stride(), v.stride(), q.dtype, tuple(pairs), None if flat is None else tuple(flat))
+    key = (q.shape, q.stride(), k.stride(), v.stride(), q.dtype, tuple(pairs), None if flat is None else tuple(flat),
+           k.shape, v.shape, k.dtype, v.dtype)
     hit = _prepared.get(key)
     if hit is None:
         B, N, H, D = q.shape
+        _covers(q, k, v)
         br, nb = _branches(pairs)
         offs = None if flat is None else (ctypes.c_int32 * len(flat))(*flat)
         hit = (_strides(q), _strides(k), _strides(v), B, H, N, D, _dtype_code(q), br, nb, offs, key)
@@ -325,6 +336,7 @@ def forward_branch(q, k, v, w, r, scale, head_offsets=None, out_b=None, lse_b=No
     import torch
     for t, nm in ((q, "q"), (k, "k"), (v, "v")):
         _gpu(t, nm)
+    _covers(q, k, v)
     B, N, H, D = q.shape
     if out_b is None:
         out_b = torch.empty((B, N, H, D), dtype=torch.float32, device=q.device)
@@ -458,6 +470,7 @@ def dense_unfused(q, k, v, scale, out=None, lse=None, workspace=None):
     B, N, H, D = q.shape
     if q.dtype != torch.bfloat16:
         raise DfaError(-4, "dense_unfused takes bf16 tensors")
+    _covers(q, k, v)
     if out is None:
         out = torch.empty((B, N, H, D), dtype=q.dtype, device=q.device)
     if lse is None:

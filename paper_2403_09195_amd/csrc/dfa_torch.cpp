@@ -2,7 +2,7 @@
 // current stream.  Small launches wait for their host side: one 256^2 image took 10.9 us a call in Python and ctypes (two
 // torch.empty 3.5 us, marshalling 2.3, the ctypes call's own conversions 1) around 2.4 us of launch and 6.6 us on the GPU.
 //
-// Only the ordinary call goes this way: 4-d GPU tensors with contiguous last dimension, lists of Python integers.  Anything else
+// Only the ordinary call goes this way: 4-d GPU tensors of one dtype with contiguous last dimension, lists of Python integers.  Anything else
 // is handed back (None) to binding.forward, which converts it or names what is wrong with it.
 #include <Python.h>
 #include <pybind11/pybind11.h>
@@ -73,6 +73,11 @@ PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const at::Tensor& q = *t[0];
     const at::ScalarType type = q.scalar_type();
     if (type != at::kBFloat16 && type != at::kFloat) Py_RETURN_NONE;
+    for (int i = 1; i < 3; ++i) {              // nor less than q, which the kernels would read past (binding.forward refuses it)
+        if (t[i]->scalar_type() != type) Py_RETURN_NONE;
+        for (int d = 0; d < 4; ++d)
+            if (t[i]->size(d) < q.size(d)) Py_RETURN_NONE;
+    }
     const int64_t B = q.size(0), N = q.size(1), H = q.size(2), D = q.size(3);
     if (B > INT32_MAX || N > INT32_MAX || H > INT32_MAX || D > INT32_MAX) Py_RETURN_NONE;
 

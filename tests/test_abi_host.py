@@ -407,3 +407,16 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0 and "one GPU" in (r.stderr + r.stdout)
+
+
+def test_binding_refuses_keys_and_values_the_kernels_would_read_past(B):
+    """k and v of another dtype than q, or with less of any dimension, never reach the library; more of one is read in part."""
+    import torch
+    q = torch.zeros((2, 64, 4, 64), dtype=torch.bfloat16)
+    for bad, code in ((q.float(), -4), (q[:1], -2), (q[:, :63], -2), (q[:, :, :3], -2), (q[..., :32], -2), (q[0], -2)):
+        for k, v in ((bad, q), (q, bad)):
+            with pytest.raises(B.DfaError) as e:
+                B._prepare(q, k, v, [(64, 1)], None)
+            assert e.value.code == code
+    more = torch.zeros((3, 80, 5, 64), dtype=torch.bfloat16)
+    assert B._prepare(q, more, more, [(64, 1)], None)[3:7] == (2, 4, 64, 64)

@@ -114,3 +114,21 @@ def test_other_threads_run_during_a_call(B):
     during = [t for t in ticks if t0 <= t <= t1]
     assert t1 - t0 > 0.05, "the call was too short to tell"
     assert len(during) > 10, (len(during), t1 - t0)
+
+
+def test_keys_and_values_smaller_than_q(B):
+    """The native call hands them back, and every entry point refuses them."""
+    import torch
+    (q, k, v), _ = make_qkv(25, 2, 64, 2, 64, "bf16")
+    (qf, _, _), _ = make_qkv(25, 2, 64, 2, 64, "f32")
+    for bad, code in ((k[:1], -2), (k[:, :32], -2), (k[:, :, :1], -2), (qf, -4)):
+        for kk, vv in ((bad, v), (k, bad)):
+            assert B._native_forward(q, kk, vv, [(64, 1)], 0.125, None) is None
+            for call in (lambda: B.forward(q, kk, vv, [(64, 1)], 0.125), lambda: B.forward_static(q, kk, vv, [(64, 1)], 0.125),
+                         lambda: B.forward_branch(q, kk, vv, 64, 1, 0.125), lambda: B.backward(q, kk, vv, q, torch.zeros((2, 2, 64), device="cuda"), q, [(64, 1)], 0.125)):
+                with pytest.raises(B.DfaError) as e:
+                    call()
+                assert e.value.code == code
+    ref = B.forward(q, k, v, [(64, 1)], 0.125)
+    longer = torch.cat((k, k), dim=1)
+    assert all(torch.equal(a, b) for a, b in zip(ref, B.forward(q, longer, v, [(64, 1)], 0.125)))
