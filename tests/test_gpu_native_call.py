@@ -71,15 +71,18 @@ def test_refusals(B):
 
 
 def test_side_stream(B):
-    """The launch goes to the current stream."""
+    """The launch goes to the current stream: there q is filled only after a wait of some milliseconds, and any other stream is idle."""
     import torch
     (q, k, v), _ = make_qkv(24, 1, 1024, 4, 64, "bf16")
     ref = B.forward(q, k, v, [(256, 1)], 0.125)
-    torch.cuda.synchronize()
+    q2 = torch.zeros_like(q)
     side = torch.cuda.Stream()
+    torch.cuda.synchronize()
     with torch.cuda.stream(side):
-        q2 = q.clone()
+        torch.cuda._sleep(20_000_000)
+        q2.copy_(q)
         out, lse = B.forward(q2, k, v, [(256, 1)], 0.125)
+        assert not side.query(), "the stream had nothing left to wait for"
     side.synchronize()
     assert torch.equal(out, ref[0]) and torch.equal(lse, ref[1])
 
