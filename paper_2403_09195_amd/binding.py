@@ -10,7 +10,7 @@ from __future__ import annotations
 import ctypes
 import os
 
-from .build import LIB_PATH
+from .build import LIB_PATH, TORCH_MODULE_PATH
 
 DFA_BF16, DFA_F32 = 0, 1
 DFA_MAX_BRANCHES = 8
@@ -68,8 +68,9 @@ def lib():
     """Loads libdfa.so (after torch, so that both share one HIP runtime)."""
     global _lib
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError(f"{LIB_PATH} is not built: run `python -c 'import __graft_entry__ as g; g.build()'`")
+        for path in (LIB_PATH, TORCH_MODULE_PATH):
+            if not os.path.exists(path):
+                raise RuntimeError(f"{path} is not built: run `python -c 'import __graft_entry__ as g; g.build()'`")
         import torch  # noqa: F401  (brings in libamdhip64 first)
         L = ctypes.CDLL(LIB_PATH)
         _one_hip_runtime()

@@ -9,7 +9,8 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_PKG, "csrc")
 INCLUDE = os.path.join(os.path.dirname(_PKG), "include")
 LIB_PATH = os.path.join(_PKG, "libdfa.so")
-TORCH_MODULE_PATH = os.path.join(_PKG, "_dfa_torch.so")
+# named for the interpreter it is built with: another one does not find it, and says so, instead of failing inside it
+TORCH_MODULE_PATH = os.path.join(_PKG, "_dfa_torch" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["dfa_api.hip", "dfa_fwd_bf16.hip", "dfa_fwd_short.hip", "dfa_fwd_f32.hip", "dfa_bwd.hip", "dfa_bwd_bf16.hip", "dfa_bwd_short.hip", "dfa_linear_bf16.hip", "dfa_dense.hip", "dfa_aux.hip", "dfa_probe.hip", "dfa_plan.cpp"]
 
@@ -28,10 +29,10 @@ def torch_module_command(out: str = TORCH_MODULE_PATH):
     """g++ command of the module that takes torch tensors to libdfa.so (host code only)."""
     import torch
     root = os.path.dirname(torch.__file__)
-    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-            "-I", INCLUDE, "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-            "-I", sysconfig.get_paths()["include"], "-I", "/opt/rocm/include", os.path.join(CSRC, "dfa_torch.cpp"), "-o", out,
+            "-I", INCLUDE, "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+            "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", os.path.join(CSRC, "dfa_torch.cpp"), "-o", out,
             "-L", os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 

@@ -420,3 +420,10 @@ def test_binding_refuses_keys_and_values_the_kernels_would_read_past(B):
             assert e.value.code == code
     more = torch.zeros((3, 80, 5, 64), dtype=torch.bfloat16)
     assert B._prepare(q, more, more, [(64, 1)], None)[3:7] == (2, 4, 64, 64)
+
+
+def test_torch_module_is_named_for_this_interpreter(B):
+    import sysconfig
+    from paper_2403_09195_amd import _dfa_torch, build
+    assert build.TORCH_MODULE_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert os.path.samefile(_dfa_torch.__file__, build.TORCH_MODULE_PATH)
