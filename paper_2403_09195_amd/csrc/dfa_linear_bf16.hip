@@ -338,23 +338,21 @@ void linear_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restri
 // 128 x BN tiles (launch_linear_bf16 says when).  A workgroup of 4 waves, one per SIMD, stays for the whole launch and works
 // through its CU's tiles one after the other, as one stream of 64-k steps: stage i + S of the ring is fetched as soon as every
 // wave has stage i in registers, whichever tile it belongs to, so neither the first trip to memory of a tile nor the write-out
-// of the one before it stops the copies.  A wave computes 64 rows x BN/2 features, one 16-feature block against its four
-// 16-row blocks at a time (a group: one weight fragment, four MFMAs of 16 cycles).  Weight fragments are read kAhead groups
-// before their use, the x fragments of a 32-k half as far before the half starts, also across the one barrier of a step,
-// which therefore stands kAhead groups before the step's end; the copies into the freed slot follow it.
-// The results leave straight from the registers: two lane-group exchanges give every lane 16 contiguous bytes of a row.
+// of the one before it stops the copies.  A wave computes 64 rows x BN/2 features; the barrier of a step stands where every wave has
+// the whole of its slot in registers, ahead of the products that use them.  The k-steps' addresses are counted along: a division by
+// the number of feature tiles in every step cost up to 0.08 us.
 // Bound, with all CUs at it: the copies (40 to 57 bytes per clock and CU) beside the MFMAs (whose power takes the clock to some
 // 2 GHz).  A 64-k step of a 128 x 288 tile takes 0.90 us: its MFMAs alone 0.71, its copies alone 0.57.  A copy waits in the
-// vector-memory queue behind the other waves' and its wave's MFMAs with it, so the copies of the wide tiles are spread over a whole
-// step (0.97 us with all of them behind the barrier); the narrow ones need theirs early.  The k-steps' addresses are
-// counted along: a division by the number of feature tiles in every step cost up to 0.08 us.
-// One 1024^2 image: QKV projection 21.5 (256 x 256 tiles on 144 CUs) -> 19.0 us (256 128 x 288 tiles).
+// vector-memory queue behind the other waves' and its wave's MFMAs with it, so the wide tiles (288, 192) spread the copies of a step over
+// all of it (0.97 us with all of them behind the barrier), one 16-feature block against the four 16-row blocks at a time, and store
+// from the registers (two lane-group exchanges give every lane 16 contiguous bytes of a row).  The steps of the narrow tiles are too short
+// for that: walked the same way, 64 features took 780 to 800 cycles a step without copies (two halves: 710) and the stores 130 more, 0.5 us
+// of a launch of 6 steps; with all copies behind the barrier a step takes 790 cycles in both forms.
+// Before / now, us: 4096 x 2304 x 768 (256 x 256 tiles on 144 CUs / 256 tiles of 128 x 288) 21.5 / 18.1; 1024 x 1152 x 384 5.1 / 5.1,
+// 1024 x 768 x 768 (64 features) 7.3 / 6.9, 4096 x 768 x 768 (96) 9.4 / 8.9, 3072 x 1152 x 384 (128) 7.0 / 6.8.
 constexpr int kStreamBM = 128;
 template <int BN> constexpr uint32_t kStreamStageBytes = (kStreamBM + BN) * kLinBK * 2;
 template <int BN> constexpr int kStreamStages = BN == 288 ? 3 : BN >= 128 ? 4 : BN == 96 ? 5 : 6;      // 160, 163, 131, 143 and 147 KB
-// fragments in flight: at most half a step's groups; the ring's length divides a step's groups
-template <int NT> constexpr int kStreamAhead = NT == 9 ? 4 : NT >= 3 ? 3 : 2;
-template <int NT> constexpr int kStreamRing = NT == 9 || NT == 3 ? 6 : 4;
 
 // Rows (16-lane groups) 1 and 3 of `a` change places with rows 0 and 2 of `b`.
 __device__ __forceinline__ void swap_lane_rows(uint32_t& a, uint32_t& b) {
@@ -378,14 +376,13 @@ __device__ __forceinline__ u32x4 pack_pair(const floatx4& a, const floatx4& b) {
 template <int BN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void linear_stream_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, uint16_t* __restrict__ y,
-                          int K, int64_t ldx, int64_t ldw, int64_t ldy, int tiles_m, int tiles_n, int parts, int dies, int cus_per_die) {
+                          int K, int64_t ldx, int64_t ldw, int64_t ldy, int part_n, int part_shift, int per_die, int part_tiles, int cus_per_die) {
     constexpr int BM = kStreamBM, S = kStreamStages<BN>, MT = 4, NT = BN / 32;        // 16-row / 16-feature blocks per wave
     constexpr int kXCopies = BM / 32, kCopies = kXCopies + BN / 32;                   // copies per wave and stage
     constexpr uint32_t kStage = kStreamStageBytes<BN>, kWBase = BM * kLinBK * 2;
-    constexpr int kAhead = kStreamAhead<NT>, kRing = kStreamRing<NT>, kGroups = 2 * NT;
-    constexpr int kSpread = BN >= 192 ? kGroups : kAhead;                            // groups that a stage's copies are spread over
-    static_assert(kGroups % kRing == 0 && kAhead < kRing && kAhead <= NT, "a fragment's place in the ring is its group's, in every step");
-    __shared__ __attribute__((aligned(1024))) char lds[S * kStage];
+    constexpr bool kWide = BN >= 192;
+    constexpr int kPitch = BN + 16;                                                   // bytes: BN / 2 features of a row, padded
+    __shared__ __attribute__((aligned(1024))) char lds[S * kStage + (kWide ? 0 : 4 * 16 * kPitch)];
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
@@ -397,12 +394,12 @@ void linear_stream_kernel(const uint16_t* __restrict__ x, const uint16_t* __rest
     const uint32_t lds_addr = (uint32_t)(uintptr_t)DFA_LDS_PTR(void, &lds[0]);
     const int wm = wave >> 1, wn = wave & 1;
 
-    // this workgroup's tiles: first, first + cus_per_die, ... of its die's list.  A group of `parts` dies has a run of the tiles
-    // (numbered band by band), each die of it a share of the features.
-    const int die = blockIdx.x % dies, part_n = tiles_n / parts, tile_n0 = die % parts * part_n;
-    const int per_die = (tiles_m * part_n * parts + dies - 1) / dies;
-    const int die_first = die / parts * per_die, die_tiles = min(per_die, tiles_m * part_n - die_first);
-    const int first = blockIdx.x / dies;
+    // this workgroup's tiles: first, first + cus_per_die, ... of its die's list.  A group of 2^part_shift dies has a run of the tiles
+    // (numbered band by band, part_n to a band), each die of it a share of the features.  (Die and place come as the grid's dimensions and the
+    // shares from the host: a launch waits for every division before its first copy, 0.17 us for five of them.)
+    const int die = blockIdx.x, tile_n0 = (die & ((1 << part_shift) - 1)) * part_n;
+    const int die_first = (die >> part_shift) * per_die, die_tiles = min(per_die, part_tiles - die_first);
+    const int first = blockIdx.y;
     if (first >= die_tiles) return;
     const int n_k = K / kLinBK;
     const int total = ((die_tiles - first - 1) / cus_per_die + 1) * n_k;             // k-steps of all its tiles
@@ -439,15 +436,12 @@ void linear_stream_kernel(const uint16_t* __restrict__ x, const uint16_t* __rest
 
     // fragments: row r16 of a 16-row block, chunk (4 * half + g4) ^ swizzle
     const int frag = r16 * kLinBK + 8 * (g4 ^ lin_swizzle(r16));
-    bf16x8 wf[kRing], xf[2][MT];
-    auto read_w = [&](const uint16_t* st, int i) {         // fragment of group i of a step
-        wf[i % kRing] = *reinterpret_cast<const bf16x8*>(st + kWBase / 2 + ((BN / 2) * wn + 16 * (i % NT)) * kLinBK + (frag ^ (32 * (i / NT))));
+    auto x_frag = [&](int slot, int half, int mt) {
+        return *reinterpret_cast<const bf16x8*>(reinterpret_cast<const uint16_t*>(lds + slot * kStage) + ((BM / 2) * wm + 16 * mt) * kLinBK + (frag ^ (32 * half)));
     };
-    auto read_x = [&](const uint16_t* st, int half) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) xf[half][mt] = *reinterpret_cast<const bf16x8*>(st + ((BM / 2) * wm + 16 * mt) * kLinBK + (frag ^ (32 * half)));
+    auto w_frag = [&](int slot, int half, int nt) {
+        return *reinterpret_cast<const bf16x8*>(reinterpret_cast<const uint16_t*>(lds + slot * kStage + kWBase) + ((BN / 2) * wn + 16 * nt) * kLinBK + (frag ^ (32 * half)));
     };
-    auto stage = [&](int slot) { return reinterpret_cast<const uint16_t*>(lds + slot * kStage); };
 
     for (int s = 0; s < S && s < total; ++s) {
 #pragma unroll
@@ -456,59 +450,145 @@ void linear_stream_kernel(const uint16_t* __restrict__ x, const uint16_t* __rest
     }
     landed(issued - 1);
     asm volatile("s_barrier" ::: "memory");
-    read_x(stage(0), 0);
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) read_w(stage(0), i);
 
     floatx4 acc[NT][MT];                   // [16-feature block][16-row block], as in linear_tile
-    int step = 0, slot = 0, fill = 0;
-    bool more = false;                     // a stage is being fetched into slot `fill`
-    for (int j = first; j < die_tiles; j += cus_per_die) {
+    auto clear = [&]() {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-        for (int ks = 0; ks < n_k; ++ks, ++step) {
-            const int next_slot = slot + 1 == S ? 0 : slot + 1;
+    };
+    int step = 0, slot = 0;
+    if constexpr (kWide) {
+        // A group: one weight fragment, four MFMAs of 16 cycles.  Weight fragments are read kAhead groups before their use, the x
+        // fragments of a half as far before it starts; the ring's length divides a step's groups.
+        constexpr int kGroups = 2 * NT, kAhead = NT == 9 ? 4 : 3, kRing = NT == 9 ? 6 : 4, kMeet = kGroups - kAhead;
+        static_assert(kGroups % kRing == 0 && kAhead < kRing && kAhead <= NT, "a fragment's place in the ring is its group's, in every step");
+        bf16x8 wf[kRing], xf[2][MT];
+        auto read_w = [&](int sl, int i) { wf[i % kRing] = w_frag(sl, i / NT, i % NT); };
+        auto read_x = [&](int sl, int half) {
 #pragma unroll
-            for (int i = 0; i < kGroups; ++i) {
-                constexpr int kMeet = kGroups - kAhead;
-                if (i == kMeet) {
-                    // every wave has the whole of this slot in registers, and stage step + 1 has landed for every wave
-                    if (more) stage_issued();
-                    landed(issued - step - 2);
-                    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                    more = issued < total;
-                    fill = slot;
+            for (int mt = 0; mt < MT; ++mt) xf[half][mt] = x_frag(sl, half, mt);
+        };
+        read_x(0, 0);
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) read_w(0, i);
+        int fill = 0;
+        bool more = false;                 // a stage is being fetched into slot `fill`
+        for (int j = first; j < die_tiles; j += cus_per_die) {
+            clear();
+            for (int ks = 0; ks < n_k; ++ks, ++step) {
+                const int next_slot = slot + 1 == S ? 0 : slot + 1;
+#pragma unroll
+                for (int i = 0; i < kGroups; ++i) {
+                    if (i == kMeet) {
+                        // every wave has the whole of this slot in registers, and stage step + 1 has landed for every wave
+                        if (more) stage_issued();
+                        landed(issued - step - 2);
+                        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                        more = issued < total;
+                        fill = slot;
+                    }
+                    // past the last step: an old slot, not used
+                    const int r = i + kAhead;
+                    if (i % NT == NT - kAhead) read_x(i < NT ? slot : next_slot, i < NT ? 1 : 0);
+                    read_w(r < kGroups ? slot : next_slot, r % kGroups);
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[i % NT][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i % kRing], xf[i / NT][mt], acc[i % NT][mt], 0, 0, 0);
+                    const int g = (i + kGroups - kMeet) % kGroups;
+                    if (more) {
+#pragma unroll
+                        for (int u = g * kCopies / kGroups; u < (g + 1) * kCopies / kGroups; ++u) copy(u, lds_addr + fill * kStage);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                // past the last step: an old slot, not used
-                const int r = i + kAhead;
-                if (i % NT == NT - kAhead) read_x(stage(i < NT ? slot : next_slot), i < NT ? 1 : 0);
-                read_w(stage(r < kGroups ? slot : next_slot), r % kGroups);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[i % NT][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i % kRing], xf[i / NT][mt], acc[i % NT][mt], 0, 0, 0);
-                const int g = (i + kGroups - kMeet) % kGroups;
-                if (g < kSpread && more) {
-#pragma unroll
-                    for (int u = g * kCopies / kSpread; u < (g + 1) * kCopies / kSpread; ++u) copy(u, lds_addr + fill * kStage);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+                slot = next_slot;
             }
-            slot = next_slot;
+            // Write-out straight from the registers: pairs of feature blocks, 64 contiguous bytes of every row per store; a last single one
+            // by pairs of row blocks.
+            const int t = die_first + j;
+            uint16_t* const yt = y + ((int64_t)(t / part_n) * BM + (BM / 2) * wm + r16) * ldy + (tile_n0 + t % part_n) * BN + (BN / 2) * wn + 8 * (g4 >> 1);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt + 1 < NT; nt += 2)
+                    *reinterpret_cast<u32x4*>(yt + (int64_t)16 * mt * ldy + 16 * (nt + (g4 & 1))) = pack_pair(acc[nt][mt], acc[nt + 1][mt]);
+            if (NT % 2 != 0) {
+#pragma unroll
+                for (int mt = 0; mt < MT; mt += 2)
+                    *reinterpret_cast<u32x4*>(yt + (int64_t)16 * (mt + (g4 & 1)) * ldy + 16 * (NT - 1)) = pack_pair(acc[NT - 1][mt], acc[NT - 1][mt + 1]);
+            }
         }
-        // write-out: pairs of feature blocks, 64 contiguous bytes of every row per store; a last single one by pairs of row blocks
-        const int t = die_first + j;
-        uint16_t* const yt = y + ((int64_t)(t / part_n) * BM + (BM / 2) * wm + r16) * ldy + (tile_n0 + t % part_n) * BN + (BN / 2) * wn + 8 * (g4 >> 1);
+    } else {
+        // The fragments of a 32-k half are read under the MFMAs of the half before, also across the step's barrier, behind which all copies
+        // into the freed slot go out: these steps are short, and every branch in them shows.
+        struct Frags { bf16x8 w[NT], x[MT]; };
+        auto read = [&](Frags& f, int sl, int half) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+            for (int nt = 0; nt < NT; ++nt) f.w[nt] = w_frag(sl, half, nt);
 #pragma unroll
-            for (int nt = 0; nt + 1 < NT; nt += 2)
-                *reinterpret_cast<u32x4*>(yt + (int64_t)16 * mt * ldy + 16 * (nt + (g4 & 1))) = pack_pair(acc[nt][mt], acc[nt + 1][mt]);
-        if (NT % 2 != 0) {
+            for (int mt = 0; mt < MT; ++mt) f.x[mt] = x_frag(sl, half, mt);
+        };
+        auto multiply = [&](const Frags& f) {
 #pragma unroll
-            for (int mt = 0; mt < MT; mt += 2)
-                *reinterpret_cast<u32x4*>(yt + (int64_t)16 * (mt + (g4 & 1)) * ldy + 16 * (NT - 1)) = pack_pair(acc[NT - 1][mt], acc[NT - 1][mt + 1]);
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[nt], f.x[mt], acc[nt][mt], 0, 0, 0);
+        };
+        // the reads of one half spread over the MFMAs of the other
+        auto weave = [&]() {
+#pragma unroll
+            for (int i = 0; i < MT + NT; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, MT * NT / (MT + NT), 0);
+            }
+        };
+        Frags f0, f1;
+        read(f0, 0, 0);
+        for (int j = first; j < die_tiles; j += cus_per_die) {
+            clear();
+            for (int ks = 0; ks < n_k; ++ks, ++step) {
+                read(f1, slot, 1);
+                multiply(f0);
+                weave();
+                const int next_slot = slot + 1 == S ? 0 : slot + 1;
+                // every wave has the whole of this slot in registers, and stage step + 1 has landed for every wave
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                landed(issued - step - 2);
+                asm volatile("s_barrier" ::: "memory");
+                if (issued < total) {
+#pragma unroll
+                    for (int u = 0; u < kCopies; ++u) copy(u, lds_addr + slot * kStage);
+                    stage_issued();
+                }
+                read(f0, next_slot, 0);    // past the last step: an old slot, not used
+                multiply(f1);
+                weave();
+                slot = next_slot;
+            }
+            // Write-out, 16 rows of the wave's tile at a time through its own piece of LDS.  No barrier: the piece belongs to this wave
+            // alone, and LDS operations of a wave complete in order.
+            const int t = die_first + j;
+            const int64_t m0 = (int64_t)(t / part_n) * BM + (BM / 2) * wm, n0 = (int64_t)(tile_n0 + t % part_n) * BN + (BN / 2) * wn;
+            constexpr int kLanesPerRow = BN / 16, kChunks = 16 * kLanesPerRow;             // 16-byte pieces of BN / 2 features
+            char* const mine = lds + S * kStage + wave * (16 * kPitch);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const floatx4& a = acc[nt][mt];
+                    const bf16x4 o = {(__bf16)a[0], (__bf16)a[1], (__bf16)a[2], (__bf16)a[3]};
+                    *reinterpret_cast<bf16x4*>(mine + r16 * kPitch + (16 * nt + 4 * g4) * 2) = o;
+                }
+#pragma unroll
+                for (int c0 = 0; c0 < kChunks; c0 += 64) {
+                    const int c = c0 + lane, row = c / kLanesPerRow, ch = c % kLanesPerRow;
+                    if (kChunks % 64 == 0 || c < kChunks)
+                        *reinterpret_cast<u32x4*>(y + (m0 + 16 * mt + row) * ldy + n0 + 8 * ch) =
+                            *reinterpret_cast<const u32x4*>(mine + row * kPitch + 16 * ch);
+                }
+            }
         }
     }
 }
@@ -519,12 +599,14 @@ hipError_t launch_stream(const void* x, const void* w, void* y, int64_t M, int32
     const int dies = chip.dies > 0 ? chip.dies : 1, cus_per_die = chip.cus / dies > 0 ? chip.cus / dies : 1;
     const int tiles_n = N / BN, tiles_m = (int)(M / kStreamBM);
     // Two dies with half the feature tiles each fetch less, and keep it more easily, than each with all (8192 x 2304 x 768 34.3 ->
-    // 31.9 us, 4096 x 2304 x 768 18.7 -> 18.5), where that deals the dies the same number of tiles.
-    const int parts = tiles_n % 2 == 0 && dies % 2 == 0 && tiles_m % (dies / 2) == 0 ? 2 : 1;
+    // 31.9 us, 4096 x 2304 x 768 18.7 -> 18.5), where that deals the dies the same number of tiles.  Not for narrow tiles, whose weights are
+    // small beside the rows that two dies then fetch (6144 x 384 x 384 6.4 us, 5.9 without; 1024 x 2304 x 768 8.5 / 8.6).
+    const int parts = BN >= 192 && tiles_n % 2 == 0 && dies % 2 == 0 && tiles_m % (dies / 2) == 0 ? 2 : 1;
     const int per_die = (tiles_m * tiles_n + dies - 1) / dies;
-    hipLaunchKernelGGL((linear_stream_kernel<BN>), dim3((per_die < cus_per_die ? per_die : cus_per_die) * dies), dim3(256), 0, st,
+    // dies along x: workgroups go to the dies in turn, x first
+    hipLaunchKernelGGL((linear_stream_kernel<BN>), dim3(dies, per_die < cus_per_die ? per_die : cus_per_die), dim3(256), 0, st,
                        static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), static_cast<uint16_t*>(y),
-                       K, ldx, ldw, ldy, tiles_m, tiles_n, parts, dies, cus_per_die);
+                       K, ldx, ldw, ldy, tiles_n / parts, parts - 1, per_die, tiles_m * (tiles_n / parts), cus_per_die);
     return hipGetLastError();
 }
 

@@ -68,7 +68,7 @@ def test_linear_identity_and_row_selection(B):
 
 # one case per tile form of the launch rule and edge of its stream of k-steps: 128 x 64 (one tile per workgroup at most; a
 # single k-step, fewer k-steps than stages, more), 128 x 128 (feature counts that 96 does not divide), 128 x 96 (one tile per
-# workgroup, and three, whose k-steps follow one another in the ring: 3, 9 and 15 of them over 5 stages), 256 x 128
+# workgroup), 128 x 288 (two), 256 x 128
 @pytest.mark.parametrize("M,N,K", [(256, 128, 320), (2048, 768, 64), (1024, 384, 448), (4096, 1024, 64), (4096, 1024, 320),
                                    (4096, 768, 192), (8192, 1152, 64), (8192, 1152, 192), (7936, 1152, 320), (2048, 2304, 128)])
 def test_linear_tile_forms(B, oracle, M, N, K):
@@ -78,6 +78,16 @@ def test_linear_tile_forms(B, oracle, M, N, K):
     ref = oracle.linear(xe, we[:, :K])
     err = np.abs(to_f64(y) - ref)
     assert np.all(err <= _linear_bar(xe, we[:, :K], ref))
+
+
+# 128 x 96 tiles, three to a workgroup, whose k-steps follow one another in the ring: 3, 9 and 15 of them over 5 stages; dies with fewer tiles
+@pytest.mark.parametrize("M,N,K", [(24576, 384, 64), (22016, 384, 192), (22272, 384, 320)])
+def test_linear_narrow_tiles_in_a_row(B, oracle, M, N, K):
+    x, xe = _bf16(408, 3, (M, K))
+    wide, we = _bf16(408, 10, (N, K + 8), std=0.02)
+    y = B.linear(x, wide[:, :K])
+    ref = oracle.linear(xe, we[:, :K])
+    assert np.all(np.abs(to_f64(y) - ref) <= _linear_bar(xe, we[:, :K], ref))
 
 
 # the wide 128-row tiles: 128 x 288 (fewer k-steps than stages, as many, more; one tile per workgroup, two whose k-steps follow one
