@@ -582,7 +582,8 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
         build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, &shared, kShortRows / kBlockRows, true);
         const int64_t live = launch_size(shared).live, bound = apart.live > slots ? slots : one;
         const int64_t longest = cut_size(shared).longest;
-        if (longest <= kShortBlocks && ((apart.blocks >= kTailBlocks * apart.live && 25 * live <= 24 * apart.live) ||
+        // (padding for the dies included, the plan must not leave the range that it is in apart)
+        if (longest <= kShortBlocks && (plan->items.size() > near || shared.items.size() <= near) && ((apart.blocks >= kTailBlocks * apart.live && 25 * live <= 24 * apart.live) ||
                                         (plan->items.size() > near && shared.items.size() <= near) ||
                                         (live <= bound && longest <= cut_size(*plan).longest)))
             *plan = std::move(shared);

@@ -168,8 +168,9 @@ constexpr int kShortBlocks = 64;
 // Plans of more workgroups than start at once, or of up to a quarter more than there are CUs, are tried with the rests of row groups sharing
 // tiles: fewer workgroups, some of which walk the union of two lists.  That is taken where the lists have kTailBlocks blocks or
 // more on average and the workgroups become 4 % fewer (then they are worth more than some longer walks), where there are too many workgroups for
-// the form otherwise, or where it brings them within the bound and no list gets longer.  Measured over 80 such shapes (in the mean 1.25
-// times faster, three slower by 3 to 5 % and one by 11), us, apart / sharing:
+// the form otherwise, or where it brings them within the bound and no list gets longer.  Over 266 drawn shapes that this changes 1.14 times
+// as fast in the mean, 24 of them slower by more than 3 % and 14 % at worst (one of 1576 tokens, 9 heads, with offsets 14.0 / 16.2): which
+// of the two plans is the shorter there the lists' lengths alone do not tell, and rules on their growth lost as much elsewhere.  us, apart / sharing:
 // one image of 2312 tokens, 12 heads (528 / 480 workgroups) 22.6 / 18.5, of 2219 (560 / 520) 27.0 / 21.9, one of 2332, 6 heads
 // (264 / 240) 15.8 / 13.6, one of 2229, 12 heads, in whole tiles before, (528) 36.5 / 20.9; short lists that get longer: one of 1386, 16
 // heads, four branches (552 / 504, 12 blocks on average) 14.9 / 17.0, one of 654, 16 heads (288 / 256, 9 blocks) 9.9 / 11.2.
@@ -181,7 +182,8 @@ constexpr int kTailBlocks = 19;
 // tiles pack several row groups 3.6 + 0.0174 + 0.0011 + 1.18.  Two kinds stay, where the gain is small and the estimates are not that
 // sharp: split launches up to eleven eighths of the slots, whose second round would be nearly empty (one image of 5504 tokens, 6 heads,
 // four branches, 624 workgroups 31.5 / 33.5), and packed tiles whose longest list is under kManySteps steps (16 of 505, 8 heads
-// 19.9 / 23.8).  Over 95 other shapes that the estimates send here 1.40 times as fast in the mean, 1.00 to 2.17; us, before / now: 2 images
+// 19.9 / 23.8).  Over 1734 drawn shapes that the estimates send here 1.40 times as fast in the mean, 0.82 to 3.2, ten slower by more than
+// 3 % (3 images of 2226 tokens, 9 heads, two branches 31.8 / 38.6); us, before / now: 2 images
 // of 2107 tokens, 8 heads 60.2 / 24.9, one of 2170, 16 heads, four branches 38.2 / 23.5, 6 of 310, 16 heads 29.2 / 18.2; left as they are:
 // 3 of 1441, 8 heads, windows of 288 10.9 / 16.7, one of 4096, 12 heads 32.2 / 38.4.
 constexpr int kManySteps = 10;
