@@ -135,7 +135,12 @@ size_t dfa_workspace_bytes(int32_t B, int32_t H, int32_t N, int32_t D, dfa_dtype
  * in the worst case (one key carrying the row), a few 1e-4 when many keys share the
  * weight.  dt = DFA_F32: fp32 throughout (products of exact three-part splits of the operands, within 2^-23 of each
  * product, 2^-26.7 on average, accumulated in fp32; operands that the parts do not hold exactly, those with bits below 2^-133 and those
- * that are not finite or round up to 2^128, take plain fp32 products; weights below 2^-109 of the row's largest are kept to 2^-133).
+ * that are not finite or round up to 2^128, take plain fp32 products, for which a launch takes up to 2.3 times as long; weights below
+ * 2^-109 of the row's largest are kept to 2^-133).
+ * Keys and values that are not finite make infinities or NaN of the rows that attend to them.  For dt = DFA_F32, for DFA_BF16 launches
+ * in 64-row tiles (dfa_launch_describe in dfa_bench.h tells) and for 256-row tiles of one row group each, of no other rows.  256-row
+ * tiles that hold several groups of rows (small images in batches) walk the union of their groups' keys: there a key or value that
+ * is not finite also makes NaN of the other groups' rows in the tile.
  */
 int dfa_forward(const void *q, const void *k, const void *v,
                 dfa_strides_t sq, dfa_strides_t sk, dfa_strides_t sv,

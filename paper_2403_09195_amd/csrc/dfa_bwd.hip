@@ -22,7 +22,8 @@
 // Buffers are refilled as soon as a block's last product with them is through, each landing under a product with the other
 // one.  The dk/dv workgroups hold 64 registers of split tile rows and the low parts in LDS, where the four waves share them: with all of
 // them in registers the walk spills.
-// Measured, forward and backward of two 512^2 images (6 heads x 1024 tokens): 60 us (fp32 matrix cores 74 us), error of the gradients
+// Measured, forward and backward of two 512^2 images (6 heads x 1024 tokens): 60 to 64 us depending on the box (fp32 matrix
+// cores 74 us), error of the gradients
 // against fp64 3.6e-7 of their 2-norm (4.3e-7).
 #include "dfa_device.h"
 #include "dfa_mfma_f32.h"

@@ -247,7 +247,7 @@ void dfa_fwd_bf16_kernel(const FwdParams p) {
         pf.t = skip;
     }
     // The first three stages on their way before anything else.  Split launches, whose workgroups start all at once, fetch the second and
-    // the third behind the wait for the first: 64 KB less per CU before the first beat (one 1024^2 image 33.4 -> 32.8 us).
+    // the third behind the wait for the first: 64 KB less per CU before the first beat (one 1024^2 image 33.2 -> 32.8 us).
     cursor_load(pf, seg_lds);
     KeyCursor cur = pf;
 #pragma unroll

@@ -12,8 +12,8 @@
 // walks of 1024 to 2048 keys over 256 CUs.  A wave copies its own blocks global -> LDS, K and V into one buffer each: a buffer is
 // refilled as soon as its block is in registers and has the rest of the beat to land, so no barrier and no second stage is needed.
 //
-// Measured, one 1024^2 image (12 heads x 4096 tokens, three branches): 126 us = 141 TFLOP/s of the distinct pairs (160 us on the fp32
-// matrix cores, whose rate is 157 TFLOP/s); error against fp64 1.8e-7 of the output's 2-norm (2.3e-7), of lse 3.3e-8 (3.4e-8).
+// Measured, one 1024^2 image (12 heads x 4096 tokens, three branches): 122 to 131 us depending on the box, 126 us =
+// 141 TFLOP/s of the distinct pairs (160 us on the fp32 matrix cores, whose rate is 157 TFLOP/s); error against fp64 1.8e-7 of the output's 2-norm (2.3e-7), of lse 3.3e-8 (3.4e-8).
 #include "dfa_device.h"
 #include "dfa_mfma_f32.h"
 

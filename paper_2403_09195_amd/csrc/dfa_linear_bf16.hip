@@ -646,13 +646,14 @@ hipError_t launch_linear_bf16(const void* x, const void* w, void* y, int64_t M, 
                               int64_t ldx, int64_t ldw, int64_t ldy, const ChipShape& chip, hipStream_t st) {
     // One workgroup per CU at a time, so a launch lasts as long as the CU with most tiles.  Per round of tiles the small forms
     // cost about as much as the bytes they fetch, 64 (BM + BN) per k-step and CU; 256 x 256, 128 x 288 and 128 x 192 tiles
-    // more (their MFMAs show), 128 x 192 ones less where K is long enough to make up for their start.  Fitted over 2048 to 32768
-    // rows and 384 to 2304 features (K = 384 and 768): the least estimate is the fastest form or within 4 % of it.
+    // more (their MFMAs show), 128 x 192 ones less where K is long enough to make up for their start.  Fitted over 256 to 32768
+    // rows and 384 to 2304 features (K = 384 and 768): on 50 of 52 shapes the least estimate is the fastest form or within 4 % of it,
+    // which is what two runs differ by (16384 x 1152 x 384 22.2 us, 21.0 with 192; 32768 x 384 x 384 17.8, 16.0 with 128).
     // Rows x features x K, us, 256 x 256 / 256 x 128 / 128 x 288 / 128 x 192 / 128 x 128 / 128 x 96 / 128 x 64 tiles:
-    // 2048 x 2304 x 768 14.9 / 14.3 / 16.4 / 13.3 / 17.2 / 15.0 / 16.7, 4096 x 2304 x 768 21.4 / 25.8 / 19.0 / 22.5 / 24.1 / 21.3 / 25.1,
-    // 8192 x 2304 x 768 34.5 / 39.3 / 33.2 / 34.4 / 38.3 / 37.9 / 42.6, 16384 x 2304 x 768 57.3 / 65.3 / 60.7 / 64.0 / 67.6 / 73.6 / 80.9,
-    // 4096 x 768 x 768 13.9 / 13.2 / - / 12.7 / 10.2 / 9.5 / 12.3, 6144 x 768 x 768 14.5 / 13.9 / - / 13.3 / 17.2 / 15.1 / 16.5,
-    // 5120 x 1152 x 384 - / 9.6 / 11.8 / 10.3 / 11.8 / 10.8 / 11.5, 8192 x 1152 x 384 - / 16.2 / 13.1 / 15.4 / 15.8 / 14.2 / 16.4.
+    // 2048 x 2304 x 768 14.3 / 13.5 / 15.8 / 13.1 / 16.7 / 14.4 / 16.6, 4096 x 2304 x 768 20.9 / 25.7 / 18.7 / 22.0 / 24.0 / 21.5 / 25.8,
+    // 8192 x 2304 x 768 34.1 / 39.2 / 32.2 / 33.6 / 39.3 / 40.1 / 44.3, 16384 x 2304 x 768 56.8 / 65.7 / 61.4 / 64.2 / 70.4 / 78.2 / 87.6,
+    // 4096 x 768 x 768 13.7 / 12.9 / - / 12.5 / 9.6 / 9.1 / 12.1, 6144 x 768 x 768 14.2 / 13.4 / - / 13.1 / 16.6 / 14.7 / 16.5,
+    // 5120 x 1152 x 384 - / 9.5 / 11.5 / 9.8 / 10.7 / 10.2 / 10.9, 8192 x 1152 x 384 - / 16.3 / 13.1 / 15.3 / 14.8 / 13.9 / 16.2.
     const int64_t dies = chip.dies > 0 ? chip.dies : 1, cus = chip.cus / dies > 0 ? chip.cus / dies : 1;
     auto per_die = [&](int bm, int bn) { return ((M / bm) * (N / bn) + dies - 1) / dies; };
     auto rounds = [&](int bm, int bn) { return (per_die(bm, bn) + cus - 1) / cus; };

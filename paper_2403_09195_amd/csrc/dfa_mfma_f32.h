@@ -11,7 +11,12 @@
 // (bf16's least number; conversion, dot products and MFMAs of gfx950 keep numbers below 2^-126) are looked for in every operand as it is
 // split; infinite and NaN operands and numbers that round up to 2^128 make a NaN (h - h) that reaches the result.  The softmax
 // weights are not looked at: what theirs lose below 2^-133 is less than what the exponential does, which ends at 2^-126.
-// (Such a second walk makes a launch 2.2 times as long, backward 2.1.)
+// A second walk of every workgroup makes a launch 2.0 to 2.3 times as long, forward or backward (q, k or v of N(0,1) 2^-120; one 1024^2
+// image 127 -> 270 and 413 -> 935 us, two 512^2 images of 6 heads 15.8 -> 31.9 and 43.5 -> 88.5); one such key, which its own and every
+// workgroup that walks it sees, 1.4 to 1.7 times.  The size of scores and weights sends nothing there (q of N(0,1) 16: 16.1 and 43.6 us).
+//
+// (Three bf16 numbers for one of fp32, products accumulated in fp32: G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype for Higher-Precision Computations", ARITH 2019.)
 //
 // Layouts (lane = 32*g + j).  v_mfma_f32_32x32x16_bf16: A is 32 x 16 with row j, slots 8*g .. +7 in lane (j, g), B 16 x 32 with the
 // same slots, column j; v_mfma_f32_32x32x2_f32: one slot g.  The result's register v of lane (j, g) is row kappa(v, g) = 8*(v/4) +
@@ -74,13 +79,14 @@ __device__ __forceinline__ uint32_t high_halves(float lo, float hi) {
 }
 
 // Whether a lane has split a number that its parts do not hold: what is left after m is cut off has then bits below 2^-133, in the
-// lower half of its word.  (One instruction for two numbers, not seen in any launch's time.)
+// lower half of its word.  (One instruction for two numbers; without it one 1024^2 image takes 124.4 us for 125.2 forward, 412 for 415 backward.)
 struct Lost {
     uint32_t bits = 0u;
     __device__ __forceinline__ void add(float a, float b) { bits |= __builtin_bit_cast(uint32_t, a) | __builtin_bit_cast(uint32_t, b); }
     __device__ __forceinline__ bool any() const { return (bits & 0xffffu) != 0u; }
 };
-// The same where there is no register to put it off (the dk/dv walk spills then).
+// The same where there is no register to put it off (the dk/dv walk spills then).  Backward, us with / without the test: two 512^2 images, 6
+// heads 43.6 / 43.2; windows of 32 to 256, 12 heads of 256 tokens 22.6 to 32.6 / 23.1 to 32.8 (4 images), 70 to 107 / 68 to 110 (16).
 struct LostAtOnce : Lost {
     __device__ __forceinline__ void add(float a, float b) {
         Lost::add(a, b);
