@@ -162,8 +162,11 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
     if (!hp.items.empty()) std::memcpy(out->bytes.data() + b_rows + b_segs, hp.items.data(), hp.items.size() * sizeof(Item));
     if (!hp.split_wgs.empty()) {
         std::memcpy(out->bytes.data() + out->off_split_wgs, hp.split_wgs.data(), hp.split_wgs.size() * sizeof(SplitWg));
-        for (size_t g = 0; g < hp.split_wgs.size(); ++g)
-            std::memcpy(out->bytes.data() + out->off_split_items + g * sizeof(Item), &hp.items[hp.split_wgs[g].item], sizeof(Item));
+        const Item padding{-1, 0, Tile{0, 0, 0, 0, 0, 0}};
+        for (size_t g = 0; g < hp.split_wgs.size(); ++g) {
+            const int32_t item = hp.split_wgs[g].item;
+            std::memcpy(out->bytes.data() + out->off_split_items + g * sizeof(Item), item < 0 ? &padding : &hp.items[item], sizeof(Item));
+        }
         std::memcpy(out->bytes.data() + out->off_item_parts, hp.item_parts.data(), hp.item_parts.size() * sizeof(ItemParts));
     }
     return DFA_OK;

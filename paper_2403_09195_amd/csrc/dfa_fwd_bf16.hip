@@ -103,15 +103,16 @@ void dfa_fwd_bf16_kernel(const FwdParams p) {
     __shared__ KeySeg seg_all[kPacked ? 4 : 1][kMaxTileSegs];
     __shared__ float bias1_all[kPacked ? 4 : 1][kMaxTileSegs];   // kPacked: log2 m of the wave's second 32-row block
 
-    int part = 0, nparts = 1;
+    int part = 0, nparts = 1, block = 0;
     if (kSplit) {
         // such a launch is one round of workgroups, as long as its start is: arguments in one trip to memory, share and item
         // in the next
         hold_args(p);
         asm volatile("" ::"s"(p.split_wgs), "s"(p.split_items), "s"(p.split_ws));
-        const int32_t part_nparts = p.split_wgs[blockIdx.x].part_nparts;
-        part = part_nparts & 0xffff;
-        nparts = part_nparts >> 16;
+        const SplitWg share = p.split_wgs[blockIdx.x];
+        part = share.part_nparts & 0xffff;
+        nparts = share.part_nparts >> 16;
+        block = share.block;
     }
     const Item item = kSplit ? load_item(p.split_items, blockIdx.x) : p.items[blockIdx.x];
     if (item.tile < 0) return;
@@ -176,7 +177,7 @@ void dfa_fwd_bf16_kernel(const FwdParams p) {
     float* const lse_out = p.lse;
     const int64_t out_bh = (int64_t)b * p.N * p.H + h;   // in rows; row n adds n * H
     // split launches: this workgroup's block of partial results, out [256][64] then lse [256], rows in tile order
-    char* const blk = kSplit ? reinterpret_cast<char*>(p.split_ws) + (int64_t)blockIdx.x * kSplitBlockBytes : nullptr;
+    char* const blk = kSplit ? reinterpret_cast<char*>(p.split_ws) + (int64_t)block * kSplitBlockBytes : nullptr;
     float* const blk_lse = reinterpret_cast<float*>(blk + kTileRows * kD * 2);
     float* const blk_scale = blk_lse + kTileRows;
     // a tile that the split launch walks whole (one part) is finished here like in any other launch
@@ -517,7 +518,7 @@ __global__ __launch_bounds__(256) void merge_split_kernel(const FwdParams p) {
     const Item item = load_item(p.items, blockIdx.x);
     if (ip.nparts <= 1) return;         // padding item, or a tile walked whole (its workgroup wrote the rows itself)
     const int r = blockIdx.y * 32 + (threadIdx.x >> 3), sub = threadIdx.x & 7;
-    const char* blk0 = reinterpret_cast<const char*>(p.split_ws) + (int64_t)ip.first_wg * kSplitBlockBytes;
+    const char* blk0 = reinterpret_cast<const char*>(p.split_ws) + (int64_t)ip.first_block * kSplitBlockBytes;
     float lb[kMaxSplit];
     typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
     float sc[kMaxSplit];

@@ -357,7 +357,7 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 
     // Launch order.  Workgroup i runs on die i mod 8, each die has its own L2, and the tiles
     // of one (b, h) read the same K/V rows: keep a (b, h) unit on one die when there are
-    // enough units to balance the dies, otherwise spread single tiles.  Within a die the
+    // enough units to balance the dies, otherwise give every die a run of tiles.  Within a die the
     // heaviest tiles go first so the tail of the launch is made of short ones.
     const int32_t T = (int32_t)plan->tiles.size();
     std::vector<std::vector<int32_t>> tiles_of_head(H);
@@ -376,6 +376,29 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     const int64_t units = (int64_t)B * H;
     const bool by_unit = units >= 4 * kNumXcd ||
                          (units >= kNumXcd && ((units + kNumXcd - 1) / kNumXcd) * kNumXcd * 8 <= units * 9);
+    // Fewer units: the tiles one after the other, unit by unit and within a unit by their first row, cut into a run of the same number for
+    // every die: the tiles of a run share most of their K/V rows, which the die then reads once.  Only where that balances the dies to
+    // within a thirty-second; otherwise single tiles are spread.  (12 heads, us, spread / runs: one 1024^2 image, forward 32.1 / 30.0, one 800^2
+    // image, forward and backward 69.4 / 64.2, two 512^2 images of 6 heads in fp32 60.9 / 58.3; one image of 10122 tokens 242 / 153.)
+    auto by_runs = [&]() {
+        const int64_t total = (int64_t)T * B;
+        int64_t at = 0, all = 0;
+        for (auto& tiles : tiles_of_head)
+            std::stable_sort(tiles.begin(), tiles.end(),
+                             [&](int32_t a, int32_t c) { return plan->rows[plan->tiles[a].row_begin] < plan->rows[plan->tiles[c].row_begin]; });
+        for (int32_t b = 0; b < B; ++b)
+            for (int32_t h = 0; h < H; ++h)
+                for (int32_t t : tiles_of_head[h]) {
+                    const int d = (int)(at++ * kNumXcd / total);
+                    per_die[d].push_back(Item{t, b, plan->tiles[t]});
+                    die_cost[d] += tile_cost[t];
+                    all += tile_cost[t];
+                }
+        if (*std::max_element(die_cost.begin(), die_cost.end()) * kNumXcd <= all + all / 32) return true;
+        for (auto& v : per_die) v.clear();
+        std::fill(die_cost.begin(), die_cost.end(), 0);
+        return false;
+    };
     if (by_unit) {
         for (int32_t b = 0; b < B; ++b)
             for (int32_t h = 0; h < H; ++h) {
@@ -383,7 +406,7 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
                 for (int32_t t : tiles_of_head[h]) per_die[d].push_back(Item{t, b, plan->tiles[t]});
                 die_cost[d] += head_cost[h];
             }
-    } else {
+    } else if (!by_runs()) {
         std::vector<int32_t> order(T);
         std::iota(order.begin(), order.end(), 0);
         std::stable_sort(order.begin(), order.end(),
@@ -402,14 +425,30 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     // multi-progression tiles of one unit together, the single-progression tiles of all units
     // last as filler.  Mode 1: strictly unit after unit.  Mode 0: heaviest first overall.
     size_t longest = 0;
+    const size_t die_cus = std::max<size_t>(kSlotsPerDie / kFwdWorkgroupsPerCu, 1);
+    auto more_pairs = [&](const Item& a, const Item& c) { return tile_cost[a.tile] > tile_cost[c.tile]; };
+    // By the length of their walks, which a tile with few rows takes as long for as a full one.  (By pairs such a tile came last and ended the
+    // launch: 2 images of 1318 tokens, 9 heads 19.2 us, by length 15.)
+    auto longer = [&](const Item& a, const Item& c) {
+        const int32_t sa = plan->tiles[a.tile].n_steps, sc = plan->tiles[c.tile].n_steps;
+        return sa != sc ? sa > sc : tile_cost[a.tile] > tile_cost[c.tile];
+    };
     for (auto& v : per_die) {
         // a die with fewer than four items per workgroup slot is too short a list for mode 3's
         // unit-after-unit body to balance: it gets mode 2
         if (order_mode == 3 && v.size() < 4 * (size_t)kSlotsPerDie) order_mode = 2;
-        if (order_mode == 0 || !by_unit) {
-            std::stable_sort(v.begin(), v.end(), [&](const Item& a, const Item& c) {
-                return tile_cost[a.tile] > tile_cost[c.tile];
-            });
+        const bool at_once = order_mode == 2 && v.size() <= (size_t)kSlotsPerDie;
+        if (order_mode == 0 || !by_unit || at_once) {
+            std::stable_sort(v.begin(), v.end(), longer);
+            if (pack && at_once && v.size() > die_cus) {
+                // Workgroups i and i + die_cus share a compute unit.  The longest have one to themselves, of the others a long one goes with a
+                // short one.  (us, by length alone / so: 3 images of 2879 tokens, 3 heads 20.6 / 19.5, 12 heads of 1059 13.3 / 12.5; units dealt
+                // whole, unit by unit / so: 2 images of 865 tokens, 12 heads 12.6 / 11.0, 3 of 905, windows of 150 11.4 / 8.7.  Backward launches,
+                // which start more workgroups per item, lose 4 to 7 % by it.)
+                const size_t twos = v.size() - die_cus;
+                std::reverse(v.end() - twos, v.end());
+                std::rotate(v.begin(), v.begin() + (die_cus - twos), v.begin() + die_cus);
+            }
         } else {
             // v is unit-major already; sort each unit's run by cost, then (mode 2) move the
             // single-segment tiles behind everything else, keeping their order
@@ -418,9 +457,7 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
                 size_t hi = lo;
                 while (hi < v.size() && v[hi].b == v[lo].b &&
                        plan->tiles[v[hi].tile].h == plan->tiles[v[lo].tile].h) ++hi;
-                std::stable_sort(v.begin() + lo, v.begin() + hi, [&](const Item& a, const Item& c) {
-                    return tile_cost[a.tile] > tile_cost[c.tile];
-                });
+                std::stable_sort(v.begin() + lo, v.begin() + hi, more_pairs);
                 lo = hi;
             }
             if (order_mode == 2)
@@ -428,9 +465,7 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
                                       [&](const Item& a) { return plan->tiles[a.tile].nseg > 1; });
             if (order_mode == 3) {
                 const size_t tail = std::min<size_t>(v.size(), kTailItemsPerDie);
-                std::stable_sort(v.end() - tail, v.end(), [&](const Item& a, const Item& c) {
-                    return tile_cost[a.tile] > tile_cost[c.tile];
-                });
+                std::stable_sort(v.end() - tail, v.end(), more_pairs);
             }
         }
         longest = std::max(longest, v.size());
@@ -474,10 +509,22 @@ void split_plan(HostPlan* plan, const ChipShape& chip) {
         any = true;
     }
     if (!any) return;
-    plan->item_parts.resize(n_items);
-    for (int64_t i = 0; i < n_items; ++i) {
-        plan->item_parts[i] = ItemParts{(int32_t)plan->split_wgs.size(), parts[i]};
-        for (int32_t x = 0; x < parts[i]; ++x) plan->split_wgs.push_back(SplitWg{(int32_t)i, x | (parts[i] << 16)});
+    // The shares die after die in the items' order, cut into a run of the same number for every die: the shares of a tile, and the tiles
+    // that read the same K/V rows, stay on a die.
+    const int64_t dies = std::max(chip.dies, 1), per_die = (total + dies - 1) / dies;
+    std::vector<SplitWg> wgs;
+    plan->item_parts.assign(n_items, ItemParts{0, 0});
+    for (int64_t d = 0; d < dies; ++d)
+        for (int64_t i = d; i < n_items; i += dies) {
+            plan->item_parts[i] = ItemParts{(int32_t)wgs.size(), parts[i]};
+            for (int32_t x = 0; x < parts[i]; ++x) wgs.push_back(SplitWg{(int32_t)i, x | (parts[i] << 16), (int32_t)wgs.size()});
+        }
+    auto share_steps = [&](const SplitWg& g) { return plan->items[g.item].t.n_steps / (double)(g.part_nparts >> 16); };
+    plan->split_wgs.assign(per_die * dies, SplitWg{-1, 0, 0});
+    for (int64_t d = 0; d * per_die < total; ++d) {
+        const auto lo = wgs.begin() + d * per_die, hi = wgs.begin() + std::min(total, (d + 1) * per_die);
+        std::stable_sort(lo, hi, [&](const SplitWg& a, const SplitWg& c) { return share_steps(a) > share_steps(c); });
+        for (auto g = lo; g != hi; ++g) plan->split_wgs[(g - lo) * dies + d] = *g;
     }
 }
 

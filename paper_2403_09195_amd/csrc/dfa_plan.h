@@ -63,15 +63,16 @@ struct ChipShape {
 };
 
 // Split launches (few workgroups, see split_plan): workgroup g of the launch walks share `part` of `nparts` of the
-// 64-key steps of launch item `item` and leaves its partial result in block g of the workspace
+// 64-key steps of launch item `item` and leaves its partial result in block `block` of the workspace
 // (kSplitBlockBytes: out [256 rows][64] in fp16, each row divided by its largest magnitude, then lse [256] and
 // those row scales [256] in fp32; rows in tile order).
 struct SplitWg {
-    int32_t item;
+    int32_t item;           // -1 = padding
     int32_t part_nparts;    // part | nparts << 16
+    int32_t block;
 };
-struct ItemParts {          // per launch item: its workgroups are first_wg .. first_wg + nparts - 1 (nparts = 0: padding)
-    int32_t first_wg;
+struct ItemParts {          // per launch item: its blocks are first_block .. first_block + nparts - 1 (nparts = 0: padding)
+    int32_t first_block;
     int32_t nparts;
 };
 constexpr int kSplitBlockBytes = kTileRows * (DFA_HEAD_DIM * 2 + 8);
@@ -116,7 +117,8 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 // small launch merges the partial results of the tiles that were cut by their log-sum-exp weights (a tile left whole
 // is written out by its one workgroup).  Launches that fill more than half the slots are left alone: cutting their
 // longest walks fills every CU with two workgroups, which slows every step by more than the shorter walks save
-// (two 1024^2 images: 54.7 us against 46.1 us).  Fills plan->split_wgs / item_parts, or
+// (two 1024^2 images: 54.7 us against 46.1 us).  The shares go to the dies in runs like the items they come from, the longest
+// of a die first.  Fills plan->split_wgs / item_parts, or
 // leaves them empty when the launch is not to be split.
 void split_plan(HostPlan* plan, const ChipShape& chip);
 

@@ -92,3 +92,18 @@ def test_plan_cache_keeps_working_past_its_bound(B, oracle):
     o_ref, l_ref = oracle.forward(ex[0][:, :64], ex[1][:, :64], ex[2][:, :64], [(64, 1)], 0.125)
     mx, mean = error_stats(to_f64(out), o_ref)
     assert mx <= 2e-2 and mean <= 2e-3
+
+
+# Shares of a tile on two dies, dies with fewer shares than others, tiles that are left whole beside tiles that are cut.  The workspace
+# holds NaN: what is merged was written.
+@pytest.mark.parametrize("H,N,branches", [(1, 2200, [(2200, 1)]), (3, 2200, [(2200, 1)]), (2, 9000, [(2250, 1), (9000, 4)])])
+def test_shares_over_the_dies(B, oracle, H, N, branches):
+    import torch
+    (q, k, v), ex = make_qkv(905, 1, N, H, 64, "bf16")
+    need = B.workspace_bytes(1, H, N, 64, B.DFA_BF16, branches)
+    assert need > 0 and B.launch_describe(1, H, N, branches)["form"] == B.FORM_SPLIT
+    out, lse = B.forward(q, k, v, branches, 0.125, workspace=torch.full((need,), 255, dtype=torch.uint8, device="cuda"))
+    o_ref, l_ref = oracle.forward(*ex, branches, 0.125)
+    mx, mean = error_stats(to_f64(out), o_ref)
+    assert mx <= 2e-2 and mean <= 2e-3
+    check_lse_bf16(to_f64(lse), oracle, ex, branches, 0.125, l_ref)

@@ -184,3 +184,35 @@ def test_only_split_launches_ask_for_a_workspace(B, Bsz, H, N, branches, offs):
     d = B.launch_describe(Bsz, H, N, branches, offs)
     need = B.workspace_bytes(Bsz, H, N, 64, B.DFA_BF16, branches, offs)
     assert need == (d["threads"] // 256 * 256 * (64 * 2 + 8) if d["form"] == B.FORM_SPLIT else 0)
+
+
+# Fewer (image, head) units than the dies can be dealt evenly: every die has a run of tiles that follow one another, no longer than the others'.
+@pytest.mark.parametrize("Bsz,H,N,branches,dtype,backward", [
+    (1, 12, 4096, [(1024, 1), (2048, 2), (4096, 4)], "bf16", False), (1, 12, 2500, [(625, 1), (1250, 2), (2500, 4)], "bf16", True),
+    (2, 6, 1024, [(256, 1), (512, 2), (1024, 4)], "f32", False), (3, 6, 1500, [(400, 1), (750, 3), (1500, 5)], "bf16", False),
+])
+def test_dies_take_runs_of_tiles(B, Bsz, H, N, branches, dtype, backward):
+    p = B.launch_describe(Bsz, H, N, branches, None, B.DFA_BF16 if dtype == "bf16" else B.DFA_F32, backward, arrays=True)
+    live = int(np.sum(p["items"][:, 0] >= 0))
+    dies = []
+    for d in range(8):
+        items = [it for it in p["items"][d::8].tolist() if it[0] >= 0]
+        assert len(items) in (live // 8, -(-live // 8))
+        keys = sorted((b, int(p["tiles"][t][0]), int(p["rows"][p["tiles"][t][1]])) for t, b in (it[:2] for it in items))
+        dies.append((keys[0], keys[-1]))
+    assert all(a[1] <= b[0] for a, b in zip(dies, dies[1:]))
+
+
+# bf16 forward, all workgroups at once: those that share a compute unit (i and i + 32 of a die's list) are a long and a short one, and a
+# longest list that has a unit to itself exists wherever units are left over.
+@pytest.mark.parametrize("Bsz,H,N,branches", [(2, 9, 467, [(116, 1), (233, 2), (467, 4)]), (3, 6, 1500, [(400, 1), (750, 3), (1500, 5)]),
+                                              (4, 16, 211, [(26, 1), (52, 2), (105, 4), (211, 8)]), (1, 12, 256, [(64, 1), (128, 2), (256, 4)])])
+def test_long_walks_share_a_unit_with_short_ones(B, Bsz, H, N, branches):
+    p = B.launch_describe(Bsz, H, N, branches, arrays=True)
+    for d in range(8):
+        steps = [int(p["tiles"][it[0]][5]) for it in p["items"][d::8].tolist() if it[0] >= 0]
+        assert len(steps) <= 64
+        twos = max(len(steps) - 32, 0)
+        alone, first, second = steps[twos:32], steps[:twos], steps[32:]
+        assert alone == sorted(alone, reverse=True) and (not twos or not alone or min(alone) >= max(first + second))
+        assert first == sorted(first, reverse=True) and second == sorted(second) and (not twos or first[-1] >= second[-1])
