@@ -186,8 +186,7 @@ __device__ __forceinline__ void issue_block_rows(const BlockSource& src, int key
     if (count == kWalkBlock) {
         const uint32_t off = (uint32_t)l.pos * pitch;
 #pragma unroll
-        for (int u = 0; u < kBlockCopies; ++u)
-            copy16_to_lds(first, off + (l.chunk ^ (kFlip * (u & 1))) + row_of(u) * pitch, lds_addr + 1024u * u);
+        for (int u = 0; u < kBlockCopies; ++u) copy16_to_lds(first, off + (l.chunk ^ (kFlip * (u & 1))), row_of(u) * pitch, lds_addr + 1024u * u);
     } else {
         const int room = max(count - 1, 0);
 #pragma unroll

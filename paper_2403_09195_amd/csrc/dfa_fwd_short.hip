@@ -1,62 +1,179 @@
 // Fused dilated flash attention forward, bf16, for launches that do not fill the chip (one image, small images; the rule is
 // short_plan's).
 //
-// Same arithmetic as dfa_fwd_bf16.hip, whose beat it runs (reference exponent moved only when a block's sums ask for it,
+// Same arithmetic as dfa_fwd_bf16.hip (reference exponent moved only when a block's sums ask for it,
 // probabilities rounded to bf16, row sums over the rounded values on the matrix cores), another split of the work: a
 // workgroup owns 64 query rows and its four waves walk a quarter of the tile's 32-key blocks each (wave w takes blocks w,
 // w + 4, ...), every wave with an online softmax of its own; the four partial results are merged through LDS in fp32, and
 // nothing but out and lse is written.
 //
-// Bound: latency.  Such a launch is as long as one workgroup's start, walk and end, so the walk is cut by four where the rows
+// Bound: a wave's own chain.  Such a launch is as long as one workgroup's start, walk and end, so the walk is cut by four where the rows
 // are, not by more workgroups that have to meet in memory (partial rows written, read back and merged by a second launch).
 // A wave copies its own blocks and waits for nobody until the merge.  The list comes cut into blocks: one record each, all of a
-// wave's records read in one trip to memory at the start and kept in LDS.  Two workgroups to a CU (registers); a beat takes
-// 0.65 us then and as much with one: a wave's own chain of wait, products and exponentials, not the rate of the copies (four
-// waves' 32 KB in that time are 23 bytes per clock and CU; copies from L2 alone reach 52 to 57).  Eight waves that share the copies of a block for 128 rows
+// wave's records read in one trip to memory at the start and kept in LDS.  Two workgroups to a CU (registers, LDS).  A beat takes some 1700
+// cycles with one wave on a SIMD and 2100 with two: 1200 for its 20 MFMAs, 32 exponentials and the rest of the softmax, the others for
+// the next blocks' addresses, records and waits; the waits themselves are 40, and rings of three or four blocks (one workgroup to a CU) were
+// slower (one image of 2000 tokens, 3 heads 16.5 us, 18.1 and 18.7).  Eight waves that share the copies of a block for 128 rows
 // need a barrier per beat and were slower (one image of 2500 tokens, 12 heads: 32.5 against 23.0 us).
-// Measured, us against 256-row tiles with split walks: three images of 1500 tokens, 6 heads 18.2 / 25.7; one of 2500, 12
-// heads 23.0 / 27.2 (18.9 now that the rests of its row groups share tiles); one of 4096, 6 heads 19.6 / 26.4.
+// Measured, us, before the query rows were copied once for all waves, the halves of a beat took turns, the merge took all rows at once and the
+// first reference was taken ahead / now: one 256^2 image, 12 heads 6.66 / 6.13, of 512^2 8.4 / 7.8, four of 1024 tokens, 6 heads 9.9 / 8.4, three of
+// 1500, 6 heads 14.05 / 13.1, one of 2500, 12 heads 15.5 / 14.3.  Against 256-row tiles with split walks, in the launch order of before: three
+// images of 1500 tokens, 6 heads 18.2 / 25.7; one of 2500, 12 heads 23.0 / 27.2; one of 4096, 6 heads 19.6 / 26.4.
 #include "dfa_blocks.h"
 #include "dfa_fwd_beat.h"
+#include <type_traits>
 
 namespace dfa {
 
 namespace {
 
-constexpr int kBuffers = 4;                // 32-key blocks in a wave's LDS: two of K, two of V
+// 16-byte chunk swizzle of the partial results in LDS ([64 rows][16 chunks] fp32 per wave): sixteen consecutive rows spread a chunk
+// column over all banks (the waves' writes), four consecutive rows and every other chunk do so too (the merge's reads).
+__device__ __forceinline__ int result_swizzle(int row) {
+    return (row & 1) | ((row & 2) << 2) | ((row & 4) >> 1) | ((row & 8) >> 1);
+}
 
 // One 32-key block of a wave's share of the list.  Wave-uniform, in scalar registers.
 struct Block {
     int32_t key0;
-    int32_t stride_count;      // stride | count << 24; count 0: past the share's end, a copy of its last block without a valid key
+    // stride | count << 24 | kTurn; count 0: past the share's end, a copy of its last block without a valid key
+    int32_t stride_count;
     float log2_mult[2];        // of the keys' multiplicity for either 32-row block of the tile; -inf: they are skipped
     __device__ __forceinline__ int stride() const { return stride_count & 0xffffff; }
-    __device__ __forceinline__ int count() const { return stride_count >> 24; }
+    __device__ __forceinline__ int count() const { return (stride_count >> 24) & 0x3f; }
+    __device__ __forceinline__ bool turns() const { return stride_count < 0; }
 };
+constexpr int32_t kTurn = (int32_t)0x80000000;     // the block is not full, or other multiplicities than those of the share's block before
 
 // Lane L's record of the wave's share.
 __device__ __forceinline__ u32x4 load_record(const FwdParams& p, const Tile& tile, int wave, int lane) {
     const int i = wave + kWalkWaves * lane, last = tile.nseg - 1;
     const int x = tile.seg_begin + (i <= last ? i : last >= wave ? last - ((last - wave) & (kWalkWaves - 1)) : 0);
+    const int before = tile.seg_begin + (lane > 0 && i - kWalkWaves <= last ? i - kWalkWaves : x - tile.seg_begin);
     const KeySeg r = p.segs[x];
     const float2 m = *reinterpret_cast<const float2*>(p.block_mult + (int64_t)kTileBlocks * x);
-    return u32x4{(uint32_t)r.key0, (uint32_t)(r.stride | ((i <= last ? r.count : 0) << 24)), __builtin_bit_cast(uint32_t, m.x),
+    const float2 mb = *reinterpret_cast<const float2*>(p.block_mult + (int64_t)kTileBlocks * before);
+    const int32_t count = i <= last ? r.count : 0;
+    const bool turn = lane == 0 || count < kWalkBlock || m.x != mb.x || m.y != mb.y;
+    return u32x4{(uint32_t)r.key0, (uint32_t)(r.stride | (count << 24) | (turn ? kTurn : 0)), __builtin_bit_cast(uint32_t, m.x),
                  __builtin_bit_cast(uint32_t, m.y)};
 }
-__device__ __forceinline__ Block read_block(const u32x4* records, int t) {
-    const u32x4 r = records[min(t, 63)];
+__device__ __forceinline__ Block block_of(const u32x4& r, int from_lane) {
     Block b;
-    b.key0 = __builtin_amdgcn_readfirstlane(r[0]);
-    b.stride_count = __builtin_amdgcn_readfirstlane(r[1]);
-    b.log2_mult[0] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(r[2]));
-    b.log2_mult[1] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(r[3]));
+    b.key0 = __builtin_amdgcn_readlane(r[0], from_lane);
+    b.stride_count = __builtin_amdgcn_readlane(r[1], from_lane);
+    const uint32_t m0 = __builtin_amdgcn_readlane(r[2], from_lane), m1 = __builtin_amdgcn_readlane(r[3], from_lane);
+    b.log2_mult[0] = __builtin_bit_cast(float, m0);
+    b.log2_mult[1] = __builtin_bit_cast(float, m1);
     return b;
+}
+__device__ __forceinline__ Block read_block(const u32x4* records, int t) { return block_of(records[min(t, 63)], 0); }
+
+// Waits until at most the youngest `blocks` blocks of this wave's copies are on their way.
+template <int kMost>
+__device__ __forceinline__ void blocks_left(int blocks) {
+    if constexpr (kMost == 0) {
+        copies_left<0>();
+    } else {
+        if (blocks >= kMost) copies_left<kBlockCopies * kMost>();
+        else blocks_left<kMost - 1>(blocks);
+    }
+}
+
+// The beat of dfa_fwd_beat.h with the scores of the next block first and the accumulation of the previous one behind them, so that either
+// needs its operand half a beat later, or frees it half a beat sooner.  `values` waits for the previous block's values, `keys`
+// refills the buffer that the next block's keys leave.  The first beat of a walk (nothing to accumulate) adds up the numerators before
+// they are rounded, as exp_block does.
+template <bool kScores, bool kAccumulate, class Values, class Keys>
+__device__ __forceinline__ void beat_halves(const uint16_t* k_next, const uint16_t* v_prev, const FragLane& fl, const bf16x8 (&qf)[2][4],
+                                            const floatx16 (&s_cur)[2], floatx16 (&s_next)[2], const u32x4 (&p_prev)[2][2], u32x4 (&p_cur)[2][2],
+                                            floatx16 (&oacc)[2][2], float c, const float (&m_ref)[2], float (&psum)[2], const bf16x8& sel,
+                                            Values values, Keys keys) {
+    bf16x8 f[4];                   // fragments: i < 4 d-step i of the keys, then (d block, 16-key step) i - 4 of the values, in f[i & 3]
+    float t[16][2];
+    floatx4 rs[2];
+    float sum[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+    auto load = [&](int i) {
+        if (i < 4) {
+            if (kScores) f[i & 3] = *reinterpret_cast<const bf16x8*>(k_next + (fl.k ^ (16 * i)));
+        } else if (kAccumulate) {
+            f[i & 3] = read_v_frag(v_prev + fl.v + 16 * (i & 1) * kRowElems + 32 * ((i - 4) >> 1));
+        }
+    };
+    auto mfma = [&](int k) {
+        const int i = k >> 1, qb = k & 1;
+        if (i < 4) {
+            if (!kScores) return;
+            floatx16 z;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) z[v] = 0.f;
+            s_next[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i & 3], qf[qb][i], i == 0 ? z : s_next[qb], 0, 0, 0);
+        } else {
+            if (!kAccumulate) return;
+            const int db = (i - 4) >> 1, st = i & 1;
+            oacc[db][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i & 3], __builtin_bit_cast(bf16x8, p_prev[qb][st]), oacc[db][qb], 0, 0, 0);
+        }
+    };
+    load(0);
+    load(1);
+#pragma unroll
+    for (int m = 0; m < 18; ++m) {
+        if (m == 6) values();
+        if (m >= 2 && m <= 12 && m % 2 == 0) load(m / 2 + 1);
+        if (m >= 2) mfma(m - 2);
+        if (m < 16) {                                   // exponents of pair m
+            const int qb = m >> 3, v = 2 * (m & 7);
+            t[m][0] = fmaf(s_cur[qb][v], c, -m_ref[qb]);
+            t[m][1] = fmaf(s_cur[qb][v + 1], c, -m_ref[qb]);
+        }
+        if (m >= 1 && m < 17) {                         // exponentials of pair m - 1
+            t[m - 1][0] = __builtin_amdgcn_exp2f(t[m - 1][0]);
+            t[m - 1][1] = __builtin_amdgcn_exp2f(t[m - 1][1]);
+        }
+        if (m >= 2) {                                   // pair m - 2: rounded into its B-operand slot
+            const int q = m - 2, qb = q >> 3, pr = q & 7;
+            const bf16x2 w = {(__bf16)t[q][0], (__bf16)t[q][1]};
+            p_cur[qb][pr >> 2][pr & 3] = __builtin_bit_cast(uint32_t, w);
+            if (!kAccumulate) {
+                sum[qb][0] += t[q][0];
+                sum[qb][1] += t[q][1];
+            }
+        }
+        if (kAccumulate && (m == 7 || m == 11 || m == 15)) {       // row sums of the 16-key group finished two slots ago
+            const int grp = (m - 7) >> 2, qb = grp >> 1, st = grp & 1;
+            rs[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, __builtin_bit_cast(bf16x8, p_cur[qb][st]),
+                                                             st == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : rs[qb], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (m == 9) keys();                             // the MFMAs with the last of the keys are behind us
+    }
+    if (kAccumulate) {
+        rs[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, __builtin_bit_cast(bf16x8, p_cur[1][1]), rs[1], 0, 0, 0);
+        psum[0] = rs[0][0];
+        psum[1] = rs[1][0];
+    } else {
+        psum[0] = wave_half_sum(sum[0][0] + sum[0][1]);
+        psum[1] = wave_half_sum(sum[1][0] + sum[1][1]);
+    }
+}
+
+// The reference exponents of a walk's first block, taken before its numerators (which settle() would otherwise take twice: 0.1 us).
+__device__ __forceinline__ void first_reference(const floatx16 (&s)[2], float c, float (&m_ref)[2]) {
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        float mx = s[qb][0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[qb][v]);
+        m_ref[qb] = fmaxf(m_ref[qb], wave_half_max(mx) * c);         // +inf, of a block that skips these keys, stays
+    }
 }
 
 __global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dfa_fwd_short_kernel(const FwdParams p) {
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[kWalkWaves][kBuffers * kBlockElems];     // per wave: K, K, V, V
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[kWalkWaves][4 * kBlockElems];     // per wave: K, K, V, V
+    __shared__ __attribute__((aligned(1024))) uint16_t q_lds[kShortRows * kRowElems];
     __shared__ u32x4 records_all[kWalkWaves][64];
+    __shared__ float stats[kWalkWaves][2][kShortRows];                                                   // merge: references and sums
     __shared__ int32_t row_lds[kShortRows];
     __shared__ __attribute__((aligned(16))) uint32_t skips_lds[kWalkWaves], odd_lds[kWalkWaves];
 
@@ -81,38 +198,42 @@ void dfa_fwd_short_kernel(const FwdParams p) {
 
     const BlockSource k_src = block_source(static_cast<const uint16_t*>(p.k) + (int64_t)b * p.skb + (int64_t)h * p.skh, p.skn);
     const BlockSource v_src = block_source(static_cast<const uint16_t*>(p.v) + (int64_t)b * p.svb + (int64_t)h * p.svh, p.svn);
+    const uint16_t* const q_src = static_cast<const uint16_t*>(p.q) + (int64_t)b * p.sqb + (int64_t)h * p.sqh;
     const BlockLane k_lane = block_lane<BlockOrder::kKeys>(lane), v_lane = block_lane<BlockOrder::kValues>(lane);
     const uint32_t k_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, lds[wave]));
     const uint32_t v_addr = k_addr + 2 * kBlockBytes;
 
-    // the share's records and the rows of the Q fragments in one trip to memory, the fragments and the first blocks in the next
+    // the share's records and the row numbers in one trip to memory, the query rows and the first blocks in the next
     u32x4* const records = records_all[wave];
     const u32x4 my_record = load_record(p, tile, wave, lane);
+    // a filler slot of a packed tile holds ~n of a row n of its group: loaded like any row, never stored
+    int32_t q_row[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        q_row[u] = rows[min(16 * wave + 8 * u + (lane >> 3), tile.nrows - 1)];
+        q_row[u] ^= q_row[u] >> 31;
+    }
     if (tid < kShortRows) row_lds[tid] = rows[min(tid, tile.nrows - 1)];
-    // Q fragments: B operand of S^T, lane (j, g) holds Q[row j][16*kk + 8*g .. +7]
-    bf16x8 qf[2][4];
-    auto load_q = [&](int j, int g, int last) {
-        // a filler slot of a packed tile holds ~n of a row n of its group: loaded like any row, never stored
-        int32_t q_row[2] = {rows[min(j, last)], rows[min(kWalkBlock + j, last)]};
-        q_row[0] ^= q_row[0] >> 31;
-        q_row[1] ^= q_row[1] >> 31;
-        const uint16_t* const qp = static_cast<const uint16_t*>(p.q) + (int64_t)b * p.sqb + (int64_t)h * p.sqh;
+    // The query rows are the same for all four waves: a quarter copied by each, whole lines.  (A wave that loaded its fragments itself
+    // touched 32 lines with every load, 32 loads of them to a workgroup.)
+    {
+        const uint32_t q_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, q_lds)) + 2048u * wave;
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) qf[qb][kk] = *reinterpret_cast<const bf16x8*>(qp + (int64_t)q_row[qb] * p.sqn + 16 * kk + 8 * g);
-    };
-    load_q(j, g, tile.nrows - 1);
-    records[lane] = my_record;                 // read back by this wave alone
+        for (int u = 0; u < 2; ++u) {
+            const int slot = 8 * u + (lane >> 3);
+            copy16_to_lds(q_src + (int64_t)q_row[u] * p.sqn + 8 * ((lane & 7) ^ k_swizzle(slot)), q_addr + 1024u * u);
+        }
+    }
     // blocks are walked in pairs: a wave with an odd number of them, or none, ends on a block that is masked as a whole
-    const int n_pairs = max((tile.nseg - wave + 2 * kWalkWaves - 1) / (2 * kWalkWaves), 1);
-    Block blk[3];                              // blocks t, t + 1 and t + 2 of the walk
+    const int n_pairs = max((tile.nseg - wave + 2 * kWalkWaves - 1) / (2 * kWalkWaves), 1), n_blocks = 2 * n_pairs;
+    Block blk[4];                              // blocks t .. t + 3 of the walk
 #pragma unroll
-    for (int x = 0; x < 3; ++x) blk[x] = read_block(records, x);
+    for (int x = 0; x < 4; ++x) blk[x] = block_of(my_record, x);
     auto issue_k = [&](const Block& b, int buf) { issue_block_rows<BlockOrder::kKeys>(k_src, b.key0, b.stride(), b.count(), k_addr + buf * kBlockBytes, k_lane); };
     auto issue_v = [&](const Block& b, int buf) { issue_block_rows<BlockOrder::kValues>(v_src, b.key0, b.stride(), b.count(), v_addr + buf * kBlockBytes, v_lane); };
     issue_k(blk[0], 0);
     issue_k(blk[1], 1);
+    records[lane] = my_record;                 // read back by this wave alone
     // does either block skip a key of the share?
     constexpr uint32_t kMinusInf = 0xff800000u;
     const bool skips = __ballot(my_record[2] == kMinusInf || my_record[3] == kMinusInf) != 0ull;
@@ -133,39 +254,33 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     // its score); while the block skips its keys, m_ref is +inf (every numerator an exact 0) and the reference waits in m_kept.
     float m_ref[2] = {kRefStart, kRefStart}, m_kept[2] = {kRefStart, kRefStart}, bias_cur[2] = {0.f, 0.f}, l_run[2] = {0.f, 0.f};
 
-    // pinned: the compiler waits for the Q loads here and places no vector-memory wait of its own in the walk (it does
-    // not see the copies, and a wait sized for these loads would drain them)
+    // Q fragments: B operand of S^T, lane (j, g) holds Q[row j][16*kk + 8*g .. +7]
+    bf16x8 qf[2][4];
+    copies_left<2 * kBlockCopies>();           // this wave's share of the query rows is there
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qf[qb][kk]));
+        for (int kk = 0; kk < 4; ++kk) qf[qb][kk] = *reinterpret_cast<const bf16x8*>(q_lds + 32 * qb * kRowElems + (fl.k ^ (16 * kk)));
 
-    // Beat t turns block t's scores into numerators, scores block t + 1 and accumulates block t - 1; buffers go by the
-    // parity of the block (odd = t & 1), left = blocks from t on.
+    // Beat t turns block t's scores into numerators, scores block t + 1 and accumulates block t - 1.  K of block t + 3 is fetched from the
+    // middle of the beat on, V of block t + 1 from its end; buffers go by the parity of the block, left = blocks from t on.
     int count = kWalkBlock;                    // valid keys of block t - 1
     // rows past the end of a block become zeros in its V buffer, so that the weights 0 they get meet finite values
     auto zero_tail = [&](int buf, int valid) {
         int ln = lane;                         // its address is worked out here, not kept in a register
         asm volatile("" : "+v"(ln));
         for (int x = ln; x < (kWalkBlock - valid) * 8; x += 64)
-            *reinterpret_cast<u32x4*>(lds[wave] + buf * kBlockElems + valid * kRowElems + 8 * x) = u32x4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<u32x4*>(lds[wave] + (2 + buf) * kBlockElems + valid * kRowElems + 8 * x) = u32x4{0u, 0u, 0u, 0u};
     };
-    auto before = [&](int t, int odd, int left, floatx16 (&s)[2]) {
-        lds_reads_done();                      // K of block t and V of block t - 2 have been read
-        if (left > 2) issue_k(blk[2], odd);
-        issue_v(blk[0], odd);
-        const Block cur = blk[0];
-        const int prev_count = count;
-        count = cur.count();
-        blk[0] = blk[1];
-        blk[1] = blk[2];
-        blk[2] = read_block(records, t + 3);
-        if (left > 2) copies_left<8>(); else copies_left<4>();       // K of block t + 1 and V of block t - 1 are there
-        if (prev_count < kWalkBlock) zero_tail(odd ? 2 : 3, prev_count);
-        if (count < kWalkBlock) {
+    // block t comes up: its keys' places past the end are masked, the references follow its multiplicities
+    auto enter = [&](floatx16 (&s)[2]) {
+        const Block& cur = blk[0];
+        if (!cur.turns()) return;
+        if (cur.count() < kWalkBlock) {
             int ln = lane;
             asm volatile("" : "+v"(ln));
-            mask_block(s, ln >> 5, count);
+            mask_block(s, ln >> 5, cur.count());
         }
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
@@ -182,84 +297,122 @@ void dfa_fwd_short_kernel(const FwdParams p) {
             }
         }
     };
-    const uint16_t* const k0 = lds[wave];
-    const uint16_t* const k1 = k0 + kBlockElems;
-    const uint16_t* const v0 = k0 + 2 * kBlockElems;
-    const uint16_t* const v1 = k0 + 3 * kBlockElems;
-
+    u32x4 coming;                              // record of block t + 4, on its way from LDS from the middle of beat t on
+    // the end of beat t, odd = t & 1: V of block t + 1, and on to that block
+    auto leave = [&](int odd, int left) {
+        if (left > 1) issue_v(blk[1], odd ^ 1);
+        count = blk[0].count();
+        blk[0] = blk[1];
+        blk[1] = blk[2];
+        blk[2] = blk[3];
+        blk[3] = block_of(coming, 0);
+    };
+    const uint16_t* const k_buf = lds[wave];
+    const uint16_t* const v_buf = k_buf + 2 * kBlockElems;
+    float psum[2];
+    auto step = [&](auto first, auto last, int odd, int t, int left, floatx16 (&s_cur)[2], floatx16 (&s_next)[2], const u32x4 (&p_prev)[2][2],
+                    u32x4 (&p_cur)[2][2]) {
+        constexpr bool kFirst = decltype(first)::value, kLast = decltype(last)::value;
+        if (!kFirst) enter(s_cur);
+        // K of block t + 1 is there; sent for after it: V of block t - 1, K of block t + 2 if there is one, V of block t
+        if (!kLast) blocks_left<3>(min(left, 3) - (kFirst ? 1 : 0));
+        const int valid = count;
+        auto values = [&]() {
+            if (kFirst) return;
+            blocks_left<2>(left > 2 ? 2 : 1);  // V of block t - 1; after it K of block t + 2 if there is one, V of block t
+            if (valid < kWalkBlock) zero_tail(odd ^ 1, valid);
+        };
+        auto keys = [&]() {
+            coming = records[min(t + 4, 63)];
+            if (!kLast && left > 3) issue_k(blk[3], odd ^ 1);
+        };
+        beat_halves<!kLast, !kFirst>(k_buf + (odd ^ 1) * kBlockElems, v_buf + (odd ^ 1) * kBlockElems, fl, qf, s_cur, s_next, p_prev, p_cur, oacc, c, m_ref,
+                                     psum, sel, values, keys);
+        settle<true>(s_cur, p_cur, c, m_ref, l_run, oacc, psum);
+        leave(odd, left);
+    };
     floatx16 s_a[2], s_b[2];
     u32x4 p_a[2][2], p_b[2][2];
-    float psum[2];
-    copies_left<4>();                          // K of block 0
-    scores_block(k0, fl, qf, s_a);
-    before(0, 0, 2 * n_pairs, s_a);
-    beat<true, false>(k1, v1, fl, qf, s_a, s_b, p_b, p_a, oacc, c, m_ref, psum, sel);
-    settle<true>(s_a, p_a, c, m_ref, l_run, oacc, psum);
+    using Yes = std::true_type;
+    using No = std::false_type;
+    copies_left<kBlockCopies>();               // K of block 0
+    scores_block(k_buf, fl, qf, s_a);
+    lds_reads_done();
+    if (n_blocks > 2) issue_k(blk[2], 0);
+    issue_v(blk[0], 0);
+    enter(s_a);
+    first_reference(s_a, c, m_ref);
+    step(Yes{}, No{}, 0, 0, n_blocks, s_a, s_b, p_b, p_a);
     for (int s = 0; s + 1 < n_pairs; ++s) {
-        before(2 * s + 1, 1, 3, s_b);
-        beat<true, true>(k0, v0, fl, qf, s_b, s_a, p_a, p_b, oacc, c, m_ref, psum, sel);
-        settle<true>(s_b, p_b, c, m_ref, l_run, oacc, psum);
-        before(2 * s + 2, 0, 2 * (n_pairs - s) - 2, s_a);
-        beat<true, true>(k1, v1, fl, qf, s_a, s_b, p_b, p_a, oacc, c, m_ref, psum, sel);
-        settle<true>(s_a, p_a, c, m_ref, l_run, oacc, psum);
+        step(No{}, No{}, 1, 2 * s + 1, n_blocks - 2 * s - 1, s_b, s_a, p_a, p_b);
+        step(No{}, No{}, 0, 2 * s + 2, n_blocks - 2 * s - 2, s_a, s_b, p_b, p_a);
     }
-    before(2 * n_pairs - 1, 1, 1, s_b);
-    beat<false, true>(k0, v0, fl, qf, s_b, s_a, p_a, p_b, oacc, c, m_ref, psum, sel);
-    settle<true>(s_b, p_b, c, m_ref, l_run, oacc, psum);
+    step(No{}, Yes{}, 1, n_blocks - 1, 1, s_b, s_a, p_a, p_b);
     copies_left<0>();
-    if (count < kWalkBlock) zero_tail(3, count);
-    accumulate_block(v1, fl, p_b, oacc);
+    if (count < kWalkBlock) zero_tail(1, count);
+    accumulate_block(v_buf + kBlockElems, fl, p_b, oacc);
     lds_reads_done();
 
-    // Merge of the four waves, one 32-row block after the other: a wave without a key for a row has a row sum and an
-    // accumulator of zeros under the start exponent, whose weight is an exact 0.
-    static_assert(sizeof(lds[0]) >= (kWalkBlock * kRedPitch + 2 * kWalkBlock) * 4, "a wave's results fit its buffers");
+    // Merge of the four waves: a wave without a key for a row has a row sum and an accumulator of zeros under the start exponent,
+    // whose weight is an exact 0.  All 64 rows at once, four threads a row: one barrier, and the chains of exponentials and divisions of
+    // the two 32-row blocks side by side (1.2 us; 1.6 where the blocks took turns, with 256 threads to 32 rows).
+    static_assert(sizeof(lds[0]) >= kShortRows * kD * 4, "a wave's results fit its buffers");
     float* const red = reinterpret_cast<float*>(lds[wave]);
     // the lane's number worked out afresh: nothing that only this part needs is carried through the walk, which has no register left
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    const int orow = 8 * wave + (ln >> 3), od = (ln & 7) * 8;        // eight threads a row, 16 bytes each
+    const int orow = 16 * wave + (ln >> 2), od = (ln & 3) * 8;       // a thread's row and its first 8 d; 8 more at od + 32
     for (int apart = 0;; apart = 1) {
-        u32x4 skips_any;
         bool odd = false;                                     // a result of this thread's is not finite
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             if (qb * kWalkBlock >= tile.nrows) break;         // uniform for the workgroup
-            if (qb > 0) __syncthreads();                      // everyone has read the first block
-            const floatx16 mine[2] = {oacc[0][qb], oacc[1][qb]};
-            result_to_lds(mine, red, ln);
+            const int r = kWalkBlock * qb + (ln & 31);
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    *reinterpret_cast<float4*>(red + r * kD + 4 * ((8 * db + 2 * t + (ln >> 5)) ^ result_swizzle(r))) =
+                        make_float4(oacc[db][qb][4 * t], oacc[db][qb][4 * t + 1], oacc[db][qb][4 * t + 2], oacc[db][qb][4 * t + 3]);
             if (ln < kWalkBlock) {
-                red[kWalkBlock * kRedPitch + ln] = bias_cur[qb] > -INFINITY ? m_ref[qb] + bias_cur[qb] : m_kept[qb];
-                red[kWalkBlock * kRedPitch + kWalkBlock + ln] = l_run[qb];
+                stats[wave][0][r] = bias_cur[qb] > -INFINITY ? m_ref[qb] + bias_cur[qb] : m_kept[qb];
+                stats[wave][1][r] = l_run[qb];
             }
-            __syncthreads();
-            if (qb == 0) skips_any = *reinterpret_cast<const u32x4*>(skips_lds);
-            const int slot = qb * kWalkBlock + orow;
-            const int32_t n_out = row_lds[slot];
-            if (slot >= tile.nrows || n_out < 0) continue;
+        }
+        __syncthreads();
+        const u32x4 skips_any = *reinterpret_cast<const u32x4*>(skips_lds);
+        const int32_t n_out = row_lds[orow];
+        if (orow < tile.nrows && n_out >= 0) {
             float m = kRefStart;
 #pragma unroll
-            for (int x = 0; x < kWalkWaves; ++x) m = fmaxf(m, reinterpret_cast<const float*>(lds[x])[kWalkBlock * kRedPitch + orow]);
-            float l = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            for (int x = 0; x < kWalkWaves; ++x) m = fmaxf(m, stats[x][0][orow]);
+            float l = 0.f, o[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[e] = 0.f;
 #pragma unroll
             for (int x = 0; x < kWalkWaves; ++x) {
-                const float* const r = reinterpret_cast<const float*>(lds[x]);
-                const float f = __builtin_amdgcn_exp2f(r[kWalkBlock * kRedPitch + orow] - m);
-                l = fmaf(r[kWalkBlock * kRedPitch + kWalkBlock + orow], f, l);
-                const float4 lo = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od);
-                const float4 hi = *reinterpret_cast<const float4*>(r + orow * kRedPitch + od + 4);
-                const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                const float* const r = reinterpret_cast<const float*>(lds[x]) + orow * kD;
+                const float f = __builtin_amdgcn_exp2f(stats[x][0][orow] - m);
+                l = fmaf(stats[x][1][orow], f, l);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = fmaf(a[e], f, o[e]);
+                for (int i = 0; i < 4; ++i) {                 // chunks od / 4, od / 4 + 1 and 8 further on
+                    const float4 a = *reinterpret_cast<const float4*>(r + 4 * ((od / 4 + (i & 1) + 4 * (i & 2)) ^ result_swizzle(orow)));
+                    o[4 * i] = fmaf(a.x, f, o[4 * i]);
+                    o[4 * i + 1] = fmaf(a.y, f, o[4 * i + 1]);
+                    o[4 * i + 2] = fmaf(a.z, f, o[4 * i + 2]);
+                    o[4 * i + 3] = fmaf(a.w, f, o[4 * i + 3]);
+                }
             }
             const float inv = 1.0f / l;
-            bf16x8 ob;
+            bf16x8 ob[2];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                ob[e] = (__bf16)(o[e] * inv);
+            for (int e = 0; e < 16; ++e) {
+                ob[e >> 3][e & 7] = (__bf16)(o[e] * inv);
                 odd |= !(fabsf(o[e]) <= 3.4028234e38f);
             }
-            *reinterpret_cast<bf16x8*>(out + (int64_t)n_out * p.H * kD + od) = ob;
+            uint16_t* const dst = out + (int64_t)n_out * p.H * kD + od;
+            *reinterpret_cast<bf16x8*>(dst) = ob[0];
+            *reinterpret_cast<bf16x8*>(dst + 32) = ob[1];
             if (lse && od == 0) lse[n_out] = (m + __builtin_amdgcn_logf(l)) * kLn2;
         }
 
@@ -274,11 +427,11 @@ void dfa_fwd_short_kernel(const FwdParams p) {
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // everyone has read the partial results; the stores may be on their way
         const u32x4 odd_any = *reinterpret_cast<const u32x4*>(odd_lds);
         end_unless(odd_any[0] | odd_any[1] | odd_any[2] | odd_any[3]);
-        int last = __builtin_amdgcn_readfirstlane(tile.nrows - 1);
-        asm volatile("" : "+s"(last));
-        load_q(ln & 31, ln >> 5, last);
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+                qf[qb][kk] = *reinterpret_cast<const bf16x8*>(q_lds + 32 * qb * kRowElems + (frag_lane(ln).k ^ (16 * kk)));
             m_ref[qb] = kRefStart;
             bias_cur[qb] = l_run[qb] = 0.f;
 #pragma unroll
@@ -289,9 +442,9 @@ void dfa_fwd_short_kernel(const FwdParams p) {
             issue_k(cur, 0);
             issue_v(cur, 0);
             copies_left<0>();
-            if (cur.count() < kWalkBlock) zero_tail(2, cur.count());
+            if (cur.count() < kWalkBlock) zero_tail(0, cur.count());
             lds_reads_done();
-            scores_block(k0, fl, qf, s_a);
+            scores_block(k_buf, fl, qf, s_a);
             if (cur.count() < kWalkBlock) mask_block(s_a, ln >> 5, cur.count());
             const bool on[2] = {cur.log2_mult[0] > -INFINITY, cur.log2_mult[1] > -INFINITY};
 #pragma unroll
@@ -306,7 +459,7 @@ void dfa_fwd_short_kernel(const FwdParams p) {
             }
             exp_block(s_a, c, m_ref, p_a, psum);
             settle<false>(s_a, p_a, c, m_ref, l_run, oacc, psum);
-            accumulate_block(v0, fl, p_a, oacc, on[0], on[1]);
+            accumulate_block(v_buf, fl, p_a, oacc, on[0], on[1]);
             lds_reads_done();
         }
     }

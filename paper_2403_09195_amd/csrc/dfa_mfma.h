@@ -109,6 +109,23 @@ __device__ __forceinline__ void copy16_to_lds(const void* gbase, uint32_t lane_b
                  : "memory", "m0");
 }
 
+// The same with a wave-uniform offset beside the lane's, added in the slot that the write of m0 has to be followed by anyway.
+__device__ __forceinline__ void copy16_to_lds(const void* gbase, uint32_t lane_byte_offset, uint32_t uniform_offset, uint32_t lds_addr) {
+    uint32_t offset;
+    asm volatile("s_mov_b32 m0, %1\n\tv_add_u32_e32 %0, %3, %2\n\tglobal_load_lds_dwordx4 %0, %4"
+                 : "=&v"(offset)
+                 : "s"(lds_addr), "v"(lane_byte_offset), "s"(uniform_offset), "s"(gbase)
+                 : "memory", "m0");
+}
+
+// The same, every lane's source given as an address.
+__device__ __forceinline__ void copy16_to_lds(const void* lane_src, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"(lds_addr), "v"(lane_src)
+                 : "memory", "m0");
+}
+
 // 4 bytes per lane: lane L's word lands at lds_addr + 4*L.
 __device__ __forceinline__ void copy4_to_lds(const float* lane_src, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
