@@ -207,4 +207,25 @@ __device__ __forceinline__ void result_to_lds(const floatx16 (&acc)[2], float* r
                 make_float4(acc[db][4 * t], acc[db][4 * t + 1], acc[db][4 * t + 2], acc[db][4 * t + 3]);
 }
 
+// The same for 64 rows, unpadded: 16-byte chunk c of row r sits at chunk c ^ result_swizzle(r).  Sixteen consecutive rows spread a chunk column
+// over all banks (these writes), four consecutive rows and every other chunk do so too (the merges' reads: four threads a row).
+__device__ __forceinline__ int result_swizzle(int row) {
+    return (row & 1) | ((row & 2) << 2) | ((row & 4) >> 1) | ((row & 8) >> 1);
+}
+// half 0: rows 0 to 31, half 1: rows 32 to 63
+__device__ __forceinline__ void half_to_lds(const floatx16& d0, const floatx16& d1, float* region, int half, int lane) {
+    const int r = kWalkBlock * half + (lane & 31);
+    const floatx16 acc[2] = {d0, d1};
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            *reinterpret_cast<float4*>(region + r * kD + 4 * ((8 * db + 2 * t + (lane >> 5)) ^ result_swizzle(r))) =
+                make_float4(acc[db][4 * t], acc[db][4 * t + 1], acc[db][4 * t + 2], acc[db][4 * t + 3]);
+}
+// Chunk i of the four that a thread takes of a row: d = od .. od + 7 and 32 further on, od = 8 * (thread & 3).
+__device__ __forceinline__ float4 result_chunk(const float* region, int row, int od, int i) {
+    return *reinterpret_cast<const float4*>(region + row * kD + 4 * ((od / 4 + (i & 1) + 4 * (i & 2)) ^ result_swizzle(row)));
+}
+
 }  // namespace dfa

@@ -12,6 +12,10 @@
 // (dq working out delta) ended each on a round of its own that was nearly empty: one image of 2500 tokens, 12 heads has 528 dq
 // and 1056 dk/dv workgroups.  Forward and backward of that image 81.7 -> 73.7 us in one launch for all gradients, of four images
 // of 1024 tokens, 6 heads 37.6 -> 34.9 us.
+// The rows that a workgroup owns are the same for its four waves: a quarter copied to LDS by each, whole lines, where every wave loaded its
+// fragments itself before (32 lines touched per load, 16 loads a wave for dq: 2.8 us from the row numbers to the last one issued), and the
+// waves' sums go out behind one barrier.  Backward alone, us, before / now: four images of 1024 tokens, 6 heads 23.9 / 20.6, one of 2500, 12 heads
+// 47.6 / 42.9, one of 256 9.2 / 8.4, 16 of 512 90.7 / 78.3.
 #include "dfa_bwd_bf16.h"
 
 namespace dfa {
@@ -33,39 +37,53 @@ __device__ __forceinline__ KeySeg read_record(const KeySeg* records, int t) {
     return k;
 }
 
-// Sum of the four waves' [32][64] results, times `scale`, written to rows of a contiguous [B, N, H, D] tensor (`grad`
-// points at image b, head h; `rows` in LDS).  Every wave has finished with its own region of LDS.
-__device__ __forceinline__ void write_sum(const floatx16 (&acc)[2], uint16_t (*lds)[kBuffers * kPairElems], int tid, const int32_t* rows,
-                                          int nrows, uint16_t* grad, int64_t row_pitch, float scale) {
-    result_to_lds(acc, reinterpret_cast<float*>(lds[tid >> 6]), tid & 63);
-    __syncthreads();
-    const int row = tid >> 3, d = (tid & 7) * 8;
-    if (row < nrows) {
-        float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int x = 0; x < kWalkWaves; ++x) {
-            const float* const r = reinterpret_cast<const float*>(lds[x]) + row * kRedPitch + d;
-            const float4 lo = *reinterpret_cast<const float4*>(r), hi = *reinterpret_cast<const float4*>(r + 4);
-            const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] += a[e];
-        }
-        bf16x8 ob;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ob[e] = (__bf16)(o[e] * scale);
-        *reinterpret_cast<bf16x8*>(grad + (int64_t)rows[row] * row_pitch + d) = ob;
-    }
-}
-
 // What a workgroup keeps in LDS: two of them fit a CU.
 struct ShortLds {
     uint16_t blocks[kWalkWaves][kBuffers * kPairElems];
     float stats[kWalkWaves][kBuffers][2 * kWalkBlock];         // dk/dv: lse and -delta of a block
     KeySeg records[kWalkWaves][kMostBlocks];
+    uint16_t own[kShortRows * kRowElems];                      // dq: query rows; dk/dv: key rows, then value rows
     int32_t rows[kShortRows];
 };
 static_assert(sizeof(ShortLds) <= 80 * 1024, "two workgroups to a CU");
-static_assert(sizeof(ShortLds::blocks) / kWalkWaves >= kWalkBlock * kRedPitch * 4, "a wave's results fit its blocks");
+static_assert(sizeof(ShortLds::blocks) / kWalkWaves >= kShortRows * kD * 4, "a wave's results fit its blocks");
+
+// The two [32][64] results of every wave into its blocks' place, rows 0 to 31 and 32 to 63: what sum_of_waves adds up.
+__device__ __forceinline__ void results_to_lds(const floatx16 (&first)[2], const floatx16 (&second)[2], ShortLds& mem, int tid) {
+    float* const mine = reinterpret_cast<float*>(mem.blocks[tid >> 6]);
+    half_to_lds(first[0], first[1], mine, 0, tid & 63);
+    half_to_lds(second[0], second[1], mine, 1, tid & 63);
+    __syncthreads();
+}
+// Row tid / 4 of the sum of the waves' results times `scale`, this thread's 16 d of it (see result_chunk), to dst[od ..] and dst[od + 32 ..].
+__device__ __forceinline__ void sum_of_waves(const ShortLds& mem, int tid, float scale, uint16_t* dst) {
+    const int row = tid >> 2, od = (tid & 3) * 8;
+    float o[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[e] = 0.f;
+#pragma unroll
+    for (int x = 0; x < kWalkWaves; ++x)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 a = result_chunk(reinterpret_cast<const float*>(mem.blocks[x]), row, od, i);
+            o[4 * i] += a.x;
+            o[4 * i + 1] += a.y;
+            o[4 * i + 2] += a.z;
+            o[4 * i + 3] += a.w;
+        }
+    bf16x8 ob[2];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) ob[e >> 3][e & 7] = (__bf16)(o[e] * scale);
+    *reinterpret_cast<bf16x8*>(dst + od) = ob[0];
+    *reinterpret_cast<bf16x8*>(dst + od + 32) = ob[1];
+}
+
+// One wave-level copy of eight of the workgroup's own rows, LDS rows 8 * u8 .. +7 of a [rows][64] tile with stage_swizzle's chunks: lane L brings
+// 16 bytes of row 8 * u8 + L / 8, `row` in memory.
+__device__ __forceinline__ void copy_own_rows(const uint16_t* base, int64_t sn, int32_t row, int u8, uint32_t lds_addr, int lane) {
+    const int slot = 8 * u8 + (lane >> 3);
+    copy16_to_lds(base + row * sn + 8 * ((lane & 7) ^ stage_swizzle(slot)), lds_addr);
+}
 
 // -delta = -(dout . out) and lse in base-2 units of every row: 8 lanes a row, 16 bytes each.  grid = (8 * rows of one image /
 // 256, B): one image is indexed with 32-bit arithmetic.
@@ -122,35 +140,64 @@ __device__ __forceinline__ void dq_short(const BwdParams& p, ShortLds& mem, cons
     // one trip to memory for the records and the row numbers, one for everything these lead to
     KeySeg* const records = mem.records[wave];
     const KeySeg my_record = p.segs[tile.seg_begin + min(wave + kWalkWaves * lane, tile.nseg - 1)];
-    const int32_t row[2] = {rows[min(j, tile.nrows - 1)], rows[min(kWalkBlock + j, tile.nrows - 1)]};
-    if (tid < kShortRows) row_lds[tid] = rows[min(tid, tile.nrows - 1)];
+    int32_t copy_row[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) copy_row[u] = rows[min(16 * wave + 8 * u + (lane >> 3), tile.nrows - 1)];
+    const int32_t lane_row = rows[min(lane, tile.nrows - 1)];
+    if (tid < kShortRows) row_lds[tid] = lane_row;
     records[lane] = my_record;                         // read back by this wave alone
     const int n = (tile.nseg - wave + kWalkWaves - 1) / kWalkWaves;
     const uint32_t addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, lds[wave]));
-    auto issue = [&](const KeySeg& blk, int buf) {
+    auto issue_keys = [&](const KeySeg& blk, int buf) {
         issue_block_rows<BlockOrder::kWalked>(k_src, blk.key0, blk.stride, blk.count, addr + buf * kPairBytes, cl);
+    };
+    auto issue_values = [&](const KeySeg& blk, int buf) {
         issue_block_rows<BlockOrder::kWalked>(v_src, blk.key0, blk.stride, blk.count, addr + buf * kPairBytes + kBlockBytes, cl);
     };
+    // The tile's own rows, a quarter copied by each wave: queries and (in the waves' places for the values of their second blocks, which
+    // are fetched once everyone has read them) dout; their lse by the first wave, -delta by the second.
+    {
+        const uint32_t own_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, mem.own)) + 2048u * wave;
+        const uint32_t stat_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, mem.stats)) + 256u * wave;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            copy_own_rows(qp, p.sqn, copy_row[u], u, own_addr + 1024u * u, lane);
+            copy_own_rows(gp, g_pitch, copy_row[u], u, addr + kPairBytes + kBlockBytes + 1024u * u, lane);
+        }
+        if (wave < 2) copy4_to_lds((wave == 0 ? p.lse2 : p.ndelta) + stat_bh + lane_row, stat_addr);
+    }
     KeySeg cur = read_record(records, 0), nx = read_record(records, 1);
+    if (n > 0) {
+        issue_keys(cur, 0);
+        issue_values(cur, 0);
+    }
+    if (n > 1) {
+        issue_keys(nx, 1);
+        copies_left<3 * kBlockCopies>();
+    } else if (n > 0) {
+        copies_left<2 * kBlockCopies>();
+    } else {
+        copies_left<0>();
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // everyone's own rows are there
+    const int frag = j * kRowElems + 8 * (g ^ stage_swizzle(j));
+    // as B operands (16 d x 32 rows): lane (j, g) holds row j, d 16*kk + 8*g .. +7
+    bf16x8 qf[2][4], gf[2][4];
     float my_l2[2], my_nd[2];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
-        my_l2[blk] = p.lse2[stat_bh + row[blk]];
-        my_nd[blk] = p.ndelta[stat_bh + row[blk]];
-    }
-    // the tile's own rows as B operands (16 d x 32 rows): lane (j, g) holds row j, d 16*kk + 8*g .. +7
-    bf16x8 qf[2][4], gf[2][4];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
+        const uint16_t* const g_rows = lds[2 * blk + (j >> 4)] + kPairElems + kBlockElems - 16 * (j >> 4) * kRowElems;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            qf[blk][kk] = *reinterpret_cast<const bf16x8*>(qp + row[blk] * p.sqn + 16 * kk + 8 * g);
-            gf[blk][kk] = *reinterpret_cast<const bf16x8*>(gp + row[blk] * g_pitch + 16 * kk + 8 * g);
+            qf[blk][kk] = *reinterpret_cast<const bf16x8*>(mem.own + kWalkBlock * blk * kRowElems + (frag ^ (16 * kk)));
+            gf[blk][kk] = *reinterpret_cast<const bf16x8*>(g_rows + (frag ^ (16 * kk)));
         }
-    if (n > 0) issue(cur, 0);
-    if (n > 1) issue(nx, 1);
+        my_l2[blk] = (&mem.stats[0][0][0])[kWalkBlock * blk + j];
+        my_nd[blk] = (&mem.stats[0][0][0])[kShortRows + kWalkBlock * blk + j];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // everyone has read them
+    if (n > 1) issue_values(nx, 1);
 
-    const int frag = j * kRowElems + 8 * (g ^ stage_swizzle(j));
     const TransposedLane tl = transposed_lane(lane);
     const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, p.scale * kLog2e)));
     floatx16 acc[2][2];                                // [own 32-row block][d block], transposed
@@ -158,19 +205,6 @@ __device__ __forceinline__ void dq_short(const BwdParams& p, ShortLds& mem, cons
     for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
         for (int db = 0; db < 2; ++db) acc[blk][db] = zero16();
-
-    // pinned: the compiler waits for the own rows here and places no vector-memory wait of its own in the loop (it does
-    // not see the copies, and a wait sized for these loads would drain them)
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            asm volatile("" : "+v"(qf[blk][kk]));
-            asm volatile("" : "+v"(gf[blk][kk]));
-        }
-        asm volatile("" : "+v"(my_l2[blk]));
-        asm volatile("" : "+v"(my_nd[blk]));
-    }
 
     for (int t = 0; t < n; ++t) {
         const KeySeg nx2 = read_record(records, t + 2);
@@ -212,17 +246,16 @@ __device__ __forceinline__ void dq_short(const BwdParams& p, ShortLds& mem, cons
                     acc[blk][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt, __builtin_bit_cast(bf16x8, pb[blk][st]), acc[blk][db], 0, 0, 0);
             }
         lds_reads_done();
-        if (t + 2 < n) issue(nx2, t & 1);
+        if (t + 2 < n) {
+            issue_keys(nx2, t & 1);
+            issue_values(nx2, t & 1);
+        }
         cur = nx;
         nx = nx2;
     }
 
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-        if (blk * kWalkBlock >= tile.nrows) break;     // uniform for the workgroup
-        if (blk > 0) __syncthreads();                  // everyone has read the first block
-        write_sum(acc[blk], lds, tid, row_lds + blk * kWalkBlock, tile.nrows - blk * kWalkBlock, grad, g_pitch, p.scale);
-    }
+    results_to_lds(acc[0], acc[1], mem, tid);
+    if (tid >> 2 < tile.nrows) sum_of_waves(mem, tid, p.scale, grad + (int64_t)row_lds[tid >> 2] * g_pitch);
 }
 
 // dk and dv of 32 rows, half `sub` of the tile: they are keys, the lists are walked as the queries that see them.
@@ -259,15 +292,8 @@ __device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, co
 
     KeySeg* const records = mem.records[wave];
     const KeySeg my_record = p.segs[tile.seg_begin + min(wave + kWalkWaves * lane, tile.nseg - 1)];
-    const int64_t row = rows[min(j, nrows - 1)];
-    if (tid < kWalkBlock) row_lds[tid] = (int32_t)row;
-    // the own rows as B operands (16 d x 32 rows): lane (j, g) holds row j, d 16*kk + 8*g .. +7
-    bf16x8 kf[4], vf[4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        kf[kk] = *reinterpret_cast<const bf16x8*>(kp + row * p.skn + 16 * kk + 8 * g);
-        vf[kk] = *reinterpret_cast<const bf16x8*>(vp + row * p.svn + 16 * kk + 8 * g);
-    }
+    const int32_t copy_row = rows[min(8 * wave + (lane >> 3), nrows - 1)];
+    if (tid < kWalkBlock) row_lds[tid] = rows[min(tid, nrows - 1)];
     records[lane] = my_record;                         // read back by this wave alone
     const int n = (tile.nseg - wave + kWalkWaves - 1) / kWalkWaves;
     const uint32_t addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, lds[wave]));
@@ -279,22 +305,33 @@ __device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, co
         copy4_to_lds(lane_stat + (blk.key0 + (int64_t)blk.stride * min(j, blk.count - 1)), stat_addr + buf * (2 * kWalkBlock * 4));
     };
     constexpr int kCopies = 2 * kBlockCopies + 1;
+    // the own rows, a quarter of keys and values copied by each wave
+    {
+        const uint32_t own_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, mem.own)) + 1024u * wave;
+        copy_own_rows(kp, p.skn, copy_row, wave, own_addr, lane);
+        copy_own_rows(vp, p.svn, copy_row, wave, own_addr + kBlockBytes, lane);
+    }
     KeySeg cur = read_record(records, 0), nx = read_record(records, 1);
     if (n > 0) issue(cur, 0);
     if (n > 1) issue(nx, 1);
+    if (n > 1) copies_left<2 * kCopies>();
+    else if (n > 0) copies_left<kCopies>();
+    else copies_left<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // everyone's own rows are there
 
     const int frag = j * kRowElems + 8 * (g ^ stage_swizzle(j));
+    // as B operands (16 d x 32 rows): lane (j, g) holds row j, d 16*kk + 8*g .. +7
+    bf16x8 kf[4], vf[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        kf[kk] = *reinterpret_cast<const bf16x8*>(mem.own + (frag ^ (16 * kk)));
+        vf[kk] = *reinterpret_cast<const bf16x8*>(mem.own + kBlockElems + (frag ^ (16 * kk)));
+    }
     const TransposedLane tl = transposed_lane(lane);
     const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, p.scale * kLog2e)));
     floatx16 dk_acc[2], dv_acc[2];                     // [d block], transposed: lane = own row
 #pragma unroll
     for (int db = 0; db < 2; ++db) dk_acc[db] = dv_acc[db] = zero16();
-    // pinned, as in the dq kernel
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        asm volatile("" : "+v"(kf[kk]));
-        asm volatile("" : "+v"(vf[kk]));
-    }
 
     for (int t = 0; t < n; ++t) {
         const KeySeg nx2 = read_record(records, t + 2);
@@ -332,9 +369,9 @@ __device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, co
         nx = nx2;
     }
 
-    write_sum(dk_acc, lds, tid, row_lds, nrows, grad_k, g_pitch, p.scale);     // dk = scale dS^T q
-    __syncthreads();                                   // everyone has read dk
-    write_sum(dv_acc, lds, tid, row_lds, nrows, grad_v, g_pitch, 1.0f);
+    results_to_lds(dk_acc, dv_acc, mem, tid);
+    const int own = (tid >> 2) & (kWalkBlock - 1);     // threads 0 to 127 write dk = scale dS^T q, the others dv
+    if (own < nrows) sum_of_waves(mem, tid, tid < 128 ? p.scale : 1.0f, (tid < 128 ? grad_k : grad_v) + (int64_t)row_lds[own] * g_pitch);
 }
 
 // The dq workgroups (an item each, padded to a multiple of the dies), then the dk/dv workgroups: the longer ones start first.

@@ -27,12 +27,6 @@ namespace dfa {
 
 namespace {
 
-// 16-byte chunk swizzle of the partial results in LDS ([64 rows][16 chunks] fp32 per wave): sixteen consecutive rows spread a chunk
-// column over all banks (the waves' writes), four consecutive rows and every other chunk do so too (the merge's reads).
-__device__ __forceinline__ int result_swizzle(int row) {
-    return (row & 1) | ((row & 2) << 2) | ((row & 4) >> 1) | ((row & 8) >> 1);
-}
-
 // One 32-key block of a wave's share of the list.  Wave-uniform, in scalar registers.
 struct Block {
     int32_t key0;
@@ -368,12 +362,7 @@ void dfa_fwd_short_kernel(const FwdParams p) {
         for (int qb = 0; qb < 2; ++qb) {
             if (qb * kWalkBlock >= tile.nrows) break;         // uniform for the workgroup
             const int r = kWalkBlock * qb + (ln & 31);
-#pragma unroll
-            for (int db = 0; db < 2; ++db)
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    *reinterpret_cast<float4*>(red + r * kD + 4 * ((8 * db + 2 * t + (ln >> 5)) ^ result_swizzle(r))) =
-                        make_float4(oacc[db][qb][4 * t], oacc[db][qb][4 * t + 1], oacc[db][qb][4 * t + 2], oacc[db][qb][4 * t + 3]);
+            half_to_lds(oacc[0][qb], oacc[1][qb], red, qb, ln);
             if (ln < kWalkBlock) {
                 stats[wave][0][r] = bias_cur[qb] > -INFINITY ? m_ref[qb] + bias_cur[qb] : m_kept[qb];
                 stats[wave][1][r] = l_run[qb];
@@ -391,12 +380,11 @@ void dfa_fwd_short_kernel(const FwdParams p) {
             for (int e = 0; e < 16; ++e) o[e] = 0.f;
 #pragma unroll
             for (int x = 0; x < kWalkWaves; ++x) {
-                const float* const r = reinterpret_cast<const float*>(lds[x]) + orow * kD;
                 const float f = __builtin_amdgcn_exp2f(stats[x][0][orow] - m);
                 l = fmaf(stats[x][1][orow], f, l);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {                 // chunks od / 4, od / 4 + 1 and 8 further on
-                    const float4 a = *reinterpret_cast<const float4*>(r + 4 * ((od / 4 + (i & 1) + 4 * (i & 2)) ^ result_swizzle(orow)));
+                for (int i = 0; i < 4; ++i) {
+                    const float4 a = result_chunk(reinterpret_cast<const float*>(lds[x]), orow, od, i);
                     o[4 * i] = fmaf(a.x, f, o[4 * i]);
                     o[4 * i + 1] = fmaf(a.y, f, o[4 * i + 1]);
                     o[4 * i + 2] = fmaf(a.z, f, o[4 * i + 2]);
