@@ -615,11 +615,6 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     // 64 rows to a workgroup: more rows than this cannot fit
     if ((uint64_t)B * H * N > (uint64_t)most * kShortRows || full.items.size() > most || N >= kMaxCutStride) return false;
     build_plan(B, H, N, br, nb, offsets, order_mode, chip, true, plan, kShortRows / kBlockRows);
-    auto estimate = [&](const HostPlan& p) {
-        const LaunchSize size = launch_size(p);
-        const double blocks = (double)cut_size(p).longest;
-        return size.live <= chip.fwd_slots() / kFwdWorkgroupsPerCu ? 6.5 + 0.18 * blocks : size.live <= chip.fwd_slots() ? 8.5 + 0.25 * blocks : 12.5 + 0.26 * blocks;
-    };
     // A little more than one round of workgroups, or than one to a CU: fewer of them where the rests of row groups share tiles (see
     // kTailBlocks).
     const int64_t slots = chip.fwd_slots(), one = slots / kFwdWorkgroupsPerCu;
@@ -635,28 +630,37 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
                                         (live <= bound && longest <= cut_size(*plan).longest)))
             *plan = std::move(shared);
     }
-    if (plan->items.size() > most || cut_size(*plan).longest > kShortBlocks) return false;
-    const LaunchSize whole = launch_size(full);
-    if (plan->items.size() > near) {
-        // two rounds and more: see kManyMargin
-        const bool split = !full.split_wgs.empty();
-        if (split ? plan->items.size() <= (size_t)chip.fwd_slots() * 11 / 8 : full.packed_tiles && whole.longest < kManySteps) return false;
-        const double per_slot = 512.0 / chip.fwd_slots();
-        const double short_us = 7.1 + per_slot * (0.0046 * plan->items.size() + 0.00078 * launch_size(*plan).blocks);
-        const double other_us = split               ? 16.2 + per_slot * 0.0034 * whole.steps + 0.13 * whole.longest
-                                : full.packed_tiles ? 3.6 + per_slot * (0.0174 * full.items.size() + 0.0011 * whole.steps) + 1.18 * whole.longest
-                                                    : 3.6 + per_slot * (0.0066 * full.items.size() + 0.00215 * whole.steps) + 0.925 * whole.longest;
-        if (short_us * kManyMargin >= other_us) return false;
-        cut_blocks(plan);
-        return true;
-    }
-    const double short_us = estimate(*plan);
-    const LaunchSize size = launch_size(*plan);
+    const int32_t longest = (int32_t)cut_size(*plan).longest;
+    if (plan->items.size() > most || longest > kShortBlocks) return false;
+    const LaunchSize size = launch_size(*plan), whole = launch_size(full);
+    const bool split = !full.split_wgs.empty();
     cut_blocks(plan);
-    if (!full.split_wgs.empty()) return true;
-    const bool one_to_a_cu = size.live <= chip.fwd_slots() / kFwdWorkgroupsPerCu;
-    if (one_to_a_cu && std::any_of(full.segs.begin(), full.segs.end(), [](const KeySeg& s) { return s.count % 64 != 0; })) return true;
-    return short_us < (full.packed_tiles ? 7.1 + 1.3 * whole.longest : 4.6 + 1.2 * whole.longest);
+    const bool one_to_a_cu = size.live <= one;
+    if (!split && one_to_a_cu && plan->items.size() <= near && std::any_of(full.segs.begin(), full.segs.end(), [](const KeySeg& s) { return s.count % 64 != 0; })) return true;
+    if (split && plan->items.size() <= near) return true;
+    if (!split && !full.packed_tiles && whole.longest <= 1) return false;
+    // packed tiles that are full walk like tiles of one group
+    const bool shared = full.packed_tiles && std::any_of(full.tiles.begin(), full.tiles.end(), [](const Tile& t) { return t.nrows != kTileRows; });
+    if (!split && full.packed_tiles && !shared && plan->items.size() > near && whole.longest < kFullSteps) return false;
+    // us, see kShortMargin
+    const double per_slot = 512.0 / slots;
+    const double items = per_slot * plan->items.size(), live = per_slot * size.live, blocks = per_slot * size.blocks;
+    const double tiles = per_slot * full.items.size(), steps = per_slot * whole.steps;
+    const bool one_round = (int64_t)plan->items.size() <= slots, live_fit = size.live <= slots;
+    const double short_us = one_to_a_cu ? 5.2 + 0.0016 * items + 0.184 * longest
+                            : one_round ? 6.3 + 0.0004 * blocks + 0.113 * longest
+                            : live_fit  ? 5.7 + 0.0029 * items + 0.00012 * blocks + 0.186 * longest
+                                        : 4.9 + 0.0025 * items + 0.0057 * live + 0.00053 * blocks + 0.052 * longest;
+    const bool few = (int64_t)full.items.size() <= one, fit = (int64_t)full.items.size() <= slots;
+    const double other_us = split               ? (shared ? 23.3 + 0.002 * steps : 12.6 + 0.0043 * steps)
+                            : full.packed_tiles ? (few   ? 6.9 + 0.0025 * tiles + 0.00012 * steps + 1.27 * whole.longest
+                                                   : fit ? 10.7 - 0.0044 * tiles + 0.00167 * steps + 0.89 * whole.longest
+                                                         : 7.4 + 0.0044 * tiles + 0.0025 * steps + 0.89 * whole.longest)
+                            : few ? 4.1 + 0.002 * tiles + 0.0002 * steps + 1.2 * whole.longest
+                            : fit ? 3.6 + 0.005 * tiles + 0.0025 * steps + 0.86 * whole.longest
+                                  : 5.5 + 0.0031 * tiles + 0.0037 * steps + 0.65 * whole.longest;
+    const double margin = live_fit && plan->items.size() > near && !one_to_a_cu && !split ? kIdleMargin : !live_fit && !(split ? shared : full.packed_tiles) ? kWholeMargin : kShortMargin;
+    return short_us * margin < other_us;
 }
 
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,

@@ -150,22 +150,8 @@ bool wants_row_tiles(const HostPlan& plan);
 
 // Launches that do not fill the chip are as long as one workgroup's start, walk and end.  The short-launch forward kernel cuts
 // the walk by four inside the workgroup and gives it a quarter of the rows, but copies every key block for 64 rows where the
-// other kernels copy it for 256.  It is considered where its workgroups start (nearly) all at once, up to an eighth more than there are
-// slots (see kTailBlocks for how they are counted, kManyMargin for launches past that), and no list has more than kShortBlocks blocks.  There it takes the place of every split launch; against whole tiles both times, in us, go by the longest list: 4.6 +
-// 1.2 per 64-key step of a 256-row tile (7.1 + 1.3 where tiles pack several row groups), against 6.5 + 0.18 per 32-key block
-// with one workgroup to a CU, 8.5 + 0.25 with two, 12.5 + 0.26 where some CUs run a second round.  With one to a CU, lists that do
-// not fill their last step stay with the short kernel whatever the times: it clears the rows past a list's end, where the
-// 256-row kernel gives them weight 0, which makes NaN of an infinite value, and its start outweighs the walk by 2 us at most
-// (whole tiles 5.7 against 7.7), less than the host takes for the call.  Over 271 shapes (1
-// to 24 heads, 100 to 8192 tokens, 1 to 16 images, plain windows, single dilated branches, two to four branches) the choice by times
-// is within 1 % of the faster form but for four, the worst two 14 % (8 images of 784 tokens, 3 heads, windows of 392 at rate 3,
-// short 9.5 / 8.4) and 12 % (2 of 2614, 3 heads, windows of 201, whole tiles 8.7 / 9.8).
-// Measured, us, short against split: 3 images of 1500 tokens, 6 heads (540 workgroups) 19.3 / 26.4; one of 2500, 12 heads (528)
-// 24.3 / 28.6; one of 4096, 6 heads (384) 20.7 / 28.3, past the range 12 heads (768) 38.4 / 35.3; lists of 4096 keys (128
-// blocks), 1 head (64) 29.4 / 27.1.  Against whole tiles: windows of 512, 9 heads (576) 20.0 / 14.9; windows of 50, 8 images of
-// 200 tokens, 16 heads (512) 10.3 / 6.3; windows of 512, 2 images of 2048, 5 heads (320) 11.7 / 14.2; one of 256 tokens, 12
-// heads, four branches (192) 6.9 / 16.5.  Builds the plan of such a launch (64-row tiles, lists cut into blocks) when it is to
-// be taken; `full` is the plan of 256-row tiles, split where split_plan cuts it.
+// other kernels copy it for 256.  It is considered up to two and a quarter times as many workgroups as there are slots, where no list has
+// more than kShortBlocks blocks, and taken where it is estimated to be the faster one (kShortMargin).
 constexpr int kShortBlocks = 64;
 // Plans of more workgroups than start at once, or of up to a quarter more than there are CUs, are tried with the rests of row groups sharing
 // tiles: fewer workgroups, some of which walk the union of two lists.  That is taken where the lists have kTailBlocks blocks or
@@ -177,19 +163,25 @@ constexpr int kShortBlocks = 64;
 // (264 / 240) 15.8 / 13.6, one of 2229, 12 heads, in whole tiles before, (528) 36.5 / 20.9; short lists that get longer: one of 1386, 16
 // heads, four branches (552 / 504, 12 blocks on average) 14.9 / 17.0, one of 654, 16 heads (288 / 256, 9 blocks) 9.9 / 11.2.
 constexpr int kTailBlocks = 19;
-// From nine eighths of the slots up to twice that, the form takes the place of split launches and whole tiles where its estimate times
-// kManyMargin is the shorter one.  The estimates, us, are linear in the plan, fitted to 270 shapes (3 to 16 heads, 200 to 8000 tokens, 1 to 16
-// images, one to four branches) with residuals of 9 to 14 %: short 7.1 + 0.0046 per workgroup + 0.00078 per 32-key block; split 16.2 + 0.0034 per
-// 64-key step + 0.13 per step of the longest list; whole tiles 3.6 + 0.0066 per tile + 0.00215 per step + 0.925 per step of the longest list, where
-// tiles pack several row groups 3.6 + 0.0174 + 0.0011 + 1.18.  Two kinds stay, where the gain is small and the estimates are not that
-// sharp: split launches up to eleven eighths of the slots, whose second round would be nearly empty (one image of 5504 tokens, 6 heads,
-// four branches, 624 workgroups 31.5 / 33.5), and packed tiles whose longest list is under kManySteps steps (16 of 505, 8 heads
-// 19.9 / 23.8).  Over 1734 drawn shapes that the estimates send here 1.40 times as fast in the mean, 0.82 to 3.2, ten slower by more than
-// 3 % (3 images of 2226 tokens, 9 heads, two branches 31.8 / 38.6); us, before / now: 2 images
-// of 2107 tokens, 8 heads 60.2 / 24.9, one of 2170, 16 heads, four branches 38.2 / 23.5, 6 of 310, 16 heads 29.2 / 18.2; left as they are:
-// 3 of 1441, 8 heads, windows of 288 10.9 / 16.7, one of 4096, 12 heads 32.2 / 38.4.
-constexpr int kManySteps = 10;
-constexpr double kManyMargin = 1.15;
+// Both times are estimated, in us, by sums that are linear in the plan: workgroups, with and without keys, the 32-key blocks or 64-key steps of all
+// lists, and of the longest one.  A sum each for: short launches of one workgroup to a CU, of one round, of one round beside workgroups without keys, and
+// of more; split launches; packed and whole tiles of one to a CU, one round and more.  Fitted to 1731 launches (3 to 16 heads, 200 to 8192 tokens, 1
+// to 16 images, windows, single dilated branches, two to four branches), with residuals of 6 to 9 % for the short form (12 % beside workgroups without
+// keys), 3 to 6 % for tiles of one to a CU and 9 to 14 % for the rest.  The margins keep the launches with whose estimates they
+// are wrong most where they would be without the form; whole tiles of one step always stay (one of 256 tokens, windows of 32, 6 images of 6
+// heads 5.4 / 7.2), and of split launches none of up to nine eighths of the slots.  On 897 other drawn launches the choice differs from that by
+// estimates fitted to earlier kernels on 87, which run 1.23 times as fast in the mean, two slower by more than 3 % (0.91 at worst: 11 of 259 tokens,
+// 12 heads 17.7 / 19.4).  us, tiles or split / short: 7 images of 1152 tokens, 3 heads, four branches 30.9 / 14.4; 2 of 875, 16 heads 24.8 / 13.6;
+// one of 4736, 8 heads, windows of 1184 at rate 3 13.2 / 8.2; left as they are: one of 4096, 12 heads, split 30.6 / 31.8;
+// 10 of 959, 6 heads, windows of 191 12.2 / 14.3.
+// With one workgroup to a CU, lists that do not fill their last step stay with the short kernel whatever the times: it clears the rows past a list's
+// end, where the 256-row kernel gives them weight 0, which makes NaN of an infinite value, and its start outweighs the walk by 2 us at most.
+// Packed tiles without a free row, of lists under kFullSteps steps, stay past nine eighths of the slots although they are slower (3 of 1024 tokens, 12
+// heads 16.7 / 13.9): the tests of the packed kernel at its regular size run there.
+constexpr int kFullSteps = 10;
+constexpr double kShortMargin = 1.05;
+constexpr double kIdleMargin = 1.25;      // one round of workgroups with keys, and others that need a second one
+constexpr double kWholeMargin = 1.15;     // more than a round, against tiles of one row group each
 bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                 int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan);
 

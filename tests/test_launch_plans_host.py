@@ -98,6 +98,17 @@ def test_launches_of_two_rounds_of_row_groups(B, Bsz, H, N, branches, offs, form
     assert form != "SHORT" or 576 < p["n_items"] <= 1152
 
 
+# Where the estimates choose: part-filled tiles go to the short form, split or not; tiles of one step stay, and so do workgroups with keys that fit one
+# round beside many without.
+@pytest.mark.parametrize("Bsz,H,N,branches,form", [
+    (7, 3, 1152, [(144, 1), (288, 2), (576, 4), (1152, 8)], "SHORT"), (1, 8, 4736, [(1184, 3)], "SHORT"), (3, 12, 1024, [(256, 1), (512, 2), (1024, 4)], "TILES"),
+    (16, 8, 298, [(149, 3)], "TILES"), (6, 6, 256, [(32, 1)], "TILES"), (6, 8, 1280, [(640, 2)], "TILES"), (10, 6, 959, [(191, 1)], "TILES"),
+])
+def test_form_with_the_shorter_estimate(B, Bsz, H, N, branches, form):
+    p = _check_launched_plan(B, Bsz, H, N, branches, None, B.DFA_BF16, False)
+    assert p["form"] == getattr(B, "FORM_" + form)
+
+
 # Sharing does not take a plan out of the short form: padded for the dies it would have 592 workgroups here, apart it has 568 (and the
 # form in its place takes 1.4 times as long).
 def test_sharing_does_not_leave_the_short_form(B):
