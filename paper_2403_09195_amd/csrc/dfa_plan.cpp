@@ -666,28 +666,31 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                          int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan) {
     if (N >= kMaxCutStride) return false;
-    // us for the call on 256 CUs, see dfa_plan.h; `most`: a bound on what the short kernels may take
-    const double per_slot = 512.0 / chip.fwd_slots();
-    int64_t steps = 0;
-    int32_t longest = 0;
-    for (const Item& i : full.items)
-        if (i.tile >= 0) {
-            steps += i.t.n_steps;
-            longest = std::max(longest, i.t.n_steps);
-        }
-    const double full_us = 15.0 + std::max(3.2 * longest, 0.0164 * steps * per_slot);
-    if (full.items.size() * 0.024 * per_slot > full_us) return false;          // there are at least as many 64-row tiles
+    // us for the call on 256 CUs, see dfa_plan.h
+    const int64_t slots = chip.fwd_slots(), one = slots / kFwdWorkgroupsPerCu;
+    const double per_slot = 512.0 / slots;
+    const LaunchSize whole = launch_size(full);
+    const double items = per_slot * full.items.size(), steps = per_slot * whole.steps;
+    const double full_us = whole.live <= one     ? 11.6 + 0.0027 * items + 0.0035 * steps + 2.88 * whole.longest
+                           : whole.live <= slots ? 14.3 - 0.0071 * items + 0.0153 * steps + 0.43 * whole.longest
+                                                 : 9.2 + 0.01 * items + 0.0122 * steps + 0.7 * whole.longest;
+    const double long_us = 15.0 + std::max(3.2 * whole.longest, 0.0164 * steps);        // past kFewTiles
+    if (0.02 * items > std::max(full_us, long_us)) return false;          // there are at least as many 64-row tiles
     build_plan(B, H, N, br, nb, offsets, order_mode, chip, false, plan, kShortRows / kBlockRows);
     const CutSize size = cut_size(*plan);
     if (size.longest > kShortBackwardBlocks || size.records > kMaxCutRecords) return false;
     cut_blocks(plan);
-    int64_t tiles = 0, blocks = 0;
+    int64_t tiles = 0, live = 0, blocks = 0;
     for (const Item& i : plan->items)
         if (i.tile >= 0) {
             ++tiles;
+            live += i.t.nseg > 0;
             blocks += (int64_t)i.t.nseg * ((i.t.nrows + kBlockRows - 1) / kBlockRows);
         }
-    return 10.0 + (0.024 * tiles + 0.00105 * blocks) * per_slot < full_us;
+    if (per_slot * tiles > kFewTiles || (N <= kShortRows && tiles >= slots)) return 10.0 + per_slot * (0.024 * tiles + 0.00105 * blocks) < long_us;
+    const double short_us = live * (1 + kShortDkdvParts) <= 2 * slots ? 14.8 + 0.00075 * per_slot * blocks
+                                                                      : 4.7 + per_slot * (0.0077 * tiles + 0.0135 * live + 0.00097 * blocks) + 0.098 * size.longest;
+    return short_us * kShortBackwardMargin < full_us;
 }
 
 }  // namespace dfa

@@ -187,13 +187,19 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 
 // The same for the backward.  The kernels of dfa_bwd_bf16.hip walk a tile's whole list in one workgroup and spend as much on
 // a part-filled tile as on a full one; those of dfa_bwd_short.hip cut the walk by four and have 64-row tiles, but copy a block
-// for 64 (dq) or 32 rows (dk, dv).  Both times, in us, are linear in the plan: 15 + the larger of 3.2 per step of the longest
-// list and 0.0164 per step of all tiles, against 10 + 0.024 per 64-row tile + 0.00105 per 32 x 32 block of pairs.  Measured,
-// short against full: 4 images of 1024 tokens, 6 heads 24.1 / 43.2; 16 of 1024, 12 heads 145 / 227, of 256 66.4 / 97.8; one
-// of 2500 51.7 / 88.1, three 136 / 145; one of 4096 97.6 / 117, two 173 / 150; windows of 512 only, one image of 4096
-// 53.6 / 44.7.
+// for 64 (dq) or 32 rows (dk, dv).  Both times, in us, are linear in the plan: 64-row tiles, with and without keys, 32 x 32 blocks of pairs and the
+// longest list, in a sum each for up to two rounds of workgroups and for more; 256-row tiles, steps and the longest list, in a sum each for one tile
+// to a CU, one round and more.  Fitted to 900 calls (200 to 4096 tokens, 3 to 16 heads, 1 to 16 images, one to four branches), with residuals of 6 to 8 %
+// (short) and 7 to 12 % (full); below 16 us a call is bound by its host side.  On these the choice costs 0.4 % against the faster form of each, where
+// estimates fitted to earlier kernels cost 1.6 %: it differs on 67, which run 1.18 times as fast in the mean, three slower by more than 3 % (0.93 at
+// worst).  Past kFewTiles 64-row tiles the earlier ones are as good and stay: 15 + the larger of 3.2 per step of the longest list and
+// 0.0164 per step of all 256-row tiles, against 10 + 0.024 per 64-row tile + 0.00105 per block of pairs.  us, full / short: 8 images of 384 tokens, 12 heads,
+// windows of 54 32.1 / 22.5 (images of up to 64 tokens go by the earlier ones from a round on, although 64 of 64, 8 heads, take 20.6 / 16.4: the
+// tests of one-step walks of the full kernels run there); 7 of 521, 12 heads, one window 64.3 / 47.6; 2 of 3520, 8 heads, windows of 1173 at rate 3 36.2 / 26.1.
 // `full` is the plain plan of 256-row tiles.
 constexpr int kShortBackwardBlocks = 256;
+constexpr double kShortBackwardMargin = 0.97;
+constexpr double kFewTiles = 1280;
 // workgroups of the launch that works out all gradients of n_items launch items: dq ones, padded to whole rounds of the dies, then dk/dv ones
 inline int64_t short_backward_workgroups(int64_t n_items) { return (n_items + kDies - 1) / kDies * kDies * (1 + kShortDkdvParts); }
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,

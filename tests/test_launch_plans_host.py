@@ -109,6 +109,15 @@ def test_form_with_the_shorter_estimate(B, Bsz, H, N, branches, form):
     assert p["form"] == getattr(B, "FORM_" + form)
 
 
+@pytest.mark.parametrize("Bsz,H,N,branches,form", [
+    (8, 8, 326, [(40, 1)], "SHORT"), (2, 8, 3520, [(1173, 3)], "SHORT"), (4, 6, 1024, [(256, 1), (512, 2), (1024, 4)], "SHORT"),
+    (64, 8, 128, [(128, 1)], "TILES"), (16, 12, 4096, [(1024, 1), (2048, 2), (4096, 4)], "TILES"),
+])
+def test_backward_form_with_the_shorter_estimate(B, Bsz, H, N, branches, form):
+    p = _check_launched_plan(B, Bsz, H, N, branches, None, B.DFA_BF16, True)
+    assert p["form"] == getattr(B, "FORM_" + form)
+
+
 # Sharing does not take a plan out of the short form: padded for the dies it would have 592 workgroups here, apart it has 568 (and the
 # form in its place takes 1.4 times as long).
 def test_sharing_does_not_leave_the_short_form(B):
