@@ -48,7 +48,8 @@ class DfaError(RuntimeError):
 
 
 _lib = None
-_native_forward = None       # the ordinary forward call in native code (csrc/dfa_torch.cpp), set by lib()
+_native_forward = None       # the ordinary forward and backward calls in native code (csrc/dfa_torch.cpp), set by lib()
+_native_backward = None
 _i32p = ctypes.POINTER(ctypes.c_int32)
 
 
@@ -110,9 +111,9 @@ def lib():
             if name not in ("dfa_error_string", "dfa_workspace_bytes", "dfa_dense_unfused_workspace_bytes"):
                 getattr(L, name).restype = ctypes.c_int
         from . import _dfa_torch
-        _dfa_torch.bind(ctypes.cast(L.dfa_forward_alloc, ctypes.c_void_p).value)
-        global _native_forward
-        _native_forward = _dfa_torch.forward
+        _dfa_torch.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (L.dfa_forward_alloc, L.dfa_backward)))
+        global _native_forward, _native_backward
+        _native_forward, _native_backward = _dfa_torch.forward, _dfa_torch.backward
         L.dfa_workspace_bytes.restype = ctypes.c_size_t
         L.dfa_dense_unfused_workspace_bytes.restype = ctypes.c_size_t
         _lib = L
@@ -446,6 +447,13 @@ def encoder_stack(x, w_qkv, w_o, H, branches, scale, head_offsets=None, buffers=
 
 def backward(q, k, v, out, lse, dout, branches, scale, head_offsets=None):
     """(dq, dk, dv) of dfa_forward for a gradient dout of its output; all [B, N, H, D] of q's dtype."""
+    if _native_backward is None:
+        lib()
+    res = _native_backward(q, k, v, out, lse, dout, branches, scale, head_offsets)
+    if type(res) is tuple:
+        return res
+    if res is not None:
+        raise DfaError(res, "dfa_backward")
     import torch
     for t, nm in ((q, "q"), (k, "k"), (v, "v"), (out, "out"), (lse, "lse"), (dout, "dout")):
         _gpu(t, nm)

@@ -39,6 +39,29 @@ def test_same_results(B, monkeypatch, N, branches, table, dtype):
         assert all(torch.equal(a, b) and a.dtype == b.dtype and a.shape == b.shape and a.is_contiguous() for a, b in zip(native, other))
 
 
+# The backward: short and whole-tile launches, fp32; packed strides; a table of offsets; gradients and results that Python refuses stay refused.
+@pytest.mark.parametrize("Bsz,N,branches,table", [(1, 200, [(50, 1), (200, 4)], False), (64, 128, [(128, 1)], False), (2, 300, [(100, 1), (150, 3)], True)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_backward_same_results(B, monkeypatch, Bsz, N, branches, table, dtype):
+    import torch
+    (q, k, v), _ = make_qkv(25, Bsz, N, 4, 64, dtype)
+    dout = v.flip(1).contiguous()
+    q, k, v = torch.stack((q, k, v), dim=2).unbind(2)
+    offsets = [[(h + x) % r for h in range(4)] for x, (_, r) in enumerate(branches)] if table else None
+    out, lse = B.forward(q, k, v, branches, 0.125, head_offsets=offsets)
+    native = B._native_backward(q, k, v, out, lse, dout, branches, 0.125, offsets)
+    assert type(native) is tuple and B._native_backward(q, k, v, out, lse, dout, branches, 1, offsets) is None
+    with monkeypatch.context() as m:
+        m.setattr(B, "_native_backward", lambda *a: None)
+        python = B.backward(q, k, v, out, lse, dout, branches, 0.125, head_offsets=offsets)
+    for other in (python, B.backward(q, k, v, out, lse, dout, tuple(branches), 0.125, head_offsets=offsets)):
+        assert all(torch.equal(a, b) and a.dtype == b.dtype and a.shape == b.shape and a.is_contiguous() for a, b in zip(native, other))
+    for bad, error in ((dict(dout=dout.transpose(1, 2)), ValueError), (dict(lse=lse.double()), TypeError), (dict(out=out.half()), TypeError),
+                       (dict(dout=dout.cpu()), RuntimeError), (dict(k=k[:, :-1]), B.DfaError), (dict(branches=[(64, 0)]), B.DfaError)):
+        with pytest.raises(error):
+            B.backward(**{**dict(q=q, k=k, v=v, out=out, lse=lse, dout=dout, branches=branches, scale=0.125, head_offsets=offsets), **bad})
+
+
 def test_calls_left_to_python(B):
     import torch
     (q, k, v), _ = make_qkv(22, 1, 64, 2, 64, "bf16")
