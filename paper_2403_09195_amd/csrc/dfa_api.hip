@@ -49,6 +49,7 @@ struct DevicePlan {
     const Item* split_items = nullptr;
     const ItemParts* item_parts = nullptr;
     int32_t n_split_wgs = 0;
+    int32_t start_bytes = 0;    // short forward: the plan is its workgroups' starts, this far apart
     bool owned = true;          // base came from hipMalloc and is freed with the plan
 
     DevicePlan() = default;
@@ -77,6 +78,7 @@ struct PackedPlan {
     int32_t n_items = 0;
     int32_t n_split_wgs = 0;
     int32_t max_tile_rows = 1;
+    int32_t start_bytes = 0;
     bool short_walk = false;
     bool cut = false;
     bool one_block = false;
@@ -138,6 +140,11 @@ int pack_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t n
     HostPlan hp;
     const int rc = choose_plan(B, H, N, br, nb, offsets, chip, kind, &hp, out);
     if (rc != DFA_OK) return rc;
+    if (packed && out->short_walk) {
+        out->bytes = pack_starts(hp);
+        out->start_bytes = hp.items.empty() ? 0 : (int32_t)(out->bytes.size() / hp.items.size());
+        return DFA_OK;
+    }
     const size_t b_rows = align256(hp.rows.size() * sizeof(int32_t));
     const size_t b_segs = align256(hp.segs.size() * sizeof(KeySeg) + sizeof(KeySeg));
     const size_t b_items = align256(hp.items.size() * sizeof(Item));
@@ -191,6 +198,7 @@ void point_plan(DevicePlan* dp, void* base, const PackedPlan& pp, int device) {
     dp->cut = pp.cut;
     dp->one_block = pp.one_block;
     dp->max_tile_rows = pp.max_tile_rows;
+    dp->start_bytes = pp.start_bytes;
 }
 
 std::vector<int32_t> plan_key(int device, PlanKind kind, int32_t B, int32_t H, int32_t N, const dfa_branch_t* br,
@@ -379,6 +387,7 @@ int launch_forward(const DevicePlan& dp, const void* q, const void* k, const voi
     p.rows = dp.rows; p.segs = dp.segs; p.items = dp.items; p.block_mult = dp.block_mult;
     p.H = H; p.N = N; p.scale = scale;
     p.split_wgs = dp.split_wgs; p.split_items = dp.split_items; p.item_parts = dp.item_parts; p.split_ws = split_ws;
+    p.starts = static_cast<const char*>(dp.base); p.start_bytes = dp.start_bytes;
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     if (dt == DFA_BF16 && !out_f32 && dp.short_walk) {

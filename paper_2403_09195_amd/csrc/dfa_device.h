@@ -40,6 +40,9 @@ struct FwdParams {
     const Item* split_items;       // the launch item of every such workgroup
     const ItemParts* item_parts;
     float* split_ws;
+    // Short launches only, in place of rows, segs, items and block_mult: a ShortStart and its records per workgroup
+    const char* starts;
+    int32_t start_bytes;
 };
 
 // Arguments of the backward kernels.  out, dout, dq, dk, dv are contiguous [B, N, H, D].

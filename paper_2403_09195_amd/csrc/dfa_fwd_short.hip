@@ -10,14 +10,14 @@
 // Bound: a wave's own chain.  Such a launch is as long as one workgroup's start, walk and end, so the walk is cut by four where the rows
 // are, not by more workgroups that have to meet in memory (partial rows written, read back and merged by a second launch).
 // A wave copies its own blocks and waits for nobody until the merge.  The list comes cut into blocks: one record each, all of a
-// wave's records read in one trip to memory at the start and kept in LDS.  Two workgroups to a CU (registers, LDS).  A beat takes some 1700
+// wave's records read with the item and the row numbers in one trip to memory (ShortStart) and kept in LDS.  Two workgroups to a CU (registers, LDS).  A beat takes some 1700
 // cycles with one wave on a SIMD and 2100 with two: 1200 for its 20 MFMAs, 32 exponentials and the rest of the softmax, the others for
 // the next blocks' addresses, records and waits; the waits themselves are 40, and rings of three or four blocks (one workgroup to a CU) were
 // slower (one image of 2000 tokens, 3 heads 16.5 us, 18.1 and 18.7).  Eight waves that share the copies of a block for 128 rows
 // need a barrier per beat and were slower (one image of 2500 tokens, 12 heads: 32.5 against 23.0 us).
 // Measured, us, before the query rows were copied once for all waves, the halves of a beat took turns, the merge took all rows at once and the
 // first reference was taken ahead / now: one 256^2 image, 12 heads 6.66 / 6.13, of 512^2 8.4 / 7.8, four of 1024 tokens, 6 heads 9.9 / 8.4, three of
-// 1500, 6 heads 14.05 / 13.1, one of 2500, 12 heads 15.5 / 14.3.  Against 256-row tiles with split walks, in the launch order of before: three
+// 1500, 6 heads 14.05 / 13.1, one of 2500, 12 heads 15.5 / 14.3 (the start in one trip not counted yet).  Against 256-row tiles with split walks, in the launch order of before: three
 // images of 1500 tokens, 6 heads 18.2 / 25.7; one of 2500, 12 heads 23.0 / 27.2; one of 4096, 6 heads 19.6 / 26.4.
 #include "dfa_blocks.h"
 #include "dfa_fwd_beat.h"
@@ -30,28 +30,12 @@ namespace {
 // One 32-key block of a wave's share of the list.  Wave-uniform, in scalar registers.
 struct Block {
     int32_t key0;
-    // stride | count << 24 | kTurn; count 0: past the share's end, a copy of its last block without a valid key
-    int32_t stride_count;
-    float log2_mult[2];        // of the keys' multiplicity for either 32-row block of the tile; -inf: they are skipped
+    int32_t stride_count;      // these as in ShortRecord
+    float log2_mult[2];
     __device__ __forceinline__ int stride() const { return stride_count & 0xffffff; }
     __device__ __forceinline__ int count() const { return (stride_count >> 24) & 0x3f; }
     __device__ __forceinline__ bool turns() const { return stride_count < 0; }
 };
-constexpr int32_t kTurn = (int32_t)0x80000000;     // the block is not full, or other multiplicities than those of the share's block before
-
-// Lane L's record of the wave's share.
-__device__ __forceinline__ u32x4 load_record(const FwdParams& p, const Tile& tile, int wave, int lane) {
-    const int i = wave + kWalkWaves * lane, last = tile.nseg - 1;
-    const int x = tile.seg_begin + (i <= last ? i : last >= wave ? last - ((last - wave) & (kWalkWaves - 1)) : 0);
-    const int before = tile.seg_begin + (lane > 0 && i - kWalkWaves <= last ? i - kWalkWaves : x - tile.seg_begin);
-    const KeySeg r = p.segs[x];
-    const float2 m = *reinterpret_cast<const float2*>(p.block_mult + (int64_t)kTileBlocks * x);
-    const float2 mb = *reinterpret_cast<const float2*>(p.block_mult + (int64_t)kTileBlocks * before);
-    const int32_t count = i <= last ? r.count : 0;
-    const bool turn = lane == 0 || count < kWalkBlock || m.x != mb.x || m.y != mb.y;
-    return u32x4{(uint32_t)r.key0, (uint32_t)(r.stride | (count << 24) | (turn ? kTurn : 0)), __builtin_bit_cast(uint32_t, m.x),
-                 __builtin_bit_cast(uint32_t, m.y)};
-}
 __device__ __forceinline__ Block block_of(const u32x4& r, int from_lane) {
     Block b;
     b.key0 = __builtin_amdgcn_readlane(r[0], from_lane);
@@ -172,13 +156,22 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     __shared__ __attribute__((aligned(16))) uint32_t skips_lds[kWalkWaves], odd_lds[kWalkWaves];
 
     hold_args(p);
-    const Item item = load_item(p.items, blockIdx.x);
+    asm volatile("" ::"s"(p.starts), "s"(p.start_bytes));
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    // All that the workgroup starts from in one trip to memory; the query rows and the first blocks come in the next.  (Item
+    // first, rows and records behind it, us / now: one image of 256 tokens, 12 heads 6.16 / 6.02, three of 1500, 6 heads 13.1 / 12.6.)
+    const char* const start = p.starts + (int64_t)blockIdx.x * p.start_bytes;
+    const Item item = load_item(reinterpret_cast<const Item*>(start), 0);
+    const int32_t* const rows = reinterpret_cast<const ShortStart*>(start)->rows;
+    const int per_wave = (p.start_bytes - (int)sizeof(ShortStart)) / (int)(sizeof(ShortRecord) * kWalkWaves);
+    u32x4 my_record = *reinterpret_cast<const u32x4*>(start + sizeof(ShortStart) + sizeof(ShortRecord) * (wave * per_wave + min(lane, per_wave - 1)));
+    // (a filler slot of a packed tile holds ~n of a row n of its group: loaded like any row, never stored)
+    int32_t q_row[2] = {rows[16 * wave + (lane >> 3)], rows[16 * wave + 8 + (lane >> 3)]}, my_row = rows[lane];
+    asm volatile("" : "+v"(my_record), "+v"(q_row[0]), "+v"(q_row[1]), "+v"(my_row));
     if (item.tile < 0) return;
     const Tile tile = item.t;
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int h = tile.h, b = item.b;
-    const int32_t* const rows = p.rows + tile.row_begin;
 
     uint16_t* const out = static_cast<uint16_t*>(p.out) + ((int64_t)b * p.N * p.H + h) * kD;     // row n adds n * H * D
     float* const lse = p.lse ? p.lse + ((int64_t)b * p.H + h) * p.N : nullptr;
@@ -197,17 +190,10 @@ void dfa_fwd_short_kernel(const FwdParams p) {
     const uint32_t k_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, lds[wave]));
     const uint32_t v_addr = k_addr + 2 * kBlockBytes;
 
-    // the share's records and the row numbers in one trip to memory, the query rows and the first blocks in the next
     u32x4* const records = records_all[wave];
-    const u32x4 my_record = load_record(p, tile, wave, lane);
-    // a filler slot of a packed tile holds ~n of a row n of its group: loaded like any row, never stored
-    int32_t q_row[2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        q_row[u] = rows[min(16 * wave + 8 * u + (lane >> 3), tile.nrows - 1)];
-        q_row[u] ^= q_row[u] >> 31;
-    }
-    if (tid < kShortRows) row_lds[tid] = rows[min(tid, tile.nrows - 1)];
+    for (int u = 0; u < 2; ++u) q_row[u] ^= q_row[u] >> 31;
+    if (tid < kShortRows) row_lds[tid] = my_row;
     // The query rows are the same for all four waves: a quarter copied by each, whole lines.  (A wave that loaded its fragments itself
     // touched 32 lines with every load, 32 loads of them to a workgroup.)
     {

@@ -663,6 +663,44 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     return short_us * margin < other_us;
 }
 
+std::vector<char> pack_starts(const HostPlan& plan) {
+    int32_t longest = 0;
+    for (const Tile& t : plan.tiles) longest = std::max(longest, t.nseg);
+    const size_t bytes = short_start_bytes(longest);
+    const int32_t per_wave = short_records(longest);
+    std::vector<char> out(plan.items.size() * bytes, 0);
+    for (size_t i = 0; i < plan.items.size(); ++i) {
+        const Item& item = plan.items[i];
+        ShortStart* const start = reinterpret_cast<ShortStart*>(out.data() + i * bytes);
+        start->item = item;
+        if (item.tile < 0) continue;
+        const Tile& t = item.t;
+        for (int32_t x = 0; x < kShortRows; ++x) start->rows[x] = plan.rows[t.row_begin + std::min(x, t.nrows - 1)];
+        if (t.nseg == 0) continue;
+        ShortRecord* const records = reinterpret_cast<ShortRecord*>(start + 1);
+        auto log2_mult = [&](int32_t x, int block) {
+            const int32_t m = plan.block_mult[(size_t)(t.seg_begin + x) * kTileBlocks + block];
+            return m > 0 ? std::log2((float)m) : -INFINITY;
+        };
+        for (int32_t wave = 0; wave < kWalkWaves; ++wave)
+            for (int32_t r = 0; r < per_wave; ++r) {
+                const int32_t at = wave + kWalkWaves * r, last = t.nseg - 1;
+                const int32_t x = at <= last ? at : last >= wave ? last - (last - wave) % kWalkWaves : 0;
+                const KeySeg& seg = plan.segs[t.seg_begin + x];
+                const int32_t count = at <= last ? seg.count : 0;
+                ShortRecord& rec = records[wave * per_wave + r];
+                rec.key0 = seg.key0;
+                bool turn = r == 0 || count < kWalkBlock;
+                for (int blk = 0; blk < 2; ++blk) {
+                    rec.log2_mult[blk] = log2_mult(x, blk);
+                    turn = turn || rec.log2_mult[blk] != log2_mult(at - kWalkWaves, blk);
+                }
+                rec.stride_count = seg.stride | (count << 24) | (turn ? kTurn : 0);
+            }
+    }
+    return out;
+}
+
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                          int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan) {
     if (N >= kMaxCutStride) return false;

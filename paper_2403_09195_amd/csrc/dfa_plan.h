@@ -79,6 +79,22 @@ constexpr int kSplitBlockBytes = kTileRows * (DFA_HEAD_DIM * 2 + 8);
 constexpr int kMaxSplit = 4;             // most shares a tile is cut into
 constexpr int kMinShareSteps = 8;        // a share of fewer 64-key steps is not worth a partial result and its merge
 
+// What a workgroup of the short forward starts from, all at one address known from its index: its launch item, the rows of its 64 slots (past the
+// tile's last slot that one again), then short_records(longest list) records for each wave: blocks wave, wave + 4, ... of the list, the
+// last one again without a valid key where the share has ended.
+struct ShortRecord {
+    int32_t key0;
+    int32_t stride_count;    // stride | count << 24 | kTurn; count 0: past the share's end
+    float log2_mult[2];      // of the keys' multiplicity for either 32-row block of the tile; -inf: they are skipped
+};
+constexpr int32_t kTurn = (int32_t)0x80000000;     // the block is not full, or other multiplicities than those of the share's block before
+struct ShortStart {
+    Item item;
+    int32_t rows[kShortRows];
+};
+inline int32_t short_records(int32_t longest) { return (longest + kWalkWaves - 1) / kWalkWaves + 1; }
+inline size_t short_start_bytes(int32_t longest) { return sizeof(ShortStart) + sizeof(ShortRecord) * kWalkWaves * short_records(longest); }
+
 struct HostPlan {
     std::vector<Tile> tiles;
     // token positions, tile after tile.  A tile that packs several row groups starts each group on a 32-row block of
@@ -92,6 +108,9 @@ struct HostPlan {
     std::vector<SplitWg> split_wgs;      // empty: the launch is not split
     std::vector<ItemParts> item_parts;
 };
+
+// Lays the starts of a short forward plan out, item after item.
+std::vector<char> pack_starts(const HostPlan& plan);
 
 // Validates the branch list (DFA_OK or a negative status).  offsets: [nb][H] or nullptr.
 int check_branches(int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets);
