@@ -65,6 +65,19 @@ int dfa_launch_describe(int32_t backward, dfa_dtype_t dt, int32_t B, int32_t H, 
                         int32_t *tiles, int32_t *rows, int32_t *segs, int32_t *block_mult, int32_t *items);
 
 /*
+ * The same plan as its kernels read it in device memory, for tests of that layout (no GPU needed).  Arguments as dfa_launch_describe.
+ *   image   out, host: the plan's size and where its parts are (bytes from its start).  start_bytes > 0: a short forward, whose plan is
+ *           one record of that many bytes per workgroup; otherwise rows at 0, segs, items, and of a split forward the shares of its
+ *           n_shares workgroups, each one's item, and the blocks of partial results of each item
+ *   bytes   out, host, NULL to skip: image->bytes bytes
+ */
+typedef struct {
+    int64_t bytes, start_bytes, segs, items, shares, share_items, item_parts, block_mult, n_shares;
+} dfa_launch_image_t;
+int dfa_launch_image(int32_t backward, dfa_dtype_t dt, int32_t B, int32_t H, int32_t N,
+                     const dfa_branch_t *branches, int32_t nb, const int32_t *head_offsets, dfa_launch_image_t *image, void *bytes);
+
+/*
  * Measurement aid (no part of the operator): what the matrix cores sustain on their own, the
  * ceiling that the kernels' MFMA rooflines are also quoted against.  Runs a loop of
  * independent v_mfma_f32_32x32x16_bf16 on the whole chip (two waves per SIMD, no memory

@@ -23,7 +23,7 @@ EXPORTS = [
     "dfa_forward_branch", "dfa_merge", "dfa_gather", "dfa_scatter", "dfa_plan_describe", "dfa_plan_describe_forward",
     "dfa_release_plans", "dfa_linear", "dfa_encoder_stack", "dfa_backward",
 ]
-BENCH_EXPORTS = ["dfa_launch_describe", "dfa_forward_timed", "dfa_mfma_peak", "dfa_dense_unfused", "dfa_dense_unfused_workspace_bytes"]
+BENCH_EXPORTS = ["dfa_launch_describe", "dfa_launch_image", "dfa_forward_timed", "dfa_mfma_peak", "dfa_dense_unfused", "dfa_dense_unfused_workspace_bytes"]
 
 
 class Branch(ctypes.Structure):
@@ -39,6 +39,10 @@ FORM_TILES, FORM_SHORT, FORM_SPLIT = 0, 1, 2
 
 class Launch(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in ("form", "packed", "cut", "n_tiles", "n_rows", "n_segs", "n_items")] + [("threads", ctypes.c_int64)]
+
+
+class LaunchImage(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int64) for n in ("bytes", "start_bytes", "segs", "items", "shares", "share_items", "item_parts", "block_mult", "n_shares")]
 
 
 class DfaError(RuntimeError):
@@ -97,6 +101,7 @@ def lib():
                                                 _i32p, _i32p, _i32p, _i32p, _i32p, _i32p, _i32p, _i32p, _i32p]
         L.dfa_launch_describe.argtypes = [i32, ctypes.c_int, i32, i32, i32, ctypes.POINTER(Branch), i32, _i32p,
                                           ctypes.POINTER(Launch), _i32p, _i32p, _i32p, _i32p, _i32p]
+        L.dfa_launch_image.argtypes = [i32, ctypes.c_int, i32, i32, i32, ctypes.POINTER(Branch), i32, _i32p, ctypes.POINTER(LaunchImage), vp]
         i64 = ctypes.c_int64
         L.dfa_linear.argtypes = [vp, vp, vp, i64, i32, i32, i64, i64, i64, vp]
         L.dfa_encoder_stack.argtypes = [vp, vp, vp, i32, i32, i32, i32, i32, f32, ctypes.POINTER(Branch), i32,
@@ -560,6 +565,19 @@ def launch_describe(B, H, N, branches, head_offsets=None, dtype_code=DFA_BF16, b
         call(*(a.ctypes.data_as(_i32p) for a in out.values()))
         res.update({k: out[k][:s[0]] for k, s in shapes.items()})
     return res
+
+
+def launch_image(B, H, N, branches, head_offsets=None, dtype_code=DFA_BF16, backward=False):
+    """The plan a call launches as its kernels read it: (dict of dfa_launch_image_t's fields, its bytes as a numpy uint8 array)."""
+    import numpy as np
+    br, nb = _branches(branches)
+    off = _i32_array(head_offsets)
+    info = LaunchImage()
+    call = lambda ptr: _check(lib().dfa_launch_image(int(backward), dtype_code, B, H, N, br, nb, off, ctypes.byref(info), ptr), "dfa_launch_image")
+    call(None)
+    data = np.zeros(info.bytes, dtype=np.uint8)
+    call(data.ctypes.data)
+    return {n: getattr(info, n) for n, _ in LaunchImage._fields_}, data
 
 
 def release_plans():

@@ -100,6 +100,10 @@ size_t split_bytes(int32_t n_split_wgs) {
 // of the fp32 kernels (plain, lists cut into blocks where that is affordable), and the plain one that single branches of bf16 inputs read.
 enum class PlanKind : int32_t { kPlain, kForward, kBackward, kBlocks };
 
+PlanKind launch_kind(bool backward, dfa_dtype_t dt) {
+    return dt == DFA_F32 ? PlanKind::kBlocks : backward ? PlanKind::kBackward : PlanKind::kForward;
+}
+
 // The plan a call of this kind launches: *hp, and of *out what the launch needs to know besides.
 int choose_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                 const ChipShape& chip, PlanKind kind, HostPlan* hp, PackedPlan* out) {
@@ -816,7 +820,7 @@ int dfa_launch_describe(int32_t backward, dfa_dtype_t dt, int32_t B, int32_t H, 
         int device = 0;
         ChipShape chip;                    // the MI355X when no device can be asked
         if (current_chip(&device, &chip) != DFA_OK) (void)hipGetLastError();
-        const PlanKind kind = dt == DFA_F32 ? PlanKind::kBlocks : backward ? PlanKind::kBackward : PlanKind::kForward;
+        const PlanKind kind = launch_kind(backward, dt);
         HostPlan hp;
         PackedPlan choice;
         rc = choose_plan(B, H, N, branches, nb, head_offsets, chip, kind, &hp, &choice);
@@ -842,6 +846,29 @@ int dfa_launch_describe(int32_t backward, dfa_dtype_t dt, int32_t B, int32_t H, 
         }
         launch->threads = 256 * workgroups;
         copy_plan(hp, tiles, rows, segs, block_mult, items);
+    } catch (const std::bad_alloc&) {
+        return DFA_ERR_LAUNCH;
+    }
+    return DFA_OK;
+}
+
+int dfa_launch_image(int32_t backward, dfa_dtype_t dt, int32_t B, int32_t H, int32_t N, const dfa_branch_t* branches, int32_t nb,
+                     const int32_t* head_offsets, dfa_launch_image_t* image, void* bytes) {
+    if (!image) return DFA_ERR_NULL;
+    int rc = check_common(B, H, N, DFA_HEAD_DIM, dt);
+    if (rc != DFA_OK) return rc;
+    rc = check_branches(H, N, branches, nb, head_offsets);
+    if (rc != DFA_OK) return rc;
+    try {
+        int device = 0;
+        ChipShape chip;                    // the MI355X when no device can be asked
+        if (current_chip(&device, &chip) != DFA_OK) (void)hipGetLastError();
+        PackedPlan pp;
+        rc = pack_plan(B, H, N, branches, nb, head_offsets, chip, launch_kind(backward, dt), &pp);
+        if (rc != DFA_OK) return rc;
+        *image = dfa_launch_image_t{(int64_t)pp.bytes.size(), pp.start_bytes, (int64_t)pp.off_segs, (int64_t)pp.off_items, (int64_t)pp.off_split_wgs,
+                                    (int64_t)pp.off_split_items, (int64_t)pp.off_item_parts, (int64_t)pp.off_block_mult, pp.n_split_wgs};
+        if (bytes) std::memcpy(bytes, pp.bytes.data(), pp.bytes.size());
     } catch (const std::bad_alloc&) {
         return DFA_ERR_LAUNCH;
     }

@@ -177,7 +177,8 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     plan->packed_tiles = false;
     const size_t tile_rows = (size_t)tile_blocks * kBlockRows;
 
-    std::vector<int64_t> tile_cost;   // (query, key) pairs of each tile
+    std::vector<int64_t>& tile_cost = plan->tile_pairs;
+    tile_cost.clear();
     // appends a key list; block_group[w] = which entry of a progression's multiplicities the rows of block w take (-1: none)
     auto add_list = [&](const std::vector<KeySeg>& list, const std::vector<MultVec>& mult, const int (&block_group)[kTileBlocks]) {
         const int32_t seg_begin = (int32_t)plan->segs.size();
@@ -488,13 +489,22 @@ void split_plan(HostPlan* plan, const ChipShape& chip) {
             parts[i] = 1;
             ++total;
         }
-    // one more share for the tile with the longest shares, as long as slots are left and the shares stay long enough
+    // One more share for the tile with the longest shares, as long as slots are left and the shares stay long enough; of several the one with
+    // the most pairs, then the first by tile and image: not by the items' order, so that results do not depend on where a launch runs.
+    std::vector<int64_t> by_work;
+    for (int64_t i = 0; i < n_items; ++i)
+        if (parts[i]) by_work.push_back(i);
+    std::sort(by_work.begin(), by_work.end(), [&](int64_t i, int64_t k) {
+        const Item &a = plan->items[i], &c = plan->items[k];
+        const int64_t pa = plan->tile_pairs[a.tile], pc = plan->tile_pairs[c.tile];
+        return pa != pc ? pa > pc : a.tile != c.tile ? a.tile < c.tile : a.b < c.b;
+    });
     bool any = false;
     while (total < slots) {
         int64_t best = -1;
         int32_t best_share = 0;
-        for (int64_t i = 0; i < n_items; ++i) {
-            if (parts[i] == 0 || parts[i] >= kMaxSplit) continue;
+        for (int64_t i : by_work) {
+            if (parts[i] >= kMaxSplit) continue;
             const int32_t steps = plan->items[i].t.n_steps;
             if (steps / (parts[i] + 1) < kMinShareSteps) continue;
             const int32_t share = (steps + parts[i] - 1) / parts[i];

@@ -97,6 +97,7 @@ inline size_t short_start_bytes(int32_t longest) { return sizeof(ShortStart) + s
 
 struct HostPlan {
     std::vector<Tile> tiles;
+    std::vector<int64_t> tile_pairs;     // (query, key) pairs of each tile
     // token positions, tile after tile.  A tile that packs several row groups starts each group on a 32-row block of
     // its own; the slots in between hold ~n of a row n of the group (valid to load, never stored).
     std::vector<int32_t> rows;

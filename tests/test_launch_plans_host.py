@@ -236,3 +236,45 @@ def test_long_walks_share_a_unit_with_short_ones(B, Bsz, H, N, branches):
         alone, first, second = steps[twos:32], steps[:twos], steps[32:]
         assert alone == sorted(alone, reverse=True) and (not twos or not alone or min(alone) >= max(first + second))
         assert first == sorted(first, reverse=True) and second == sorted(second) and (not twos or first[-1] >= second[-1])
+
+
+# What a split launch reads: its shares cover every item's steps once, each with a block of partial results of its own, and which of several tiles with
+# equally long shares gets one more goes by the tiles (most pairs, then the first tile, then the first image), not by where the launch runs them.
+@pytest.mark.parametrize("Bsz,H,N,branches", [
+    (1, 12, 4096, [(1024, 1), (2048, 2), (4096, 4)]),                # 32 tiles of 32 steps have four shares, 16 of them three
+    (2, 6, 4096, [(1024, 1), (2048, 2), (4096, 4)]), (1, 20, 2048, [(512, 1), (1024, 2), (2048, 4)]),
+    (1, 2, 4224, [(1056, 1), (2112, 2), (4224, 4)]), (4, 1, 8448, [(8448, 1)]), (4, 3, 4032, [(4032, 1)]), (1, 3, 9664, [(2416, 1), (4832, 2), (9664, 4)]),
+])
+def test_shares_of_a_split_launch(B, Bsz, H, N, branches):
+    p = B.launch_describe(Bsz, H, N, branches, arrays=True)
+    image, data = B.launch_image(Bsz, H, N, branches)
+    assert p["form"] == B.FORM_SPLIT and image["n_shares"] == p["threads"] // 256
+    ints = lambda at, rows, cols: data[at:at + 4 * rows * cols].view(np.int32).reshape(rows, cols)
+    tiles, items = p["tiles"], ints(image["items"], len(p["items"]), 8)
+    assert np.array_equal(items[:, :2], p["items"])
+    shares, share_items = ints(image["shares"], image["n_shares"], 3), ints(image["share_items"], image["n_shares"], 8)
+    first, parts = ints(image["item_parts"], len(items), 2).T
+    total = int(parts.sum())
+    real = shares[:, 0] >= 0
+    assert int(real.sum()) == total <= 512 and np.all(share_items[~real, 0] < 0) and len(shares) - total < 8
+    assert np.array_equal(share_items[real], items[shares[real, 0]])
+    assert sorted(shares[real, 2].tolist()) == list(range(total))                # a block each
+    for item, part_nparts, block in shares[real].tolist():
+        part, nparts = part_nparts & 0xffff, part_nparts >> 16
+        assert nparts == parts[item] and 0 <= part < nparts and block == first[item] + part
+    # the same by the rule
+    pairs = np.zeros(len(tiles), dtype=np.int64)
+    for t, (_, rb, nr, sb, ns, _) in enumerate(tiles.tolist()):
+        slots = p["rows"][rb:rb + nr]
+        rows = np.array([int((slots[32 * w:32 * w + 32] >= 0).sum()) for w in range(8)])
+        pairs[t] = int((p["segs"][sb:sb + ns, 2].astype(np.int64) * ((p["block_mult"][sb:sb + ns] > 0) @ rows)).sum())
+    live = sorted((i for i in range(len(items)) if items[i, 0] >= 0), key=lambda i: (-pairs[items[i, 0]], items[i, 0], items[i, 1]))
+    want = np.zeros(len(items), dtype=np.int64)
+    want[live] = 1
+    steps = tiles[np.maximum(items[:, 0], 0), 5]
+    while want.sum() < 512:
+        able = [i for i in live if want[i] < 4 and steps[i] // (want[i] + 1) >= 8]
+        if not able:
+            break
+        want[max(able, key=lambda i: -(-int(steps[i]) // int(want[i])))] += 1     # the first of the longest
+    assert np.array_equal(want, parts)
