@@ -194,6 +194,16 @@ def _covers(q, k, v):
             raise DfaError(-2, f"{name} is smaller than q")
 
 
+def _holds(t, *want):
+    """Whether contiguous t, read as a contiguous array of these sizes, has the elements of t[:want[0], :want[1], ...]; with another
+    number of dimensions, as many elements in this order.  (The kernels would read past the end of less.)"""
+    need, same = 1, t.dim() == len(want)
+    for d in reversed(range(len(want))):
+        same = same and t.shape[d] >= want[d] and (want[d] == 1 or t.stride(d) == need)
+        need *= want[d]
+    return same if t.dim() == len(want) else t.numel() >= need
+
+
 # What the C calls take besides pointers, scale and stream, marshalled once per combination of shape, strides, dtype,
 # branches and offsets.  Small calls wait for their host side: a forward call that made these ctypes objects every time took 16.4 us
 # on the host, with a table of offsets 23.4, this way 10.9 and 12.0 (and 5.7 in native code).  Keyed by value throughout; no entry depends on a tensor's
@@ -451,7 +461,7 @@ def encoder_stack(x, w_qkv, w_o, H, branches, scale, head_offsets=None, buffers=
 
 
 def backward(q, k, v, out, lse, dout, branches, scale, head_offsets=None):
-    """(dq, dk, dv) of dfa_forward for a gradient dout of its output; all [B, N, H, D] of q's dtype."""
+    """(dq, dk, dv) of dfa_forward for a gradient dout of its output; all [B, N, H, D] of q's dtype, lse fp32 [B, H, N]."""
     if _native_backward is None:
         lib()
     res = _native_backward(q, k, v, out, lse, dout, branches, scale, head_offsets)
@@ -467,6 +477,9 @@ def backward(q, k, v, out, lse, dout, branches, scale, head_offsets=None):
         raise ValueError("backward: out, dout and lse must be contiguous")
     if out.dtype != q.dtype or dout.dtype != q.dtype or lse.dtype != torch.float32:
         raise TypeError("backward: out and dout must have q's dtype, lse fp32")
+    for t, nm, want in ((out, "out", (B, N, H, D)), (dout, "dout", (B, N, H, D)), (lse, "lse", (B, H, N))):
+        if not _holds(t, *want):
+            raise DfaError(-2, f"{nm} {tuple(t.shape)} is not what the call's {want} is read from")
     sq, sk, sv, _, _, _, _, code, br, nb, offs, _ = _prepare(q, k, v, branches, head_offsets)
     dq, dk, dv = (torch.empty((B, N, H, D), dtype=q.dtype, device=q.device) for _ in range(3))
     delta = torch.empty((2, B, H, N), dtype=torch.float32, device=q.device)

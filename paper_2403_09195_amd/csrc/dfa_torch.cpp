@@ -119,6 +119,18 @@ bool read_call(PyObject* const* qkv, PyObject* const* rest, Call* c) {
     return true;
 }
 
+// Whether contiguous t, read as a contiguous array of the n sizes `want`, has the elements of t[:want[0], :want[1], ...]; with another number of
+// dimensions, as many elements in this order.  (The kernels would read past the end of less.)
+bool holds(const at::Tensor& t, const int64_t* want, int64_t n) {
+    int64_t stride = 1;
+    bool same = t.dim() == n;
+    for (int64_t d = n - 1; d >= 0; --d) {
+        same = same && t.size(d) >= want[d] && (want[d] == 1 || t.stride(d) == stride);
+        stride *= want[d];
+    }
+    return t.dim() == n ? same : t.numel() >= stride;
+}
+
 // A tuple of tensors, which are given up.
 template <size_t n>
 PyObject* as_tuple(at::Tensor (&t)[n]) {
@@ -165,10 +177,12 @@ PyObject* backward(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     if (nargs != 9 || !g_backward || !read_call(args, args + 6, &c)) Py_RETURN_NONE;
     const at::Tensor& q = *c.t[0];
     const at::Tensor* x[3];                    // out, lse, dout
+    const int64_t rows[4] = {c.B, c.N, c.H, c.D}, stats[3] = {c.B, c.H, c.N};
     for (int i = 0; i < 3; ++i) {
         if (!THPVariable_CheckExact(args[3 + i])) Py_RETURN_NONE;
         x[i] = &THPVariable_Unpack(args[3 + i]);
         if (!x[i]->is_cuda() || !x[i]->is_contiguous() || x[i]->scalar_type() != (i == 1 ? at::kFloat : q.scalar_type())) Py_RETURN_NONE;
+        if (!(i == 1 ? holds(*x[i], stats, 3) : holds(*x[i], rows, 4))) Py_RETURN_NONE;
     }
     at::Tensor res[3];
     for (at::Tensor& r : res) r = at::empty({c.B, c.N, c.H, c.D}, q.options());

@@ -427,3 +427,19 @@ def test_torch_module_is_named_for_this_interpreter(B):
     from paper_2403_09195_amd import _dfa_torch, build
     assert build.TORCH_MODULE_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
     assert os.path.samefile(_dfa_torch.__file__, build.TORCH_MODULE_PATH)
+
+
+def test_which_tensors_hold_what_a_call_reads(B):
+    """out, dout [B, N, H, D] and lse [B, H, N] of the backward: contiguous tensors that may be larger, or lack dimensions."""
+    import torch
+    e = torch.empty
+    for shape, want, ok in [
+            ((2, 9, 3, 64), (2, 9, 3, 64), True), ((3, 9, 3, 64), (2, 9, 3, 64), True), ((1, 9, 3, 64), (2, 9, 3, 64), False),
+            ((2, 8, 3, 64), (2, 9, 3, 64), False), ((2, 10, 3, 64), (2, 9, 3, 64), False), ((1, 10, 3, 64), (1, 9, 3, 64), True),
+            ((2, 3, 9, 64), (2, 9, 3, 64), False), ((2, 9, 4, 64), (2, 9, 3, 64), False), ((1, 1, 4, 64), (1, 1, 3, 64), True),
+            ((4, 9, 3, 32), (2, 9, 3, 64), False), ((0, 9, 3, 64), (2, 9, 3, 64), False), ((2, 9, 192), (2, 9, 3, 64), True),
+            ((2, 9, 191), (2, 9, 3, 64), False), ((3456,), (2, 9, 3, 64), True), ((3455,), (2, 9, 3, 64), False),
+            ((2, 3, 9), (2, 3, 9), True), ((2, 9, 3), (2, 3, 9), False), ((6, 9), (2, 3, 9), True), ((2, 3, 8), (2, 3, 9), False)]:
+        assert B._holds(e(shape), *want) == ok, (shape, want)
+    # the stride of a dimension of one element says nothing
+    assert B._holds(e((1, 9, 3, 64)).as_strided((1, 9, 3, 64), (5, 192, 64, 1)), 1, 9, 3, 64)

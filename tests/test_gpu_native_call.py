@@ -62,6 +62,45 @@ def test_backward_same_results(B, monkeypatch, Bsz, N, branches, table, dtype):
             B.backward(**{**dict(q=q, k=k, v=v, out=out, lse=lse, dout=dout, branches=branches, scale=0.125, head_offsets=offsets), **bad})
 
 
+# out, lse and dout that hold less than the call reads, or something else in its order, are refused on both paths before anything is launched; what
+# holds more, or the same without all dimensions, is read as ever.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Bsz", [1, 2])
+def test_backward_refuses_what_it_would_read_past(B, monkeypatch, Bsz, dtype):
+    import torch
+    N, H, D, branches = 96, 4, 64, [(48, 1), (96, 3)]
+    (q, k, v), _ = make_qkv(26, Bsz, N, H, D, dtype)
+    out, lse = B.forward(q, k, v, branches, 0.125)
+    dout = v.flip(1).contiguous()
+    call = lambda **kw: B.backward(**{**dict(q=q, k=k, v=v, out=out, lse=lse, dout=dout, branches=branches, scale=0.125), **kw})
+    ref = call()
+    flat = lambda t, *shape: t.reshape(shape)
+    twice = lambda t: torch.cat((t, t))
+    bad = [(name, b) for name, t in (("out", out), ("dout", dout)) for b in
+           (t[:, :-1].contiguous(), t[:, :, :-1].contiguous(), t[:, :, :, :32].contiguous(), t[:0], t.transpose(1, 2).contiguous(), flat(t, -1)[:-64],
+            t[:, :N // 2].contiguous(), torch.empty((Bsz, N, 2 * H, D), dtype=t.dtype, device="cuda"))]
+    bad += [("lse", b) for b in (lse[:, :, :-1].contiguous(), lse[:, :-1].contiguous(), lse.transpose(1, 2).contiguous(), lse[:0], flat(lse, -1)[:-1],
+                                 torch.empty((Bsz, H, 2 * N), device="cuda"))]
+    if Bsz > 1:
+        bad += [("out", out[:1]), ("dout", dout[:1]), ("lse", lse[:1]), ("dout", torch.cat((dout, dout), dim=1))]
+    good = [("out", twice(out)), ("dout", twice(dout)), ("lse", twice(lse)), ("dout", flat(dout, Bsz, N, H * D)), ("out", flat(out, -1)),
+            ("lse", flat(lse, Bsz * H, N))]
+    if Bsz == 1:
+        good += [("dout", torch.cat((dout, dout), dim=1)), ("lse", torch.cat((lse, lse), dim=1))]
+    native = B._native_backward
+    for path in (native, lambda *a: None):
+        monkeypatch.setattr(B, "_native_backward", path)
+        for name, t in bad:
+            assert t.is_contiguous()
+            with pytest.raises(B.DfaError):
+                call(**{name: t})
+        for name, t in good:
+            assert all(torch.equal(a, b) for a, b in zip(ref, call(**{name: t}))), (name, tuple(t.shape))
+    for name, t in good:                       # and the native call takes them itself
+        args = {**dict(out=out, lse=lse, dout=dout), name: t}
+        assert type(native(q, k, v, args["out"], args["lse"], args["dout"], branches, 0.125, None)) is tuple
+
+
 def test_calls_left_to_python(B):
     import torch
     (q, k, v), _ = make_qkv(22, 1, 64, 2, 64, "bf16")
