@@ -375,7 +375,7 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     // whole units per die when that balances the dies to within an eighth (always with 4 units per die or more);
     // every die then reads only its own units' K/V rows from memory
     const int64_t units = (int64_t)B * H;
-    const bool by_unit = units >= 4 * kNumXcd ||
+    const bool by_unit = plan->whole_units = units >= 4 * kNumXcd ||
                          (units >= kNumXcd && ((units + kNumXcd - 1) / kNumXcd) * kNumXcd * 8 <= units * 9);
     // Fewer units: the tiles one after the other, unit by unit and within a unit by their first row, cut into a run of the same number for
     // every die: the tiles of a run share most of their K/V rows, which the die then reads once.  Only where that balances the dies to
@@ -489,16 +489,27 @@ void split_plan(HostPlan* plan, const ChipShape& chip) {
             parts[i] = 1;
             ++total;
         }
-    // One more share for the tile with the longest shares, as long as slots are left and the shares stay long enough; of several the one with
-    // the most pairs, then the first by tile and image: not by the items' order, so that results do not depend on where a launch runs.
+    // One more share for the tile with the longest shares, as long as slots are left and the shares stay long enough.  Of several tiles with the
+    // same shares the one with the most pairs comes first, then the first tile, then the first image; where whole units are dealt to the dies, the
+    // first unit of every die tile by tile, then the second.  (By the tiles, not by the place in the launch: how a row is rounded then does
+    // not change with the order of a launch.)
+    const int64_t dies = std::max(chip.dies, 1), heads = plan->tiles.back().h + 1;
+    std::vector<int32_t> by_pairs(plan->tiles.size()), rank(plan->tiles.size());
+    std::iota(by_pairs.begin(), by_pairs.end(), 0);
+    std::stable_sort(by_pairs.begin(), by_pairs.end(), [&](int32_t t, int32_t u) { return plan->tile_pairs[t] > plan->tile_pairs[u]; });
+    {
+        std::vector<int32_t> next(heads, 0);
+        for (int32_t t : by_pairs) rank[t] = plan->whole_units ? next[plan->tiles[t].h]++ : next[0]++;
+    }
+    auto place = [&](int64_t i) {
+        const Item& it = plan->items[i];
+        const int64_t unit = it.b * heads + it.t.h;
+        return plan->whole_units ? std::array<int64_t, 4>{it.t.nseg <= 1, unit / dies, rank[it.tile], unit % dies} : std::array<int64_t, 4>{0, 0, rank[it.tile], it.b};
+    };
     std::vector<int64_t> by_work;
     for (int64_t i = 0; i < n_items; ++i)
         if (parts[i]) by_work.push_back(i);
-    std::sort(by_work.begin(), by_work.end(), [&](int64_t i, int64_t k) {
-        const Item &a = plan->items[i], &c = plan->items[k];
-        const int64_t pa = plan->tile_pairs[a.tile], pc = plan->tile_pairs[c.tile];
-        return pa != pc ? pa > pc : a.tile != c.tile ? a.tile < c.tile : a.b < c.b;
-    });
+    std::sort(by_work.begin(), by_work.end(), [&](int64_t i, int64_t k) { return place(i) < place(k); });
     bool any = false;
     while (total < slots) {
         int64_t best = -1;
@@ -519,9 +530,6 @@ void split_plan(HostPlan* plan, const ChipShape& chip) {
         any = true;
     }
     if (!any) return;
-    // The shares die after die in the items' order, cut into a run of the same number for every die: the shares of a tile, and the tiles
-    // that read the same K/V rows, stay on a die.
-    const int64_t dies = std::max(chip.dies, 1), per_die = (total + dies - 1) / dies;
     std::vector<SplitWg> wgs;
     plan->item_parts.assign(n_items, ItemParts{0, 0});
     for (int64_t d = 0; d < dies; ++d)
@@ -529,13 +537,50 @@ void split_plan(HostPlan* plan, const ChipShape& chip) {
             plan->item_parts[i] = ItemParts{(int32_t)wgs.size(), parts[i]};
             for (int32_t x = 0; x < parts[i]; ++x) wgs.push_back(SplitWg{(int32_t)i, x | (parts[i] << 16), (int32_t)wgs.size()});
         }
+    // The shares die after die in the items' order, cut into a run of the same number for every die: the shares of a tile, and the tiles that read
+    // the same K/V rows, are on a die but where a run ends.  Where a compute unit then walks longer, the shares of every length are cut so on
+    // their own (the rest of a length goes to the dies with the fewest shares so far): a die has as many of every length as any other.
+    // (us, all in one run per die / every length on its own: 2 images of 8043 tokens, windows of 4021, whose last tokens are a tile of
+    // one step 37.6 / 27.4; one list over all tokens, tiles of two and of three shares: 8 heads of 6464 112 / 91, 2 images of 2486, 10 heads 50.8 /
+    // 43.5; 12 heads of 4096, three branches, shares of 8 to 11 steps 34.4 / 34.6.)
     auto share_steps = [&](const SplitWg& g) { return plan->items[g.item].t.n_steps / (double)(g.part_nparts >> 16); };
-    plan->split_wgs.assign(per_die * dies, SplitWg{-1, 0, 0});
-    for (int64_t d = 0; d * per_die < total; ++d) {
-        const auto lo = wgs.begin() + d * per_die, hi = wgs.begin() + std::min(total, (d + 1) * per_die);
-        std::stable_sort(lo, hi, [&](const SplitWg& a, const SplitWg& c) { return share_steps(a) > share_steps(c); });
-        for (auto g = lo; g != hi; ++g) plan->split_wgs[(g - lo) * dies + d] = *g;
+    auto longer = [&](const SplitWg& a, const SplitWg& c) { return share_steps(a) > share_steps(c); };
+    using Dies = std::vector<std::vector<SplitWg>>;
+    auto runs = [&](Dies* of_die, size_t lo, size_t hi) {
+        std::vector<int64_t> run(dies, (int64_t)(hi - lo) / dies);
+        for (int64_t rest = (int64_t)(hi - lo) % dies; rest > 0; --rest) {
+            int64_t fewest = 0;
+            for (int64_t d = 1; d < dies; ++d)
+                if ((int64_t)(*of_die)[d].size() + run[d] < (int64_t)(*of_die)[fewest].size() + run[fewest]) fewest = d;
+            ++run[fewest];
+        }
+        for (int64_t d = 0; d < dies; lo += run[d++]) (*of_die)[d].insert((*of_die)[d].end(), wgs.begin() + lo, wgs.begin() + lo + run[d]);
+    };
+    const size_t die_cus = std::max(chip.cus / (int32_t)dies, 1);
+    auto longest_unit = [&](const Dies& of_die) {              // workgroups i, i + die_cus, ... of a die share a compute unit
+        double most = 0;
+        for (const auto& v : of_die)
+            for (size_t cu = 0; cu < std::min(die_cus, v.size()); ++cu) {
+                double steps = 0;
+                for (size_t x = cu; x < v.size(); x += die_cus) steps += share_steps(v[x]);
+                most = std::max(most, steps);
+            }
+        return most;
+    };
+    Dies of_die(dies), by_length(dies);
+    runs(&of_die, 0, wgs.size());
+    for (auto& v : of_die) std::stable_sort(v.begin(), v.end(), longer);
+    std::stable_sort(wgs.begin(), wgs.end(), longer);
+    for (size_t lo = 0, hi = 0; lo < wgs.size(); lo = hi) {
+        while (hi < wgs.size() && share_steps(wgs[hi]) == share_steps(wgs[lo])) ++hi;
+        runs(&by_length, lo, hi);
     }
+    if (longest_unit(of_die) > longest_unit(by_length)) of_die.swap(by_length);
+    size_t longest = 0;
+    for (const auto& v : of_die) longest = std::max(longest, v.size());
+    plan->split_wgs.assign(longest * dies, SplitWg{-1, 0, 0});
+    for (int64_t d = 0; d < dies; ++d)
+        for (size_t x = 0; x < of_die[d].size(); ++x) plan->split_wgs[x * dies + d] = of_die[d][x];
 }
 
 CutSize cut_size(const HostPlan& plan) {

@@ -106,6 +106,7 @@ struct HostPlan {
     std::vector<int32_t> block_mult; // [segs][kTileBlocks]: multiplicity for the rows of each 32-row block, 0 = they skip the keys
     bool packed_tiles = false;       // some tile packs several row groups (block_mult differs between blocks, filler slots)
     std::vector<Item> items;
+    bool whole_units = false;            // the launch order keeps all tiles of an (image, head) on one die
     std::vector<SplitWg> split_wgs;      // empty: the launch is not split
     std::vector<ItemParts> item_parts;
 };
@@ -137,8 +138,8 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 // small launch merges the partial results of the tiles that were cut by their log-sum-exp weights (a tile left whole
 // is written out by its one workgroup).  Launches that fill more than half the slots are left alone: cutting their
 // longest walks fills every CU with two workgroups, which slows every step by more than the shorter walks save
-// (two 1024^2 images: 54.7 us against 46.1 us).  The shares go to the dies in runs like the items they come from, the longest
-// of a die first.  Fills plan->split_wgs / item_parts, or
+// (two 1024^2 images: 54.7 us against 46.1 us).  The shares go to the dies in runs like the
+// items they come from, the longest of a die first.  Fills plan->split_wgs / item_parts, or
 // leaves them empty when the launch is not to be split.
 void split_plan(HostPlan* plan, const ChipShape& chip);
 

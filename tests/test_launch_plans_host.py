@@ -238,12 +238,16 @@ def test_long_walks_share_a_unit_with_short_ones(B, Bsz, H, N, branches):
         assert first == sorted(first, reverse=True) and second == sorted(second) and (not twos or first[-1] >= second[-1])
 
 
-# What a split launch reads: its shares cover every item's steps once, each with a block of partial results of its own, and which of several tiles with
-# equally long shares gets one more goes by the tiles (most pairs, then the first tile, then the first image), not by where the launch runs them.
+# What a split launch reads: its shares cover every item's steps once, each with a block of partial results of its own; every die has as many as the
+# others, and no compute unit walks longer than if every length were dealt out in turn; and which of several tiles with equally long shares gets one more goes by the tiles (most pairs, then the
+# first tile, then the first image; where units are dealt whole, every die's first unit before its second), not by where the launch runs them.
 @pytest.mark.parametrize("Bsz,H,N,branches", [
     (1, 12, 4096, [(1024, 1), (2048, 2), (4096, 4)]),                # 32 tiles of 32 steps have four shares, 16 of them three
     (2, 6, 4096, [(1024, 1), (2048, 2), (4096, 4)]), (1, 20, 2048, [(512, 1), (1024, 2), (2048, 4)]),
     (1, 2, 4224, [(1056, 1), (2112, 2), (4224, 4)]), (4, 1, 8448, [(8448, 1)]), (4, 3, 4032, [(4032, 1)]), (1, 3, 9664, [(2416, 1), (4832, 2), (9664, 4)]),
+    (2, 1, 8043, [(4021, 1)]),                                       # 256 shares of 15 or 16 steps, two of one step
+    (1, 8, 6464, [(6464, 1)]), (2, 8, 3072, [(3072, 1)]),            # units dealt whole, one and two to a die
+    (1, 8, 5568, [(1391, 1), (2778, 3), (5568, 5)]), (2, 10, 2486, [(2486, 1)]),
 ])
 def test_shares_of_a_split_launch(B, Bsz, H, N, branches):
     p = B.launch_describe(Bsz, H, N, branches, arrays=True)
@@ -262,16 +266,29 @@ def test_shares_of_a_split_launch(B, Bsz, H, N, branches):
     for item, part_nparts, block in shares[real].tolist():
         part, nparts = part_nparts & 0xffff, part_nparts >> 16
         assert nparts == parts[item] and 0 <= part < nparts and block == first[item] + part
+    steps = tiles[np.maximum(items[:, 0], 0), 5]
+    dies = [[int(steps[i]) / int(parts[i]) for i in shares[d::8, 0] if i >= 0] for d in range(8)]
+    assert all(v == sorted(v, reverse=True) for v in dies) and max(map(len, dies)) - min(map(len, dies)) <= 1
+    walks = lambda dies: max(sum(v[cu::32]) for v in dies for cu in range(min(32, len(v))))      # of a compute unit's workgroups
+    in_turn = sorted(sum(dies, []), reverse=True)
+    assert walks(dies) <= walks([in_turn[d::8] for d in range(8)])
     # the same by the rule
     pairs = np.zeros(len(tiles), dtype=np.int64)
     for t, (_, rb, nr, sb, ns, _) in enumerate(tiles.tolist()):
         slots = p["rows"][rb:rb + nr]
         rows = np.array([int((slots[32 * w:32 * w + 32] >= 0).sum()) for w in range(8)])
         pairs[t] = int((p["segs"][sb:sb + ns, 2].astype(np.int64) * ((p["block_mult"][sb:sb + ns] > 0) @ rows)).sum())
-    live = sorted((i for i in range(len(items)) if items[i, 0] >= 0), key=lambda i: (-pairs[items[i, 0]], items[i, 0], items[i, 1]))
+    units = Bsz * H
+    if units >= 32 or (units >= 8 and -(-units // 8) * 64 <= 9 * units):
+        def place(i):
+            t, unit = items[i, 0], items[i, 1] * H + tiles[items[i, 0], 0]
+            rank = int(sum(tiles[u, 0] == tiles[t, 0] and (-pairs[u], u) < (-pairs[t], t) for u in range(len(tiles))))
+            return (tiles[t, 4] <= 1, unit // 8, rank, unit % 8)
+    else:
+        place = lambda i: (-pairs[items[i, 0]], items[i, 0], items[i, 1])
+    live = sorted((i for i in range(len(items)) if items[i, 0] >= 0), key=place)
     want = np.zeros(len(items), dtype=np.int64)
     want[live] = 1
-    steps = tiles[np.maximum(items[:, 0], 0), 5]
     while want.sum() < 512:
         able = [i for i in live if want[i] < 4 and steps[i] // (want[i] + 1) >= 8]
         if not able:
