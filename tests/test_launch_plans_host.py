@@ -295,3 +295,51 @@ def test_shares_of_a_split_launch(B, Bsz, H, N, branches):
             break
         want[max(able, key=lambda i: -(-int(steps[i]) // int(want[i])))] += 1     # the first of the longest
     assert np.array_equal(want, parts)
+
+
+# What a short forward reads, one record of start_bytes per workgroup: its item, the tokens of its 64 slots, and for each of the four waves the blocks
+# wave, wave + 4, ... of the tile's list, then at least one record without a valid key (the last block again, for the copies that run ahead).
+@pytest.mark.parametrize("Bsz,H,N,branches,offs", [(2, 3, 32 * n - 7, [(32 * n - 7, 1)], None) for n in range(1, 10)] + [
+    (2, 3, 2048, [(2048, 1)], None),                                 # the longest lists: 16 records a wave
+    (1, 12, 256, [(64, 1), (128, 2), (256, 4)], None),               # filler slots, skipped blocks, multiplicities up to 3
+    (2, 3, 300, [(20, 1), (60, 3), (300, 5)], None),
+    (2, 2, 130, [(65, 2)], None),                                    # rows without keys
+    (3, 6, 1500, [(400, 1), (750, 3), (1500, 5)], [[(3 * h + x + 1) % r for h in range(6)] for x, r in enumerate((1, 3, 5))]),
+    (6, 2, 2500, [(625, 1), (1250, 2), (2500, 4)], None),
+])
+def test_starts_of_a_short_forward(B, Bsz, H, N, branches, offs):
+    p = B.launch_describe(Bsz, H, N, branches, offs, arrays=True)
+    image, data = B.launch_image(Bsz, H, N, branches, offs)
+    assert p["form"] == B.FORM_SHORT and len(data) == image["start_bytes"] * p["n_items"]
+    longest = int(p["tiles"][:, 4].max())
+    per_wave = -(-longest // 4) + 1
+    assert image["start_bytes"] == 4 * (8 + 64) + 16 * 4 * per_wave and per_wave <= 64
+    starts = data.reshape(p["n_items"], image["start_bytes"])
+    for start, (tile, b) in zip(starts, p["items"].tolist()):
+        item = start[:32].view(np.int32)
+        assert item[0] == tile
+        if tile < 0:
+            continue
+        assert item[1] == b and np.array_equal(item[2:], p["tiles"][tile])
+        _, rb, nr, sb, ns, _ = p["tiles"][tile].tolist()
+        assert np.array_equal(start[32:288].view(np.int32), p["rows"][rb + np.minimum(np.arange(64), nr - 1)])
+        if ns == 0:
+            assert not start[288:].any()
+            continue
+        ints = start[288:].view(np.uint32).reshape(4, per_wave, 4)
+        mult = start[288:].view(np.float32).reshape(4, per_wave, 4)[:, :, 2:]
+        with np.errstate(divide="ignore"):
+            want = np.log2(p["block_mult"][sb:sb + ns, :2].astype(np.float32))
+        for wave in range(4):
+            mine = np.arange(wave, ns, 4)
+            stride, count, turn = ints[wave, :, 1] & 0xffffff, ints[wave, :, 1] >> 24 & 0x3f, ints[wave, :, 1] >> 31
+            assert len(mine) < per_wave                                          # every share is followed by one without keys
+            n, segs = len(mine), p["segs"][sb + mine]
+            assert np.array_equal(np.stack((ints[wave, :n, 0], stride[:n], count[:n])).T, segs[:, :3])
+            assert np.array_equal(mult[wave, :n], want[mine])
+            changes = np.any(want[mine][1:] != want[mine][:-1], axis=1)
+            assert np.array_equal(turn[:n], np.concatenate(([True], changes))[:n] | (count[:n] < 32))
+            last = mine[-1] if n else 0                                          # a valid source for copies, masked as a whole
+            assert np.all(count[n:] == 0) and np.all(turn[n:] == 1)
+            assert np.all(ints[wave, n:, 0] == p["segs"][sb + last, 0]) and np.all(stride[n:] == p["segs"][sb + last, 1])
+            assert np.array_equal(mult[wave, n:], np.broadcast_to(want[last], (per_wave - n, 2)))
