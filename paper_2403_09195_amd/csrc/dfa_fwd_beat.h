@@ -142,6 +142,47 @@ __device__ __forceinline__ void accumulate_block(const uint16_t* vblk, const Fra
         }
 }
 
+// The vector side of slot m of a beat's 18: exponents of score pair m, exponentials of pair m - 1, pair m - 2 rounded into its B-operand
+// slot (a vector instruction that needs the result of the one just before it stalls the wave, so a pair moves one stage per slot).
+// kSum: the numerators are added up before they are rounded.
+template <bool kSum>
+__device__ __forceinline__ void numerator_slot(int m, const floatx16 (&s_cur)[2], float c, const float (&m_ref)[2], float (&t)[16][2],
+                                               u32x4 (&p_cur)[2][2], float (&sum)[2][2]) {
+    if (m < 16) {
+        const int qb = m >> 3, v = 2 * (m & 7);
+        t[m][0] = fmaf(s_cur[qb][v], c, -m_ref[qb]);
+        t[m][1] = fmaf(s_cur[qb][v + 1], c, -m_ref[qb]);
+    }
+    if (m >= 1 && m < 17) {
+        t[m - 1][0] = __builtin_amdgcn_exp2f(t[m - 1][0]);
+        t[m - 1][1] = __builtin_amdgcn_exp2f(t[m - 1][1]);
+    }
+    if (m >= 2) {
+        const int q = m - 2, qb = q >> 3, pr = q & 7;
+        const bf16x2 w = {(__bf16)t[q][0], (__bf16)t[q][1]};
+        p_cur[qb][pr >> 2][pr & 3] = __builtin_bit_cast(uint32_t, w);
+        if (kSum) {
+            sum[qb][0] += t[q][0];
+            sum[qb][1] += t[q][1];
+        }
+    }
+}
+
+// Row sums of the rounded numerators on the matrix cores (register 0 of rs), 16-key group by group: a group goes two slots after its last pair.
+__device__ __forceinline__ void row_sum_group(int grp, const u32x4 (&p_cur)[2][2], const bf16x8& sel, floatx4 (&rs)[2]) {
+    const int qb = grp >> 1, st = grp & 1;
+    rs[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, __builtin_bit_cast(bf16x8, p_cur[qb][st]), st == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : rs[qb], 0, 0, 0);
+}
+__device__ __forceinline__ void row_sum_slot(int m, const u32x4 (&p_cur)[2][2], const bf16x8& sel, floatx4 (&rs)[2]) {
+    if (m == 7 || m == 11 || m == 15) row_sum_group((m - 7) >> 2, p_cur, sel, rs);
+}
+// the last group, after the beat's slots, and the sums
+__device__ __forceinline__ void row_sums(const u32x4 (&p_cur)[2][2], const bf16x8& sel, floatx4 (&rs)[2], float (&psum)[2]) {
+    row_sum_group(3, p_cur, sel, rs);
+    psum[0] = rs[0][0];
+    psum[1] = rs[1][0];
+}
+
 // One pipeline beat (32 keys).  Three independent pieces of work are woven into one
 // instruction stream, so that the matrix cores and the vector ALU of the SIMD are busy at the
 // same time from within a single wave:
@@ -149,9 +190,7 @@ __device__ __forceinline__ void accumulate_block(const uint16_t* vblk, const Fra
 //                  PREVIOUS block (V at v_prev, probabilities p_prev);
 //   vector ALU   : softmax numerators of the CURRENT block (s_cur -> p_cur).
 // The stream is laid out slot by slot: one MFMA, then the exponent, exponential and rounding
-// instructions of three different score pairs (a vector instruction that needs the
-// result of the one just before it stalls the wave, so each pair moves one stage per slot).
-// Whenever a 16-key group of p_cur is complete, one row-sum MFMA (selector `sel` times that group)
+// instructions of three different score pairs (numerator_slot).  Whenever a 16-key group of p_cur is complete, one row-sum MFMA (selector `sel` times that group)
 // adds it to psum: register 0 of its result is the sum over the group's 16 keys of the lane's query.
 // Scheduling fences keep the compiler from regrouping the slots.
 // kScores / kAccumulate: the beat has a next block to score / a previous block to accumulate (the first
@@ -164,7 +203,8 @@ __device__ __forceinline__ void beat(const uint16_t* k_next, const uint16_t* v_p
                                      float c, const float (&m_ref)[2], float (&psum)[2], const bf16x8& sel) {
     bf16x8 kf[2], vf[2];           // fragments of MFMA group r live in slot r & 1
     float t[16][2];                // exponents, then exponentials, of score pair q
-    floatx4 rs[2];                 // row sums of the rounded numerators, from the matrix cores (register 0)
+    floatx4 rs[2];                 // row sums of the rounded numerators
+    float no_sum[2][2];
 
     auto load_group = [&](int r) {     // group r: d-step r of the scores, (d block r/2, 16-key step r%2) of the accumulation
         if (kScores) kf[r & 1] = *reinterpret_cast<const bf16x8*>(k_next + (fl.k ^ (16 * r)));
@@ -191,30 +231,11 @@ __device__ __forceinline__ void beat(const uint16_t* k_next, const uint16_t* v_p
         // fragment reads run four slots ahead of their first MFMA
         if (m >= 2 && m < 14 && ((m - 2) & 3) == 0) load_group(((m - 2) >> 2) + 1);
         if (m >= 2 && m < 18) mfma(m - 2);
-        if (m < 16) {                                   // exponents of pair m
-            const int qb = m >> 3, v = 2 * (m & 7);
-            t[m][0] = fmaf(s_cur[qb][v], c, -m_ref[qb]);
-            t[m][1] = fmaf(s_cur[qb][v + 1], c, -m_ref[qb]);
-        }
-        if (m >= 1 && m < 17) {                         // exponentials of pair m - 1
-            t[m - 1][0] = __builtin_amdgcn_exp2f(t[m - 1][0]);
-            t[m - 1][1] = __builtin_amdgcn_exp2f(t[m - 1][1]);
-        }
-        if (m >= 2 && m < 18) {                         // pair m - 2: round into its B-operand slot, add to the row sums
-            const int q = m - 2, qb = q >> 3, pr = q & 7;
-            const bf16x2 w = {(__bf16)t[q][0], (__bf16)t[q][1]};
-            p_cur[qb][pr >> 2][pr & 3] = __builtin_bit_cast(uint32_t, w);
-        }
-        if (m == 7 || m == 11 || m == 15) {             // row sums of the 16-key group finished two slots ago
-            const int grp = (m - 7) >> 2, qb = grp >> 1, st = grp & 1;
-            rs[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, __builtin_bit_cast(bf16x8, p_cur[qb][st]),
-                                                             st == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : rs[qb], 0, 0, 0);
-        }
+        numerator_slot<false>(m, s_cur, c, m_ref, t, p_cur, no_sum);
+        row_sum_slot(m, p_cur, sel, rs);
         __builtin_amdgcn_sched_barrier(0);
     }
-    rs[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, __builtin_bit_cast(bf16x8, p_cur[1][1]), rs[1], 0, 0, 0);
-    psum[0] = rs[0][0];
-    psum[1] = rs[1][0];
+    row_sums(p_cur, sel, rs, psum);
 }
 
 // The wave-uniform end of a beat: accept the numerators, or (rarely) move the reference

@@ -99,36 +99,13 @@ __device__ __forceinline__ void beat_halves(const uint16_t* k_next, const uint16
         if (m == 6) values();
         if (m >= 2 && m <= 12 && m % 2 == 0) load(m / 2 + 1);
         if (m >= 2) mfma(m - 2);
-        if (m < 16) {                                   // exponents of pair m
-            const int qb = m >> 3, v = 2 * (m & 7);
-            t[m][0] = fmaf(s_cur[qb][v], c, -m_ref[qb]);
-            t[m][1] = fmaf(s_cur[qb][v + 1], c, -m_ref[qb]);
-        }
-        if (m >= 1 && m < 17) {                         // exponentials of pair m - 1
-            t[m - 1][0] = __builtin_amdgcn_exp2f(t[m - 1][0]);
-            t[m - 1][1] = __builtin_amdgcn_exp2f(t[m - 1][1]);
-        }
-        if (m >= 2) {                                   // pair m - 2: rounded into its B-operand slot
-            const int q = m - 2, qb = q >> 3, pr = q & 7;
-            const bf16x2 w = {(__bf16)t[q][0], (__bf16)t[q][1]};
-            p_cur[qb][pr >> 2][pr & 3] = __builtin_bit_cast(uint32_t, w);
-            if (!kAccumulate) {
-                sum[qb][0] += t[q][0];
-                sum[qb][1] += t[q][1];
-            }
-        }
-        if (kAccumulate && (m == 7 || m == 11 || m == 15)) {       // row sums of the 16-key group finished two slots ago
-            const int grp = (m - 7) >> 2, qb = grp >> 1, st = grp & 1;
-            rs[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, __builtin_bit_cast(bf16x8, p_cur[qb][st]),
-                                                             st == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : rs[qb], 0, 0, 0);
-        }
+        numerator_slot<!kAccumulate>(m, s_cur, c, m_ref, t, p_cur, sum);
+        if (kAccumulate) row_sum_slot(m, p_cur, sel, rs);
         __builtin_amdgcn_sched_barrier(0);
         if (m == 9) keys();                             // the MFMAs with the last of the keys are behind us
     }
     if (kAccumulate) {
-        rs[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, __builtin_bit_cast(bf16x8, p_cur[1][1]), rs[1], 0, 0, 0);
-        psum[0] = rs[0][0];
-        psum[1] = rs[1][0];
+        row_sums(p_cur, sel, rs, psum);
     } else {
         psum[0] = wave_half_sum(sum[0][0] + sum[0][1]);
         psum[1] = wave_half_sum(sum[1][0] + sum[1][1]);
