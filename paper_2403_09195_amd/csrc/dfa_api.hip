@@ -657,7 +657,7 @@ int dfa_backward(const void* q, const void* k, const void* v, const void* out, c
         p.rows = dp.rows; p.segs = dp.segs; p.items = dp.items;
         p.H = H; p.N = N; p.scale = scale;
         if (dp.short_walk)
-            return launch_bwd_short(p, dp.n_items, B, static_cast<hipStream_t>(stream)) == hipSuccess ? DFA_OK : DFA_ERR_LAUNCH;
+            return launch_bwd_short(p, dp.n_items, dp.max_tile_rows, B, static_cast<hipStream_t>(stream)) == hipSuccess ? DFA_OK : DFA_ERR_LAUNCH;
         return launch_bwd(p, dp.n_items, dp.max_tile_rows, dp.cut, B, dt == DFA_BF16, static_cast<hipStream_t>(stream)) == hipSuccess
                    ? DFA_OK : DFA_ERR_LAUNCH;
     } catch (const std::bad_alloc&) {
@@ -835,7 +835,7 @@ int dfa_launch_describe(int32_t backward, dfa_dtype_t dt, int32_t B, int32_t H, 
         // the largest of the call's kernel launches, as the launchers of each form size it
         int64_t workgroups = choice.n_items;
         if (choice.short_walk) {
-            if (backward) workgroups = short_backward_workgroups(std::min(choice.n_items, kLaunchItems));
+            if (backward) workgroups = short_backward_workgroups(std::min(choice.n_items, kLaunchItems), short_dkdv_parts(choice.max_tile_rows));
         } else if (kind == PlanKind::kBlocks) {
             const int parts = (backward ? 2 : 1) * ((choice.max_tile_rows + kWalkBlock - 1) / kWalkBlock);
             workgroups = (int64_t)std::min(choice.n_items, kLaunchItems) * parts;

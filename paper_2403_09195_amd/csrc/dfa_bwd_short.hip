@@ -16,6 +16,9 @@
 // fragments itself before (32 lines touched per load, 16 loads a wave for dq: 2.8 us from the row numbers to the last one issued), and the
 // waves' sums go out behind one barrier.  Backward alone, us, before / now: four images of 1024 tokens, 6 heads 23.9 / 20.6, one of 2500, 12 heads
 // 47.6 / 42.9, one of 256 9.2 / 8.4, 16 of 512 90.7 / 78.3.
+// Tiles of a few rows or one short list pay for rows and waves that there are not: waves without a block write no results and copies of rows past the
+// tile's end are left out, no second dk/dv workgroup is launched where no tile has more than 32 rows.  Four branches, us, own rows loaded by every
+// wave / copied / copied so: 106 images of 34 tokens, 2 heads 114 / 125 / 83, 22 of 13, 12 heads 69 / 73 / 49, 8 of 64, 12 heads 28.2 / 28.1 / 20.0, one of 256 9.5 / 8.4 / 8.2, of 2500 52.1 / 42.7 / 42.9.
 #include "dfa_bwd_bf16.h"
 
 namespace dfa {
@@ -49,21 +52,23 @@ struct ShortLds {
 static_assert(sizeof(ShortLds) <= 80 * 1024, "two workgroups to a CU");
 static_assert(sizeof(ShortLds::blocks) / kWalkWaves >= kShortRows * kD * 4, "a wave's results fit its blocks");
 
-// The two [32][64] results of every wave into its blocks' place, rows 0 to 31 and 32 to 63: what sum_of_waves adds up.
-__device__ __forceinline__ void results_to_lds(const floatx16 (&first)[2], const floatx16 (&second)[2], ShortLds& mem, int tid) {
+// The two [32][64] results of a wave that walked (n blocks) into its blocks' place, rows 0 to 31 and, if `both`, 32 to 63: what sum_of_waves adds up.
+__device__ __forceinline__ void results_to_lds(const floatx16 (&first)[2], const floatx16 (&second)[2], ShortLds& mem, int tid, int n, bool both) {
     float* const mine = reinterpret_cast<float*>(mem.blocks[tid >> 6]);
-    half_to_lds(first[0], first[1], mine, 0, tid & 63);
-    half_to_lds(second[0], second[1], mine, 1, tid & 63);
+    if (n > 0) {
+        half_to_lds(first[0], first[1], mine, 0, tid & 63);
+        if (both) half_to_lds(second[0], second[1], mine, 1, tid & 63);
+    }
     __syncthreads();
 }
-// Row tid / 4 of the sum of the waves' results times `scale`, this thread's 16 d of it (see result_chunk), to dst[od ..] and dst[od + 32 ..].
-__device__ __forceinline__ void sum_of_waves(const ShortLds& mem, int tid, float scale, uint16_t* dst) {
+// Row tid / 4 of the sum of the first `walkers` waves' results times `scale`, this thread's 16 d of it (see result_chunk), to dst[od ..] and
+// dst[od + 32 ..].
+__device__ __forceinline__ void sum_of_waves(const ShortLds& mem, int tid, int walkers, float scale, uint16_t* dst) {
     const int row = tid >> 2, od = (tid & 3) * 8;
     float o[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[e] = 0.f;
-#pragma unroll
-    for (int x = 0; x < kWalkWaves; ++x)
+    auto add = [&](int x) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float4 a = result_chunk(reinterpret_cast<const float*>(mem.blocks[x]), row, od, i);
@@ -72,6 +77,13 @@ __device__ __forceinline__ void sum_of_waves(const ShortLds& mem, int tid, float
             o[4 * i + 2] += a.z;
             o[4 * i + 3] += a.w;
         }
+    };
+    if (walkers == kWalkWaves) {
+#pragma unroll
+        for (int x = 0; x < kWalkWaves; ++x) add(x);
+    } else {
+        for (int x = 0; x < walkers; ++x) add(x);
+    }
     bf16x8 ob[2];
 #pragma unroll
     for (int e = 0; e < 16; ++e) ob[e >> 3][e & 7] = (__bf16)(o[e] * scale);
@@ -98,6 +110,7 @@ void bwd_rows_short_kernel(const BwdParams p) {
     float lse[kTurns];
 #pragma unroll
     for (int u = 0; u < kTurns; ++u) {
+        if ((int)blockIdx.x * kStatRows + kRows * u >= p.N) break;
         const int n = min(n0 + kRows * u, p.N - 1);
         const int64_t at = ((b * p.N + n) * p.H + h) * kD + 8 * part;
         go[u] = *reinterpret_cast<const bf16x8*>(static_cast<const uint16_t*>(p.dout) + at);
@@ -107,6 +120,7 @@ void bwd_rows_short_kernel(const BwdParams p) {
 #pragma unroll
     for (int u = 0; u < kTurns; ++u) {
         const int n = n0 + kRows * u;
+        if ((int)blockIdx.x * kStatRows + kRows * u >= p.N) break;
         float sum = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) sum = fmaf((float)go[u][e], (float)oo[u][e], sum);
@@ -170,6 +184,7 @@ __device__ __forceinline__ void dq_short(const BwdParams& p, ShortLds& mem, cons
         const uint32_t stat_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, mem.stats)) + 256u * wave;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
+            if (16 * wave + 8 * u >= tile.nrows) break;            // columns of rows that there are not: whatever LDS holds, never written
             copy_own_rows(qp, p.sqn, copy_row[u], u, own_addr + 1024u * u, lane);
             copy_own_rows(gp, g_pitch, copy_row[u], u, addr + kPairBytes + kBlockBytes + 1024u * u, lane);
         }
@@ -195,6 +210,7 @@ __device__ __forceinline__ void dq_short(const BwdParams& p, ShortLds& mem, cons
     float my_l2[2], my_nd[2];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
+        if (n == 0) break;
         const uint16_t* const g_rows = lds[2 * blk + (j >> 4)] + kPairElems + kBlockElems - 16 * (j >> 4) * kRowElems;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
@@ -263,8 +279,8 @@ __device__ __forceinline__ void dq_short(const BwdParams& p, ShortLds& mem, cons
         nx = nx2;
     }
 
-    results_to_lds(acc[0], acc[1], mem, tid);
-    if (tid >> 2 < tile.nrows) sum_of_waves(mem, tid, p.scale, grad + (int64_t)row_lds[tid >> 2] * g_pitch);
+    results_to_lds(acc[0], acc[1], mem, tid, n, tile.nrows > kWalkBlock);
+    if (tid >> 2 < tile.nrows) sum_of_waves(mem, tid, min(tile.nseg, kWalkWaves), p.scale, grad + (int64_t)row_lds[tid >> 2] * g_pitch);
 }
 
 // dk and dv of 32 rows, half `sub` of the tile: they are keys, the lists are walked as the queries that see them.
@@ -315,7 +331,7 @@ __device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, co
     };
     constexpr int kCopies = 2 * kBlockCopies + 1;
     // the own rows, a quarter of keys and values copied by each wave
-    {
+    if (8 * wave < nrows) {
         const uint32_t own_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, mem.own)) + 1024u * wave;
         copy_own_rows(kp, p.skn, copy_row, wave, own_addr, lane);
         copy_own_rows(vp, p.svn, copy_row, wave, own_addr + kBlockBytes, lane);
@@ -333,6 +349,7 @@ __device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, co
     bf16x8 kf[4], vf[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
+        if (n == 0) break;
         kf[kk] = *reinterpret_cast<const bf16x8*>(mem.own + (frag ^ (16 * kk)));
         vf[kk] = *reinterpret_cast<const bf16x8*>(mem.own + kBlockElems + (frag ^ (16 * kk)));
     }
@@ -378,14 +395,15 @@ __device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, co
         nx = nx2;
     }
 
-    results_to_lds(dk_acc, dv_acc, mem, tid);
+    results_to_lds(dk_acc, dv_acc, mem, tid, n, true);
     const int own = (tid >> 2) & (kWalkBlock - 1);     // threads 0 to 127 write dk = scale dS^T q, the others dv
-    if (own < nrows) sum_of_waves(mem, tid, tid < 128 ? p.scale : 1.0f, (tid < 128 ? grad_k : grad_v) + (int64_t)row_lds[own] * g_pitch);
+    if (own < nrows)
+        sum_of_waves(mem, tid, min(tile.nseg, kWalkWaves), tid < 128 ? p.scale : 1.0f, (tid < 128 ? grad_k : grad_v) + (int64_t)row_lds[own] * g_pitch);
 }
 
 // The dq workgroups (an item each, padded to a multiple of the dies), then the dk/dv workgroups: the longer ones start first.
 __global__ __launch_bounds__(64 * kWalkWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void bwd_short_kernel(const BwdParams p, int n_items, int n_dq) {
+void bwd_short_kernel(const BwdParams p, int n_items, int n_dq, int parts) {
     __shared__ __attribute__((aligned(1024))) ShortLds mem;
     hold_args(p);
     if ((int)blockIdx.x < n_dq) {
@@ -393,20 +411,21 @@ void bwd_short_kernel(const BwdParams p, int n_items, int n_dq) {
         return;
     }
     int item_index, sub;
-    item_of_part((int)blockIdx.x - n_dq, kShortDkdvParts, item_index, sub);
+    item_of_part((int)blockIdx.x - n_dq, parts, item_index, sub);
     if (item_index < n_items) dkdv_short(p, mem, load_item(p.items, item_index), sub);
 }
 
 }  // namespace
 
-hipError_t launch_bwd_short(const BwdParams& p, int n_items, int32_t B, hipStream_t st) {
+hipError_t launch_bwd_short(const BwdParams& p, int n_items, int max_tile_rows, int32_t B, hipStream_t st) {
     hipLaunchKernelGGL(bwd_rows_short_kernel, dim3((unsigned)((p.N + kStatRows - 1) / kStatRows), p.H, B), dim3(256), 0, st, p);
+    const int parts = short_dkdv_parts(max_tile_rows);
     for (int i0 = 0; i0 < n_items; i0 += kLaunchItems) {         // a grid holds fewer than 2^32 threads
         BwdParams q = p;
         q.items += i0;
         const int n = n_items - i0 < kLaunchItems ? n_items - i0 : kLaunchItems;
         const int n_dq = (n + kDies - 1) / kDies * kDies;
-        hipLaunchKernelGGL(bwd_short_kernel, dim3((unsigned)short_backward_workgroups(n)), dim3(64 * kWalkWaves), 0, st, q, n, n_dq);
+        hipLaunchKernelGGL(bwd_short_kernel, dim3((unsigned)short_backward_workgroups(n, parts)), dim3(64 * kWalkWaves), 0, st, q, n, n_dq, parts);
     }
     return hipGetLastError();
 }

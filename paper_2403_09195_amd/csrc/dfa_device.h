@@ -97,7 +97,7 @@ hipError_t launch_fwd_f32(const FwdParams& p, int n_items, int max_tile_rows, bo
 hipError_t launch_bwd(const BwdParams& p, int n_items, int max_tile_rows, bool cut, int32_t B, bool bf16, hipStream_t st);
 hipError_t launch_bwd_bf16(const BwdParams& p, int n_items, hipStream_t st);
 // plans of plain 64-row tiles with their lists cut into blocks
-hipError_t launch_bwd_short(const BwdParams& p, int n_items, int32_t B, hipStream_t st);
+hipError_t launch_bwd_short(const BwdParams& p, int n_items, int max_tile_rows, int32_t B, hipStream_t st);
 hipError_t launch_linear_bf16(const void* x, const void* w, void* y, int64_t M, int32_t N, int32_t K,
                               int64_t ldx, int64_t ldw, int64_t ldy, const ChipShape& chip, hipStream_t st);
 // batch of products of one shape: matrix (z0, z1) starts at x + z0 * xs0 + z1 * xs1 etc.; M % 256 == 0, N % 64 == 0, K % 64 == 0

@@ -221,8 +221,11 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 constexpr int kShortBackwardBlocks = 256;
 constexpr double kShortBackwardMargin = 0.97;
 constexpr double kFewTiles = 1280;
+// dk/dv workgroups of every tile of a plan whose tiles have up to max_tile_rows rows (tiles of up to 32 have no second half: an empty workgroup
+// still waits for a place on a CU)
+inline int short_dkdv_parts(int max_tile_rows) { return max_tile_rows > kWalkBlock ? kShortDkdvParts : 1; }
 // workgroups of the launch that works out all gradients of n_items launch items: dq ones, padded to whole rounds of the dies, then dk/dv ones
-inline int64_t short_backward_workgroups(int64_t n_items) { return (n_items + kDies - 1) / kDies * kDies * (1 + kShortDkdvParts); }
+inline int64_t short_backward_workgroups(int64_t n_items, int parts) { return (n_items + kDies - 1) / kDies * kDies * (1 + parts); }
 bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t nb, const int32_t* offsets,
                          int order_mode, const ChipShape& chip, const HostPlan& full, HostPlan* plan);
 

@@ -129,6 +129,34 @@ def test_backward_launch_of_more_than_one_slice(B):
     assert all(bool(torch.isfinite(t[-1].float()).all()) for t in grads)
 
 
+# Backward tiles of a few rows, without a second dk/dv workgroup (33 rows: with one), and lists of one to twelve blocks, so that no wave, some or
+# all have one.  A call of NaN before it leaves them in LDS, where the rows and the waves' places are that the call does not fill.
+@pytest.mark.parametrize("N,branches,most", [
+    (7, [(3, 1), (7, 2)], 2), (32, [(32, 1)], 32), (33, [(33, 1)], 33), (34, [(4, 1), (8, 2), (17, 4), (34, 8)], 2), (64, [(16, 1), (64, 1)], 16),
+    (96, [(24, 1), (96, 1)], 24), (160, [(32, 1), (160, 1)], 32), (165, [(33, 1), (165, 1)], 33), (340, [(17, 1), (340, 1)], 17),
+])
+def test_backward_of_tiles_of_few_rows(B, oracle, N, branches, most):
+    from paper_2403_09195_amd import synth
+    import torch
+    plan = B.launch_describe(3, 5, N, branches, backward=True, arrays=True)
+    assert plan["form"] == B.FORM_SHORT and int(plan["tiles"][:, 2].max()) == most
+    assert plan["threads"] == 256 * (2 if most <= 32 else 3) * plan["n_items"]
+    (q, k, v), ex = make_qkv(1600 + N, 3, N, 5, 64, "bf16")
+    out, lse = B.forward(q, k, v, branches, 0.125)
+    st, ge = synth.tensor(1600 + N, 7, (3, N, 5, 64), "bf16")
+    nan = torch.full((4, 1024, 6, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+    assert B.launch_describe(4, 6, 1024, [(1024, 1)], backward=True)["form"] == B.FORM_SHORT
+    B.backward(nan, nan, nan, nan, nan[..., 0].transpose(1, 2).float().contiguous(), nan, [(1024, 1)], 0.125)
+    grads = B.backward(q, k, v, out, lse, to_device(st), branches, 0.125)
+    refs = oracle.backward(*ex, ge, branches, 0.125)
+    bounds = helpers.multiset_attention_backward(*ex, ge, 0.125, branches)[3:]
+    eps = 2.0 ** -9
+    for name, got, ref, absum in zip(("dq", "dk", "dv"), grads, refs, bounds):
+        d = np.abs(to_f64(got) - ref)
+        assert np.all(d <= 2.0 ** -8 * np.abs(ref) + 4 * eps * absum + 1e-6), name
+        assert d.mean() <= eps * absum.mean() + 1e-7, name
+
+
 # launches of more than a round of workgroups: in place of whole tiles (ragged, offsets) and of a split launch
 @pytest.mark.parametrize("Bsz,H,N,branches,offs", [
     (3, 6, 2053, [(511, 1), (1029, 3), (2053, 5)], [[(3 * h + x + 1) % r for h in range(6)] for x, r in enumerate((1, 3, 5))]),
