@@ -709,8 +709,8 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     const bool few = (int64_t)full.items.size() <= one, fit = (int64_t)full.items.size() <= slots;
     const double other_us = split               ? (shared ? 23.3 + 0.002 * steps : 12.6 + 0.0043 * steps)
                             : full.packed_tiles ? (few   ? 6.9 + 0.0025 * tiles + 0.00012 * steps + 1.27 * whole.longest
-                                                   : fit ? 10.7 - 0.0044 * tiles + 0.00167 * steps + 0.89 * whole.longest
-                                                         : 7.4 + 0.0044 * tiles + 0.0025 * steps + 0.89 * whole.longest)
+                                                   : fit ? 6.8 + 0.0023 * steps + 1.06 * whole.longest
+                                                         : 5.0 + 0.0053 * steps + 0.74 * whole.longest)
                             : few ? 4.1 + 0.002 * tiles + 0.0002 * steps + 1.2 * whole.longest
                             : fit ? 3.6 + 0.005 * tiles + 0.0025 * steps + 0.86 * whole.longest
                                   : 5.5 + 0.0031 * tiles + 0.0037 * steps + 0.65 * whole.longest;

@@ -195,6 +195,9 @@ constexpr int kTailBlocks = 19;
 // 12 heads 17.7 / 19.4).  us, tiles or split / short: 7 images of 1152 tokens, 3 heads, four branches 30.9 / 14.4; 2 of 875, 16 heads 24.8 / 13.6;
 // one of 4736, 8 heads, windows of 1184 at rate 3 13.2 / 8.2; left as they are: one of 4096, 12 heads, split 30.6 / 31.8;
 // 10 of 959, 6 heads, windows of 191 12.2 / 14.3.
+// (Packed tiles of more than one to a CU: fitted again to 399 launches of 1 to 32 heads and 16 tokens on.  Lists of a few steps had been estimated up to a
+// fifth too long, and the short form was taken where it is the slower one: 23 images of 98 tokens, 4 heads, two branches 12.4 us in tiles, 14.9
+// short.  Of 1600 launches the choice is more than 5 % slower than the other form on 47, where it was on 61, and 0.4 % in the mean.)
 // With one workgroup to a CU, lists that do not fill their last step stay with the short kernel whatever the times: it clears the rows past a list's
 // end, where the 256-row kernel gives them weight 0, which makes NaN of an infinite value, and its start outweighs the walk by 2 us at most.
 // Packed tiles without a free row, of lists under kFullSteps steps, stay past nine eighths of the slots although they are slower (3 of 1024 tokens, 12
