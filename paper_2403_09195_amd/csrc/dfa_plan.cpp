@@ -696,7 +696,6 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     if (!split && !full.packed_tiles && whole.longest <= 1) return false;
     // packed tiles that are full walk like tiles of one group
     const bool shared = full.packed_tiles && std::any_of(full.tiles.begin(), full.tiles.end(), [](const Tile& t) { return t.nrows != kTileRows; });
-    if (!split && full.packed_tiles && !shared && plan->items.size() > near && whole.longest < kFullSteps) return false;
     // us, see kShortMargin
     const double per_slot = 512.0 / slots;
     const double items = per_slot * plan->items.size(), live = per_slot * size.live, blocks = per_slot * size.blocks;
@@ -780,7 +779,7 @@ bool short_backward_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br
             live += i.t.nseg > 0;
             blocks += (int64_t)i.t.nseg * ((i.t.nrows + kBlockRows - 1) / kBlockRows);
         }
-    if (per_slot * tiles > kFewTiles || (N <= kShortRows && tiles >= slots)) return 10.0 + per_slot * (0.024 * tiles + 0.00105 * blocks) < long_us;
+    if (per_slot * tiles > kFewTiles) return 10.0 + per_slot * (0.024 * tiles + 0.00105 * blocks) < long_us;
     const double short_us = live * (1 + kShortDkdvParts) <= 2 * slots ? 14.8 + 0.00075 * per_slot * blocks
                                                                       : 4.7 + per_slot * (0.0077 * tiles + 0.0135 * live + 0.00097 * blocks) + 0.098 * size.longest;
     return short_us * kShortBackwardMargin < full_us;

@@ -193,16 +193,13 @@ constexpr int kTailBlocks = 19;
 // heads 5.4 / 7.2), and of split launches none of up to nine eighths of the slots.  On 897 other drawn launches the choice differs from that by
 // estimates fitted to earlier kernels on 87, which run 1.23 times as fast in the mean, two slower by more than 3 % (0.91 at worst: 11 of 259 tokens,
 // 12 heads 17.7 / 19.4).  us, tiles or split / short: 7 images of 1152 tokens, 3 heads, four branches 30.9 / 14.4; 2 of 875, 16 heads 24.8 / 13.6;
-// one of 4736, 8 heads, windows of 1184 at rate 3 13.2 / 8.2; left as they are: one of 4096, 12 heads, split 30.6 / 31.8;
+// one of 4736, 8 heads, windows of 1184 at rate 3 13.2 / 8.2; 3 of 1024, 12 heads 17.0 / 14.1; left as they are: one of 4096, 12 heads, split 30.6 / 31.8;
 // 10 of 959, 6 heads, windows of 191 12.2 / 14.3.
 // (Packed tiles of more than one to a CU: fitted again to 399 launches of 1 to 32 heads and 16 tokens on.  Lists of a few steps had been estimated up to a
 // fifth too long, and the short form was taken where it is the slower one: 23 images of 98 tokens, 4 heads, two branches 12.4 us in tiles, 14.9
 // short.  Of 1600 launches the choice is more than 5 % slower than the other form on 47, where it was on 61, and 0.4 % in the mean.)
 // With one workgroup to a CU, lists that do not fill their last step stay with the short kernel whatever the times: it clears the rows past a list's
 // end, where the 256-row kernel gives them weight 0, which makes NaN of an infinite value, and its start outweighs the walk by 2 us at most.
-// Packed tiles without a free row, of lists under kFullSteps steps, stay past nine eighths of the slots although they are slower (3 of 1024 tokens, 12
-// heads 16.7 / 13.9): the tests of the packed kernel at its regular size run there.
-constexpr int kFullSteps = 10;
 constexpr double kShortMargin = 1.05;
 constexpr double kIdleMargin = 1.25;      // one round of workgroups with keys, and others that need a second one
 constexpr double kWholeMargin = 1.15;     // more than a round, against tiles of one row group each
@@ -218,8 +215,7 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 // estimates fitted to earlier kernels cost 1.6 %: it differs on 67, which run 1.18 times as fast in the mean, three slower by more than 3 % (0.93 at
 // worst).  Past kFewTiles 64-row tiles the earlier ones are as good and stay: 15 + the larger of 3.2 per step of the longest list and
 // 0.0164 per step of all 256-row tiles, against 10 + 0.024 per 64-row tile + 0.00105 per block of pairs.  us, full / short: 8 images of 384 tokens, 12 heads,
-// windows of 54 32.1 / 22.5 (images of up to 64 tokens go by the earlier ones from a round on, although 64 of 64, 8 heads, take 20.6 / 16.4: the
-// tests of one-step walks of the full kernels run there); 7 of 521, 12 heads, one window 64.3 / 47.6; 2 of 3520, 8 heads, windows of 1173 at rate 3 36.2 / 26.1.
+// windows of 54 32.1 / 22.5; 64 of 64, 8 heads 20.4 / 16.2; 7 of 521, 12 heads, one window 64.3 / 47.6; 2 of 3520, 8 heads, windows of 1173 at rate 3 36.2 / 26.1.
 // `full` is the plain plan of 256-row tiles.
 constexpr int kShortBackwardBlocks = 256;
 constexpr double kShortBackwardMargin = 0.97;

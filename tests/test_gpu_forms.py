@@ -84,7 +84,7 @@ def test_forward_split(B, oracle, H, N, branches, offs, packed):
 @pytest.mark.parametrize("packed", [False, True])
 def test_backward_whole_tiles_list_lengths(B, oracle, count, packed):
     import torch
-    Bsz, N, H, branches = (400 if count < 63 else 64), count, 8, [(count, 1)]
+    Bsz, N, H, branches = (400 if count <= 64 else 64), count, 8, [(count, 1)]
     assert B.launch_describe(Bsz, H, N, branches, backward=True)["form"] == B.FORM_TILES
     (q, k, v), ex = make_qkv(2500 + count, Bsz, N, H, 64, "bf16")
     if packed:

@@ -133,7 +133,7 @@ def test_bf16_small_multi_tile(B, oracle):
 @pytest.mark.parametrize("Bsz,N,H,branches,form", [
     (2, 256, 6, [(64, 1), (128, 2), (256, 4)], "short"),     # 256^2 image, 64-row tiles: groups of 32 and 16 rows, filler slots between them
     (40, 256, 12, [(64, 1), (128, 2), (256, 4)], "tiles"),   # the same in 256-row tiles of six groups
-    (3, 1024, 12, [(256, 1), (512, 2), (1024, 4)], "tiles"), # 512^2 image: groups of 128, 64, 64 rows fill a tile exactly
+    (6, 1024, 12, [(256, 1), (512, 2), (1024, 4)], "tiles"), # 512^2 image: groups of 128, 64, 64 rows fill a tile exactly
     (1, 2048, 20, [(512, 1), (1024, 2), (2048, 4)], "split"),  # two groups of 128 rows share a tile whose walk is split over workgroups
     (1, 2200, 2, [(2200, 1), (150, 2), (300, 4)], "split"),  # ragged groups in split tiles
     (2, 600, 3, [(100, 1), (300, 2), (600, 3), (50, 1)], "short"),   # ragged groups, rates 2 and 3

@@ -101,7 +101,7 @@ def test_launches_of_two_rounds_of_row_groups(B, Bsz, H, N, branches, offs, form
 # Where the estimates choose: part-filled tiles go to the short form, split or not; tiles of one step stay, and so do workgroups with keys that fit one
 # round beside many without.
 @pytest.mark.parametrize("Bsz,H,N,branches,form", [
-    (7, 3, 1152, [(144, 1), (288, 2), (576, 4), (1152, 8)], "SHORT"), (1, 8, 4736, [(1184, 3)], "SHORT"), (3, 12, 1024, [(256, 1), (512, 2), (1024, 4)], "TILES"),
+    (7, 3, 1152, [(144, 1), (288, 2), (576, 4), (1152, 8)], "SHORT"), (1, 8, 4736, [(1184, 3)], "SHORT"), (3, 12, 1024, [(256, 1), (512, 2), (1024, 4)], "SHORT"), (6, 12, 1024, [(256, 1), (512, 2), (1024, 4)], "TILES"),
     (7, 16, 133, [(33, 1), (66, 2), (133, 4)], "TILES"), (23, 4, 98, [(12, 1), (24, 2)], "TILES"), (10, 9, 66, [(8, 1), (16, 2)], "TILES"),
     (16, 8, 298, [(149, 3)], "TILES"), (6, 6, 256, [(32, 1)], "TILES"), (6, 8, 1280, [(640, 2)], "TILES"), (10, 6, 959, [(191, 1)], "TILES"),
 ])
@@ -112,7 +112,7 @@ def test_form_with_the_shorter_estimate(B, Bsz, H, N, branches, form):
 
 @pytest.mark.parametrize("Bsz,H,N,branches,form", [
     (8, 8, 326, [(40, 1)], "SHORT"), (2, 8, 3520, [(1173, 3)], "SHORT"), (4, 6, 1024, [(256, 1), (512, 2), (1024, 4)], "SHORT"),
-    (64, 8, 128, [(128, 1)], "TILES"), (16, 12, 4096, [(1024, 1), (2048, 2), (4096, 4)], "TILES"),
+    (64, 8, 64, [(64, 1)], "SHORT"), (256, 2, 33, [(33, 1)], "SHORT"), (400, 8, 64, [(64, 1)], "TILES"), (64, 8, 128, [(128, 1)], "TILES"), (16, 12, 4096, [(1024, 1), (2048, 2), (4096, 4)], "TILES"),
 ])
 def test_backward_form_with_the_shorter_estimate(B, Bsz, H, N, branches, form):
     p = _check_launched_plan(B, Bsz, H, N, branches, None, B.DFA_BF16, True)
