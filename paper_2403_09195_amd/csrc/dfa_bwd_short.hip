@@ -16,9 +16,9 @@
 // fragments itself before (32 lines touched per load, 16 loads a wave for dq: 2.8 us from the row numbers to the last one issued), and the
 // waves' sums go out behind one barrier.  Backward alone, us, before / now: four images of 1024 tokens, 6 heads 23.9 / 20.6, one of 2500, 12 heads
 // 47.6 / 42.9, one of 256 9.2 / 8.4, 16 of 512 90.7 / 78.3.
-// Tiles of a few rows or one short list pay for rows and waves that there are not: waves without a block write no results and copies of rows past the
-// tile's end are left out, no second dk/dv workgroup is launched where no tile has more than 32 rows.  Four branches, us, own rows loaded by every
-// wave / copied / copied so: 106 images of 34 tokens, 2 heads 114 / 125 / 83, 22 of 13, 12 heads 69 / 73 / 49, 8 of 64, 12 heads 28.2 / 28.1 / 20.0, one of 256 9.5 / 8.4 / 8.2, of 2500 52.1 / 42.7 / 42.9.
+// Tiles of a few rows or one short list pay for rows and waves that there are not: rows past 32 that a tile does not have and waves without a block write no
+// results and are not added up, no second dk/dv workgroup is launched where no tile has more than 32 rows.  Four branches, us, own rows loaded by every
+// wave / copied / copied so: 106 images of 34 tokens, 2 heads 114 / 125 / 83, 22 of 13, 12 heads 69 / 73 / 49, 8 of 64, 12 heads 28.2 / 28.1 / 20.0, one of 256 9.5 / 8.4 / 8.2, of 2500 52.1 / 42.7 / 42.7.
 #include "dfa_bwd_bf16.h"
 
 namespace dfa {
@@ -184,7 +184,6 @@ __device__ __forceinline__ void dq_short(const BwdParams& p, ShortLds& mem, cons
         const uint32_t stat_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, mem.stats)) + 256u * wave;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            if (16 * wave + 8 * u >= tile.nrows) break;            // columns of rows that there are not: whatever LDS holds, never written
             copy_own_rows(qp, p.sqn, copy_row[u], u, own_addr + 1024u * u, lane);
             copy_own_rows(gp, g_pitch, copy_row[u], u, addr + kPairBytes + kBlockBytes + 1024u * u, lane);
         }
@@ -210,7 +209,6 @@ __device__ __forceinline__ void dq_short(const BwdParams& p, ShortLds& mem, cons
     float my_l2[2], my_nd[2];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
-        if (n == 0) break;
         const uint16_t* const g_rows = lds[2 * blk + (j >> 4)] + kPairElems + kBlockElems - 16 * (j >> 4) * kRowElems;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
@@ -331,7 +329,7 @@ __device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, co
     };
     constexpr int kCopies = 2 * kBlockCopies + 1;
     // the own rows, a quarter of keys and values copied by each wave
-    if (8 * wave < nrows) {
+    {
         const uint32_t own_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)DFA_LDS_PTR(void, mem.own)) + 1024u * wave;
         copy_own_rows(kp, p.skn, copy_row, wave, own_addr, lane);
         copy_own_rows(vp, p.svn, copy_row, wave, own_addr + kBlockBytes, lane);
@@ -349,7 +347,6 @@ __device__ __forceinline__ void dkdv_short(const BwdParams& p, ShortLds& mem, co
     bf16x8 kf[4], vf[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-        if (n == 0) break;
         kf[kk] = *reinterpret_cast<const bf16x8*>(mem.own + (frag ^ (16 * kk)));
         vf[kk] = *reinterpret_cast<const bf16x8*>(mem.own + kBlockElems + (frag ^ (16 * kk)));
     }
@@ -411,7 +408,9 @@ void bwd_short_kernel(const BwdParams p, int n_items, int n_dq, int parts) {
         return;
     }
     int item_index, sub;
-    item_of_part((int)blockIdx.x - n_dq, parts, item_index, sub);
+    // (both counts as constants: the division by a variable one took 0.3 us of the 43 of one image of 2500 tokens)
+    if (parts == 1) item_of_part((int)blockIdx.x - n_dq, 1, item_index, sub);
+    else item_of_part((int)blockIdx.x - n_dq, kShortDkdvParts, item_index, sub);
     if (item_index < n_items) dkdv_short(p, mem, load_item(p.items, item_index), sub);
 }
 

@@ -130,7 +130,7 @@ def test_backward_launch_of_more_than_one_slice(B):
 
 
 # Backward tiles of a few rows, without a second dk/dv workgroup (33 rows: with one), and lists of one to twelve blocks, so that no wave, some or
-# all have one.  A call of NaN before it leaves them in LDS, where the rows and the waves' places are that the call does not fill.
+# all have one.  A call of NaN before it leaves them in LDS, where the places of rows and waves are that the call does not fill.
 @pytest.mark.parametrize("N,branches,most", [
     (7, [(3, 1), (7, 2)], 2), (32, [(32, 1)], 32), (33, [(33, 1)], 33), (34, [(4, 1), (8, 2), (17, 4), (34, 8)], 2), (64, [(16, 1), (64, 1)], 16),
     (96, [(24, 1), (96, 1)], 24), (160, [(32, 1), (160, 1)], 32), (165, [(33, 1), (165, 1)], 33), (340, [(17, 1), (340, 1)], 17),
