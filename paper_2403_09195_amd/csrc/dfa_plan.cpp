@@ -380,7 +380,9 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
     // Fewer units: the tiles one after the other, unit by unit and within a unit by their first row, cut into a run of the same number for
     // every die: the tiles of a run share most of their K/V rows, which the die then reads once.  Only where that balances the dies to
     // within a thirty-second; otherwise single tiles are spread.  (12 heads, us, spread / runs: one 1024^2 image, forward 32.1 / 30.0, one 800^2
-    // image, forward and backward 69.4 / 64.2, two 512^2 images of 6 heads in fp32 60.9 / 58.3; one image of 10122 tokens 242 / 153.)
+    // image, forward and backward 69.4 / 64.2, two 512^2 images of 6 heads in fp32 60.9 / 58.3; one image of 10122 tokens 242 / 153.  Of 890 drawn
+    // launches those of 64 tiles and more take 0.91 to 0.99 of the time of spread ones, those of fewer the same.  So would the runs that the bound
+    // turns away, up to two fifths apart in pairs, and so do those whose dies are that far apart in steps: it could be wider.)
     auto by_runs = [&]() {
         const int64_t total = (int64_t)T * B;
         int64_t at = 0, all = 0;
@@ -441,7 +443,7 @@ void build_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
         const bool at_once = order_mode == 2 && v.size() <= (size_t)kSlotsPerDie;
         if (order_mode == 0 || !by_unit || at_once) {
             std::stable_sort(v.begin(), v.end(), longer);
-            if (pack && at_once && v.size() > die_cus) {
+            if (pack && at_once && v.size() > die_cus) {       // pack: a forward launch in bf16, one workgroup per item
                 // Workgroups i and i + die_cus share a compute unit.  The longest have one to themselves, of the others a long one goes with a
                 // short one.  (us, by length alone / so: 3 images of 2879 tokens, 3 heads 20.6 / 19.5, 12 heads of 1059 13.3 / 12.5; units dealt
                 // whole, unit by unit / so: 2 images of 865 tokens, 12 heads 12.6 / 11.0, 3 of 905, windows of 150 11.4 / 8.7.  Backward launches,

@@ -213,7 +213,8 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 // to a CU, one round and more.  Fitted to 900 calls (200 to 4096 tokens, 3 to 16 heads, 1 to 16 images, one to four branches), with residuals of 6 to 8 %
 // (short) and 7 to 12 % (full); below 16 us a call is bound by its host side.  On these the choice costs 0.4 % against the faster form of each, where
 // estimates fitted to earlier kernels cost 1.6 %: it differs on 67, which run 1.18 times as fast in the mean, three slower by more than 3 % (0.93 at
-// worst).  Past kFewTiles 64-row tiles the earlier ones are as good and stay: 15 + the larger of 3.2 per step of the longest list and
+// worst).  Past kFewTiles 64-row tiles the earlier ones stay (of 3010 launches, most of them past that, 326 would be more than 5 % shorter in the other
+// form since tiles of a few rows got shorter there; 4 % in the mean): 15 + the larger of 3.2 per step of the longest list and
 // 0.0164 per step of all 256-row tiles, against 10 + 0.024 per 64-row tile + 0.00105 per block of pairs.  us, full / short: 8 images of 384 tokens, 12 heads,
 // windows of 54 32.1 / 22.5; 64 of 64, 8 heads 20.4 / 16.2; 7 of 521, 12 heads, one window 64.3 / 47.6; 2 of 3520, 8 heads, windows of 1173 at rate 3 36.2 / 26.1.
 // `full` is the plain plan of 256-row tiles.
