@@ -210,7 +210,8 @@ bool short_plan(int32_t B, int32_t H, int32_t N, const dfa_branch_t* br, int32_t
 // a part-filled tile as on a full one; those of dfa_bwd_short.hip cut the walk by four and have 64-row tiles, but copy a block
 // for 64 (dq) or 32 rows (dk, dv).  Both times, in us, are linear in the plan: 64-row tiles, with and without keys, 32 x 32 blocks of pairs and the
 // longest list, in a sum each for up to two rounds of workgroups and for more; 256-row tiles, steps and the longest list, in a sum each for one tile
-// to a CU, one round and more.  Fitted to 900 calls (200 to 4096 tokens, 3 to 16 heads, 1 to 16 images, one to four branches), with residuals of 6 to 8 %
+// to a CU, one round and more.  (In the middle one tiles weigh less than nothing: of the same steps, more tiles are shorter walks.  Fitted without
+// that, to 498 calls, it sends 86 of 3010 elsewhere, to no gain in the mean and 1.65 times the time at worst.)  Fitted to 900 calls (200 to 4096 tokens, 3 to 16 heads, 1 to 16 images, one to four branches), with residuals of 6 to 8 %
 // (short) and 7 to 12 % (full); below 16 us a call is bound by its host side.  On these the choice costs 0.4 % against the faster form of each, where
 // estimates fitted to earlier kernels cost 1.6 %: it differs on 67, which run 1.18 times as fast in the mean, three slower by more than 3 % (0.93 at
 // worst).  Past kFewTiles 64-row tiles the earlier ones stay (of 3010 launches, most of them past that, 326 would be more than 5 % shorter in the other
