@@ -131,19 +131,20 @@ def test_backward_launch_of_more_than_one_slice(B):
 
 # Backward tiles of a few rows, without a second dk/dv workgroup (33 rows: with one), and lists of one to twelve blocks, so that no wave, some or
 # all have one.  A call of NaN before it leaves them in LDS, where the places of rows and waves are that the call does not fill.
-@pytest.mark.parametrize("N,branches,most", [
-    (7, [(3, 1), (7, 2)], 2), (32, [(32, 1)], 32), (33, [(33, 1)], 33), (34, [(4, 1), (8, 2), (17, 4), (34, 8)], 2), (64, [(16, 1), (64, 1)], 16),
-    (96, [(24, 1), (96, 1)], 24), (160, [(32, 1), (160, 1)], 32), (165, [(33, 1), (165, 1)], 33), (340, [(17, 1), (340, 1)], 17),
+@pytest.mark.parametrize("Bsz,N,branches,most", [
+    (3, 7, [(3, 1), (7, 2)], 2), (3, 32, [(32, 1)], 32), (3, 33, [(33, 1)], 33), (3, 34, [(4, 1), (8, 2), (17, 4), (34, 8)], 2), (3, 64, [(16, 1), (64, 1)], 16),
+    (3, 96, [(24, 1), (96, 1)], 24), (3, 160, [(32, 1), (160, 1)], 32), (3, 165, [(33, 1), (165, 1)], 33), (3, 340, [(17, 1), (340, 1)], 17),
+    (105, 33, [(33, 1)], 33), (110, 63, [(63, 1)], 63), (102, 64, [(64, 1)], 64),          # images of a tile each, more than a round of them
 ])
-def test_backward_of_tiles_of_few_rows(B, oracle, N, branches, most):
+def test_backward_of_tiles_of_few_rows(B, oracle, Bsz, N, branches, most):
     from paper_2403_09195_amd import synth
     import torch
-    plan = B.launch_describe(3, 5, N, branches, backward=True, arrays=True)
+    plan = B.launch_describe(Bsz, 5, N, branches, backward=True, arrays=True)
     assert plan["form"] == B.FORM_SHORT and int(plan["tiles"][:, 2].max()) == most
     assert plan["threads"] == 256 * (2 if most <= 32 else 3) * plan["n_items"]
-    (q, k, v), ex = make_qkv(1600 + N, 3, N, 5, 64, "bf16")
+    (q, k, v), ex = make_qkv(1600 + N, Bsz, N, 5, 64, "bf16")
     out, lse = B.forward(q, k, v, branches, 0.125)
-    st, ge = synth.tensor(1600 + N, 7, (3, N, 5, 64), "bf16")
+    st, ge = synth.tensor(1600 + N, 7, (Bsz, N, 5, 64), "bf16")
     nan = torch.full((4, 1024, 6, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
     assert B.launch_describe(4, 6, 1024, [(1024, 1)], backward=True)["form"] == B.FORM_SHORT
     B.backward(nan, nan, nan, nan, nan[..., 0].transpose(1, 2).float().contiguous(), nan, [(1024, 1)], 0.125)
